@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256) void check_pages_kernel(const SeqMeta* __restr
 }
 
 struct WorkLayout {
-    size_t seqs, dec, cmb, pf, pfcmb, pfmap, rows, queue, q_off, apt, apr, wide, wide_base, total;
+    size_t seqs, dec, cmb, pf, pfcmb, pfmap, rt, rtcut, queue, q_off, apt, apr, wide, wide_base, total;
 };
 
 WorkLayout layout_of(const Plan& p)
@@ -353,7 +353,8 @@ WorkLayout layout_of(const Plan& p)
     w.pf = o;   o = align16(o + p.pf.size() * sizeof(PfItem));
     w.pfcmb = o; o = align16(o + p.pfcmb.size() * sizeof(PfCmb));
     w.pfmap = o; o = align16(o + p.pfmap.size() * sizeof(PfSlot));
-    w.rows = o; o = align16(o + p.rows.size() * sizeof(RowItem));
+    w.rt = o; o = align16(o + p.rt.size() * sizeof(RowTile));
+    w.rtcut = o; o = align16(o + p.rtcut.size() * sizeof(RowCut));
     w.queue = o; o = align16(o + p.queue.size() * sizeof(QItem));
     w.q_off = o; o = align16(o + p.q_off.size() * sizeof(int32_t));
     w.apt = o; o = align16(o + p.apt.size() * sizeof(AppTile));
@@ -384,7 +385,8 @@ int upload_plan(ts_ctx* c, hipStream_t st, const WorkLayout& w, UploadJob* defer
     if (!p.pf.empty()) memcpy(h + w.pf, p.pf.data(), p.pf.size() * sizeof(PfItem));
     if (!p.pfcmb.empty()) memcpy(h + w.pfcmb, p.pfcmb.data(), p.pfcmb.size() * sizeof(PfCmb));
     if (!p.pfmap.empty()) memcpy(h + w.pfmap, p.pfmap.data(), p.pfmap.size() * sizeof(PfSlot));
-    if (!p.rows.empty()) memcpy(h + w.rows, p.rows.data(), p.rows.size() * sizeof(RowItem));
+    if (!p.rt.empty()) memcpy(h + w.rt, p.rt.data(), p.rt.size() * sizeof(RowTile));
+    if (!p.rtcut.empty()) memcpy(h + w.rtcut, p.rtcut.data(), p.rtcut.size() * sizeof(RowCut));
     if (!p.queue.empty()) memcpy(h + w.queue, p.queue.data(), p.queue.size() * sizeof(QItem));
     if (!p.q_off.empty()) memcpy(h + w.q_off, p.q_off.data(), p.q_off.size() * sizeof(int32_t));
     if (!p.apt.empty()) memcpy(h + w.apt, p.apt.data(), p.apt.size() * sizeof(AppTile));
@@ -685,8 +687,12 @@ extern "C" int ts_reserve(ts_ctx* c, int64_t max_tokens, int64_t max_seqs, int64
     const size_t TT = (size_t)std::max<int32_t>(1, c->opt.tile_tokens > 0 ? c->opt.tile_tokens : prefill_tile_tokens(c->desc));
     const size_t items = P / L + S;
     const size_t tiles = T / TT + S + (size_t)c->opt.n_cu;      // (cutting tiles along the keys adds at most one item per CU)
+    // generic row tiles: at most one whole tile per token, or the cut ones (a cut has at least one partial result)
+    const bool rows_possible = !desc_uses_mfma_decode(c->desc) || c->opt.prefill_generic || c->opt.generic_only ||
+                               (c->desc.head_dim == 64 && c->desc.kv_dtype == TS_FP8_E4M3);
+    const size_t row_slots = rows_possible ? (size_t)row_tile_slots_bound(c->desc, c->opt.n_cu, max_tokens, max_ctx_pages) : 0;
     const size_t bytes = (S + 1) * sizeof(SeqMeta) + items * (sizeof(DecItem) + sizeof(CmbItem)) + tiles * (sizeof(PfItem) + sizeof(PfCmb)) +
-                         tiles * Hkv * xcds * sizeof(PfSlot) + T * sizeof(RowItem) +
+                         tiles * Hkv * xcds * sizeof(PfSlot) + T * sizeof(RowTile) + row_slots * (sizeof(RowTile) + sizeof(RowCut) + sizeof(CmbItem)) +
                          (items + tiles) * Hkv * sizeof(QItem) + (xcds + 1) * sizeof(int32_t) +
                          (T / kPage + 2 * S) * sizeof(AppTile) + T * sizeof(AppRow) +
                          (size_t)std::min<int64_t>((int64_t)P, c->opt.widen_pages) * sizeof(WideItem) + S * sizeof(int32_t) + 16 * 16;
@@ -705,7 +711,7 @@ extern "C" int ts_reserve(ts_ctx* c, int64_t max_tokens, int64_t max_seqs, int64
         rc = acquire_slot(c, bytes, &s);
         if (rc != TS_OK) return rc;
     }
-    return ensure_partials(c, (int64_t)items);
+    return ensure_partials(c, (int64_t)(items + row_slots));
 }
 
 extern "C" int ts_set_option(ts_ctx* c, const char* name, int64_t value)
@@ -816,7 +822,7 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
     if (c->plan.info.total_tokens == 0) return TS_OK;
     if (!k_new || !v_new) return fail(c, TS_ERR_INVALID_ARG, "k_new / v_new is NULL");
     // only the sequence table is needed on the device
-    c->plan.dec.clear(); c->plan.cmb.clear(); c->plan.pf.clear(); c->plan.rows.clear(); c->plan.pfmap.clear();
+    c->plan.dec.clear(); c->plan.cmb.clear(); c->plan.pf.clear(); c->plan.rt.clear(); c->plan.rtcut.clear(); c->plan.pfmap.clear();
     c->plan.queue.clear(); c->plan.q_off.clear();
     const WorkLayout w = layout_of(c->plan);
     hipStream_t st = (hipStream_t)stream;
@@ -871,6 +877,8 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         if (c->static_call) {                              // (no scratch for widened pages or for partial results of cut tiles)
             opt.widen_pages = 0;
             opt.pf_split_min_keys = 0;
+            opt.row_part_slots = static_partial_slots(c);
+            opt.row_cut_few_only = true;                   // (a large batch's lists must fit as well)
         }
         build_plan(c->desc, q_lens, ctx_lens, num_seqs, opt, &c->plan);
     }
@@ -894,7 +902,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     const bool ride = k_new && !c->validate_pages && !c->static_call;
     // decode-only batch of matrix-core items whose lists fit into the kernel arguments: the items append the new tokens
     const bool fuse = k_new && !c->validate_pages && c->fused_append && desc_uses_mfma_decode(c->desc) && !p.dec.empty() && p.pf.empty() &&
-                p.rows.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 && !c->merge_in_kernel &&
+                p.rt.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 && !c->merge_in_kernel &&
                 p.dec.size() <= (size_t)kSmallDec && p.cmb.size() <= (size_t)kSmallCmb;
     UploadJob job;
     rc = upload_plan(c, st, w, ride || fuse ? &job : nullptr);   // (fused form: nothing to upload)
@@ -934,12 +942,12 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     a.pfcmb = (const PfCmb*)(wb + w.pfcmb); a.n_pfcmb = (int32_t)p.pfcmb.size();
     a.pf_part_o = c->d_pf_part_o; a.pf_part_ml = c->d_pf_part_ml;
     a.pfmap = (const PfSlot*)(wb + w.pfmap); a.n_pfmap = (int32_t)p.pfmap.size();
-    a.rows = (const RowItem*)(wb + w.rows); a.n_rows = (int32_t)p.rows.size();
+    a.rt = (const RowTile*)(wb + w.rt);     a.n_rt = (int32_t)p.rt.size(); a.rtcut = (const RowCut*)(wb + w.rtcut);
     a.queue = (const QItem*)(wb + w.queue); a.q_off = (const int32_t*)(wb + w.q_off);
     a.n_queue = (int32_t)p.queue.size(); a.n_xcd = p.q_off.empty() ? 0 : (int32_t)p.q_off.size() - 1;
     a.q_ctr = q_ctr_of(c);
     // (the merging form of the decode kernel exists for a prefetch depth of two tiles and outside the one-kernel launch)
-    a.cmb_ctr = c->merge_in_kernel && c->dec_nbuf == 2 && p.info.mixed_mode != TS_MIXED_ONE_KERNEL ? cmb_ctr_of(c, p.cmb.size()) : nullptr;
+    a.cmb_ctr = c->merge_in_kernel && p.rt.empty() && c->dec_nbuf == 2 && p.info.mixed_mode != TS_MIXED_ONE_KERNEL ? cmb_ctr_of(c, p.cmb.size()) : nullptr;
     a.dec_nbuf = c->dec_nbuf; a.mixed_wgs = c->mixed_wgs; a.n_cu = c->opt.n_cu; a.pf_wgs = p.info.prefill_workgroups;
     a.part_o = part_o_of(c); a.part_ml = part_ml_of(c);
     if (!p.wide.empty()) {
@@ -992,6 +1000,8 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     } else {
         e = (hipError_t)timed_launch(c, TS_K_DECODE, a.n_dec > 0, st, [&] { return launch_decode(a, stream); });
         if (e != hipSuccess) return hip_fail(c, e, "decode launch");
+        e = (hipError_t)timed_launch(c, TS_K_ROWS, a.n_rt > 0, st, [&] { return launch_rows(a, stream); });
+        if (e != hipSuccess) return hip_fail(c, e, "rows launch");
         e = (hipError_t)timed_launch(c, TS_K_COMBINE, a.n_cmb > 0 && !a.cmb_ctr, st, [&] { return a.cmb_ctr ? 0 : launch_combine(a, stream); });
         if (e != hipSuccess) return hip_fail(c, e, "combine launch");
         e = (hipError_t)timed_launch(c, TS_K_PREFILL, a.n_pf > 0, st, [&] { return launch_prefill(a, stream); });
@@ -999,9 +1009,6 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     }
     e = (hipError_t)timed_launch(c, TS_K_COMBINE, a.n_pfcmb > 0, st, [&] { return launch_prefill_combine(a, stream); });
     if (e != hipSuccess) return hip_fail(c, e, "prefill combine launch");
-    e = (hipError_t)timed_launch(c, TS_K_ROWS, a.n_rows > 0, st, [&] { return launch_rows(a, stream); });
-    if (e != hipSuccess) return hip_fail(c, e, "rows launch");
-
     rc = mark_work_done(c, st);
     if (rc != TS_OK) return rc;
     {

@@ -13,6 +13,9 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+// the same for buffers that only promise the alignment of one element
+typedef f32x4 __attribute__((aligned(4))) f32x4_u;
+typedef __attribute__((ext_vector_type(2))) uint32_t __attribute__((aligned(2))) u32x2_u;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;

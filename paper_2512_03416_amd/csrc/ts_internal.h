@@ -81,11 +81,11 @@ struct AppTile {          // one cache page of a chunk's new tokens; launched on
     int32_t pad0, pad1, pad2;
 };
 constexpr int kAppendTileMin = 8;   // sequences with at least this many new tokens are appended page-wise
-struct AppRow {           // one new token that is appended on its own
+struct AppRow {           // one new token of the token-wise list
     int32_t row;
     int32_t seq;
     int32_t pos;          // its position in the sequence (prefix + index among the new tokens)
-    int32_t pad;
+    int32_t run;          // fp32 caches: first new token of its page: how many new tokens the page gets; else 0
 };
 
 struct WideItem {         // one page of a prefill chunk's sequence that is widened from e4m3 to bf16 before the tiles run
@@ -93,11 +93,18 @@ struct WideItem {         // one page of a prefill chunk's sequence that is wide
     int32_t page_idx;     // index into the sequence's page list; the widened copy is page number = index in this list
 };
 
-struct RowItem {          // one query row for the generic kernel
-    int32_t row;
+struct RowTile {          // generic kernel: consecutive tokens of one sequence over a page range; launched once per KV head
     int32_t seq;
-    int32_t n_keys;
-    int32_t pad;
+    int32_t row0;         // row of the tile's first token
+    int32_t pos0;         // its position: token t sees pos0 + t + 1 keys
+    int32_t n_tok_cut;    // tokens (low 8 bits, at most 16 / G); the rest: 0 = all pages, else 1 + index of its RowCut
+};
+
+struct RowCut {           // a range of a row tile's pages
+    int32_t page_begin;   // [page_begin, page_end) of the sequence's page list
+    int32_t page_end;
+    int32_t part;         // token t's partial result goes to slot part + t * n_split
+    int32_t n_split;      // ranges the tile's pages are cut into
 };
 
 struct Plan {
@@ -111,7 +118,8 @@ struct Plan {
     std::vector<AppRow> apr;         // token-wise append work: short sequences, and everything the page-wise kernel does not cover
     std::vector<QItem> queue;        // mixed batches: per-die queues, concatenated
     std::vector<int32_t> q_off;      // xcds + 1 offsets into queue
-    std::vector<RowItem> rows;
+    std::vector<RowTile> rt;         // generic kernel: row tiles, longest first
+    std::vector<RowCut> rtcut;       // ... and the page ranges of the cut ones
     std::vector<WideItem> wide;      // fp8 caches: pages to widen, in the order of their widened copies
     std::vector<int32_t> wide_base;  // per sequence: number of its first widened page, -1 = not widened
     ts_plan_info info{};
@@ -128,6 +136,8 @@ struct PlanOptions {
     int32_t tile_tokens = 0;    // query tokens per prefill tile
     int32_t pf_split_min_keys = 512;    // shortest key range of a cut prefill tile (multiple of 64; 0 = never cut)
     int32_t pf_resident_wgs = 0; // co-resident launch: resident prefill workgroups (0 = from the batch's two costs)
+    int64_t row_part_slots = 1 << 20;   // most partial results of cut generic row tiles (beyond: the tiles stay whole)
+    bool row_cut_few_only = false;      // cut generic row tiles only where they are too few to fill the GPU
     int64_t widen_pages = 16384; // fp8 caches: most pages of prefill sequences that are widened to bf16 per pass (0 = never)
 };
 
@@ -138,6 +148,9 @@ bool desc_uses_mfma(const ts_attn_desc& d);
 bool desc_uses_mfma_decode(const ts_attn_desc& d);
 bool desc_uses_mfma_tiles(const ts_attn_desc& d);      // (head dim 64: bf16 pages only, one launch per class)
 int32_t prefill_tile_tokens(const ts_attn_desc& d);
+
+// Upper bound of the partial results that the cut generic row tiles of such a batch take.
+int64_t row_tile_slots_bound(const ts_attn_desc& d, int32_t n_cu, int64_t max_tokens, int64_t max_ctx_pages);
 
 // Validates lengths; returns TS_OK or an error and fills err.
 int validate_batch(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx_lens,
@@ -187,7 +200,7 @@ struct AttnArgs {
     const PfSlot* pfmap; int32_t n_pfmap;
     const QItem* queue; const int32_t* q_off; int32_t n_queue; int32_t n_xcd;
     int32_t* q_ctr;            // n_xcd queue heads + 1 finished-workgroup count, zero between launches
-    const RowItem* rows; int32_t n_rows;
+    const RowTile* rt; int32_t n_rt; const RowCut* rtcut;
     // fp8 caches: bf16 copies of the prefill sequences' pages (tiles [page][kv head], bf16 operand order), made
     // once per pass; wide_base[seq] = number of the sequence's first widened page.  NULL = the tiles read the
     // fp8 cache and widen it themselves.

@@ -2,7 +2,8 @@
 //
 // Prefill builds cache entries for all input tokens, a decode iteration adds the entry of the
 // last token (paper Sec. 2.1); in a Convertible Decoder both kinds of rows arrive in one batch
-// (Sec. 3.4).  Two kernels:
+// (Sec. 3.4).  Three kernels:
+//   - append_run_kernel: fp32 caches, see there;
 //   - append_token_kernel: one workgroup per new token of a short sequence (decode rows): looks up the
 //     token's page and slot and scatters its Hkv x D values of K (16-byte dim-chunks) and V
 //     (token-fastest tile) into place.  The copy of the call's work lists from the pinned staging
@@ -12,23 +13,13 @@
 //     to 16 new rows with full 256-byte reads, turns them into the K tile and -- through LDS --
 //     into the token-fastest V tile, and writes whole 16-byte vectors.  (Scattering a chunk token
 //     by token wrote 5.5x the new bytes: every 2-byte V element dirtied its own cache sector.)
-// Both convert to the cache element type with the same functions, so the bytes are identical.
+// All convert to the cache element type with the same functions, so the bytes are identical.
 #include "ts_device.h"
 
 namespace ts {
 
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    static __device__ __forceinline__ float load(const void* p, int64_t i) { return ((const float*)p)[i]; }
-};
-template <> struct Elem<uint16_t> {
-    static __device__ __forceinline__ float load(const void* p, int64_t i)
-    { return bf16_bits_to_float(((const uint16_t*)p)[i]); }
-};
-
-// SRC: element type of k_new/v_new (float or uint16_t holding bf16 bits).
-// DST: cache element type (float, uint16_t bf16 bits, uint8_t e4m3).
-template <typename SRC, typename DST>
+// bf16 source rows; DST: cache element type (uint16_t bf16 bits, uint8_t e4m3).
+template <typename DST>
 __global__ __launch_bounds__(256) void append_token_kernel(AppendArgs a)
 {
     if ((int)blockIdx.x >= a.n_apr) {                  // work-list upload riding along
@@ -42,20 +33,20 @@ __global__ __launch_bounds__(256) void append_token_kernel(AppendArgs a)
     const int Hkv = a.geo.Hkv, D = a.geo.D;
     constexpr int X = 16 / (int)sizeof(DST);       // elements per 16-byte dim-chunk
     const int n_elems = Hkv * D;
-    const SRC* ks = (const SRC*)a.k_new + (int64_t)row * n_elems;
-    const SRC* vs = (const SRC*)a.v_new + (int64_t)row * n_elems;
+    const uint16_t* ks = (const uint16_t*)a.k_new + (int64_t)row * n_elems;
+    const uint16_t* vs = (const uint16_t*)a.v_new + (int64_t)row * n_elems;
     DST* kc = (DST*)a.k_cache;
     DST* vc = (DST*)a.v_cache;
     // (the values are requested before the page id is needed: the two loads wait together)
     const int32_t* page_ptr = a.block_table + (int64_t)r.seq * a.geo.max_pages + (pos >> 4);
     const int slot = pos & 15;
     for (int e0 = 0; e0 < n_elems; e0 += 4 * 256) {
-        SRC kv[4], vv[4];
+        uint16_t kv[4], vv[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int e = e0 + i * 256 + threadIdx.x;
-            kv[i] = e < n_elems ? ks[e] : SRC(0);
-            vv[i] = e < n_elems ? vs[e] : SRC(0);
+            kv[i] = e < n_elems ? ks[e] : (uint16_t)0;
+            vv[i] = e < n_elems ? vs[e] : (uint16_t)0;
         }
         const int64_t page = *page_ptr;
 #pragma unroll
@@ -67,8 +58,8 @@ __global__ __launch_bounds__(256) void append_token_kernel(AppendArgs a)
             const int64_t kidx = tile + (dim / X) * (kPage * X) + slot * X + (dim % X);
             const int64_t vidx = tile + dim * kPage + slot;
             if constexpr (sizeof(DST) == 1) {
-                const float kf = Elem<SRC>::load(&kv[i], 0) / a.k_scale[g];
-                const float vf = Elem<SRC>::load(&vv[i], 0) / a.v_scale[g];
+                const float kf = bf16_bits_to_float(kv[i]) / a.k_scale[g];
+                const float vf = bf16_bits_to_float(vv[i]) / a.v_scale[g];
                 __builtin_nontemporal_store((uint8_t)float_to_e4m3_bits(kf), &kc[kidx]);
                 __builtin_nontemporal_store((uint8_t)float_to_e4m3_bits(vf), &vc[vidx]);
             } else {
@@ -76,6 +67,55 @@ __global__ __launch_bounds__(256) void append_token_kernel(AppendArgs a)
                 __builtin_nontemporal_store((DST)vv[i], &vc[vidx]);
             }
         }
+    }
+}
+
+// fp32 cache: one workgroup per (run of new tokens of one page, KV head); the run's first record leads, the others'
+// workgroups have nothing to do.  Waves 0-1 write K (16-byte chunks, neighbouring slots together), waves 2-3 write V:
+// a thread holds all slots of one dim and stores them as whole 16-byte pieces, so a page's V lines leave the
+// L2 complete.  (One token per workgroup stored V in single 4-byte pieces, 64 bytes apart.)
+template <int D>
+__global__ __launch_bounds__(256) void append_run_kernel(AppendArgs a)
+{
+    const int Hkv = a.geo.Hkv;
+    if ((int)blockIdx.x >= a.n_apr * Hkv) {            // work-list upload riding along
+        const int64_t stride = (int64_t)a.up_blocks * blockDim.x;
+        for (int64_t i = (int64_t)(blockIdx.x - a.n_apr * Hkv) * blockDim.x + threadIdx.x; i < a.up_n16; i += stride)
+            ((uint4*)a.up_dst)[i] = ((const uint4*)a.up_src)[i];
+        return;
+    }
+    const int g = blockIdx.x % Hkv;
+    const AppRow rec = a.apr[blockIdx.x / Hkv];
+    if (rec.run == 0) return;
+    const int64_t page = a.block_table[(int64_t)rec.seq * a.geo.max_pages + (rec.pos >> 4)];
+    const int64_t tile = tile_elem_base(page, Hkv, g, D);
+    const int lo = rec.pos & (kPage - 1), hi = lo + rec.run;
+    const int64_t src0 = ((int64_t)(rec.row - lo) * Hkv + g) * D, row_step = (int64_t)Hkv * D;   // of slot 0
+    const int tid = threadIdx.x;
+    if (tid < 128) {
+        const float* src = (const float*)a.k_new;
+        float* kt = (float*)a.k_cache + tile;
+#pragma unroll
+        for (int i = tid; i < 4 * D; i += 128) {       // (chunk of 4 dims, slot): slots fastest, as in the tile
+            const int c = i >> 4, slot = i & 15;
+            if (slot >= lo && slot < hi) *(f32x4*)(kt + i * 4) = *(const f32x4_u*)(src + src0 + slot * row_step + 4 * c);
+        }
+        return;
+    }
+    const int dim = tid - 128;
+    if (dim >= D) return;
+    const float* src = (const float*)a.v_new + src0 + dim;
+    float* vt = (float*)a.v_cache + tile + dim * kPage;
+    float v[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) v[s] = s >= lo && s < hi ? src[s * row_step] : 0.f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if (4 * b >= lo && 4 * b + 4 <= hi) *(f32x4*)(vt + 4 * b) = f32x4{v[4 * b], v[4 * b + 1], v[4 * b + 2], v[4 * b + 3]};
+        else
+#pragma unroll
+            for (int s = 4 * b; s < 4 * b + 4; ++s)
+                if (s >= lo && s < hi) vt[s] = v[s];
     }
 }
 
@@ -212,12 +252,15 @@ int launch_append(const AppendArgs& args, void* stream)
     }
     if (a.n_apr > 0) {
         dim3 grid((unsigned)(a.n_apr + a.up_blocks));
-        if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32)
-            hipLaunchKernelGGL((append_token_kernel<float, float>), grid, block, 0, st, a);
+        const dim3 rgrid((unsigned)a.n_apr * (unsigned)a.geo.Hkv + (unsigned)a.up_blocks);
+        if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32 && a.geo.D == 128)
+            hipLaunchKernelGGL(append_run_kernel<128>, rgrid, block, 0, st, a);
+        else if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32 && a.geo.D == 64)
+            hipLaunchKernelGGL(append_run_kernel<64>, rgrid, block, 0, st, a);
         else if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16)
-            hipLaunchKernelGGL((append_token_kernel<uint16_t, uint16_t>), grid, block, 0, st, a);
+            hipLaunchKernelGGL((append_token_kernel<uint16_t>), grid, block, 0, st, a);
         else if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3)
-            hipLaunchKernelGGL((append_token_kernel<uint16_t, uint8_t>), grid, block, 0, st, a);
+            hipLaunchKernelGGL((append_token_kernel<uint8_t>), grid, block, 0, st, a);
         else
             return (int)hipErrorInvalidValue;
         a.up_blocks = 0;                               // done; the page-wise kernel finds its list on the device

@@ -81,7 +81,9 @@ __device__ __forceinline__ void combine_row(const AttnArgs& a, const CmbItem it)
         }
     }
     const float vscale = (a.geo.kv_dtype == TS_FP8_E4M3) ? a.v_scale[h / a.geo.G] : 1.0f;
-    ((uint16_t*)a.out)[((int64_t)it.row * Hq + h) * D + d] = (uint16_t)float_to_bf16_bits(o * vscale / L);
+    const int64_t oi = ((int64_t)it.row * Hq + h) * D + d;
+    if (a.geo.q_dtype == TS_F32) ((float*)a.out)[oi] = o * vscale / L;
+    else ((uint16_t*)a.out)[oi] = (uint16_t)float_to_bf16_bits(o * vscale / L);
 }
 
 __global__ __launch_bounds__(128) void combine_kernel(AttnArgs a)

@@ -1,157 +1,262 @@
-// Generic row kernel: softmax attention of one (query row, query head) per wavefront, fp32
-// arithmetic throughout, any supported element type and head_dim 64/128.  It serves the fp32
-// configuration (where the 1e-5 bar rules out bf16 matrix instructions) and the shapes the MFMA
-// kernels do not cover.  Decode rows and prefill-chunk rows differ only in how many keys they
-// see (paper Sec. 2.1, Sec. 3.4: a chunk row attends to its cached prefix and, causally, to
-// its own chunk).
+// Generic row tiles: softmax attention in fp32 arithmetic throughout, any supported element type and head dim.
+// They serve the fp32 configuration (where the 1e-5 bar rules out bf16 matrix instructions) and the chunk rows
+// that the bf16 tiles do not take (option prefill_path; head dim 64 over an e4m3 cache too large to widen).
 //
-// Per 64 keys: lane j scores key j (its K values arrive as 16-byte dim-chunks of the tile),
-// the wave agrees on the running maximum and sum with shuffle reductions (online softmax), the
-// 64 weights go through LDS, then lane d accumulates output dims d, d+64 from the token-fastest
-// V tile.
+// A tile is 16 columns = (16 / G consecutive tokens of one sequence) x (G query heads of one KV head) over a range
+// of cache pages; a decode row is a tile of one token (paper Sec. 2.1, Sec. 3.4: the two differ only in how many
+// keys they see).  Both products run on the fp32 matrix instruction 16x16x4 -- an fp32 fused multiply-add per
+// element into fp32 accumulators -- so every K/V byte that is loaded serves 16 columns:
+//   - S^T = K Q^T: a lane's 16-byte piece of a K tile is X consecutive dims of one token; step e of piece b
+//     multiplies dims (4 b + r) X + e of the four lane groups r.  The order of a contraction is free, and this
+//     one takes the cache layout as it is;
+//   - O^T += V^T P^T: the accumulator of S^T (lane (r, n): tokens 4r .. 4r+3 of column n) is the B operand of
+//     step e as it stands, a lane's four tokens of a V row are the matching A operands.
+// Four waves share a tile: each takes every fourth page with the next page's loads in flight, and their states
+// meet in LDS.  Long tiles are cut along the pages like decode rows (merged by combine_kernel).
+//
+// What bounds it: chunk rows, the matrix instruction (64 flop per clock and SIMD: 2048 clocks per page and KV head
+// with head dim 128); decode rows, HBM.
+#include <type_traits>
+
 #include "ts_device.h"
 
 namespace ts {
 
-template <typename T> struct Ld;
-template <> struct Ld<float> {
-    static constexpr int X = 4;
-    static __device__ __forceinline__ void chunk(const void* base, int64_t elem, float* o)
-    {
-        const float4 v = *(const float4*)((const float*)base + elem);
-        o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-    }
-    static __device__ __forceinline__ float one(const void* base, int64_t elem)
-    { return ((const float*)base)[elem]; }
-};
-template <> struct Ld<uint16_t> {
-    static constexpr int X = 8;
-    static __device__ __forceinline__ void chunk(const void* base, int64_t elem, float* o)
-    {
-        const uint4 v = *(const uint4*)((const uint16_t*)base + elem);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o[2 * i] = __uint_as_float(w[i] << 16);
-            o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-    static __device__ __forceinline__ float one(const void* base, int64_t elem)
-    { return bf16_bits_to_float(((const uint16_t*)base)[elem]); }
-};
-template <> struct Ld<uint8_t> {
-    static constexpr int X = 16;
-    static __device__ __forceinline__ void chunk(const void* base, int64_t elem, float* o)
-    {
-        const uint4 v = *(const uint4*)((const uint8_t*)base + elem);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[i] = e4m3_bits_to_float((w[i >> 2] >> (8 * (i & 3))) & 0xffu);
-    }
-    static __device__ __forceinline__ float one(const void* base, int64_t elem)
-    { return e4m3_bits_to_float(((const uint8_t*)base)[elem]); }
+constexpr int kRtWaves = 4;
+constexpr float kRaiseRt = 16.0f;      // log2 units a score may exceed the reference maximum by before it is raised
+constexpr float kNoKey = -3.0e38f;     // reference maximum of a column that has seen no key (finite: differences stay defined)
+
+// One (page, KV head) tile in registers: D / 4 elements of K and of V per lane.
+template <typename KT, int D> struct RtTile {
+    static constexpr int X = 16 / (int)sizeof(KT), KB = D / (4 * X), VB = D / 16;
+    using VPiece = std::conditional_t<sizeof(KT) == 4, uint4, std::conditional_t<sizeof(KT) == 2, uint2, uint32_t>>;
+    uint4 k[KB];
+    VPiece v[VB];
 };
 
-__device__ __forceinline__ float wave_max(float v)
+template <typename KT, int D>
+__device__ __forceinline__ void rt_load(RtTile<KT, D>& t, const char* kc, const char* vc, int64_t tile, int lane)
 {
+    using T = RtTile<KT, D>;
+    constexpr int ES = (int)sizeof(KT);
+    const char* kt = kc + tile * (16 * D * ES) + lane * 16;
+    const char* vt = vc + tile * (16 * D * ES) + (lane & 15) * (16 * ES) + (lane >> 4) * (4 * ES);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ float wave_sum(float v)
-{
+    for (int b = 0; b < T::KB; ++b) t.k[b] = *(const uint4*)(kt + b * 1024);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int b = 0; b < T::VB; ++b) t.v[b] = *(const typename T::VPiece*)(vt + b * (256 * ES));
 }
 
+// element e of a register's worth of cache elements, as fp32 (exact for every type)
+template <typename KT> __device__ __forceinline__ float rt_elem(uint32_t w, int e)
+{
+    if constexpr (sizeof(KT) == 4) return __uint_as_float(w);
+    else if constexpr (sizeof(KT) == 2) return __uint_as_float(e ? w & 0xffff0000u : w << 16);
+    else {
+        const auto p = e < 2 ? __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false) : __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
+        return p[e & 1];
+    }
+}
+__device__ __forceinline__ uint32_t word_of(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+__device__ __forceinline__ uint32_t word_of(const uint2& v, int i) { return i == 0 ? v.x : v.y; }
+__device__ __forceinline__ uint32_t word_of(const uint32_t& v, int) { return v; }
+
+template <int D> struct RtMerge {                          // LDS image of the non-leading waves' state
+    float o[kRtWaves - 1][D / 16][64][4];
+    float m[kRtWaves - 1][16];
+    float l[kRtWaves - 1][16];
+};
+
+// KV heads vary fastest over the grid (as in the decode kernel: the Hkv tiles of a page are neighbours in memory,
+// and with eight heads every tile of a (sequence, head) stream runs on one die, whose L2 then holds its pages).
 template <typename QT, typename KT, int D>
-__global__ __launch_bounds__(64) void rows_kernel(AttnArgs a)
+__global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
 {
-    const RowItem it = a.rows[blockIdx.x];
-    const int h = blockIdx.y;
-    const int Hkv = a.geo.Hkv, g = h / a.geo.G;
-    const int lane = threadIdx.x;
-    constexpr int X = Ld<KT>::X;
-    constexpr int ND = D / 64;
-    __shared__ float q_s[D];
-    __shared__ float p_s[64];
-
-    for (int d = lane; d < D; d += 64)
-        q_s[d] = Ld<QT>::one(a.q, ((int64_t)it.row * a.geo.Hq + h) * D + d);
-    __syncthreads();
-
-    const float kscale = (sizeof(KT) == 1) ? a.k_scale[g] : 1.0f;
-    const float vscale = (sizeof(KT) == 1) ? a.v_scale[g] : 1.0f;
-    const float c = a.sm_scale * kscale * kLog2e;       // scores in log2 units
-    const int32_t* bt = a.block_table + (int64_t)it.seq * a.geo.max_pages;
-
-    float m = -INFINITY, l = 0.0f;
-    float o[ND];
-#pragma unroll
-    for (int i = 0; i < ND; ++i) o[i] = 0.0f;
-
-    for (int base = 0; base < it.n_keys; base += 64) {
-        const int j = base + lane;
-        float s = -INFINITY;
-        if (j < it.n_keys) {
-            const int64_t tile = tile_elem_base(bt[j >> 4], Hkv, g, D);
-            const int slot = j & 15;
-            float acc = 0.0f;
-#pragma unroll 4
-            for (int cidx = 0; cidx < D / X; ++cidx) {
-                float kv[X];
-                Ld<KT>::chunk(a.k_cache, tile + (int64_t)cidx * (kPage * X) + slot * X, kv);
-#pragma unroll
-                for (int e = 0; e < X; ++e) acc = fmaf(q_s[cidx * X + e], kv[e], acc);
-            }
-            s = acc * c;
-        }
-        const float m_new = fmaxf(m, wave_max(s));           // finite: key `base` is always valid
-        const float alpha = exp2f(m - m_new);                // first block: exp2(-inf) = 0
-        const float p = (j < it.n_keys) ? exp2f(s - m_new) : 0.0f;
-        l = l * alpha + wave_sum(p);
-        m = m_new;
-        p_s[lane] = p;
-        __syncthreads();
-        const int n_here = min(64, it.n_keys - base);
-#pragma unroll
-        for (int i = 0; i < ND; ++i) {
-            const int d = lane + 64 * i;
-            float acc = o[i] * alpha;
-            for (int t0 = 0; t0 < n_here; t0 += 16) {
-                const int64_t vrow = tile_elem_base(bt[(base + t0) >> 4], Hkv, g, D) + (int64_t)d * kPage;
-                const int nt = min(16, n_here - t0);
-                for (int t = 0; t < nt; ++t)                 // slots past n_keys are never read
-                    acc = fmaf(p_s[t0 + t], Ld<KT>::one(a.v_cache, vrow + t), acc);
-            }
-            o[i] = acc;
-        }
-        __syncthreads();
+    using T = RtTile<KT, D>;
+    constexpr int X = T::X, KB = T::KB, VB = T::VB, EW = 4 / (int)sizeof(KT);   // EW: elements per register
+    __shared__ RtMerge<D> mg;
+    const int Hq = a.geo.Hq, Hkv = a.geo.Hkv, G = a.geo.G;
+    const int32_t TS_CONSTANT* w = as_constant((const int32_t*)(a.rt + blockIdx.x / Hkv));
+    struct { int seq, row0, pos0, n_tok, page_begin, page_end, part, n_split; } it{w[0], w[1], w[2], w[3] & 255, 0, 0, -1, 1};
+    it.page_end = (it.pos0 + it.n_tok - 1) / kPage + 1;
+    if (w[3] >> 8) {                                       // a range of the tile's pages
+        const int32_t TS_CONSTANT* cut = as_constant((const int32_t*)(a.rtcut + ((w[3] >> 8) - 1)));
+        it.page_begin = cut[0]; it.page_end = cut[1]; it.part = cut[2]; it.n_split = cut[3];
     }
-    const float inv = vscale / l;
+    const int g = blockIdx.x % Hkv;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, r = lane >> 4, n = lane & 15;
+
+    // column n = (token t, head g G + hd); columns past the tile's last token repeat it and are never stored
+    const int t_raw = n / G, hd = n - t_raw * G;
+    const int t = min(t_raw, it.n_tok - 1);
+    const int keys = it.pos0 + t + 1;                      // keys this column sees
+    const int keys_min = it.pos0 + 1, keys_max = it.pos0 + it.n_tok;   // over the tile's columns
+
+    // this wave's pages: page_begin + wave + kRtWaves * k, k = 0 .. np - 1
+    const int np = max(0, (it.page_end - it.page_begin - wave + kRtWaves - 1) / kRtWaves);
+    const int32_t TS_CONSTANT* bt = as_constant(a.block_table) + (int64_t)it.seq * a.geo.max_pages + it.page_begin + wave;
+
+    f32x4 acc[VB];
 #pragma unroll
-    for (int i = 0; i < ND; ++i) {
-        const int64_t oi = ((int64_t)it.row * a.geo.Hq + h) * D + lane + 64 * i;
-        const float r = o[i] * inv;
-        if constexpr (sizeof(QT) == 4) ((float*)a.out)[oi] = r;
-        else ((uint16_t*)a.out)[oi] = (uint16_t)float_to_bf16_bits(r);
+    for (int b = 0; b < VB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_ref = kNoKey, l = 0.0f;
+
+    if (np > 0) {                                          // wave-uniform
+        float q[D / 4];                                    // B operands of K Q^T: dims (4 b + r) X + e of the column
+        {
+            const QT* qrow = (const QT*)a.q + ((int64_t)(it.row0 + t) * Hq + g * G + hd) * D;
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+                for (int e = 0; e < X; ++e) {
+                    const QT v = qrow[(4 * b + r) * X + e];
+                    if constexpr (sizeof(QT) == 4) q[b * X + e] = v;
+                    else q[b * X + e] = bf16_bits_to_float(v);
+                }
+        }
+        const float c = a.sm_scale * (sizeof(KT) == 1 ? a.k_scale[g] : 1.0f) * kLog2e;
+        const char* kc = (const char*)a.k_cache;
+        const char* vc = (const char*)a.v_cache;
+        int next_k = 0, next_id = bt[0];
+        auto fetch = [&](T& tile) {
+            rt_load<KT, D>(tile, kc, vc, (int64_t)next_id * Hkv + g, lane);
+            next_k = min(next_k + 1, np - 1);              // past the end: stay on the last page
+            next_id = bt[kRtWaves * next_k];
+        };
+        auto step = [&](T& tile, int page) {
+            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;      // (two chains: half the rounding steps in a row)
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+                for (int e = 0; e < X; ++e) {
+                    const float kv = rt_elem<KT>(word_of(tile.k[b], e / EW), e % EW);
+                    f32x4& s = (e & 1) ? s1 : s0;
+                    s = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, q[b * X + e], s, 0, 0, 0);
+                }
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = (s0[i] + s1[i]) * c;
+            const int tok0 = page * kPage + 4 * r;
+            if ((page + 1) * kPage > keys_min) {           // wave-uniform: the page reaches a column's last key
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = tok0 + i < keys ? x[i] : -INFINITY;
+            }
+            const float lmax = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+            if (__any(lmax > m_ref + kRaiseRt)) {          // raise the reference (rare)
+                float full = fmaxf(lmax, __shfl_xor(lmax, 16, 64));
+                full = fmaxf(full, __shfl_xor(full, 32, 64));
+                const float m_new = fmaxf(m_ref, full);
+                const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+#pragma unroll
+                for (int b = 0; b < VB; ++b) acc[b] *= alpha;
+                l *= alpha;
+                m_ref = m_new;
+            }
+            float p[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(x[i] - m_ref);
+            l += (p[0] + p[1]) + (p[2] + p[3]);
+            if ((page + 1) * kPage > keys_max) {           // slots that no column sees hold whatever was there before
+#pragma unroll
+                for (int b = 0; b < VB; ++b) {
+                    if constexpr (sizeof(KT) == 4) {
+                        tile.v[b].x = tok0 < keys_max ? tile.v[b].x : 0u;
+                        tile.v[b].y = tok0 + 1 < keys_max ? tile.v[b].y : 0u;
+                        tile.v[b].z = tok0 + 2 < keys_max ? tile.v[b].z : 0u;
+                        tile.v[b].w = tok0 + 3 < keys_max ? tile.v[b].w : 0u;
+                    } else {
+                        constexpr int EB = 8 * (int)sizeof(KT);
+                        const int nv = min(max(keys_max - tok0, 0), 4);
+                        const uint64_t keep = nv * EB >= 64 ? ~0ull : (1ull << (nv * EB)) - 1ull;
+                        if constexpr (sizeof(KT) == 2) {
+                            tile.v[b].x &= (uint32_t)keep;
+                            tile.v[b].y &= (uint32_t)(keep >> 32);
+                        } else tile.v[b] &= (uint32_t)keep;
+                    }
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int b = 0; b < VB; ++b)
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(rt_elem<KT>(word_of(tile.v[b], e / EW), e % EW), p[e], acc[b], 0, 0, 0);
+        };
+        T buf[2];
+        fetch(buf[0]);
+        fetch(buf[1]);
+        for (int k = 0; k < np; k += 2) {
+            step(buf[0], it.page_begin + wave + kRtWaves * k);
+            fetch(buf[0]);
+            if (k + 1 < np) step(buf[1], it.page_begin + wave + kRtWaves * (k + 1));   // wave-uniform
+            fetch(buf[1]);
+        }
+    }
+
+    float l_tot = l + __shfl_xor(l, 16, 64);
+    l_tot += __shfl_xor(l_tot, 32, 64);
+
+    // merge the waves' states in wave order (results are run-to-run identical)
+    if (wave > 0) {
+#pragma unroll
+        for (int b = 0; b < VB; ++b) *(f32x4*)mg.o[wave - 1][b][lane] = acc[b];
+        if (r == 0) { mg.m[wave - 1][n] = m_ref; mg.l[wave - 1][n] = l_tot; }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    float M = m_ref;
+#pragma unroll
+    for (int v = 0; v < kRtWaves - 1; ++v) M = fmaxf(M, mg.m[v][n]);
+    {
+        const float w0 = __builtin_amdgcn_exp2f(m_ref - M);
+#pragma unroll
+        for (int b = 0; b < VB; ++b) acc[b] *= w0;
+        l_tot *= w0;
+    }
+#pragma unroll
+    for (int v = 0; v < kRtWaves - 1; ++v) {
+        const float wv = __builtin_amdgcn_exp2f(mg.m[v][n] - M);
+        l_tot += mg.l[v][n] * wv;
+#pragma unroll
+        for (int b = 0; b < VB; ++b) acc[b] += *(const f32x4*)mg.o[v][b][lane] * wv;
+    }
+    if (t_raw >= it.n_tok) return;
+    const int h = g * G + hd;
+    if (it.part >= 0) {                                    // a cut tile: token t's partial results are n_split slots in a row
+        const int64_t slot = (int64_t)it.part + (int64_t)t * it.n_split;
+        float* o = a.part_o + (slot * Hq + h) * D + 4 * r;
+#pragma unroll
+        for (int b = 0; b < VB; ++b) *(f32x4*)(o + 16 * b) = acc[b];
+        if (r == 0) *(float2*)(a.part_ml + (slot * Hq + h) * 2) = make_float2(M, l_tot);
+        return;
+    }
+    const float inv = (sizeof(KT) == 1 ? a.v_scale[g] : 1.0f) / l_tot;
+    QT* o = (QT*)a.out + ((int64_t)(it.row0 + t) * Hq + h) * D + 4 * r;
+#pragma unroll
+    for (int b = 0; b < VB; ++b) {
+        if constexpr (sizeof(QT) == 4) {
+            *(f32x4_u*)(o + 16 * b) = acc[b] * inv;
+        } else {
+            *(u32x2_u*)(o + 16 * b) = u32x2{
+                __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{acc[b][0] * inv, acc[b][1] * inv}, bf16x2)),
+                __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{acc[b][2] * inv, acc[b][3] * inv}, bf16x2))};
+        }
     }
 }
 
 template <typename QT, typename KT>
 static int launch_rows_d(const AttnArgs& a, hipStream_t st)
 {
-    dim3 grid((unsigned)a.n_rows, (unsigned)a.geo.Hq), block(64);
-    if (a.geo.D == 64) hipLaunchKernelGGL((rows_kernel<QT, KT, 64>), grid, block, 0, st, a);
-    else if (a.geo.D == 128) hipLaunchKernelGGL((rows_kernel<QT, KT, 128>), grid, block, 0, st, a);
+    const dim3 grid((unsigned)a.n_rt * (unsigned)a.geo.Hkv), block(64 * kRtWaves);
+    if (a.geo.D == 64) hipLaunchKernelGGL((row_tile_kernel<QT, KT, 64>), grid, block, 0, st, a);
+    else if (a.geo.D == 128) hipLaunchKernelGGL((row_tile_kernel<QT, KT, 128>), grid, block, 0, st, a);
     else return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }
 
 int launch_rows(const AttnArgs& a, void* stream)
 {
-    if (a.n_rows <= 0) return (int)hipSuccess;
+    if (a.n_rt <= 0) return (int)hipSuccess;
     hipStream_t st = (hipStream_t)stream;
     if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32) return launch_rows_d<float, float>(a, st);
     if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16) return launch_rows_d<uint16_t, uint16_t>(a, st);

@@ -7,6 +7,7 @@
 // over all CUs; prefill chunks are cut into causal query tiles.  Items are ordered longest first
 // so that the hardware dispatcher, which hands out workgroups in order, balances the tail.
 #include <algorithm>
+#include <array>
 #include <climits>
 #include <cmath>
 #include <cstdio>
@@ -145,6 +146,53 @@ static int32_t auto_split_pages(int64_t decode_tiles, int64_t decode_pages, int6
     return (int32_t)std::min<int64_t>(L, 1 << 20);
 }
 
+// Generic row tiles longer than a fair share of the workgroups that the GPU holds at once (two of four waves per
+// CU) are cut along the pages into ranges of at most that share; a range has at least 16 pages (four per wave:
+// shorter ones spend longer starting up and merging than multiplying).
+constexpr int kRowTileMinPages = 16, kRowTileWgsPerCu = 2;
+
+static int32_t row_tile_tokens(const ts_attn_desc& d) { return 16 / (d.num_q_heads / d.num_kv_heads); }
+
+// At most S / Hkv tiles exceed a fair share of S slots, and they are cut into at most 2 S / Hkv ranges; and no token has more partial results than its pages make ranges.
+int64_t row_tile_slots_bound(const ts_attn_desc& d, int32_t n_cu, int64_t max_tokens, int64_t max_ctx_pages)
+{
+    return std::min(2 * (int64_t)row_tile_tokens(d) * (kRowTileWgsPerCu * (int64_t)n_cu / d.num_kv_heads + 1),
+                    max_tokens * (max_ctx_pages / kRowTileMinPages + 1));
+}
+
+static int32_t row_tile_pages(const Plan& p, const RowTile& t)
+{
+    const int32_t cut = t.n_tok_cut >> 8;
+    return cut ? p.rtcut[cut - 1].page_end - p.rtcut[cut - 1].page_begin : (t.pos0 + t.n_tok_cut - 1) / kPage + 1;
+}
+
+static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t part)
+{
+    const int64_t slots = kRowTileWgsPerCu * (int64_t)std::max(1, opt.n_cu);
+    if (opt.row_cut_few_only && (int64_t)p.rt.size() * Hkv >= slots) return part;
+    int64_t pages = 0;
+    for (const RowTile& t : p.rt) pages += row_tile_pages(p, t);
+    const int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
+    auto cuts = [&](const RowTile& t) { return (row_tile_pages(p, t) + L - 1) / L; };
+    int64_t need = part;
+    for (const RowTile& t : p.rt)
+        if (cuts(t) > 1) need += (int64_t)cuts(t) * t.n_tok_cut;
+    if (need > opt.row_part_slots) return part;
+    std::vector<RowTile> whole;
+    whole.swap(p.rt);
+    for (const RowTile& t : whole) {
+        const int32_t n_pages = row_tile_pages(p, t), want = cuts(t), per = (n_pages + want - 1) / want, n_split = (n_pages + per - 1) / per;
+        if (n_split == 1) { p.rt.push_back(t); continue; }
+        for (int32_t i = 0; i < t.n_tok_cut; ++i) p.cmb.push_back(CmbItem{t.row0 + i, part + i * n_split, n_split, 0});
+        for (int32_t k = 0; k < n_split; ++k) {
+            p.rtcut.push_back(RowCut{k * per, std::min(n_pages, (k + 1) * per), part + k, n_split});
+            p.rt.push_back(RowTile{t.seq, t.row0, t.pos0, t.n_tok_cut | (int32_t)(p.rtcut.size() << 8)});
+        }
+        part += t.n_tok_cut * n_split;
+    }
+    return part;
+}
+
 // Launch order of the prefill workgroups.  Workgroups are dispatched to the accelerator dies
 // round-robin (workgroup i runs on die i % xcds) and every die has its own L2.  All tiles of one
 // (chunk, KV head) stream read the same K/V pages, so a stream is pinned to one die and its tiles
@@ -259,6 +307,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     const bool mfma_tiles = desc_uses_mfma_tiles(d) && !opt.generic_only && !opt.prefill_generic &&
                             (d.head_dim == 128 || d.kv_dtype == TS_BF16 || widen);
     const int Hkv = d.num_kv_heads;
+    int64_t rt_tokens = 0;                                 // rows the generic kernel gets
     p.seqs.resize((size_t)num_seqs + 1);
     int32_t off = 0;
     int64_t decode_tiles = 0, decode_pages = 0;
@@ -282,7 +331,11 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     for (int s = 0; s < num_seqs; ++s) {
         const SeqMeta& m = p.seqs[s];
         if (!page_wise || m.q_len < kAppendTileMin) {
-            for (int32_t i = 0; i < m.q_len; ++i) p.apr.push_back(AppRow{m.q_off + i, s, m.prefix + i, 0});
+            for (int32_t i = 0; i < m.q_len; ++i) {
+                const int32_t pos = m.prefix + i;
+                const bool leads = d.kv_dtype == TS_F32 && (i == 0 || pos % kPage == 0);
+                p.apr.push_back(AppRow{m.q_off + i, s, pos, leads ? std::min(kPage - pos % kPage, m.q_len - i) : 0});
+            }
             continue;
         }
         for (int32_t pg = m.prefix / kPage; pg <= (m.ctx_len - 1) / kPage; ++pg) {
@@ -392,10 +445,15 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
                 p.pfcmb.push_back(PfCmb{(int32_t)p.pf.size() - made, first, made, 0});
             }
         } else {
-            for (int32_t i = 0; i < m.q_len; ++i)
-                p.rows.push_back(RowItem{m.q_off + i, s, m.prefix + i + 1, 0});
+            const int32_t TR = row_tile_tokens(d);
+            for (int32_t i = 0; i < m.q_len; i += TR) {
+                const int32_t cnt = std::min(TR, m.q_len - i);
+                p.rt.push_back(RowTile{s, m.q_off + i, m.prefix + i, cnt});
+            }
+            rt_tokens += m.q_len;
         }
     }
+    if (!p.rt.empty()) part = cut_row_tiles(p, Hkv, opt, part);
     // fp8 caches: the pages of the chunks' sequences are widened to bf16 once per pass (every tile of a chunk
     // reads the whole prefix: widening inside the tiles repeats the conversion once per tile and costs the tile
     // kernel 8 % of its time), provided they fit the scratch the option allows
@@ -427,12 +485,13 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         for (PfCmb& cm : p.pfcmb) cm.item = where[cm.item];
     }
     map_prefill_to_xcds(p, Hkv, std::max(1, opt.xcds), mixed_mode);
-    std::stable_sort(p.rows.begin(), p.rows.end(),
-                     [](const RowItem& a, const RowItem& b) { return a.n_keys > b.n_keys; });
+    std::stable_sort(p.rt.begin(), p.rt.end(), [&](const RowTile& a, const RowTile& b) {
+        return row_tile_pages(p, a) > row_tile_pages(p, b);
+    });
     p.info.n_decode_items = (int32_t)p.dec.size();
     p.info.n_combine_rows = (int32_t)p.cmb.size();
     p.info.n_prefill_tiles = (int32_t)p.pf.size();
-    p.info.n_generic_rows = (int32_t)p.rows.size();
+    p.info.n_generic_rows = (int32_t)rt_tokens;
     p.info.partial_slots = part;
     p.info.prefill_parts = pf_part;
     p.info.prefill_workgroups = (int32_t)std::min<int64_t>(pf_wgs, (int64_t)p.queue.size());
@@ -492,16 +551,26 @@ extern "C" int64_t ts_plan_export(const ts_attn_desc* desc, const int32_t* q_len
     ts::build_plan(*desc, q_lens, ctx_lens, num_seqs, opt, &plan);
     const void* src = nullptr;
     int64_t n = 0, words = 0;
+    std::vector<std::array<int32_t, 4>> rows;              // the generic kernel's tiles, row by row
+    if (which == TS_LIST_ROWS) {
+        for (const ts::RowTile& t : plan.rt)
+            for (int32_t i = 0; i < (t.n_tok_cut & 255) && (t.n_tok_cut < 256 || plan.rtcut[(t.n_tok_cut >> 8) - 1].page_begin == 0); ++i) rows.push_back({t.row0 + i, t.seq, t.pos0 + i + 1, 0});
+        std::stable_sort(rows.begin(), rows.end(), [](const std::array<int32_t, 4>& a, const std::array<int32_t, 4>& b) {
+            return a[2] != b[2] ? a[2] > b[2] : a[0] < b[0];
+        });
+    }
     switch (which) {
     case TS_LIST_DECODE:  src = plan.dec.data();   n = (int64_t)plan.dec.size();   words = sizeof(ts::DecItem) / 4; break;
     case TS_LIST_COMBINE: src = plan.cmb.data();   n = (int64_t)plan.cmb.size();   words = sizeof(ts::CmbItem) / 4; break;
     case TS_LIST_PREFILL: src = plan.pf.data();    n = (int64_t)plan.pf.size();    words = sizeof(ts::PfItem) / 4; break;
     case TS_LIST_PFMAP:   src = plan.pfmap.data(); n = (int64_t)plan.pfmap.size(); words = sizeof(ts::PfSlot) / 4; break;
-    case TS_LIST_ROWS:    src = plan.rows.data();  n = (int64_t)plan.rows.size();  words = sizeof(ts::RowItem) / 4; break;
+    case TS_LIST_ROWS:    src = rows.data();       n = (int64_t)rows.size();       words = 4; break;
     case TS_LIST_QUEUE:   src = plan.queue.data(); n = (int64_t)plan.queue.size(); words = sizeof(ts::QItem) / 4; break;
     case TS_LIST_QOFF:    src = plan.q_off.data(); n = (int64_t)plan.q_off.size(); words = 1; break;
     case TS_LIST_APPEND:  src = plan.apt.data();   n = (int64_t)plan.apt.size();   words = sizeof(ts::AppTile) / 4; break;
-    case TS_LIST_APPEND_ROWS: src = plan.apr.data(); n = (int64_t)plan.apr.size(); words = sizeof(ts::AppRow) / 4; break;
+    case TS_LIST_APPEND_ROWS:
+        for (ts::AppRow& r : plan.apr) r.run = 0;           // (launch detail)
+        src = plan.apr.data(); n = (int64_t)plan.apr.size(); words = sizeof(ts::AppRow) / 4; break;
     case TS_LIST_PFCOMBINE: src = plan.pfcmb.data(); n = (int64_t)plan.pfcmb.size(); words = sizeof(ts::PfCmb) / 4; break;
     case TS_LIST_WIDEN:   src = plan.wide.data();  n = (int64_t)plan.wide.size();  words = sizeof(ts::WideItem) / 4; break;
     default: return TS_ERR_INVALID_ARG;

@@ -60,6 +60,21 @@ def test_generic_rows_shapes(shape):
     check(b)
 
 
+@pytest.mark.parametrize("heads", [(4, 1), (6, 2), (5, 1), (16, 1), (2, 2), (32, 8)], ids=lambda h: f"{h[0]}q{h[1]}kv")
+@pytest.mark.parametrize("dtypes,head_dim", [(("f32", "f32"), 64), (("f32", "f32"), 128), (("bf16", "bf16"), 128),
+                                             (("bf16", "fp8"), 64)], ids=["f32-64", "f32-128", "bf16-128", "fp8-64"])
+def test_generic_row_tiles(dtypes, head_dim, heads):
+    """Row tiles where they can go wrong: chunks that end inside a tile of 16 / G tokens, tiles that straddle a
+    page, prefixes inside a page, rows of one key, and tiles whose pages are cut (long
+    rows in a small batch).  Bars as everywhere: fp32 sums of at most 3000
+    unit-variance terms, weights and outputs rounded to the output type."""
+    shape = AttnShape(heads[0], heads[1], head_dim, *dtypes)
+    opts = {"prefill_path": 1} if dtypes[0] == "bf16" else None
+    check(make_batch(shape, [1, 1, 7, 1, 33, 2, 1, 17], [1, 16, 22, 2500, 64, 290, 17, 3000], seed=23, pool_rule=1.3,
+                     value_mult=0.7), options=opts)
+    check(make_batch(shape, [130], [1800], seed=24, value_mult=0.7), options=opts)
+
+
 # ---------------------------------------------------------------------------------------------
 # MFMA decode path (bf16 / fp8 cache, head_dim 128 and 64)
 # ---------------------------------------------------------------------------------------------
