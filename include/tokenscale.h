@@ -182,11 +182,11 @@ const char *ts_last_error(const ts_ctx *ctx);
 
 /* Tuning knobs (all optional).  Names:
  *   "decode_split_pages"  longest page range of one decode item (0 = choose from the batch)
- *   "decode_merge_in_kernel"  0 (default) = a decode row cut into several items is merged by a small launch behind
- *                         the decode items; 1 = by whichever of its items finishes last (arrival counters,
- *                         device-scope release/acquire around the partial results; the merge reads the partials
- *                         in item order, so the result does not depend on which item came last).  The second
- *                         form saves a launch and is slower on this GPU (the release writes the L2 back)
+ *   "decode_merge_in_kernel"  decode rows cut into several items are merged by whichever item of a row finishes last
+ *                         (arrival counters; the partials are read in item order, so the result does not depend on
+ *                         which item came last), or by a small launch behind the items.  0 (default) = in the kernel
+ *                         while no row of the batch has more than 16 items, 1 = in the kernel always.  (Prefetch
+ *                         depths other than the default and mixed_mode 1 always take the launch.)  Same results
  *   "decode_fused_append"  1 (default) / 0.  A pass that appends, holds decode rows only and is small (at most 64
  *                         decode items and 32 split rows: its work lists travel as kernel arguments) leaves
  *                         the append to the decode items: the workgroup that reads a row's last page takes the

@@ -117,11 +117,7 @@ struct ts_ctx {
     int32_t* h_probe = nullptr;        // pinned: one answer word per try
     int32_t* h_probe_dev = nullptr;    // the same words as the GPU addresses them
     std::vector<hipStream_t> parked;   // side streams that ran in turn with the caller's stream
-    // Split decode rows are merged by a launch of their own (default) or by whichever item of a row finishes
-    // last.  The second form saves a launch but needs a device-scope release in every item and an acquire in the
-    // last one; on this GPU the release writes the L2 back, and 8 rows of 1500 tokens took 30 us per pass
-    // instead of 20, a 256-token chunk next to 16 decode rows 154 us instead of 106.
-    bool merge_in_kernel = false;
+    bool merge_in_kernel = false;      // option: however many items a row has (see merge_counters)
     // Small decode-only batches are bound by their launches: when the work lists are short enough to travel as
     // kernel arguments, the decode items append the rows' new tokens themselves (no append launch, no upload).
     // 8 rows of 1500 tokens: 19.4 -> 15.1 us per pass (e4m3 cache: 19.7 -> 14.4), 16 rows: 29.1 -> 25.8
@@ -209,6 +205,17 @@ int32_t* cmb_ctr_of(const ts_ctx* c, size_t n_rows)
 {
     if (!c->static_call) return c->d_cmb_ctr;
     return n_rows * (size_t)c->desc.num_kv_heads <= (size_t)kStaticCmbCtrs ? (int32_t*)c->d_static + 256 : nullptr;
+}
+// Split decode rows are merged by whichever item of a row finishes last when the rows have few items (at most
+// kMergeInKernelMax, or by option), else by a launch behind them (NULL).  The last item of a row adds up its partials
+// on one CU; the launch spreads a row over one workgroup per head.
+constexpr int kMergeInKernelMax = 16;
+int32_t* merge_counters(const ts_ctx* c, const Plan& p)
+{
+    if (p.cmb.empty() || !p.rt.empty() || p.info.mixed_mode == TS_MIXED_ONE_KERNEL) return nullptr;
+    if (!c->merge_in_kernel && p.max_split > kMergeInKernelMax) return nullptr;
+    if ((int64_t)p.max_split * c->desc.num_q_heads * c->desc.head_dim * 4 >= (int64_t)1 << 31) return nullptr;
+    return cmb_ctr_of(c, p.cmb.size());
 }
 float* part_o_of(const ts_ctx* c) { return c->static_call ? (float*)(c->d_static + kStaticPartOff) : c->d_part_o; }
 float* part_ml_of(const ts_ctx* c)
@@ -340,7 +347,7 @@ __global__ __launch_bounds__(256) void check_pages_kernel(const SeqMeta* __restr
 }
 
 struct WorkLayout {
-    size_t seqs, dec, cmb, pf, pfcmb, pfmap, rt, rtcut, queue, q_off, apt, apr, wide, wide_base, total;
+    size_t seqs, dec, dec_wg, cmb, pf, pfcmb, pfmap, rt, rtcut, queue, q_off, apt, apr, wide, wide_base, total;
 };
 
 WorkLayout layout_of(const Plan& p)
@@ -349,6 +356,7 @@ WorkLayout layout_of(const Plan& p)
     size_t o = 0;
     w.seqs = o; o = align16(o + p.seqs.size() * sizeof(SeqMeta));
     w.dec = o;  o = align16(o + p.dec.size() * sizeof(DecItem));
+    w.dec_wg = o; o = align16(o + p.dec_wg.size() * sizeof(int32_t));
     w.cmb = o;  o = align16(o + p.cmb.size() * sizeof(CmbItem));
     w.pf = o;   o = align16(o + p.pf.size() * sizeof(PfItem));
     w.pfcmb = o; o = align16(o + p.pfcmb.size() * sizeof(PfCmb));
@@ -381,6 +389,7 @@ int upload_plan(ts_ctx* c, hipStream_t st, const WorkLayout& w, UploadJob* defer
     char* h = (char*)slot->ptr;
     memcpy(h + w.seqs, p.seqs.data(), p.seqs.size() * sizeof(SeqMeta));
     if (!p.dec.empty()) memcpy(h + w.dec, p.dec.data(), p.dec.size() * sizeof(DecItem));
+    if (!p.dec_wg.empty()) memcpy(h + w.dec_wg, p.dec_wg.data(), p.dec_wg.size() * sizeof(int32_t));
     if (!p.cmb.empty()) memcpy(h + w.cmb, p.cmb.data(), p.cmb.size() * sizeof(CmbItem));
     if (!p.pf.empty()) memcpy(h + w.pf, p.pf.data(), p.pf.size() * sizeof(PfItem));
     if (!p.pfcmb.empty()) memcpy(h + w.pfcmb, p.pfcmb.data(), p.pfcmb.size() * sizeof(PfCmb));
@@ -691,7 +700,7 @@ extern "C" int ts_reserve(ts_ctx* c, int64_t max_tokens, int64_t max_seqs, int64
     const bool rows_possible = !desc_uses_mfma_decode(c->desc) || c->opt.prefill_generic || c->opt.generic_only ||
                                (c->desc.head_dim == 64 && c->desc.kv_dtype == TS_FP8_E4M3);
     const size_t row_slots = rows_possible ? (size_t)row_tile_slots_bound(c->desc, c->opt.n_cu, max_tokens, max_ctx_pages) : 0;
-    const size_t bytes = (S + 1) * sizeof(SeqMeta) + items * (sizeof(DecItem) + sizeof(CmbItem)) + tiles * (sizeof(PfItem) + sizeof(PfCmb)) +
+    const size_t bytes = (S + 1) * sizeof(SeqMeta) + items * (sizeof(DecItem) + sizeof(int32_t) + sizeof(CmbItem)) + tiles * (sizeof(PfItem) + sizeof(PfCmb)) +
                          tiles * Hkv * xcds * sizeof(PfSlot) + T * sizeof(RowTile) + row_slots * (sizeof(RowTile) + sizeof(RowCut) + sizeof(CmbItem)) +
                          (items + tiles) * Hkv * sizeof(QItem) + (xcds + 1) * sizeof(int32_t) +
                          (T / kPage + 2 * S) * sizeof(AppTile) + T * sizeof(AppRow) +
@@ -822,7 +831,7 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
     if (c->plan.info.total_tokens == 0) return TS_OK;
     if (!k_new || !v_new) return fail(c, TS_ERR_INVALID_ARG, "k_new / v_new is NULL");
     // only the sequence table is needed on the device
-    c->plan.dec.clear(); c->plan.cmb.clear(); c->plan.pf.clear(); c->plan.rt.clear(); c->plan.rtcut.clear(); c->plan.pfmap.clear();
+    c->plan.dec.clear(); c->plan.dec_wg.clear(); c->plan.cmb.clear(); c->plan.pf.clear(); c->plan.rt.clear(); c->plan.rtcut.clear(); c->plan.pfmap.clear();
     c->plan.queue.clear(); c->plan.q_off.clear();
     const WorkLayout w = layout_of(c->plan);
     hipStream_t st = (hipStream_t)stream;
@@ -877,7 +886,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         if (c->static_call) {                              // (no scratch for widened pages or for partial results of cut tiles)
             opt.widen_pages = 0;
             opt.pf_split_min_keys = 0;
-            opt.row_part_slots = static_partial_slots(c);
+            opt.part_slots = static_partial_slots(c);
             opt.row_cut_few_only = true;                   // (a large batch's lists must fit as well)
         }
         build_plan(c->desc, q_lens, ctx_lens, num_seqs, opt, &c->plan);
@@ -900,9 +909,10 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     // new tokens to append and no page check: the upload rides along in the first append launch (not in the
     // allocation-free call, whose upload launch also puts the shared queue heads back to zero)
     const bool ride = k_new && !c->validate_pages && !c->static_call;
+    int32_t* const ctr = merge_counters(c, p);
     // decode-only batch of matrix-core items whose lists fit into the kernel arguments: the items append the new tokens
     const bool fuse = k_new && !c->validate_pages && c->fused_append && desc_uses_mfma_decode(c->desc) && !p.dec.empty() && p.pf.empty() &&
-                p.rt.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 && !c->merge_in_kernel &&
+                p.rt.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 && (p.cmb.empty() || ctr) &&
                 p.dec.size() <= (size_t)kSmallDec && p.cmb.size() <= (size_t)kSmallCmb;
     UploadJob job;
     rc = upload_plan(c, st, w, ride || fuse ? &job : nullptr);   // (fused form: nothing to upload)
@@ -937,6 +947,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     a.sm_scale = sm_scale > 0.0f ? sm_scale : 1.0f / sqrtf((float)c->desc.head_dim);
     a.out = out;
     a.dec = (const DecItem*)(wb + w.dec);   a.n_dec = (int32_t)p.dec.size();
+    a.dec_wg = p.dec_wg.empty() ? nullptr : (const int32_t*)(wb + w.dec_wg); a.n_dec_wg = (int32_t)p.dec_wg.size() - 1;
     a.cmb = (const CmbItem*)(wb + w.cmb);   a.n_cmb = (int32_t)p.cmb.size();
     a.pf = (const PfItem*)(wb + w.pf);      a.n_pf = (int32_t)p.pf.size();
     a.pfcmb = (const PfCmb*)(wb + w.pfcmb); a.n_pfcmb = (int32_t)p.pfcmb.size();
@@ -946,9 +957,8 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     a.queue = (const QItem*)(wb + w.queue); a.q_off = (const int32_t*)(wb + w.q_off);
     a.n_queue = (int32_t)p.queue.size(); a.n_xcd = p.q_off.empty() ? 0 : (int32_t)p.q_off.size() - 1;
     a.q_ctr = q_ctr_of(c);
-    // (the merging form of the decode kernel exists for a prefetch depth of two tiles and outside the one-kernel launch)
-    a.cmb_ctr = c->merge_in_kernel && p.rt.empty() && c->dec_nbuf == 2 && p.info.mixed_mode != TS_MIXED_ONE_KERNEL ? cmb_ctr_of(c, p.cmb.size()) : nullptr;
-    a.dec_nbuf = c->dec_nbuf; a.mixed_wgs = c->mixed_wgs; a.n_cu = c->opt.n_cu; a.pf_wgs = p.info.prefill_workgroups;
+    a.cmb_ctr = ctr;
+    a.dec_nbuf = p.dec_deep ? std::max(3, c->dec_nbuf) : c->dec_nbuf; a.mixed_wgs = c->mixed_wgs; a.n_cu = c->opt.n_cu; a.pf_wgs = p.info.prefill_workgroups;
     a.part_o = part_o_of(c); a.part_ml = part_ml_of(c);
     if (!p.wide.empty()) {
         a.wide = (const WideItem*)(wb + w.wide); a.n_wide = (int32_t)p.wide.size();
@@ -993,6 +1003,8 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         // (nothing was uploaded: the staging slot only lends the call its event)
         SmallLists sl{};
         sl.n_dec = (int32_t)p.dec.size(); sl.n_cmb = (int32_t)p.cmb.size();
+        sl.n_wg = p.dec_wg.empty() ? sl.n_dec : (int32_t)p.dec_wg.size() - 1;
+        for (int32_t i = 0; i <= sl.n_wg; ++i) sl.wg[i] = (uint8_t)(p.dec_wg.empty() ? i : p.dec_wg[i]);
         std::copy(p.dec.begin(), p.dec.end(), sl.dec);
         std::copy(p.cmb.begin(), p.cmb.end(), sl.cmb);
         e = (hipError_t)timed_launch(c, TS_K_DECODE, true, st, [&] { return launch_decode_fused(a, sl, stream); });

@@ -61,6 +61,43 @@ __device__ __forceinline__ void load_tile(KVTile<uint8_t, D>& t, const char* kc,
     for (int b = 0; b < D / 16; ++b) t.v[b] = __builtin_nontemporal_load((const uint32_t*)(vt + b * 256));
 }
 
+// The same through buffer descriptors of the tile.  With `in` false they have no bytes, and the loads return zeros
+// without touching memory: a prefetch past the end of an item keeps the number of loads in flight static and
+// costs no bandwidth.  (Takes about six vector registers more than the form above, which the lean kernel lacks.)
+constexpr int kRawBuffer = 0x00027000;                     // untyped 32-bit data, offsets in bytes
+constexpr int kNonTemporal = 2;                            // cache policy bit
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_buffer(const char* p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, bytes, kRawBuffer);
+}
+template <int D>
+__device__ __forceinline__ void load_tile_if(KVTile<uint16_t, D>& t, const char* kc, const char* vc,
+                                             int64_t tile, int lane, bool in)
+{
+    const int bytes = in ? 32 * D : 0;
+    const auto kr = tile_buffer(kc + tile * (32 * D), bytes), vr = tile_buffer(vc + tile * (32 * D), bytes);
+    const int ko = lane * 16, vo = (lane & 15) * 32 + (lane >> 4) * 8;
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+        t.k[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kr, ko + b * 1024, 0, kNonTemporal));
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b)
+        t.v[b] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, vo + b * 512, 0, kNonTemporal));
+}
+template <int D>
+__device__ __forceinline__ void load_tile_if(KVTile<uint8_t, D>& t, const char* kc, const char* vc,
+                                             int64_t tile, int lane, bool in)
+{
+    const int bytes = in ? 16 * D : 0;
+    const auto kr = tile_buffer(kc + tile * (16 * D), bytes), vr = tile_buffer(vc + tile * (16 * D), bytes);
+    const int ko = lane * 16, vo = (lane & 15) * 16 + (lane >> 4) * 4;
+#pragma unroll
+    for (int b = 0; b < D / 64; ++b)
+        t.k[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kr, ko + b * 1024, 0, kNonTemporal));
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b) t.v[b] = __builtin_amdgcn_raw_buffer_load_b32(vr, vo + b * 256, 0, kNonTemporal);
+}
+
 // four e4m3 bytes -> four bf16 (exact: every e4m3 value is a bf16 value): one packed conversion per pair
 __device__ __forceinline__ uint2 fp8x4_to_bf16x4(uint32_t w)
 {
@@ -124,6 +161,89 @@ struct DecMerge {                          // LDS image of the non-leading waves
     float l[WAVES - 1][16];
 };
 
+// Partial results of consecutive splits of a row.  Plain form: read or written across a launch boundary.
+struct SplitParts {
+    float* o; float* ml; int Hq, D;
+    __device__ __forceinline__ SplitParts(const AttnArgs& a, int first, int)
+        : o(a.part_o + (int64_t)first * a.geo.Hq * a.geo.D), ml(a.part_ml + (int64_t)first * a.geo.Hq * 2), Hq(a.geo.Hq), D(a.geo.D) {}
+    __device__ __forceinline__ void store_o(int k, int h, int d, f32x4 v) const { *(f32x4*)(o + ((int64_t)k * Hq + h) * D + d) = v; }
+    __device__ __forceinline__ void store_ml(int k, int h, f32x2 v) const { *(f32x2*)(ml + ((int64_t)k * Hq + h) * 2) = v; }
+    __device__ __forceinline__ f32x4 load_o(int k, int h, int d) const { return *(const f32x4*)(o + ((int64_t)k * Hq + h) * D + d); }
+    __device__ __forceinline__ f32x2 load_ml(int k, int h) const { return *(const f32x2*)(ml + ((int64_t)k * Hq + h) * 2); }
+};
+// The same for partials that pass from one workgroup to another within a launch, perhaps between dies, whose L2
+// caches do not see each other's lines: stores and loads carry the device-scope bit (sc1), which takes them past
+// the L2.  (Plain stores and a device-scope release instead write back the whole L2 of the die for every item: 8
+// rows of 1500 tokens then took 27.7 us a pass where the merge by a launch took 19.6.)  Byte offsets are 32 bits wide:
+// n * Hq * D * 4 stays below 2^31.
+struct SplitPartsThrough {
+    static constexpr int kDevice = 16;                     // cache policy bit sc1
+    __amdgpu_buffer_rsrc_t o, ml; int Hq, D;
+    __device__ __forceinline__ SplitPartsThrough(const AttnArgs& a, int first, int n) : Hq(a.geo.Hq), D(a.geo.D)
+    {
+        o = __builtin_amdgcn_make_buffer_rsrc((void*)(a.part_o + (int64_t)first * Hq * D), (short)0, n * Hq * D * 4, kRawBuffer);
+        ml = __builtin_amdgcn_make_buffer_rsrc((void*)(a.part_ml + (int64_t)first * Hq * 2), (short)0, n * Hq * 8, kRawBuffer);
+    }
+    __device__ __forceinline__ void store_o(int k, int h, int d, f32x4 v) const
+    { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), o, ((k * Hq + h) * D + d) * 4, 0, kDevice); }
+    __device__ __forceinline__ void store_ml(int k, int h, f32x2 v) const
+    { __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), ml, (k * Hq + h) * 8, 0, kDevice); }
+    __device__ __forceinline__ f32x4 load_o(int k, int h, int d) const
+    { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(o, ((k * Hq + h) * D + d) * 4, 0, kDevice)); }
+    __device__ __forceinline__ f32x2 load_ml(int k, int h) const
+    { return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(ml, (k * Hq + h) * 8, 0, kDevice)); }
+};
+
+// Merge of a row's splits, four dims of a head per thread:  out = sum o_i 2^(m_i - M) / sum l_i 2^(m_i - M).
+// The splits are taken in chunks of eight, whose loads wait together; a chunk is summed relative to its own
+// maximum and the chunks are added in order.  Whoever adds up a row -- its last item, or the merge launch with
+// several chunks at a time -- thus rounds alike.
+constexpr int kMergeChunk = 8;
+struct SplitSum {
+    float m = -INFINITY, l = 0.0f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    __device__ __forceinline__ void add(const SplitSum& c)
+    {
+        const float mn = fmaxf(m, c.m);                    // (finite: every split of a row has a key of every head)
+        const float w0 = __builtin_amdgcn_exp2f(m - mn), w1 = __builtin_amdgcn_exp2f(c.m - mn);
+        l = l * w0 + c.l * w1;
+        o = o * w0 + c.o * w1;
+        m = mn;
+    }
+};
+template <typename PARTS>
+__device__ __forceinline__ SplitSum merge_chunk(const PARTS& parts, int k0, int n_split, int h, int d)
+{
+    f32x2 ml[kMergeChunk];
+    f32x4 o[kMergeChunk];
+#pragma unroll
+    for (int j = 0; j < kMergeChunk; ++j) ml[j] = parts.load_ml(min(k0 + j, n_split - 1), h);
+#pragma unroll
+    for (int j = 0; j < kMergeChunk; ++j) o[j] = parts.load_o(min(k0 + j, n_split - 1), h, d);
+    SplitSum c;
+#pragma unroll
+    for (int j = 0; j < kMergeChunk; ++j) c.m = fmaxf(c.m, ml[j].x);
+#pragma unroll
+    for (int j = 0; j < kMergeChunk; ++j) {
+        const float w = k0 + j < n_split ? __builtin_amdgcn_exp2f(ml[j].x - c.m) : 0.0f;
+        c.l += ml[j].y * w;
+        c.o += o[j] * w;
+    }
+    return c;
+}
+__device__ __forceinline__ void store_merged(const AttnArgs& a, const SplitSum& s, int row, int h, int d)
+{
+    const float inv = (a.geo.kv_dtype == TS_FP8_E4M3 ? a.v_scale[h / a.geo.G] : 1.0f) / s.l;
+    const int64_t at = ((int64_t)row * a.geo.Hq + h) * a.geo.D + d;
+    if (a.geo.q_dtype == TS_F32) {
+        *(f32x4_u*)((float*)a.out + at) = s.o * inv;
+    } else {
+        *(u32x2_u*)((uint16_t*)a.out + at) = u32x2{
+            __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{s.o[0] * inv, s.o[1] * inv}, bf16x2)),
+            __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{s.o[2] * inv, s.o[3] * inv}, bf16x2))};
+    }
+}
+
 // An item of the device work list, through the scalar cache.
 __device__ __forceinline__ DecItem load_dec_item(const DecItem* p)
 {
@@ -132,20 +252,22 @@ __device__ __forceinline__ DecItem load_dec_item(const DecItem* p)
 }
 
 // One decode item for KV head g, executed by a workgroup of WAVES waves.  All waves must call
-// it; it contains one workgroup barrier, and the caller must place another barrier before mg is
-// reused.
-// MERGE: the code for merging a split row by its last item is compiled in (it is used when a.cmb_ctr is set).
+// it; it contains one workgroup barrier, and another one must come before mg is reused: the caller's, or (mg_busy)
+// one in here just before mg is written, so that the waves that have nothing to merge start on the next item.
+// EXACT: prefetches past the end read nothing (load_tile_if).
+// THROUGH: partial results of split rows are stored for arrive_and_merge.
 // FUSED: the row's new token comes from a.k_new / a.v_new and is written into the cache here (see AttnArgs).
-template <typename KT, int NBUF, int WAVES, int D = 128, bool MERGE = false, bool FUSED = false>
-__device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it, int g, DecMerge<WAVES, D>& mg)
+template <typename KT, int NBUF, int WAVES, int D = 128, bool THROUGH = false, bool FUSED = false, bool EXACT = false>
+__device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it, int g, DecMerge<WAVES, D>& mg, bool mg_busy = false)
 {
     constexpr int KB = D / 32, DB = D / 16;    // 32-dim steps of K Q^T, 16-dim blocks of O^T
     const int it_row = it.row, it_seq = it.seq, it_keys = it.n_keys, it_pb = it.page_begin, it_pe = it.page_end, it_part = it.part;
-    const int it_cmb = MERGE ? it.cmb : -1, it_part_first = MERGE ? it.part_first : -1;
     // (readfirstlane tells the compiler the wave index is uniform, which keeps everything derived
     // from it -- the page-id loads above all -- on the scalar unit)
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, r = lane >> 4, n = lane & 15;
+    // (an opaque copy: the lane offsets are worked out per item instead of being kept across a caller's loop)
+    const int tid = opaque((int)threadIdx.x);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, r = lane >> 4, n = lane & 15;
     const int Hq = a.geo.Hq, Hkv = a.geo.Hkv, G = a.geo.G;
 
     // this wave's pages: it_pb + wave + WAVES * k, k = 0 .. np-1
@@ -203,9 +325,16 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
         int next_k = 0;
         int next_id = bt[0];
         auto fetch = [&](KVTile<KT, D>& t) {
-            load_tile(t, kc, vc, (int64_t)next_id * Hkv + g, lane);
-            next_k = min(next_k + 1, np - 1);                     // past the end: stay on the last page
-            next_id = bt[WAVES * next_k];
+            if constexpr (EXACT) {
+                // (past the end nothing is read, but a refill of the last page's own slot repeats that page)
+                load_tile_if(t, kc, vc, (int64_t)next_id * Hkv + g, lane, next_k < np || next_k == np - 1 + NBUF);
+                next_k += 1;
+                next_id = bt[WAVES * min(next_k, np - 1)];
+            } else {
+                load_tile(t, kc, vc, (int64_t)next_id * Hkv + g, lane);
+                next_k = min(next_k + 1, np - 1);                 // past the end: stay on the last page
+                next_id = bt[WAVES * next_k];
+            }
         };
         KVTile<KT, D> buf[NBUF];
 #pragma unroll
@@ -316,13 +445,11 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
             for (int j = 0; j < NBUF; ++j) {
                 const int k = base + j;
                 if (k < np_main) page_step(buf[j], it_pb + wave + WAVES * k, std::false_type{});   // wave-uniform
-                fetch(buf[j]);                                    // refill (clamped to the wave's last page)
+                fetch(buf[j]);                                    // refill
             }
         }
         if (has_tail) {
-            // fetch number f reads page min(f, np - 1) into slot f % NBUF and at least np + NBUF - 1 fetches were
-            // made: slot (np - 1) % NBUF holds the last page
-            const int jt = (np - 1) % NBUF;
+            const int jt = (np - 1) % NBUF;                       // the last page's slot
 #pragma unroll
             for (int j = 0; j < NBUF; ++j)
                 if (j == jt) page_step(buf[j], page_last, std::true_type{});
@@ -332,17 +459,19 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
     float l_tot = l + __shfl_xor(l, 16, 64);
     l_tot += __shfl_xor(l_tot, 32, 64);
 
+    const int lane_o = opaque((int)threadIdx.x) & 63, r_o = lane_o >> 4, n_o = lane_o & 15;   // (derived afresh: see above)
     // ---- merge the waves' states (wave order, so the result is reproducible) ----------------------
+    if (mg_busy) __syncthreads();
     if (wave > 0) {
 #pragma unroll
-        for (int b = 0; b < DB; ++b) *(f32x4*)mg.o[wave - 1][b][lane] = acc[b];
-        if (r == 0) { mg.m[wave - 1][n] = m_ref; mg.l[wave - 1][n] = l_tot; }
+        for (int b = 0; b < DB; ++b) *(f32x4*)mg.o[wave - 1][b][lane_o] = acc[b];
+        if (r_o == 0) { mg.m[wave - 1][n_o] = m_ref; mg.l[wave - 1][n_o] = l_tot; }
     }
     __syncthreads();
     if (wave != 0) return;                                        // (leaves this function only)
     float M = m_ref;
 #pragma unroll
-    for (int w = 0; w < WAVES - 1; ++w) M = fmaxf(M, mg.m[w][n]);
+    for (int w = 0; w < WAVES - 1; ++w) M = fmaxf(M, mg.m[w][n_o]);
     // wave 0 always holds the item's first page, so M is finite
     {
         const float w0 = __builtin_amdgcn_exp2f(m_ref - M);
@@ -352,18 +481,18 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
     }
 #pragma unroll
     for (int w = 0; w < WAVES - 1; ++w) {
-        const float ww = __builtin_amdgcn_exp2f(mg.m[w][n] - M);  // exp2(-inf) = 0 for a wave without pages
-        l_tot += mg.l[w][n] * ww;
+        const float ww = __builtin_amdgcn_exp2f(mg.m[w][n_o] - M);  // exp2(-inf) = 0 for a wave without pages
+        l_tot += mg.l[w][n_o] * ww;
 #pragma unroll
-        for (int b = 0; b < DB; ++b) acc[b] += *(const f32x4*)mg.o[w][b][lane] * ww;
+        for (int b = 0; b < DB; ++b) acc[b] += *(const f32x4*)mg.o[w][b][lane_o] * ww;
     }
 
-    if (n < G) {
-        const int h = g * G + n;
+    if (n_o < G) {
+        const int h = g * G + n_o;
         if (it_part < 0) {
             const float vscale = (sizeof(KT) == 1) ? a.v_scale[g] : 1.0f;
             const float inv = vscale / l_tot;
-            uint16_t* o = (uint16_t*)a.out + ((int64_t)it_row * Hq + h) * D + 4 * r;
+            uint16_t* o = (uint16_t*)a.out + ((int64_t)it_row * Hq + h) * D + 4 * r_o;
 #pragma unroll
             for (int b = 0; b < DB; ++b) {
                 const bf16x2 x = __builtin_convertvector(f32x2{acc[b][0] * inv, acc[b][1] * inv}, bf16x2);
@@ -374,74 +503,51 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
                 *(uint2*)(o + 16 * b) = w;
             }
         } else {
-            float* o = a.part_o + ((int64_t)it_part * Hq + h) * D + 4 * r;
+            const std::conditional_t<THROUGH, SplitPartsThrough, SplitParts> parts(a, it_part, 1);
 #pragma unroll
-            for (int b = 0; b < DB; ++b) *(f32x4*)(o + 16 * b) = acc[b];
-            if (r == 0) {
-                float* ml = a.part_ml + ((int64_t)it_part * Hq + h) * 2;
-                ml[0] = M;
-                ml[1] = l_tot;
-            }
+            for (int b = 0; b < DB; ++b) parts.store_o(0, h, 16 * b + 4 * r_o, acc[b]);
+            if (r_o == 0) parts.store_ml(0, h, f32x2{M, l_tot});
         }
     }
-    if constexpr (!MERGE) return;
-    if (it_part < 0 || a.cmb_ctr == nullptr) return;
+}
 
-    // ---- a split row: the last of its items to get here merges the partials (no launch for the merge) ----
-    // Release: this item's partials are visible device-wide before its arrival is counted; acquire: the item
-    // that counts the last arrival sees every other item's partials.  The merge reads all partials back from
-    // memory, its own included, in split order: the result does not depend on which item came last.
-    const int32_t TS_CONSTANT* cm = as_constant((const int32_t*)(a.cmb + it_cmb));
-    const int n_split = cm[2];
-    __threadfence();
-    int last = 0;
-    if (lane == 0) {
-        int32_t* ctr = a.cmb_ctr + (int64_t)it_cmb * Hkv + g;
-        const int seen = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        last = seen == n_split - 1;
-        if (last) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
-    }
-    last = __builtin_amdgcn_readfirstlane(last);
-    if (!last) return;
-    __threadfence();
-    if (n < G) {
-        constexpr int kBatch = 4;
-        const int h = g * G + n;
-        const float* pml = a.part_ml + ((int64_t)it_part_first * Hq + h) * 2;     // split k: pml[k * Hq * 2 + {0, 1}]
-        const float* po = a.part_o + ((int64_t)it_part_first * Hq + h) * D + 4 * r;   // split k: po[k * Hq * D + 16 b]
-        const int64_t ml_step = (int64_t)Hq * 2, po_step = (int64_t)Hq * D;
-        float Mx = -INFINITY;
-        for (int k = 0; k < n_split; ++k) Mx = fmaxf(Mx, pml[k * ml_step]);
-        f32x4 sum[DB];
-#pragma unroll
-        for (int b = 0; b < DB; ++b) sum[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float L = 0.0f;
-        for (int k0 = 0; k0 < n_split; k0 += kBatch) {
-            float w[kBatch];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const int k = min(k0 + j, n_split - 1);
-                w[j] = k0 + j < n_split ? __builtin_amdgcn_exp2f(pml[k * ml_step] - Mx) : 0.0f;
-                L += k0 + j < n_split ? pml[k * ml_step + 1] * w[j] : 0.0f;
-            }
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const int k = min(k0 + j, n_split - 1);
-#pragma unroll
-                for (int b = 0; b < DB; ++b) sum[b] += *(const f32x4*)(po + k * po_step + 16 * b) * w[j];
-            }
+// The end of a workgroup whose items [first, first + n) held parts of split rows: the last item of a row to get here
+// merges the row's partials (no launch for the merge).  The partials were stored past the die's L2 (see
+// SplitPartsThrough), so once the stores are acknowledged they are where every other workgroup's loads of the same
+// kind find them; only then is the arrival counted.  Whoever counts a row's last arrival reads all its partials
+// back, its own included, in split order: the result does not depend on which item came last.  One wait and one
+// round of counting serve all items of the workgroup (n <= 64).  All threads call it.
+template <int D, int THREADS>
+__device__ __forceinline__ void arrive_and_merge(const AttnArgs& a, const DecItem* items, int n, const CmbItem* rows, int g)
+{
+    __shared__ uint64_t s_last;
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (wave 0 stored the partials)
+        bool last = false;
+        const int row = tid < n ? items[tid].cmb : -1;
+        if (row >= 0) {
+            int32_t* ctr = a.cmb_ctr + (int64_t)row * a.geo.Hkv + g;
+            const int n_split = rows[row].n_split;
+            last = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_split - 1;
+            if (last) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
         }
-        const float vscale = (sizeof(KT) == 1) ? a.v_scale[g] : 1.0f;
-        const float inv = vscale / L;
-        uint16_t* o = (uint16_t*)a.out + ((int64_t)it_row * Hq + h) * D + 4 * r;
-#pragma unroll
-        for (int b = 0; b < DB; ++b) {
-            const bf16x2 x = __builtin_convertvector(f32x2{sum[b][0] * inv, sum[b][1] * inv}, bf16x2);
-            const bf16x2 y = __builtin_convertvector(f32x2{sum[b][2] * inv, sum[b][3] * inv}, bf16x2);
-            uint2 wv;
-            wv.x = __builtin_bit_cast(uint32_t, x);
-            wv.y = __builtin_bit_cast(uint32_t, y);
-            *(uint2*)(o + 16 * b) = wv;
+        const uint64_t m = __ballot(last);
+        if (tid == 0) s_last = m;
+    }
+    __syncthreads();
+    uint64_t todo = s_last;
+    asm volatile("" ::: "memory");
+    while (todo) {                                         // (the same for every thread)
+        const int j = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const CmbItem row = rows[items[j].cmb];
+        const SplitPartsThrough parts(a, row.part_begin, row.n_split);
+        for (int i = tid; i < a.geo.G * (D / 4); i += THREADS) {
+            const int h = g * a.geo.G + i / (D / 4), d = i % (D / 4) * 4;
+            SplitSum sum;
+            for (int k0 = 0; k0 < row.n_split; k0 += kMergeChunk) sum.add(merge_chunk(parts, k0, row.n_split, h, d));
+            store_merged(a, sum, row.row, h, d);
         }
     }
 }

@@ -27,7 +27,7 @@ struct DecItem {          // one split of one decode row; launched once per KV h
     int32_t page_end;
     int32_t part;         // partial slot, or -1 when the row has a single split
     int32_t cmb;          // split rows: index of the row in the combine list (its arrival counters), else -1
-    int32_t part_first;   // split rows: partial slot of the row's first split (the splits' slots are consecutive)
+    int32_t pad;
 };
 
 struct CmbItem {          // a decode row whose splits must be merged
@@ -110,6 +110,8 @@ struct RowCut {           // a range of a row tile's pages
 struct Plan {
     std::vector<SeqMeta> seqs;       // S + 1
     std::vector<DecItem> dec;
+    std::vector<int32_t> dec_wg;     // decode items dealt out evenly: offsets of the workgroups' items (else empty)
+    bool dec_deep = false;           // ... for the kernel with three KV tiles in flight per wave
     std::vector<CmbItem> cmb;
     std::vector<PfItem> pf;
     std::vector<PfCmb> pfcmb;        // tiles cut along the keys: what to merge
@@ -121,6 +123,7 @@ struct Plan {
     std::vector<RowTile> rt;         // generic kernel: row tiles, longest first
     std::vector<RowCut> rtcut;       // ... and the page ranges of the cut ones
     std::vector<WideItem> wide;      // fp8 caches: pages to widen, in the order of their widened copies
+    int32_t max_split = 1;           // most items that a decode row is cut into
     std::vector<int32_t> wide_base;  // per sequence: number of its first widened page, -1 = not widened
     ts_plan_info info{};
 };
@@ -136,7 +139,7 @@ struct PlanOptions {
     int32_t tile_tokens = 0;    // query tokens per prefill tile
     int32_t pf_split_min_keys = 512;    // shortest key range of a cut prefill tile (multiple of 64; 0 = never cut)
     int32_t pf_resident_wgs = 0; // co-resident launch: resident prefill workgroups (0 = from the batch's two costs)
-    int64_t row_part_slots = 1 << 20;   // most partial results of cut generic row tiles (beyond: the tiles stay whole)
+    int64_t part_slots = (int64_t)1 << 40;   // most partial results the launch has room for (beyond: cut generic row tiles stay whole, decode rows are not dealt out evenly)
     bool row_cut_few_only = false;      // cut generic row tiles only where they are too few to fill the GPU
     int64_t widen_pages = 16384; // fp8 caches: most pages of prefill sequences that are widened to bf16 per pass (0 = never)
 };
@@ -195,6 +198,7 @@ struct AttnArgs {
     void* out;
     // work lists
     const DecItem* dec; int32_t n_dec;
+    const int32_t* dec_wg; int32_t n_dec_wg;   // workgroup w works through the items [dec_wg[w], dec_wg[w + 1]); NULL = one item each
     const CmbItem* cmb; int32_t n_cmb;
     const PfItem* pf;   int32_t n_pf;
     const PfSlot* pfmap; int32_t n_pfmap;
@@ -216,7 +220,8 @@ struct AttnArgs {
     float* pf_part_o; float* pf_part_ml;
     // Arrival counters of the split decode rows, one per (combine row, KV head), zero between launches: the
     // workgroup that finds n_split - 1 in it is the last of the row and merges the partials itself.  NULL = the
-    // items only write their partials and combine_kernel merges them.
+    // items only write their partials and combine_kernel merges them (always so for the prefetch depths other than
+    // the default and in the one-kernel launch, whose kernels do not hold the merge).
     int32_t* cmb_ctr;
     // split-K partials: o [slot][Hq][D] fp32 (unnormalised), ml [slot][Hq][2] = (max, sum) in log2 units
     float* part_o; float* part_ml;
@@ -229,9 +234,10 @@ struct AttnArgs {
 // Work lists short enough to travel as kernel arguments (fused form of small decode-only batches).
 constexpr int kSmallDec = 64, kSmallCmb = 32;
 struct SmallLists {
-    int32_t n_dec, n_cmb, pad0, pad1;
+    int32_t n_dec, n_cmb, n_wg, pad;
     DecItem dec[kSmallDec];
     CmbItem cmb[kSmallCmb];
+    uint8_t wg[kSmallDec + 4];       // workgroup w works through the items [wg[w], wg[w + 1])
 };
 
 // Launchers (defined in the .hip files).  All return a hipError_t cast to int.

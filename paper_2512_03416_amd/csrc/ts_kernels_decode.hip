@@ -5,12 +5,24 @@ namespace ts {
 
 // KV heads vary fastest over the grid: the Hkv workgroups of one item start together and read the
 // Hkv adjacent tiles of each page (one contiguous run of the cache) at about the same time.
-template <typename KT, int NBUF, int D>
-__global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a)
+template <typename KT, int NBUF, int D, bool EXACT>
+__device__ __forceinline__ void decode_workgroup(const AttnArgs& a)
 {
     __shared__ DecMerge<kDecWaves, D> mg;
-    decode_item<KT, NBUF, kDecWaves, D>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+    const int w = blockIdx.x / a.geo.Hkv, g = blockIdx.x % a.geo.Hkv;
+    int first = w, end = w + 1;
+    if (a.dec_wg) { first = as_constant(a.dec_wg)[w]; end = as_constant(a.dec_wg)[w + 1]; }
+    bool split = false;
+    for (int i = first; i < end; ++i) {
+        const DecItem it = load_dec_item(a.dec + i);
+        split |= it.part >= 0;
+        decode_item<KT, NBUF, kDecWaves, D, true, false, EXACT>(a, it, g, mg, i > first);
+    }
+    if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves>(a, a.dec + first, end - first, a.cmb, g);
 }
+
+template <typename KT, int NBUF, int D>
+__global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { decode_workgroup<KT, NBUF, D, true>(a); }
 
 // The default form, two KV tiles in flight per wave, held to 128 vector registers per lane (the attribute
 // counts in units of two here): one such workgroup then fits on a CU next to a resident prefill workgroup
@@ -19,16 +31,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a)
 template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean(AttnArgs a)
 {
-    __shared__ DecMerge<kDecWaves, D> mg;
-    decode_item<KT, 2, kDecWaves, D>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
-}
-
-// The same with the merge of split rows by their last item compiled in (option "decode_merge_in_kernel").
-template <typename KT, int D>
-__global__ __launch_bounds__(64 * kDecWaves) void decode_kernel_merging(AttnArgs a)
-{
-    __shared__ DecMerge<kDecWaves, D> mg;
-    decode_item<KT, 2, kDecWaves, D, true>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+    decode_workgroup<KT, 2, D, false>(a);
 }
 
 // Small decode-only batches are bound by their launches and by the chain of dependent reads at the start of an
@@ -39,71 +42,53 @@ template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel_fused(AttnArgs a, SmallLists s)
 {
     __shared__ DecMerge<kDecWaves, D> mg;
-    decode_item<KT, 2, kDecWaves, D, false, true>(a, s.dec[blockIdx.x / a.geo.Hkv], blockIdx.x % a.geo.Hkv, mg);
+    const int w = blockIdx.x / a.geo.Hkv, g = blockIdx.x % a.geo.Hkv;
+    const int first = s.wg[w], end = s.wg[w + 1];
+    bool split = false;
+    for (int i = first; i < end; ++i) {
+        split |= s.dec[i].part >= 0;
+        decode_item<KT, 2, kDecWaves, D, true, true, true>(a, s.dec[i], g, mg, i > first);
+    }
+    if (split) arrive_and_merge<D, 64 * kDecWaves>(a, s.dec + first, end - first, s.cmb, g);
 }
 
-// Merge of a row's splits, in split order:  M = max m_i, out = sum o_i 2^(m_i-M) / sum l_i 2^(m_i-M).
-// The partials of up to eight splits are requested together and then added one after the other: the
-// sums keep their order, and a row of ten splits waits for four loads instead of thirty.
-__device__ __forceinline__ void combine_row(const AttnArgs& a, const CmbItem it)
+// Merge of split rows as a launch: one workgroup per (row, head); its groups of D / 4 lanes take a chunk of eight
+// splits each, the first group adds the chunks up in order.  (A row of 100 splits waits for two loads; one group
+// walking all its splits took 10.6 us for three rows of 32 splits.)
+__global__ __launch_bounds__(256) void combine_kernel(AttnArgs a)
 {
-    constexpr int kBatch = 8;
-    const int h = blockIdx.y, d = threadIdx.x;
-    const int Hq = a.geo.Hq, D = a.geo.D;
-    const float* ml = a.part_ml + ((int64_t)it.part_begin * Hq + h) * 2;      // split k: ml[k * Hq * 2 + {0, 1}]
-    const float* po = a.part_o + ((int64_t)it.part_begin * Hq + h) * D + d;    // split k: po[k * Hq * D]
-    const int64_t ml_step = (int64_t)Hq * 2, po_step = (int64_t)Hq * D;
-    float M = -INFINITY;
-    for (int k0 = 0; k0 < it.n_split; k0 += kBatch) {
-        float m[kBatch];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) m[j] = k0 + j < it.n_split ? ml[(k0 + j) * ml_step] : -INFINITY;
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) M = fmaxf(M, m[j]);
-    }
-    float o = 0.0f, L = 0.0f;
-    for (int k0 = 0; k0 < it.n_split; k0 += kBatch) {
-        float m[kBatch], l[kBatch], v[kBatch];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const bool in = k0 + j < it.n_split;
-            m[j] = in ? ml[(k0 + j) * ml_step] : 0.0f;
-            l[j] = in ? ml[(k0 + j) * ml_step + 1] : 0.0f;
-            v[j] = in ? po[(k0 + j) * po_step] : 0.0f;
+    constexpr int kMaxGroups = 16;                         // 256 threads / (64 dims / 4)
+    __shared__ f32x4 s_o[kMaxGroups][32];
+    __shared__ float s_m[kMaxGroups], s_l[kMaxGroups];
+    const CmbItem it = a.cmb[blockIdx.x];
+    const int h = blockIdx.y, DQ = a.geo.D / 4, groups = 256 / DQ;
+    const int grp = threadIdx.x / DQ, lane = threadIdx.x % DQ;
+    const SplitParts parts(a, it.part_begin, it.n_split);
+    SplitSum sum;
+    for (int k0 = 0; k0 < it.n_split; k0 += groups * kMergeChunk) {
+        const int mine = k0 + grp * kMergeChunk;
+        if (mine < it.n_split) {
+            const SplitSum c = merge_chunk(parts, mine, it.n_split, h, 4 * lane);
+            s_o[grp][lane] = c.o;
+            if (lane == 0) { s_m[grp] = c.m; s_l[grp] = c.l; }
         }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (k0 + j < it.n_split) {
-                const float w = __builtin_amdgcn_exp2f(m[j] - M);
-                L += l[j] * w;
-                o += v[j] * w;
+        __syncthreads();
+        if (grp == 0) {
+            for (int j = 0; j < groups && k0 + j * kMergeChunk < it.n_split; ++j) {
+                SplitSum c;
+                c.m = s_m[j]; c.l = s_l[j]; c.o = s_o[j][lane];
+                sum.add(c);
             }
         }
+        __syncthreads();
     }
-    const float vscale = (a.geo.kv_dtype == TS_FP8_E4M3) ? a.v_scale[h / a.geo.G] : 1.0f;
-    const int64_t oi = ((int64_t)it.row * Hq + h) * D + d;
-    if (a.geo.q_dtype == TS_F32) ((float*)a.out)[oi] = o * vscale / L;
-    else ((uint16_t*)a.out)[oi] = (uint16_t)float_to_bf16_bits(o * vscale / L);
-}
-
-__global__ __launch_bounds__(128) void combine_kernel(AttnArgs a)
-{
-    combine_row(a, a.cmb[blockIdx.x]);
-}
-
-__global__ __launch_bounds__(128) void combine_kernel_small(AttnArgs a, SmallLists s)
-{
-    combine_row(a, s.cmb[blockIdx.x]);
+    if (grp == 0) store_merged(a, sum, it.row, h, 4 * lane);
 }
 
 template <typename KT, int D>
 static int launch_decode_t(const AttnArgs& a, hipStream_t st)
 {
-    dim3 grid((unsigned)a.n_dec * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
-    if (a.cmb_ctr) {
-        hipLaunchKernelGGL((decode_kernel_merging<KT, D>), grid, block, 0, st, a);
-        return (int)hipGetLastError();
-    }
+    dim3 grid((unsigned)(a.dec_wg ? a.n_dec_wg : a.n_dec) * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
     switch (a.dec_nbuf) {
     case 3: hipLaunchKernelGGL((decode_kernel<KT, 3, D>), grid, block, 0, st, a); break;
     case 4: hipLaunchKernelGGL((decode_kernel<KT, 4, D>), grid, block, 0, st, a); break;
@@ -150,19 +135,15 @@ int launch_decode(const AttnArgs& a, void* stream)
 template <typename KT, int D>
 static int launch_fused_t(const AttnArgs& a, const SmallLists& s, hipStream_t st)
 {
-    dim3 grid((unsigned)s.n_dec * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
+    dim3 grid((unsigned)s.n_wg * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
     hipLaunchKernelGGL((decode_kernel_fused<KT, D>), grid, block, 0, st, a, s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || s.n_cmb <= 0) return (int)e;
-    dim3 cgrid((unsigned)s.n_cmb, (unsigned)a.geo.Hq), cblock((unsigned)a.geo.D);
-    hipLaunchKernelGGL(combine_kernel_small, cgrid, cblock, 0, st, a, s);
     return (int)hipGetLastError();
 }
 
 int launch_decode_fused(const AttnArgs& a, const SmallLists& s, void* stream)
 {
     if (s.n_dec <= 0) return (int)hipSuccess;
-    if (s.n_dec > kSmallDec || s.n_cmb > kSmallCmb || !a.k_new || !a.v_new || a.cmb_ctr) return (int)hipErrorInvalidValue;
+    if (s.n_dec > kSmallDec || s.n_cmb > kSmallCmb || !a.k_new || !a.v_new || (s.n_cmb > 0 && !a.cmb_ctr)) return (int)hipErrorInvalidValue;
     if ((a.geo.D != 128 && a.geo.D != 64) || a.geo.q_dtype != TS_BF16) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
     if (a.geo.kv_dtype == TS_BF16) return a.geo.D == 64 ? launch_fused_t<uint16_t, 64>(a, s, st) : launch_fused_t<uint16_t, 128>(a, s, st);
@@ -173,8 +154,7 @@ int launch_decode_fused(const AttnArgs& a, const SmallLists& s, void* stream)
 int launch_combine(const AttnArgs& a, void* stream)
 {
     if (a.n_cmb <= 0) return (int)hipSuccess;
-    dim3 grid((unsigned)a.n_cmb, (unsigned)a.geo.Hq), block((unsigned)a.geo.D);
-    hipLaunchKernelGGL(combine_kernel, grid, block, 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)a.n_cmb, (unsigned)a.geo.Hq), dim3(256), 0, (hipStream_t)stream, a);
     return (int)hipGetLastError();
 }
 

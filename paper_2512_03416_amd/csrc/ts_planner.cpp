@@ -12,6 +12,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
+#include <queue>
+#include <utility>
 
 #include "ts_internal.h"
 
@@ -99,17 +102,25 @@ int validate_batch(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* 
     return TS_OK;
 }
 
-// Pages per decode item.  A row that fits one item is finished by its workgroup without any
-// partial result in HBM, so rows are cut only (a) when they exceed one workgroup slot's fair share
-// of the batch (they would otherwise finish last), or (b) when the batch has fewer (row, KV head)
-// pairs than the GPU has CUs: then the pages are dealt out so that there is about one workgroup per
-// CU.  Pieces have at least 32 pages.  (Measured on 2-64 rows of 1500-6000 tokens: more and shorter
-// items than that only add start-up, merge and combine work; 8 rows of 1500 tokens take 22 us per
-// pass in pieces of 32 pages against 26 us in pieces of 8, next to a 256-token chunk 50 against 64 us;
-// for 16-48 rows every choice between 32 and 128 pages lies within 10 % of the best.)
+// How the decode rows are cut.  A row that fits one item is finished by its workgroup without any partial result
+// in HBM.  Two facts decide the rest (measured): the memory system serves the CUs alike, so that what counts is the
+// pages per CU, and a launch of one item per CU and a bit (a few CUs with two) takes nearly twice as long as one of
+// exactly one per CU; and every item costs its start (page ids, queries, first tiles: 2-3 us, hidden only by other
+// workgroups of the CU) and every cut its partial results and their merge.  So, for a launch of decode items alone:
+//   1. rows that give every CU a workgroup and come out even over the CUs stay whole (rows_stay_whole);
+//   2. else long batches are dealt out evenly: each workgroup gets the same number of pages, whatever rows they
+//      belong to (deal_decode_evenly);
+//   3. else (less than a workgroup per CU): pieces of one length, the shortest with which the items do not
+//      outnumber the CUs, and at least 32 pages (auto_split_pages).  8 rows of 1500 tokens in pieces of 32 pages
+//      take 17.3 us a pass, in pieces of 28 (a few items more than CUs) 20.5; 16 rows of 500-3000 tokens 28.1 us
+//      in 28 items per KV head, 36.2 us in pieces of 32 pages (64 items);
+//   4. batches whose rows outnumber the resident workgroups: a row is cut when it exceeds 5/4 of a workgroup slot's
+//      fair share, and the dispatcher balances the items, longest first (180 rows of 600-5700 tokens: 382 us
+//      against 390 cut at the fair share itself; with a heavy tail, 600-25 700 tokens and e4m3: 290, at 3/2: 298,
+//      uncut: 382).
 // In a mixed batch launched with resident workgroups (co-resident launch or one persistent kernel: a CU that
-// holds a resident workgroup has room for one decode workgroup, a third of the stand-alone slots), (b) does not
-// apply and the fair share in (a) is that of the slots actually there: measured on the burst configuration,
+// holds a resident workgroup has room for one decode workgroup, a third of the stand-alone slots), 3 does not
+// apply and the fair share is that of the slots actually there: measured on the burst configuration,
 // 706 -> 692 us and no combine launch.
 // Rates the two kinds of work reach on their own (decode scan: bytes per microsecond; prefill tiles: flop per
 // microsecond, all CUs).
@@ -130,7 +141,9 @@ constexpr double kPfShare1 = 0.6;
 // 85 against 89 us; 8 rows of 1500 tokens (8 us) next to 1024 tokens over 2048 (34 us): 85 against 100 us.
 constexpr double kCoresidentMinUs = 20.0;
 
-static int32_t auto_split_pages(int64_t decode_tiles, int64_t decode_pages, int64_t n_rows, int Hkv,
+constexpr int64_t kMinSplitPages = 32;
+
+static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tiles, int64_t decode_pages, int Hkv,
                                 int32_t wg_slots, int32_t n_cu, bool filled_by_prefill, int32_t pf_wgs)
 {
     // (next to a resident prefill workgroup a CU has room for one decode workgroup; the CUs without one hold
@@ -138,10 +151,18 @@ static int32_t auto_split_pages(int64_t decode_tiles, int64_t decode_pages, int6
     int64_t slots = std::max<int32_t>(1, filled_by_prefill ? n_cu : wg_slots);
     if (filled_by_prefill && pf_wgs > 0 && pf_wgs < n_cu)
         slots = pf_wgs + (int64_t)(n_cu - pf_wgs) * std::max(1, wg_slots / n_cu);
-    int64_t L = std::max<int64_t>(32, (decode_tiles + slots - 1) / slots);
-    if (!filled_by_prefill && n_rows * Hkv < n_cu && decode_pages > 0) {
-        const int64_t want_items = (n_cu + Hkv - 1) / Hkv;             // per KV head
-        L = std::min<int64_t>(L, std::max<int64_t>(32, (decode_pages + want_items - 1) / want_items));
+    int64_t L = std::max<int64_t>(kMinSplitPages, (decode_tiles + slots - 1) / slots);
+    if (!filled_by_prefill && p.info.decode_tokens * Hkv <= n_cu && decode_pages > 0) {
+        const int64_t want_items = std::max<int64_t>(1, n_cu / Hkv);   // per KV head
+        int64_t fit = std::max<int64_t>(kMinSplitPages, (decode_pages + want_items - 1) / want_items);
+        auto items = [&] {
+            int64_t n = 0;
+            for (int s = 0; s < num_seqs; ++s)
+                if (p.seqs[s].q_len == 1) n += ((p.seqs[s].ctx_len + kPage - 1) / kPage + fit - 1) / fit;
+            return n;
+        };
+        for (int tries = 0; tries < 64 && items() > want_items; ++tries) fit += std::max<int64_t>(1, fit / 16);
+        L = fit;
     }
     return (int32_t)std::min<int64_t>(L, 1 << 20);
 }
@@ -153,7 +174,8 @@ constexpr int kRowTileMinPages = 16, kRowTileWgsPerCu = 2;
 
 static int32_t row_tile_tokens(const ts_attn_desc& d) { return 16 / (d.num_q_heads / d.num_kv_heads); }
 
-// At most S / Hkv tiles exceed a fair share of S slots, and they are cut into at most 2 S / Hkv ranges; and no token has more partial results than its pages make ranges.
+// At most S / Hkv tiles exceed a fair share of S slots, and they are cut into at most 2 S / Hkv ranges; and no token
+// has more partial results than its pages make ranges.
 int64_t row_tile_slots_bound(const ts_attn_desc& d, int32_t n_cu, int64_t max_tokens, int64_t max_ctx_pages)
 {
     return std::min(2 * (int64_t)row_tile_tokens(d) * (kRowTileWgsPerCu * (int64_t)n_cu / d.num_kv_heads + 1),
@@ -177,7 +199,7 @@ static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t p
     int64_t need = part;
     for (const RowTile& t : p.rt)
         if (cuts(t) > 1) need += (int64_t)cuts(t) * t.n_tok_cut;
-    if (need > opt.row_part_slots) return part;
+    if (need > opt.part_slots) return part;
     std::vector<RowTile> whole;
     whole.swap(p.rt);
     for (const RowTile& t : whole) {
@@ -191,6 +213,119 @@ static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t p
         part += t.n_tok_cut * n_split;
     }
     return part;
+}
+
+// Decode items dealt out evenly: every workgroup gets the same number of pages, whatever rows they belong to; one
+// workgroup per CU with three KV tiles in flight per wave (two per CU with two tiles where a tile is only 2 KB, head
+// dim 64 and e4m3; twice as many where the rows are many, so that a workgroup has not more than two or three).
+// Measured against pieces of one length: 3 rows of 30-131 Ki tokens (64/8 heads, e4m3) 95 us for 119-123, 48 rows of
+// 200-6000 tokens (head dim 64) 57.6 for 61.9, 20 rows of 500-8000 tokens 62 for 74, 100 rows of 1600-5700 tokens
+// (e4m3) 142 for 150; shares below about 80 pages lose to rule 3 (16 rows of 500-4000 tokens, e4m3, 68 pages each:
+// 24.6 us against 23.8).
+constexpr int64_t kItemPages = 4;                          // pages that the start and the merge of an item are worth
+constexpr int64_t kMinEvenShare = 80;
+constexpr int32_t kMaxItemsPerWg = 48;                     // (the workgroup counts its arrivals with one wave: at most 64)
+
+static bool deal_decode_evenly(Plan& p, int num_seqs, int64_t pages, const ts_attn_desc& d, const PlanOptions& opt, int32_t* part)
+{
+    const int64_t Hkv = d.num_kv_heads, per_cu = std::max<int64_t>(1, opt.n_cu / Hkv), rows = p.info.decode_tokens;
+    const int64_t total = pages + rows * kItemPages;
+    const bool small_tile = d.head_dim == 64 && d.kv_dtype == TS_FP8_E4M3;
+    int64_t k = small_tile ? 2 : 1;
+    if (rows >= 2 * k * per_cu) k *= 2;
+    const int64_t W = k * per_cu;                          // workgroups per KV head
+    if (rows >= 2 * W || total < W * kMinEvenShare || W + rows > opt.part_slots) return false;
+    p.dec_deep = !small_tile;
+    const int64_t snap = std::max<int64_t>(2, total / W / 16);
+    int64_t done = 0, w = 1;                               // cost of the rows so far; workgroup w ends at total * w / W
+    p.dec_wg.push_back(0);
+    auto next_workgroup = [&] { if ((int32_t)p.dec.size() > p.dec_wg.back()) p.dec_wg.push_back((int32_t)p.dec.size()); };
+    for (int s = 0; s < num_seqs; ++s) {
+        const SeqMeta& m = p.seqs[s];
+        if (m.q_len != 1) continue;
+        const int64_t n_pages = (m.ctx_len + kPage - 1) / kPage;
+        const size_t first = p.dec.size();
+        for (int64_t begin = 0; begin < n_pages;) {
+            auto cut = [&] { return total * w / W - done - kItemPages; };     // page of this row at which workgroup w ends
+            for (; w < W && cut() <= begin + snap; ++w) next_workgroup();
+            if ((int32_t)p.dec.size() - p.dec_wg.back() >= kMaxItemsPerWg) next_workgroup();
+            const int64_t end = w < W && cut() < n_pages - snap ? cut() : n_pages;
+            p.dec.push_back(DecItem{m.q_off, s, m.ctx_len, (int32_t)begin, (int32_t)end, -1, -1, 0});
+            begin = end;
+        }
+        const int32_t n_split = (int32_t)(p.dec.size() - first);
+        if (n_split > 1) {
+            p.max_split = std::max(p.max_split, n_split);
+            for (int32_t i = 0; i < n_split; ++i) { p.dec[first + i].part = *part + i; p.dec[first + i].cmb = (int32_t)p.cmb.size(); }
+            p.cmb.push_back(CmbItem{m.q_off, *part, n_split, 0});
+            *part += n_split;
+        }
+        done += n_pages + kItemPages;
+    }
+    next_workgroup();
+    return true;
+}
+
+// Whole rows over the CUs when all their workgroups are resident at once: the memory system serves the CUs alike, so
+// what matters is the pages per CU.  Rows go, longest first, to the CU with the least; returns the most loaded CU's
+// pages.  order: rows in the order of launch (workgroups are placed round-robin: the first rows of all CUs, then the
+// second rows, ...).
+static int64_t pack_rows(const std::vector<int32_t>& pages, int64_t cus, std::vector<int32_t>* order)
+{
+    std::vector<int32_t> by_len(pages.size());
+    for (size_t i = 0; i < by_len.size(); ++i) by_len[i] = (int32_t)i;
+    std::stable_sort(by_len.begin(), by_len.end(), [&](int32_t a, int32_t b) { return pages[a] > pages[b]; });
+    const size_t most = (pages.size() + cus - 1) / cus;
+    std::vector<std::vector<int32_t>> bin(cus);
+    std::priority_queue<std::pair<int64_t, int64_t>, std::vector<std::pair<int64_t, int64_t>>, std::greater<>> open;   // (load, CU)
+    for (int64_t b = 0; b < cus; ++b) open.push({0, b});
+    int64_t longest = 0;
+    for (int32_t i : by_len) {
+        const auto [load, b] = open.top();
+        open.pop();
+        bin[b].push_back(i);
+        longest = std::max(longest, load + pages[i] + kItemPages);
+        if (bin[b].size() < most) open.push({load + pages[i] + kItemPages, b});
+    }
+    if (order) {
+        std::stable_sort(bin.begin(), bin.end(), [](const std::vector<int32_t>& a, const std::vector<int32_t>& b) { return a.size() > b.size(); });
+        for (size_t r = 0; r < most; ++r)
+            for (const auto& v : bin)
+                if (r < v.size()) order->push_back(v[r]);
+    }
+    return longest;
+}
+
+// Rows stay whole when the most loaded CU gets at most 24 pages of 8 KB (or as many bytes in smaller ones) more than
+// the average: dealing out costs about as much (60 rows of 300-1000 tokens: 36.6 us whole, 41.5 us dealt out; 40 rows
+// of 500-1220 tokens, 20 pages over the average: 34.5 against 39.1; 100 rows of 1600-5700 tokens, e4m3, 36 over:
+// 155 against 142; 48 rows, head dim 64, 44 over: 62.3 against 57.6).
+static bool rows_stay_whole(const Plan& p, int num_seqs, int64_t pages, const ts_attn_desc& d, const PlanOptions& opt)
+{
+    const int64_t cus = std::max<int64_t>(1, opt.n_cu / d.num_kv_heads), rows = p.info.decode_tokens;
+    if (rows < cus || rows * d.num_kv_heads > opt.wg_slots) return false;
+    std::vector<int32_t> n;
+    for (int s = 0; s < num_seqs; ++s)
+        if (p.seqs[s].q_len == 1) n.push_back((p.seqs[s].ctx_len + kPage - 1) / kPage);
+    const int64_t page_bytes = 2 * kPage * d.head_dim * (d.kv_dtype == TS_FP8_E4M3 ? 1 : 2);
+    return pack_rows(n, cus, nullptr) <= (pages + rows * kItemPages) / cus + 24 * 8192 / page_bytes;
+}
+
+static void balance_over_cus(Plan& p, int64_t cus)
+{
+    std::vector<int32_t> pages, order;
+    for (const DecItem& it : p.dec) pages.push_back(it.page_end - it.page_begin);
+    pack_rows(pages, cus, &order);
+    std::vector<DecItem> packed;
+    for (int32_t i : order) packed.push_back(p.dec[i]);
+    p.dec.swap(packed);
+}
+
+static void sort_decode_items(std::vector<DecItem>& v)
+{
+    std::stable_sort(v.begin(), v.end(), [](const DecItem& a, const DecItem& b) {
+        return (a.page_end - a.page_begin) > (b.page_end - b.page_begin);
+    });
 }
 
 // Launch order of the prefill workgroups.  Workgroups are dispatched to the accelerator dies
@@ -388,12 +523,19 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     const bool filled_by_prefill = mixed_mode != TS_MIXED_SEPARATE && (tile_heads >= opt.n_cu || pf_wgs > 0);
     const int32_t L = opt.split_pages > 0
                           ? opt.split_pages
-                          : auto_split_pages(decode_tiles, decode_pages, p.info.decode_tokens, Hkv, opt.wg_slots,
+                          : auto_split_pages(p, num_seqs, decode_tiles, decode_pages, Hkv, opt.wg_slots,
                                              std::max(1, opt.n_cu), filled_by_prefill, pf_wgs);
-    p.info.split_pages = L;
+    // (rows up to this many pages stay whole: see 4. above)
+    const bool many = mixed_mode == TS_MIXED_SEPARATE && p.info.decode_tokens * Hkv > opt.wg_slots;
+    const int32_t keep_whole = opt.split_pages > 0 || !many ? L : L + L / 4;
+    p.info.split_pages = keep_whole;
     p.info.tile_tokens = TT;
 
     int32_t part = 0, pf_part = 0;
+    // rows that give every CU a workgroup and come out even over the CUs stay whole; else they are dealt out evenly
+    const bool whole = mfma_dec && opt.split_pages == 0 && mixed_mode == TS_MIXED_SEPARATE && rows_stay_whole(p, num_seqs, decode_pages, d, opt);
+    const bool even = mfma_dec && !whole && opt.split_pages == 0 && mixed_mode == TS_MIXED_SEPARATE &&
+                      deal_decode_evenly(p, num_seqs, decode_pages, d, opt, &part);
     // parts per prefill tile that would give every CU a workgroup (1 = the tiles fill the GPU as they are)
     const int64_t pf_parts_wanted = tile_heads > 0 ? std::min<int64_t>(16, (pf_wgs > 0 ? pf_wgs : opt.n_cu) / tile_heads) : 1;
     for (int s = 0; s < num_seqs; ++s) {
@@ -401,16 +543,18 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         if (m.q_len == 0) continue;
         const bool as_decode = mfma_dec && m.q_len == 1;
         const bool as_tiles = mfma_tiles && m.q_len > 1;
+        if (as_decode && even) continue;
         if (as_decode) {
             int32_t n_pages = (m.ctx_len + kPage - 1) / kPage;
-            int32_t n_split = (n_pages + L - 1) / L;
+            int32_t n_split = whole || n_pages <= keep_whole ? 1 : (n_pages + L - 1) / L;
             int32_t per = (n_pages + n_split - 1) / n_split;
             n_split = (n_pages + per - 1) / per;
             const int32_t cmb_idx = n_split > 1 ? (int32_t)p.cmb.size() : -1;
+            p.max_split = std::max(p.max_split, n_split);
             if (n_split > 1) p.cmb.push_back(CmbItem{m.q_off, part, n_split, 0});
             for (int32_t k = 0; k < n_split; ++k) {
                 int32_t b = k * per, e = std::min(n_pages, b + per);
-                p.dec.push_back(DecItem{m.q_off, s, m.ctx_len, b, e, n_split > 1 ? part + k : -1, cmb_idx, n_split > 1 ? part : -1});
+                p.dec.push_back(DecItem{m.q_off, s, m.ctx_len, b, e, n_split > 1 ? part + k : -1, cmb_idx, 0});
             }
             if (n_split > 1) part += n_split;
         } else if (as_tiles) {
@@ -468,9 +612,10 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     }
     p.info.widened_pages = (int64_t)p.wide.size();
     // longest first (stable, so equal lengths keep batch order and runs stay reproducible)
-    std::stable_sort(p.dec.begin(), p.dec.end(), [](const DecItem& a, const DecItem& b) {
-        return (a.page_end - a.page_begin) > (b.page_end - b.page_begin);
-    });
+    if (!even) {
+        sort_decode_items(p.dec);
+        if (whole) balance_over_cus(p, std::max<int64_t>(1, opt.n_cu / Hkv));
+    }
     {
         // (the merge list refers to the tiles by position: sort a permutation and carry the references along)
         auto keys_of = [](const PfItem& t) {
@@ -489,6 +634,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         return row_tile_pages(p, a) > row_tile_pages(p, b);
     });
     p.info.n_decode_items = (int32_t)p.dec.size();
+    for (const DecItem& it : p.dec) p.info.split_pages = std::max(p.info.split_pages, it.page_end - it.page_begin);
     p.info.n_combine_rows = (int32_t)p.cmb.size();
     p.info.n_prefill_tiles = (int32_t)p.pf.size();
     p.info.n_generic_rows = (int32_t)rt_tokens;
@@ -560,7 +706,9 @@ extern "C" int64_t ts_plan_export(const ts_attn_desc* desc, const int32_t* q_len
         });
     }
     switch (which) {
-    case TS_LIST_DECODE:  src = plan.dec.data();   n = (int64_t)plan.dec.size();   words = sizeof(ts::DecItem) / 4; break;
+    case TS_LIST_DECODE:
+        ts::sort_decode_items(plan.dec);                    // (dealt out evenly they are listed workgroup by workgroup)
+        src = plan.dec.data();   n = (int64_t)plan.dec.size();   words = sizeof(ts::DecItem) / 4; break;
     case TS_LIST_COMBINE: src = plan.cmb.data();   n = (int64_t)plan.cmb.size();   words = sizeof(ts::CmbItem) / 4; break;
     case TS_LIST_PREFILL: src = plan.pf.data();    n = (int64_t)plan.pf.size();    words = sizeof(ts::PfItem) / 4; break;
     case TS_LIST_PFMAP:   src = plan.pfmap.data(); n = (int64_t)plan.pfmap.size(); words = sizeof(ts::PfSlot) / 4; break;

@@ -178,9 +178,34 @@ def test_head_dim_64_mixed_batch_and_every_fp8_code():
     assert np.array_equal(out, ref)                          # weight 1 on one key: exact
 
 
+@pytest.mark.parametrize("kv,head_dim", [("bf16", 128), ("fp8", 128), ("bf16", 64), ("fp8", 64)])
+@pytest.mark.parametrize("lengths", ["whole", "even", "even_short_rows", "even_long", "fit", "many"])
+def test_decode_rows_dealt_out(lengths, kv, head_dim):
+    """The ways decode rows are cut (whole rows packed over the CUs; dealt out evenly, one or more items per workgroup,
+    rows of one page between long ones, a row cut into more items than are merged in the kernel; pieces that fit
+    the CUs; more rows than workgroups), each against the oracle on every row, and run-to-run identical."""
+    import paper_2512_03416_amd as ts
+    rng = np.random.default_rng(5)
+    ctx = {"whole": rng.integers(300, 700, 64), "even": rng.integers(500, 9000, 36), "fit": rng.integers(20, 900, 16),
+           "even_short_rows": np.where(np.arange(60) % 3 == 0, rng.integers(3000, 9000, 60), rng.integers(1, 17, 60)),
+           "even_long": np.array([50000, 1, 3000, 17, 20000]), "many": rng.integers(1, 200, 300)}[lengths]
+    shape = AttnShape(8, 4, head_dim, "bf16", kv)
+    ones = [1] * len(ctx)
+    b = make_batch(shape, ones, ctx, seed=36, pool_rule=1.1, value_mult=0.5 if kv == "bf16" else 1.0)
+    print(f"[case] {lengths} kv={kv} D={head_dim} rows={len(ctx)}", flush=True)
+    ref, rk, rv = oracle.run_batch(W.to_cpu(b))
+    first = None
+    for rep in range(3):
+        out, gk, gv = gpu().run_batch(b, fused_append=rep > 0)
+        assert same_bytes(gk, rk) and same_bytes(gv, rv)
+        assert float(np.max(np.abs(out - ref))) <= TOL[kv]
+        assert first is None or rep == 1 or np.array_equal(out, first)
+        first = out
+
+
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_split_rows_merged_by_their_last_item_or_by_a_launch(kv):
-    """Rows cut into 2 ... 60 items: merged by the merge launch (default) and inside the decode kernel by the last
+    """Rows cut into 2 ... 60 items: merged by the merge launch (the default for that many) and inside the decode kernel by the last
     item to arrive; both within the bar, each bit-identical over 20 repetitions on one context (the order of the
     sums is fixed, whichever item comes last), next to a prefill chunk in all three launch modes."""
     import paper_2512_03416_amd as ts
