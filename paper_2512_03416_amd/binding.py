@@ -129,17 +129,23 @@ def _np_ptr(a: Optional[np.ndarray]):
     return ctypes.c_void_p(a.ctypes.data if a is not None and a.size else 0) if a is not None else ctypes.c_void_p(0)
 
 
-def _dev_ptr(t) -> ctypes.c_void_p:
-    """Device pointer of a torch tensor (or None / int)."""
+def _dev_ptr(t) -> int:
+    """Device pointer of a torch tensor (or None / int), as the integer that a void* argument takes."""
     if t is None:
-        return ctypes.c_void_p(0)
+        return 0
     if isinstance(t, int):
-        return ctypes.c_void_p(t)
+        return t
     if not t.is_cuda:
         raise ValueError("expected a GPU tensor")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _i32_bytes(a) -> bytes:
+    """int32 values as bytes, which a void* argument takes as they are (host arrays are consumed by the call).
+    A quarter of the time of going through numpy's ctypes interface, twice per pass."""
+    return np.asarray(a, dtype=np.int32).tobytes()
 
 
 def check_desc(desc: Desc) -> int:
@@ -186,6 +192,21 @@ def plan_decode_items(desc: Desc, q_lens, ctx_lens, split_pages: int = 0) -> np.
     return plan_export(desc, q_lens, ctx_lens, "decode", split_pages)[:, :5]
 
 
+_raw_stream = None
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream.  torch.cuda.current_stream() builds a Stream object for it (2.9 us a call); the
+    function under it returns the handle itself (0.1 us)."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()                        # initialises the GPU if nothing has yet
+        get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        _raw_stream = (lambda: get(device())) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
+
+
 class Context:
     """Owns a ts_ctx.  Methods mirror the C entry points one to one."""
 
@@ -218,13 +239,12 @@ class Context:
             raise TokenScaleError(rc, self.last_error())
 
     @staticmethod
-    def _stream(stream) -> ctypes.c_void_p:
+    def _stream(stream) -> int:
         if stream is None:
-            import torch
-            return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+            return _current_stream()
         if isinstance(stream, int):
-            return ctypes.c_void_p(stream)
-        return ctypes.c_void_p(stream.cuda_stream)
+            return stream
+        return stream.cuda_stream
 
     def reserve(self, max_tokens: int, max_seqs: int, max_ctx_pages: int):
         self._check(self._lib.ts_reserve(self._h, max_tokens, max_seqs, max_ctx_pages))
@@ -241,22 +261,20 @@ class Context:
 
     def kv_append(self, k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_table, q_lens,
                   ctx_lens, stream=None):
-        ql, cl = _i32(q_lens), _i32(ctx_lens)
         self._check(self._lib.ts_kv_append(self._h, self._stream(stream), _dev_ptr(k_new), _dev_ptr(v_new),
                                            _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(k_scale),
-                                           _dev_ptr(v_scale), _dev_ptr(block_table), _np_ptr(ql),
-                                           _np_ptr(cl), len(ql)))
+                                           _dev_ptr(v_scale), _dev_ptr(block_table), _i32_bytes(q_lens),
+                                           _i32_bytes(ctx_lens), len(q_lens)))
 
     def mixed_paged_attention(self, q, k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_table,
                               q_lens, ctx_lens, sm_scale: float, out, stream=None, noalloc: bool = False):
         """noalloc=True calls ts_mixed_paged_attention_noalloc (same arguments)."""
-        ql, cl = _i32(q_lens), _i32(ctx_lens)
         fn = self._lib.ts_mixed_paged_attention_noalloc if noalloc else self._lib.ts_mixed_paged_attention
-        self._check(fn(
-            self._h, self._stream(stream), _dev_ptr(q), _dev_ptr(k_new), _dev_ptr(v_new),
-            _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(k_scale), _dev_ptr(v_scale),
-            _dev_ptr(block_table), _np_ptr(ql), _np_ptr(cl), len(ql), ctypes.c_float(sm_scale),
-            _dev_ptr(out)))
+        rc = fn(self._h, self._stream(stream), _dev_ptr(q), _dev_ptr(k_new), _dev_ptr(v_new),
+                _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(k_scale), _dev_ptr(v_scale),
+                _dev_ptr(block_table), _i32_bytes(q_lens), _i32_bytes(ctx_lens), len(q_lens), sm_scale, _dev_ptr(out))
+        if rc != TS_OK:
+            self._check(rc)
 
     def kernel_times(self, reset: bool = False) -> dict:
         """{kernel name: (launches, mean ms)} of the launches timed since the last reset."""

@@ -827,12 +827,10 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
     DeviceGuard guard(c->device);
     c->timing_now = c->timing > 0 && (c->timing_pass++ % (uint64_t)c->timing) == 0;
     PlanOptions opt = c->opt;
+    opt.append_only = true;
     build_plan(c->desc, q_lens, ctx_lens, num_seqs, opt, &c->plan);
     if (c->plan.info.total_tokens == 0) return TS_OK;
     if (!k_new || !v_new) return fail(c, TS_ERR_INVALID_ARG, "k_new / v_new is NULL");
-    // only the sequence table is needed on the device
-    c->plan.dec.clear(); c->plan.dec_wg.clear(); c->plan.cmb.clear(); c->plan.pf.clear(); c->plan.rt.clear(); c->plan.rtcut.clear(); c->plan.pfmap.clear();
-    c->plan.queue.clear(); c->plan.q_off.clear();
     const WorkLayout w = layout_of(c->plan);
     hipStream_t st = (hipStream_t)stream;
     // no page check: the upload rides along in the first append launch
@@ -883,6 +881,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     if (c->dec_slots > 0) c->opt.wg_slots = c->dec_slots;
     {
         PlanOptions opt = c->opt;
+        opt.for_launch = true;
         if (c->static_call) {                              // (no scratch for widened pages or for partial results of cut tiles)
             opt.widen_pages = 0;
             opt.pf_split_min_keys = 0;

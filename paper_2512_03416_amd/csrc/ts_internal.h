@@ -65,20 +65,16 @@ struct PfSlot {           // workgroup -> (prefill tile, KV head); item < 0 = no
     int32_t head_kv;
 };
 
-struct QItem {            // entry of a per-die work queue of the persistent mixed kernel
-    int32_t kind;         // 0 = decode item, 1 = prefill tile
+struct QItem {            // entry of a per-die work queue of the persistent kernels
     int32_t item;
-    int32_t head_kv;
-    int32_t pad;
+    int32_t kind_head;    // KV head (low 16 bits); above it 0 = decode item, 1 = prefill tile
 };
 
 struct AppTile {          // one cache page of a chunk's new tokens; launched once per KV head
     int32_t seq;
     int32_t page_idx;     // index into the sequence's page list
-    int32_t slot_lo;      // new tokens occupy slots [slot_lo, slot_hi) of the page
-    int32_t slot_hi;
+    int32_t slots;        // new tokens occupy slots [slots & 255, slots >> 8) of the page
     int32_t row_slot0;    // row (in k_new / v_new) that slot 0 of the page would hold
-    int32_t pad0, pad1, pad2;
 };
 constexpr int kAppendTileMin = 8;   // sequences with at least this many new tokens are appended page-wise
 struct AppRow {           // one new token of the token-wise list
@@ -126,6 +122,8 @@ struct Plan {
     int32_t max_split = 1;           // most items that a decode row is cut into
     std::vector<int32_t> wide_base;  // per sequence: number of its first widened page, -1 = not widened
     ts_plan_info info{};
+
+    void clear();                    // empties the lists, keeps their memory
 };
 
 struct PlanOptions {
@@ -134,6 +132,8 @@ struct PlanOptions {
     int32_t n_cu = 256;         // compute units of the GPU
     int32_t xcds = 8;           // accelerator dies; workgroup i is dispatched to die i % xcds
     int32_t mixed_mode = TS_MIXED_CORESIDENT;   // how a batch with decode rows and prefill chunks is launched
+    bool append_only = false;   // only the append lists are wanted
+    bool for_launch = false;    // leave out the one of pfmap / queue that the launch form does not read
     bool generic_only = false;  // every row through the generic kernel
     bool prefill_generic = false;
     int32_t tile_tokens = 0;    // query tokens per prefill tile

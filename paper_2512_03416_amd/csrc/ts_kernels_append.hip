@@ -166,10 +166,11 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
     }
     const int g = blockIdx.x % Hkv;
     const AppTile it = a.apt[blockIdx.x / Hkv];
+    const int slot_lo = it.slots & 255, slot_hi = it.slots >> 8;
     const int tid = threadIdx.x, t = tid / CPR, c = tid % CPR;
     const bool loader = tid < kPage * CPR;
     const int64_t page = a.block_table[(int64_t)it.seq * a.geo.max_pages + it.page_idx];
-    const bool mine = loader && t >= it.slot_lo && t < it.slot_hi;
+    const bool mine = loader && t >= slot_lo && t < slot_hi;
     uint4 kv = make_uint4(0, 0, 0, 0), vv = kv;
     if (mine) {
         const int64_t src = ((int64_t)(it.row_slot0 + t) * Hkv + g) * D + 8 * c;
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
         if constexpr (sizeof(DST) == 1) *(uint4*)(ks + t * kRowPad + 8 * c) = kv;
     }
     __syncthreads();
-    const bool full = it.slot_lo == 0 && it.slot_hi == kPage;
+    const bool full = slot_lo == 0 && slot_hi == kPage;
 
     if constexpr (sizeof(DST) == 2) {
         uint16_t* kt = (uint16_t*)a.k_cache + tile_elem_base(page, Hkv, g, D);
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
             } else {
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    if (8 * hf + i >= it.slot_lo && 8 * hf + i < it.slot_hi) __builtin_nontemporal_store(e[i], &dst[i]);
+                    if (8 * hf + i >= slot_lo && 8 * hf + i < slot_hi) __builtin_nontemporal_store(e[i], &dst[i]);
             }
         }
     } else {
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
         if (tid < D) {
             // K tile [D/16 chunks of 16 dims][16 slots][16]: thread (chunk = tid / 16, slot = tid % 16)
             const int c16 = tid >> 4, slot = tid & 15;
-            if (slot >= it.slot_lo && slot < it.slot_hi) {
+            if (slot >= slot_lo && slot < slot_hi) {
                 float x[16];
 #pragma unroll
                 for (int i = 0; i < 16; ++i) x[i] = bf16_bits_to_float(ks[slot * kRowPad + 16 * c16 + i]) / kscale;
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
             } else {
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    if (i >= it.slot_lo && i < it.slot_hi)
+                    if (i >= slot_lo && i < slot_hi)
                         __builtin_nontemporal_store((uint8_t)(w[i >> 2] >> (8 * (i & 3))), &dst[i]);
             }
         }

@@ -339,58 +339,55 @@ static int64_t pf_keys(const PfItem& t)
     return std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
 }
 
-static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode)
+static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool for_launch)
 {
-    p.pfmap.clear();
-    p.queue.clear();
-    p.q_off.clear();
     if (p.pf.empty()) return;
-    struct Stream { int32_t seq; int32_t g; int64_t work; std::vector<int32_t> items; };
+    const bool queued = mixed_mode != TS_MIXED_SEPARATE && !p.dec.empty();
+    // the tiles sequence by sequence, longest first (p.pf is sorted longest first, the stable sort keeps that)
+    std::vector<int32_t> tiles(p.pf.size());
+    for (size_t i = 0; i < tiles.size(); ++i) tiles[i] = (int32_t)i;
+    std::stable_sort(tiles.begin(), tiles.end(), [&](int32_t a, int32_t b) { return p.pf[a].seq < p.pf[b].seq; });
+    struct Stream { int32_t begin, end, g; int64_t work; };        // tiles[begin, end) of one sequence, for one KV head
     std::vector<Stream> streams;
-    {
-        std::vector<int32_t> order(p.pf.size());
-        for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
-        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return p.pf[a].seq < p.pf[b].seq; });
-        size_t i = 0;
-        while (i < order.size()) {
-            size_t j = i;
-            int64_t work = 0;
-            std::vector<int32_t> items;
-            while (j < order.size() && p.pf[order[j]].seq == p.pf[order[i]].seq) {
-                const PfItem& it = p.pf[order[j]];
-                work += std::min(it.prefix + it.tok_begin + it.tok_count, it.kv_end) - it.kv_begin;
-                items.push_back(order[j]);       // p.pf is sorted longest first, the stable sort keeps that
-                ++j;
-            }
-            for (int g = 0; g < Hkv; ++g) streams.push_back(Stream{p.pf[order[i]].seq, g, work, items});
-            i = j;
-        }
+    for (size_t i = 0, j; i < tiles.size(); i = j) {
+        int64_t work = 0;
+        for (j = i; j < tiles.size() && p.pf[tiles[j]].seq == p.pf[tiles[i]].seq; ++j) work += pf_keys(p.pf[tiles[j]]);
+        for (int g = 0; g < Hkv; ++g) streams.push_back(Stream{(int32_t)i, (int32_t)j, g, work});
     }
     std::stable_sort(streams.begin(), streams.end(), [](const Stream& a, const Stream& b) { return a.work > b.work; });
-    std::vector<std::vector<PfSlot>> per(xcds);
+    std::vector<std::vector<Stream>> on(xcds);
     std::vector<int64_t> load(xcds, 0);
+    std::vector<size_t> n_tiles(xcds, 0);
     for (const Stream& st : streams) {
-        int best = 0;
-        for (int x = 1; x < xcds; ++x) if (load[x] < load[best]) best = x;
+        const size_t best = std::min_element(load.begin(), load.end()) - load.begin();
         load[best] += st.work;
-        for (int32_t it : st.items) per[best].push_back(PfSlot{it, st.g});
+        n_tiles[best] += st.end - st.begin;
+        on[best].push_back(st);
     }
-    size_t longest = 0;
-    for (auto& v : per) longest = std::max(longest, v.size());
-    p.pfmap.assign(longest * xcds, PfSlot{-1, 0});
-    for (int x = 0; x < xcds; ++x)
-        for (size_t k = 0; k < per[x].size(); ++k) p.pfmap[k * xcds + x] = per[x][k];
-    if (mixed_mode == TS_MIXED_SEPARATE || p.dec.empty()) return;
+    if (!(for_launch && queued)) {
+        p.pfmap.assign(*std::max_element(n_tiles.begin(), n_tiles.end()) * xcds, PfSlot{-1, 0});
+        for (int x = 0; x < xcds; ++x) {
+            size_t k = x;
+            for (const Stream& st : on[x])
+                for (int32_t t = st.begin; t < st.end; ++t, k += xcds) p.pfmap[k] = PfSlot{tiles[t], st.g};
+        }
+    }
+    if (!queued) return;
     if (mixed_mode == TS_MIXED_CORESIDENT) {
         // The tiles alone, die by die in the launch order above, for the resident prefill workgroups; the
         // decode items run as a grid of their own next to them.
         p.q_off.assign(xcds + 1, 0);
         for (int x = 0; x < xcds; ++x) {
-            for (const PfSlot& t : per[x]) p.queue.push_back(QItem{1, t.item, t.head_kv, 0});
+            for (const Stream& st : on[x])
+                for (int32_t t = st.begin; t < st.end; ++t) p.queue.push_back(QItem{tiles[t], st.g | 1 << 16});
             p.q_off[x + 1] = (int32_t)p.queue.size();
         }
         return;
     }
+    std::vector<std::vector<PfSlot>> per(xcds);
+    for (int x = 0; x < xcds; ++x)
+        for (const Stream& st : on[x])
+            for (int32_t t = st.begin; t < st.end; ++t) per[x].push_back(PfSlot{tiles[t], st.g});
 
     // Mixed batch: one queue per die for the persistent kernel.  Decode items (HBM-bound) and
     // prefill tiles (MFMA-bound) are interleaved by their share of their own kind's total cost, so
@@ -414,22 +411,31 @@ static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode)
             if (dkey <= pkey) {                            // decode first on ties (Sec. 4.5.2)
                 const PfSlot& d = dper[x][di++];
                 dacc += p.dec[d.item].page_end - p.dec[d.item].page_begin;
-                p.queue.push_back(QItem{0, d.item, d.head_kv, 0});
+                p.queue.push_back(QItem{d.item, d.head_kv});
             } else {
                 const PfSlot& t = per[x][ti++];
                 pacc += pf_keys(p.pf[t.item]);
-                p.queue.push_back(QItem{1, t.item, t.head_kv, 0});
+                p.queue.push_back(QItem{t.item, t.head_kv | 1 << 16});
             }
         }
         p.q_off[x + 1] = (int32_t)p.queue.size();
     }
 }
 
+void Plan::clear()
+{
+    seqs.clear(); dec.clear(); dec_wg.clear(); cmb.clear(); pf.clear(); pfcmb.clear(); pfmap.clear(); apt.clear(); apr.clear();
+    queue.clear(); q_off.clear(); rt.clear(); rtcut.clear(); wide.clear(); wide_base.clear();
+    dec_deep = false;
+    max_split = 1;
+    info = ts_plan_info{};
+}
+
 void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs,
                 const PlanOptions& opt, Plan* plan)
 {
     Plan& p = *plan;
-    p = Plan();
+    p.clear();
     const bool mfma = desc_uses_mfma(d) && !opt.generic_only;
     const bool mfma_dec = desc_uses_mfma_decode(d) && !opt.generic_only;
     // fp8 caches: can the pages of the chunks' sequences be widened to bf16 for this pass (see below)?
@@ -476,10 +482,11 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         for (int32_t pg = m.prefix / kPage; pg <= (m.ctx_len - 1) / kPage; ++pg) {
             const int32_t lo = std::max(m.prefix, pg * kPage) - pg * kPage;
             const int32_t hi = std::min(m.ctx_len, (pg + 1) * kPage) - pg * kPage;
-            p.apt.push_back(AppTile{s, pg, lo, hi, m.q_off + pg * kPage - m.prefix, 0, 0, 0});
+            p.apt.push_back(AppTile{s, pg, lo | hi << 8, m.q_off + pg * kPage - m.prefix});
         }
     }
 
+    if (opt.append_only) return;
     const int32_t TT = opt.tile_tokens > 0 ? opt.tile_tokens : prefill_tile_tokens(d);
     int64_t tile_heads = 0;                                // prefill workgroups of the batch
     if (mfma_tiles)
@@ -629,7 +636,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         p.pf.swap(sorted);
         for (PfCmb& cm : p.pfcmb) cm.item = where[cm.item];
     }
-    map_prefill_to_xcds(p, Hkv, std::max(1, opt.xcds), mixed_mode);
+    map_prefill_to_xcds(p, Hkv, std::max(1, opt.xcds), mixed_mode, opt.for_launch);
     std::stable_sort(p.rt.begin(), p.rt.end(), [&](const RowTile& a, const RowTile& b) {
         return row_tile_pages(p, a) > row_tile_pages(p, b);
     });
@@ -697,7 +704,7 @@ extern "C" int64_t ts_plan_export(const ts_attn_desc* desc, const int32_t* q_len
     ts::build_plan(*desc, q_lens, ctx_lens, num_seqs, opt, &plan);
     const void* src = nullptr;
     int64_t n = 0, words = 0;
-    std::vector<std::array<int32_t, 4>> rows;              // the generic kernel's tiles, row by row
+    std::vector<std::array<int32_t, 4>> rows;              // lists whose records are packed on the device
     if (which == TS_LIST_ROWS) {
         for (const ts::RowTile& t : plan.rt)
             for (int32_t i = 0; i < (t.n_tok_cut & 255) && (t.n_tok_cut < 256 || plan.rtcut[(t.n_tok_cut >> 8) - 1].page_begin == 0); ++i) rows.push_back({t.row0 + i, t.seq, t.pos0 + i + 1, 0});
@@ -713,9 +720,16 @@ extern "C" int64_t ts_plan_export(const ts_attn_desc* desc, const int32_t* q_len
     case TS_LIST_PREFILL: src = plan.pf.data();    n = (int64_t)plan.pf.size();    words = sizeof(ts::PfItem) / 4; break;
     case TS_LIST_PFMAP:   src = plan.pfmap.data(); n = (int64_t)plan.pfmap.size(); words = sizeof(ts::PfSlot) / 4; break;
     case TS_LIST_ROWS:    src = rows.data();       n = (int64_t)rows.size();       words = 4; break;
-    case TS_LIST_QUEUE:   src = plan.queue.data(); n = (int64_t)plan.queue.size(); words = sizeof(ts::QItem) / 4; break;
+    case TS_LIST_QUEUE:
+        for (const ts::QItem& q : plan.queue) rows.push_back({q.kind_head >> 16, q.item, q.kind_head & 0xffff, 0});
+        src = rows.data();       n = (int64_t)rows.size();       words = 4; break;
     case TS_LIST_QOFF:    src = plan.q_off.data(); n = (int64_t)plan.q_off.size(); words = 1; break;
-    case TS_LIST_APPEND:  src = plan.apt.data();   n = (int64_t)plan.apt.size();   words = sizeof(ts::AppTile) / 4; break;
+    case TS_LIST_APPEND:
+        for (const ts::AppTile& t : plan.apt) {
+            rows.push_back({t.seq, t.page_idx, t.slots & 255, t.slots >> 8});
+            rows.push_back({t.row_slot0, 0, 0, 0});
+        }
+        src = rows.data();       n = (int64_t)rows.size() / 2;   words = 8; break;
     case TS_LIST_APPEND_ROWS:
         for (ts::AppRow& r : plan.apr) r.run = 0;           // (launch detail)
         src = plan.apr.data(); n = (int64_t)plan.apr.size(); words = sizeof(ts::AppRow) / 4; break;
