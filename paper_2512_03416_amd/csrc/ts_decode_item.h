@@ -264,8 +264,9 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
     const int it_row = it.row, it_seq = it.seq, it_keys = it.n_keys, it_pb = it.page_begin, it_pe = it.page_end, it_part = it.part;
     // (readfirstlane tells the compiler the wave index is uniform, which keeps everything derived
     // from it -- the page-id loads above all -- on the scalar unit)
-    // (an opaque copy: the lane offsets are worked out per item instead of being kept across a caller's loop)
-    const int tid = opaque((int)threadIdx.x);
+    // (an opaque copy where the caller loops over items: the lane offsets are worked out per item instead of being
+    // kept across the loop)
+    const int tid = THROUGH ? opaque((int)threadIdx.x) : (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, r = lane >> 4, n = lane & 15;
     const int Hq = a.geo.Hq, Hkv = a.geo.Hkv, G = a.geo.G;
@@ -459,7 +460,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
     float l_tot = l + __shfl_xor(l, 16, 64);
     l_tot += __shfl_xor(l_tot, 32, 64);
 
-    const int lane_o = opaque((int)threadIdx.x) & 63, r_o = lane_o >> 4, n_o = lane_o & 15;   // (derived afresh: see above)
+    const int lane_o = THROUGH ? opaque((int)threadIdx.x) & 63 : lane, r_o = lane_o >> 4, n_o = lane_o & 15;   // (derived afresh: see above)
     // ---- merge the waves' states (wave order, so the result is reproducible) ----------------------
     if (mg_busy) __syncthreads();
     if (wave > 0) {

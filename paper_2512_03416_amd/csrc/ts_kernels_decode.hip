@@ -24,12 +24,20 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a)
 template <typename KT, int NBUF, int D>
 __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { decode_workgroup<KT, NBUF, D, true>(a); }
 
-// The default form, two KV tiles in flight per wave, held to 128 vector registers per lane (the attribute
+// The default forms, two KV tiles in flight per wave, held to 128 vector registers per lane (the attribute
 // counts in units of two here): one such workgroup then fits on a CU next to a resident prefill workgroup
 // (see prefill_resident_kernel), and four fit on a CU of their own.  A single workgroup of four waves per CU
 // already keeps enough loads in flight for the bf16 scan to run at its full rate.
+// decode_kernel_lean: one item per workgroup, no merge in the kernel -- next to resident prefill workgroups the
+// shorter code is worth 1.5 % of the pair (the burst configuration: 633 us a pass against 643).
 template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean(AttnArgs a)
+{
+    __shared__ DecMerge<kDecWaves, D> mg;
+    decode_item<KT, 2, kDecWaves, D>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+}
+template <typename KT, int D>
+__global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean_merging(AttnArgs a)
 {
     decode_workgroup<KT, 2, D, false>(a);
 }
@@ -92,7 +100,10 @@ static int launch_decode_t(const AttnArgs& a, hipStream_t st)
     switch (a.dec_nbuf) {
     case 3: hipLaunchKernelGGL((decode_kernel<KT, 3, D>), grid, block, 0, st, a); break;
     case 4: hipLaunchKernelGGL((decode_kernel<KT, 4, D>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((decode_kernel_lean<KT, D>), grid, block, 0, st, a); break;
+    default:
+        if (a.dec_wg || a.cmb_ctr) hipLaunchKernelGGL((decode_kernel_lean_merging<KT, D>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((decode_kernel_lean<KT, D>), grid, block, 0, st, a);
+        break;
     }
     return (int)hipGetLastError();
 }
