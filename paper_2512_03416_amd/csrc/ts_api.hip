@@ -347,14 +347,15 @@ __global__ __launch_bounds__(256) void check_pages_kernel(const SeqMeta* __restr
 }
 
 struct WorkLayout {
-    size_t seqs, dec, dec_wg, cmb, pf, pfcmb, pfmap, rt, rtcut, queue, q_off, apt, apr, wide, wide_base, total;
+    size_t seqs, dec, dec_wg, cmb, pf, pfcmb, pfmap, rt, rtcut, queue, q_off, apt, apr, wide, wide_base, total; bool with_seqs;
 };
 
-WorkLayout layout_of(const Plan& p)
+WorkLayout layout_of(const Plan& p, bool with_seqs)        // (the sequence table serves the page check only)
 {
     WorkLayout w{};
     size_t o = 0;
-    w.seqs = o; o = align16(o + p.seqs.size() * sizeof(SeqMeta));
+    w.seqs = o; o = align16(o + (with_seqs ? p.seqs.size() * sizeof(SeqMeta) : 0));
+    w.with_seqs = with_seqs;
     w.dec = o;  o = align16(o + p.dec.size() * sizeof(DecItem));
     w.dec_wg = o; o = align16(o + p.dec_wg.size() * sizeof(int32_t));
     w.cmb = o;  o = align16(o + p.cmb.size() * sizeof(CmbItem));
@@ -387,7 +388,7 @@ int upload_plan(ts_ctx* c, hipStream_t st, const WorkLayout& w, UploadJob* defer
     if (rc != TS_OK) return rc;
     const Plan& p = c->plan;
     char* h = (char*)slot->ptr;
-    memcpy(h + w.seqs, p.seqs.data(), p.seqs.size() * sizeof(SeqMeta));
+    if (w.with_seqs) memcpy(h + w.seqs, p.seqs.data(), p.seqs.size() * sizeof(SeqMeta));
     if (!p.dec.empty()) memcpy(h + w.dec, p.dec.data(), p.dec.size() * sizeof(DecItem));
     if (!p.dec_wg.empty()) memcpy(h + w.dec_wg, p.dec_wg.data(), p.dec_wg.size() * sizeof(int32_t));
     if (!p.cmb.empty()) memcpy(h + w.cmb, p.cmb.data(), p.cmb.size() * sizeof(CmbItem));
@@ -544,6 +545,25 @@ struct WorkDoneGuard {                                     // records the event 
     ts_ctx* c; hipStream_t st;
     ~WorkDoneGuard() { if (c->cur_slot) (void)mark_work_done(c, st); }
 };
+
+// The append of a batch of few sequences, described by kernel arguments; false = not such a batch (or source rows that
+// are not 16-byte aligned, which only the token-wise kernel takes).
+bool append_seqs_of(const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs, const void* k_new, const void* v_new, AppendSeqs* s)
+{
+    if ((((uintptr_t)k_new | (uintptr_t)v_new) & 15) != 0) return false;
+    s->n = s->n_pages = 0;
+    int32_t row = 0;
+    for (int i = 0; i < num_seqs; ++i) {
+        if (q_lens[i] == 0) continue;
+        if (s->n == kAppendSeqs) return false;
+        const int32_t prefix = ctx_lens[i] - q_lens[i];
+        s->seq[s->n++] = AppendSeq{row, i, prefix, s->n_pages};
+        s->n_pages += (ctx_lens[i] - 1) / kPage - prefix / kPage + 1;
+        row += q_lens[i];
+    }
+    s->seq[s->n] = AppendSeq{row, 0, 0, s->n_pages};
+    return s->n > 0;
+}
 
 Geometry geometry_of(const ts_attn_desc& d)
 {
@@ -826,12 +846,14 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
     if (rc != TS_OK) return rc;
     DeviceGuard guard(c->device);
     c->timing_now = c->timing > 0 && (c->timing_pass++ % (uint64_t)c->timing) == 0;
+    AppendSeqs few;
     PlanOptions opt = c->opt;
     opt.append_only = true;
+    opt.append_lists = !append_seqs_of(q_lens, ctx_lens, num_seqs, k_new, v_new, &few);
     build_plan(c->desc, q_lens, ctx_lens, num_seqs, opt, &c->plan);
     if (c->plan.info.total_tokens == 0) return TS_OK;
     if (!k_new || !v_new) return fail(c, TS_ERR_INVALID_ARG, "k_new / v_new is NULL");
-    const WorkLayout w = layout_of(c->plan);
+    const WorkLayout w = layout_of(c->plan, c->validate_pages);
     hipStream_t st = (hipStream_t)stream;
     // no page check: the upload rides along in the first append launch
     const bool ride = !c->validate_pages;
@@ -845,16 +867,15 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
     a.geo = geometry_of(c->desc);
     a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache;
     a.k_scale = k_scale; a.v_scale = v_scale; a.block_table = block_table;
-    a.seqs = (const SeqMeta*)(c->d_work + w.seqs);
-    a.num_seqs = num_seqs; a.total_tokens = (int32_t)c->plan.info.total_tokens;
+    a.total_tokens = (int32_t)c->plan.info.total_tokens;
     a.apt = (const AppTile*)(c->d_work + w.apt); a.n_apt = (int32_t)c->plan.apt.size();
     a.apr = (const AppRow*)(c->d_work + w.apr); a.n_apr = (int32_t)c->plan.apr.size();
-    if (ride) {
+    if (ride && opt.append_lists) {
         a.apr_host = (const AppRow*)(job.host_lists + w.apr);
         a.apt_host = (const AppTile*)(job.host_lists + w.apt);
         a.up_src = job.src; a.up_dst = job.dst; a.up_n16 = job.n16; a.up_blocks = job.blocks;
     }
-    hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return launch_append(a, stream); });
+    hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return opt.append_lists ? launch_append(a, stream) : launch_append_few(a, few, stream); });
     if (e != hipSuccess) return hip_fail(c, e, "append launch");
     return mark_work_done(c, st);
 }
@@ -879,9 +900,12 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     DeviceGuard guard(c->device);
     c->timing_now = !c->static_call && c->timing > 0 && (c->timing_pass++ % (uint64_t)c->timing) == 0;
     if (c->dec_slots > 0) c->opt.wg_slots = c->dec_slots;
+    AppendSeqs few;
+    const bool append_lists = !k_new || !append_seqs_of(q_lens, ctx_lens, num_seqs, k_new, v_new, &few);
     {
         PlanOptions opt = c->opt;
         opt.for_launch = true;
+        opt.append_lists = k_new && append_lists;
         if (c->static_call) {                              // (no scratch for widened pages or for partial results of cut tiles)
             opt.widen_pages = 0;
             opt.pf_split_min_keys = 0;
@@ -903,7 +927,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         rc = ensure_pf_parts(c, p.info.prefill_parts);
         if (rc != TS_OK) return rc;
     }
-    const WorkLayout w = layout_of(p);
+    const WorkLayout w = layout_of(p, c->validate_pages);
     hipStream_t st = (hipStream_t)stream;
     // new tokens to append and no page check: the upload rides along in the first append launch (not in the
     // allocation-free call, whose upload launch also puts the shared queue heads back to zero)
@@ -927,8 +951,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         ap.geo = geo;
         ap.k_new = k_new; ap.v_new = v_new; ap.k_cache = k_cache; ap.v_cache = v_cache;
         ap.k_scale = k_scale; ap.v_scale = v_scale; ap.block_table = block_table;
-        ap.seqs = (const SeqMeta*)(wb + w.seqs);
-        ap.num_seqs = num_seqs; ap.total_tokens = (int32_t)p.info.total_tokens;
+        ap.total_tokens = (int32_t)p.info.total_tokens;
         ap.apt = (const AppTile*)(wb + w.apt); ap.n_apt = (int32_t)p.apt.size();
         ap.apr = (const AppRow*)(wb + w.apr); ap.n_apr = (int32_t)p.apr.size();
         if (ride) {
@@ -936,7 +959,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
             ap.apt_host = (const AppTile*)(job.host_lists + w.apt);
             ap.up_src = job.src; ap.up_dst = job.dst; ap.up_n16 = job.n16; ap.up_blocks = job.blocks;
         }
-        hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return launch_append(ap, stream); });
+        hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return append_lists ? launch_append(ap, stream) : launch_append_few(ap, few, stream); });
         if (e != hipSuccess) return hip_fail(c, e, "append launch");
     }
     AttnArgs a{};

@@ -132,7 +132,8 @@ struct PlanOptions {
     int32_t n_cu = 256;         // compute units of the GPU
     int32_t xcds = 8;           // accelerator dies; workgroup i is dispatched to die i % xcds
     int32_t mixed_mode = TS_MIXED_CORESIDENT;   // how a batch with decode rows and prefill chunks is launched
-    bool append_only = false;   // only the append lists are wanted
+    bool append_only = false;   // nothing but the append lists is wanted
+    bool append_lists = true;   // the append lists are wanted
     bool for_launch = false;    // leave out the one of pfmap / queue that the launch form does not read
     bool generic_only = false;  // every row through the generic kernel
     bool prefill_generic = false;
@@ -177,7 +178,7 @@ struct AppendArgs {
     void* k_cache; void* v_cache;
     const float* k_scale; const float* v_scale;
     const int32_t* block_table;
-    const SeqMeta* seqs; int32_t num_seqs; int32_t total_tokens;
+    int32_t total_tokens;
     const AppTile* apt; int32_t n_apt;
     const AppRow* apr; int32_t n_apr;
     // Work-list upload riding along in the first append launch (up_blocks > 0): extra workgroups copy
@@ -186,6 +187,19 @@ struct AppendArgs {
     // launch has finished).
     const void* up_src; void* up_dst; int64_t up_n16; int32_t up_blocks;
     const AppRow* apr_host; const AppTile* apt_host;
+};
+
+// Sequences short enough a list to travel as kernel arguments (append of small batches).
+constexpr int kAppendSeqs = 128;
+struct AppendSeq {
+    int32_t row0;              // first new token's row; the next entry's row0 (a last one behind the sequences) ends it
+    int32_t seq;
+    int32_t prefix;
+    int32_t first_page;        // pages that the sequences before it append to
+};
+struct AppendSeqs {
+    int32_t n, n_pages, pad0, pad1;
+    AppendSeq seq[kAppendSeqs + 1];
 };
 
 struct AttnArgs {
@@ -242,6 +256,7 @@ struct SmallLists {
 
 // Launchers (defined in the .hip files).  All return a hipError_t cast to int.
 int launch_append(const AppendArgs& a, void* stream);
+int launch_append_few(const AppendArgs& a, const AppendSeqs& s, void* stream);
 int launch_rows(const AttnArgs& a, void* stream);
 int launch_decode(const AttnArgs& a, void* stream);
 int launch_combine(const AttnArgs& a, void* stream);

@@ -2,7 +2,8 @@
 //
 // Prefill builds cache entries for all input tokens, a decode iteration adds the entry of the
 // last token (paper Sec. 2.1); in a Convertible Decoder both kinds of rows arrive in one batch
-// (Sec. 3.4).  Three kernels:
+// (Sec. 3.4).  Kernels:
+//   - append_small_kernel: batches of few sequences, see there;
 //   - append_run_kernel: fp32 caches, see there;
 //   - append_token_kernel: one workgroup per new token of a short sequence (decode rows): looks up the
 //     token's page and slot and scatters its Hkv x D values of K (16-byte dim-chunks) and V
@@ -18,16 +19,19 @@
 
 namespace ts {
 
+// The work-list upload that rides along in the workgroups from first_block on.
+__device__ __forceinline__ void upload_lists(const AppendArgs& a, int first_block)
+{
+    const int64_t stride = (int64_t)a.up_blocks * blockDim.x;
+    for (int64_t i = (int64_t)((int)blockIdx.x - first_block) * blockDim.x + threadIdx.x; i < a.up_n16; i += stride)
+        ((uint4*)a.up_dst)[i] = ((const uint4*)a.up_src)[i];
+}
+
 // bf16 source rows; DST: cache element type (uint16_t bf16 bits, uint8_t e4m3).
 template <typename DST>
 __global__ __launch_bounds__(256) void append_token_kernel(AppendArgs a)
 {
-    if ((int)blockIdx.x >= a.n_apr) {                  // work-list upload riding along
-        const int64_t stride = (int64_t)a.up_blocks * blockDim.x;
-        for (int64_t i = (int64_t)(blockIdx.x - a.n_apr) * blockDim.x + threadIdx.x; i < a.up_n16; i += stride)
-            ((uint4*)a.up_dst)[i] = ((const uint4*)a.up_src)[i];
-        return;
-    }
+    if ((int)blockIdx.x >= a.n_apr) { upload_lists(a, a.n_apr); return; }
     const AppRow r = a.apr[blockIdx.x];
     const int row = r.row, pos = r.pos;
     const int Hkv = a.geo.Hkv, D = a.geo.D;
@@ -70,27 +74,17 @@ __global__ __launch_bounds__(256) void append_token_kernel(AppendArgs a)
     }
 }
 
-// fp32 cache: one workgroup per (run of new tokens of one page, KV head); the run's first record leads, the others'
-// workgroups have nothing to do.  Waves 0-1 write K (16-byte chunks, neighbouring slots together), waves 2-3 write V:
-// a thread holds all slots of one dim and stores them as whole 16-byte pieces, so a page's V lines leave the
-// L2 complete.  (One token per workgroup stored V in single 4-byte pieces, 64 bytes apart.)
+// fp32 cache, the new tokens of one page for one KV head: waves 0-1 write K (16-byte chunks, neighbouring slots
+// together), waves 2-3 write V: a thread holds all slots of one dim and stores them as whole 16-byte pieces, so a
+// page's V lines leave the L2 complete.  (One token per workgroup stored V in single 4-byte pieces, 64 bytes apart.)
 template <int D>
-__global__ __launch_bounds__(256) void append_run_kernel(AppendArgs a)
+__device__ __forceinline__ void append_page_f32(const AppendArgs& a, const AppTile it, int g)
 {
     const int Hkv = a.geo.Hkv;
-    if ((int)blockIdx.x >= a.n_apr * Hkv) {            // work-list upload riding along
-        const int64_t stride = (int64_t)a.up_blocks * blockDim.x;
-        for (int64_t i = (int64_t)(blockIdx.x - a.n_apr * Hkv) * blockDim.x + threadIdx.x; i < a.up_n16; i += stride)
-            ((uint4*)a.up_dst)[i] = ((const uint4*)a.up_src)[i];
-        return;
-    }
-    const int g = blockIdx.x % Hkv;
-    const AppRow rec = a.apr[blockIdx.x / Hkv];
-    if (rec.run == 0) return;
-    const int64_t page = a.block_table[(int64_t)rec.seq * a.geo.max_pages + (rec.pos >> 4)];
+    const int64_t page = a.block_table[(int64_t)it.seq * a.geo.max_pages + it.page_idx];
     const int64_t tile = tile_elem_base(page, Hkv, g, D);
-    const int lo = rec.pos & (kPage - 1), hi = lo + rec.run;
-    const int64_t src0 = ((int64_t)(rec.row - lo) * Hkv + g) * D, row_step = (int64_t)Hkv * D;   // of slot 0
+    const int lo = it.slots & 255, hi = it.slots >> 8;
+    const int64_t src0 = ((int64_t)it.row_slot0 * Hkv + g) * D, row_step = (int64_t)Hkv * D;
     const int tid = threadIdx.x;
     if (tid < 128) {
         const float* src = (const float*)a.k_new;
@@ -148,24 +142,16 @@ __device__ __forceinline__ void encode_e4m3x16(const float (&x)[16], uint32_t (&
 }
 
 // bf16 source rows, head dim D = 64 or 128; DST = uint16_t (bf16 cache) or uint8_t (e4m3 cache).
-// Thread (t = tid / (D/8), c = tid % (D/8)) loads the 16 bytes (dims 8c .. 8c+7) of slot t's K and V row
+// One cache page for one KV head: thread (t = tid / (D/8), c = tid % (D/8)) loads the 16 bytes (dims 8c .. 8c+7) of slot t's K and V row
 // (head dim 64: the first 128 threads).
 template <typename DST, int D>
-__global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
+__device__ __forceinline__ void append_page(const AppendArgs& a, const AppTile it, int g)
 {
     constexpr int CPR = D / 8;                         // 16-byte pieces per source row
     constexpr int kRowPad = D + 8;                     // LDS row stride in elements: avoids bank conflicts
     __shared__ __align__(16) uint16_t ks[16 * kRowPad];
     __shared__ __align__(16) uint16_t vs[16 * kRowPad];
     const int Hkv = a.geo.Hkv;
-    if ((int)blockIdx.x >= a.n_apt * Hkv) {            // work-list upload riding along
-        const int64_t stride = (int64_t)a.up_blocks * blockDim.x;
-        for (int64_t i = (int64_t)(blockIdx.x - a.n_apt * Hkv) * blockDim.x + threadIdx.x; i < a.up_n16; i += stride)
-            ((uint4*)a.up_dst)[i] = ((const uint4*)a.up_src)[i];
-        return;
-    }
-    const int g = blockIdx.x % Hkv;
-    const AppTile it = a.apt[blockIdx.x / Hkv];
     const int slot_lo = it.slots & 255, slot_hi = it.slots >> 8;
     const int tid = threadIdx.x, t = tid / CPR, c = tid % CPR;
     const bool loader = tid < kPage * CPR;
@@ -239,6 +225,78 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
             }
         }
     }
+}
+
+template <typename DST, int D>
+__device__ __forceinline__ void append_any_page(const AppendArgs& a, const AppTile it, int g)
+{
+    if constexpr (sizeof(DST) == 4) append_page_f32<D>(a, it, g);
+    else append_page<DST, D>(a, it, g);
+}
+
+// Page-wise list of the plan.
+template <typename DST, int D>
+__global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
+{
+    const int pages = a.n_apt * a.geo.Hkv;
+    if ((int)blockIdx.x >= pages) upload_lists(a, pages);
+    else append_page<DST, D>(a, a.apt[blockIdx.x / a.geo.Hkv], blockIdx.x % a.geo.Hkv);
+}
+
+// fp32 cache, token-wise list: the first record of a page's run of new tokens stands for the run, the workgroups of
+// the others have nothing to do.
+template <int D>
+__global__ __launch_bounds__(256) void append_run_kernel(AppendArgs a)
+{
+    const int n = a.n_apr * a.geo.Hkv;
+    if ((int)blockIdx.x >= n) { upload_lists(a, n); return; }
+    const AppRow r = a.apr[blockIdx.x / a.geo.Hkv];
+    const int lo = r.pos & (kPage - 1);
+    if (r.run > 0) append_page_f32<D>(a, AppTile{r.seq, r.pos >> 4, lo | (lo + r.run) << 8, r.row - lo}, blockIdx.x % a.geo.Hkv);
+}
+
+// Batches of few sequences: every new token goes page by page (a decode row is a page with one new token), and the
+// sequences' descriptions arrive as kernel arguments: one launch instead of two for a batch of both kinds, and no
+// list to read over PCIe before the first page id can be asked for.  A workgroup finds its sequence by comparing its
+// page number with the sequences' first page numbers, one per lane.
+template <typename DST, int D>
+__global__ __launch_bounds__(256) void append_small_kernel(AppendArgs a, AppendSeqs s)
+{
+    const int Hkv = a.geo.Hkv;
+    const int u = blockIdx.x / Hkv, g = blockIdx.x % Hkv;
+    if (u >= s.n_pages) { upload_lists(a, s.n_pages * Hkv); return; }
+    const int lane = threadIdx.x & 63;
+    int i = -1;
+#pragma unroll
+    for (int b = 0; b < kAppendSeqs; b += 64)
+        i += __builtin_popcountll(__ballot(b + lane < s.n && s.seq[min(b + lane, kAppendSeqs - 1)].first_page <= u));
+    const AppendSeq q = s.seq[i];
+    const int q_len = s.seq[i + 1].row0 - q.row0, page_idx = (q.prefix >> 4) + u - q.first_page;
+    const int lo = max(q.prefix - page_idx * kPage, 0), hi = min(q.prefix + q_len - page_idx * kPage, kPage);
+    append_any_page<DST, D>(a, AppTile{q.seq, page_idx, lo | hi << 8, q.row0 + page_idx * kPage - q.prefix}, g);
+}
+
+template <typename DST, int D>
+static int launch_append_small(const AppendArgs& a, const AppendSeqs& s, hipStream_t st)
+{
+    const dim3 grid((unsigned)s.n_pages * (unsigned)a.geo.Hkv + (unsigned)a.up_blocks);
+    hipLaunchKernelGGL((append_small_kernel<DST, D>), grid, dim3(256), 0, st, a, s);
+    return (int)hipGetLastError();
+}
+
+int launch_append_few(const AppendArgs& a, const AppendSeqs& s, void* stream)
+{
+    if (s.n <= 0) return (int)hipSuccess;
+    if (s.n > kAppendSeqs || s.n_pages <= 0 || (a.geo.D != 128 && a.geo.D != 64)) return (int)hipErrorInvalidValue;
+    hipStream_t st = (hipStream_t)stream;
+    const bool d128 = a.geo.D == 128;
+    if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32)
+        return d128 ? launch_append_small<float, 128>(a, s, st) : launch_append_small<float, 64>(a, s, st);
+    if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16)
+        return d128 ? launch_append_small<uint16_t, 128>(a, s, st) : launch_append_small<uint16_t, 64>(a, s, st);
+    if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3)
+        return d128 ? launch_append_small<uint8_t, 128>(a, s, st) : launch_append_small<uint8_t, 64>(a, s, st);
+    return (int)hipErrorInvalidValue;
 }
 
 int launch_append(const AppendArgs& args, void* stream)
