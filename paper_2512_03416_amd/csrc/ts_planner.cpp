@@ -334,12 +334,20 @@ static void sort_decode_items(std::vector<DecItem>& v)
 // are launched next to each other: they walk the stream's pages almost in step, and the pages are
 // fetched from HBM about once instead of once per tile.  Streams are spread over the dies by
 // decreasing work (greedy), longest tiles of a stream first.
+// A die with at most two tiles per CU whose streams' K/V stay in its 4 MB of L2 anyway (kDieResidentBytes) launches
+// its tiles longest first instead: by streams, the later streams' long tiles come last and set the time.  8 prompts
+// of 128-512 tokens (1.5 tiles per CU) 33.9 -> 30.6 us, 16 of 64-256 (1.25) 32.4 -> 29.3; with more tiles the dispatch
+// evens out by itself and the order by streams is the better one: 8 prompts of 512-1024 tokens (3 tiles per CU)
+// 81 us, longest first 84; 16 of them 143 against 153.
+constexpr int64_t kDieResidentBytes = 2 << 20;
+constexpr size_t kLongestFirstTilesPerCu = 2;
 static int64_t pf_keys(const PfItem& t)
 {
     return std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
 }
 
-static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool for_launch)
+static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool for_launch, int64_t kv_row_bytes,
+                                int32_t n_cu)
 {
     if (p.pf.empty()) return;
     const bool queued = mixed_mode != TS_MIXED_SEPARATE && !p.dec.empty();
@@ -364,12 +372,23 @@ static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool
         n_tiles[best] += st.end - st.begin;
         on[best].push_back(st);
     }
+    // the die's (tile, head) pairs in launch order
+    auto tiles_of = [&](int x) {
+        std::vector<PfSlot> v;
+        int64_t keys = 0;
+        for (const Stream& st : on[x]) {
+            keys += p.pf[tiles[st.begin]].ctx_len;
+            for (int32_t t = st.begin; t < st.end; ++t) v.push_back(PfSlot{tiles[t], st.g});
+        }
+        if (v.size() <= kLongestFirstTilesPerCu * (size_t)(n_cu / xcds) && keys * kv_row_bytes <= kDieResidentBytes)
+            std::stable_sort(v.begin(), v.end(), [&](const PfSlot& a, const PfSlot& b) { return pf_keys(p.pf[a.item]) > pf_keys(p.pf[b.item]); });
+        return v;
+    };
     if (!(for_launch && queued)) {
         p.pfmap.assign(*std::max_element(n_tiles.begin(), n_tiles.end()) * xcds, PfSlot{-1, 0});
         for (int x = 0; x < xcds; ++x) {
             size_t k = x;
-            for (const Stream& st : on[x])
-                for (int32_t t = st.begin; t < st.end; ++t, k += xcds) p.pfmap[k] = PfSlot{tiles[t], st.g};
+            for (const PfSlot& t : tiles_of(x)) { p.pfmap[k] = t; k += xcds; }
         }
     }
     if (!queued) return;
@@ -378,8 +397,7 @@ static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool
         // decode items run as a grid of their own next to them.
         p.q_off.assign(xcds + 1, 0);
         for (int x = 0; x < xcds; ++x) {
-            for (const Stream& st : on[x])
-                for (int32_t t = st.begin; t < st.end; ++t) p.queue.push_back(QItem{tiles[t], st.g | 1 << 16});
+            for (const PfSlot& t : tiles_of(x)) p.queue.push_back(QItem{t.item, t.head_kv | 1 << 16});
             p.q_off[x + 1] = (int32_t)p.queue.size();
         }
         return;
@@ -636,7 +654,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         p.pf.swap(sorted);
         for (PfCmb& cm : p.pfcmb) cm.item = where[cm.item];
     }
-    map_prefill_to_xcds(p, Hkv, std::max(1, opt.xcds), mixed_mode, opt.for_launch);
+    map_prefill_to_xcds(p, Hkv, std::max(1, opt.xcds), mixed_mode, opt.for_launch, 2 * 2 * d.head_dim, opt.n_cu);
     std::stable_sort(p.rt.begin(), p.rt.end(), [&](const RowTile& a, const RowTile& b) {
         return row_tile_pages(p, a) > row_tile_pages(p, b);
     });

@@ -320,6 +320,29 @@ def test_plan_invariants_on_seeded_random_batches(seed):
     assert seen == {(s, p) for s in range(n) for p in range(ctx[s] - ql[s], ctx[s])}
 
 
+@pytest.mark.parametrize("lens,longest_first", [([512, 128, 300, 130, 444, 257, 65, 2], True), ([64] * 16, True),
+                                                ([1024] * 8, False), ([300] * 24, False)])
+def test_launch_order_of_few_prompts(lens, longest_first):
+    """A die with at most two tiles per CU takes them longest first; with more, one (chunk, KV head) stream after the
+    other.  Either way every (tile, head) is launched once and a stream stays on one die."""
+    desc = ts.Desc.make(32, 8, 128, "bf16", "bf16", 4096, 128)
+    pf = ts.plan_export(desc, lens, lens, "prefill")
+    pfmap = ts.plan_export(desc, lens, lens, "pfmap")
+    live = [(int(t), int(g)) for t, g in pfmap if t >= 0]
+    assert sorted(live) == sorted((t, g) for t in range(len(pf)) for g in range(8))
+    home = {}
+    for x in range(8):
+        die = [(int(t), int(g)) for t, g in pfmap[x::8] if t >= 0]
+        keys = [pf[t][3] + pf[t][4] + pf[t][5] for t, _ in die]
+        streams = [(int(pf[t][0]), g) for t, g in die]
+        for st in streams:
+            assert home.setdefault(st, x) == x
+        if longest_first:
+            assert keys == sorted(keys, reverse=True)
+        else:
+            assert len([1 for a, b in zip([None] + streams, streams) if a != b]) == len(set(streams))
+
+
 def test_kernels_fit_their_register_budget_without_spilling():
     """The co-resident launch rests on register budgets: resident prefill workgroups at <= 192 vector registers
     per lane (two waves per SIMD) next to a lean decode workgroup at <= 128, and no kernel may spill (a spill
