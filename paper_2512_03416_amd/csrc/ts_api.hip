@@ -59,6 +59,7 @@ hipError_t static_scratch_of(int device, unsigned char** out)
 }
 
 constexpr int kRing = 4;
+constexpr int kPfCtrWord = 128;
 
 struct HostSlot {
     void* ptr = nullptr;             // pinned host memory ...
@@ -80,7 +81,8 @@ struct ts_ctx {
     char* d_work = nullptr;  size_t work_cap = 0;
     float* d_part_o = nullptr; float* d_part_ml = nullptr; int64_t part_cap = 0;
     int32_t* d_cmb_ctr = nullptr;    // arrival counters of split decode rows (part_cap x Hkv, zero between launches)
-    int32_t* d_q_ctr = nullptr;      // queue heads of the persistent kernel (zero between launches)
+    int32_t* d_q_ctr = nullptr;      // queue heads of the persistent kernel and, from word kPfCtrWord on, arrival
+                                     // counters of cut prefill tiles (zero between launches)
     float* d_pf_part_o = nullptr; float* d_pf_part_ml = nullptr; int64_t pf_part_cap = 0;   // partial results of cut prefill tiles
     char* d_wide_k = nullptr; char* d_wide_v = nullptr; int64_t wide_cap = 0;   // fp8 caches: widened pages (capacity in pages)
     unsigned char* d_static = nullptr;  // this GPU's copy of the static scratch array
@@ -626,8 +628,9 @@ extern "C" int ts_create(const ts_attn_desc* desc, int device, ts_ctx** out)
     rc = ensure_work(c, 1 << 16);
     if (rc == TS_OK) rc = ensure_partials(c, 1024);
     if (rc == TS_OK) {
-        if (hipMalloc((void**)&c->d_q_ctr, 128 * sizeof(int32_t)) != hipSuccess ||
-            hipMemset(c->d_q_ctr, 0, 128 * sizeof(int32_t)) != hipSuccess) {
+        const size_t words = kPfCtrWord + (size_t)c->opt.n_cu;
+        if (hipMalloc((void**)&c->d_q_ctr, words * sizeof(int32_t)) != hipSuccess ||
+            hipMemset(c->d_q_ctr, 0, words * sizeof(int32_t)) != hipSuccess) {
             c->err = "queue counter allocation failed";
             rc = TS_ERR_NOMEM;
         }
@@ -973,6 +976,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     a.cmb = (const CmbItem*)(wb + w.cmb);   a.n_cmb = (int32_t)p.cmb.size();
     a.pf = (const PfItem*)(wb + w.pf);      a.n_pf = (int32_t)p.pf.size();
     a.pfcmb = (const PfCmb*)(wb + w.pfcmb); a.n_pfcmb = (int32_t)p.pfcmb.size();
+    a.pf_ctr = c->d_q_ctr + kPfCtrWord;
     a.pf_part_o = c->d_pf_part_o; a.pf_part_ml = c->d_pf_part_ml;
     a.pfmap = (const PfSlot*)(wb + w.pfmap); a.n_pfmap = (int32_t)p.pfmap.size();
     a.rt = (const RowTile*)(wb + w.rt);     a.n_rt = (int32_t)p.rt.size(); a.rtcut = (const RowCut*)(wb + w.rtcut);
@@ -1041,7 +1045,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         e = (hipError_t)timed_launch(c, TS_K_PREFILL, a.n_pf > 0, st, [&] { return launch_prefill(a, stream); });
         if (e != hipSuccess) return hip_fail(c, e, "prefill launch");
     }
-    e = (hipError_t)timed_launch(c, TS_K_COMBINE, a.n_pfcmb > 0, st, [&] { return launch_prefill_combine(a, stream); });
+    e = (hipError_t)timed_launch(c, TS_K_COMBINE, p.pf_merge_launch, st, [&] { return p.pf_merge_launch ? launch_prefill_combine(a, stream) : 0; });
     if (e != hipSuccess) return hip_fail(c, e, "prefill combine launch");
     rc = mark_work_done(c, st);
     if (rc != TS_OK) return rc;

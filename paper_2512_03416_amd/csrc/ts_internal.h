@@ -49,16 +49,21 @@ struct PfItem {           // a causal tile of a prefill chunk; launched once per
                           // keys [kv_begin, kv_end) only and writes partial result number `part`
     int32_t kv_begin;     // multiple of 64, at most the tile's first query position: every row sees key kv_begin
     int32_t kv_end;       // multiple of 64, or INT32_MAX for "up to the tile's last key"
-    int32_t pad0, pad1;
+    int32_t merge;        // cut tile: 1 + its index in the merge list when the last of its parts merges them, else 0
+    int32_t pad1;
 };
 
 struct PfCmb {            // a tile whose key range was cut: its partial results part_begin .. part_begin + n_part - 1
     int32_t item;         // index of the tile's first part in the prefill list (for the rows it covers)
     int32_t part_begin;
     int32_t n_part;
-    int32_t pad;
+    int32_t in_kernel;    // 1 = the tile's last part merges them, 0 = prefill_combine_kernel
 };
 constexpr int kPfPartRows = 256;   // rows of one prefill partial result (a whole tile)
+// A tile of at most this many parts is merged by its last one.  512 tokens over 8200 cached ones (64/8 heads, e4m3, 2
+// parts) 154.3 -> 144.0 us a pass, 400 over 4096 (32/8 heads, 4 parts) 53.1 -> 45.2.  The last part of a tile of
+// eight reads 0.9 MB by itself: 256 tokens over 4096 take 40.3 us that way, 38.6 with the merge launch.
+constexpr int kPfMergeParts = 4;
 
 struct PfSlot {           // workgroup -> (prefill tile, KV head); item < 0 = nothing to do
     int32_t item;
@@ -107,6 +112,7 @@ struct Plan {
     std::vector<SeqMeta> seqs;       // S + 1
     std::vector<DecItem> dec;
     std::vector<int32_t> dec_wg;     // decode items dealt out evenly: offsets of the workgroups' items (else empty)
+    bool pf_merge_launch = false;    // some cut tiles are left to prefill_combine_kernel
     bool dec_deep = false;           // ... for the kernel with three KV tiles in flight per wave
     std::vector<CmbItem> cmb;
     std::vector<PfItem> pf;
@@ -228,9 +234,10 @@ struct AttnArgs {
     int32_t mixed_wgs;         // workgroups of the persistent kernel that are resident on the GPU at once
     int32_t n_cu;              // compute units of the GPU
     int32_t pf_wgs;            // co-resident launch: resident workgroups for the prefill tiles (at most one per CU)
-    // prefill tiles cut along the keys: partial results o [part][kv head][256 rows][D] fp32 (unnormalised),
-    // ml [part][kv head][256 rows][2] = (reference maximum in log2 units, weight sum)
-    const PfCmb* pfcmb; int32_t n_pfcmb;
+    // prefill tiles cut along the keys: partial results o [part][kv head][256 x D] fp32 (unnormalised, see PfParts),
+    // ml [part][kv head][256 rows][2] = (reference maximum in log2 units, weight sum); pf_ctr: arrival counters of
+    // the tiles merged by their last part, one per (entry of the merge list, KV head), zero between launches
+    const PfCmb* pfcmb; int32_t n_pfcmb; int32_t* pf_ctr;
     float* pf_part_o; float* pf_part_ml;
     // Arrival counters of the split decode rows, one per (combine row, KV head), zero between launches: the
     // workgroup that finds n_split - 1 in it is the last of the row and merges the partials itself.  NULL = the

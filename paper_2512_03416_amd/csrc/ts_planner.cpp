@@ -444,7 +444,7 @@ void Plan::clear()
 {
     seqs.clear(); dec.clear(); dec_wg.clear(); cmb.clear(); pf.clear(); pfcmb.clear(); pfmap.clear(); apt.clear(); apr.clear();
     queue.clear(); q_off.clear(); rt.clear(); rtcut.clear(); wide.clear(); wide_base.clear();
-    dec_deep = false;
+    dec_deep = pf_merge_launch = false;
     max_split = 1;
     info = ts_plan_info{};
 }
@@ -612,6 +612,14 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
                 p.pf.push_back(PfItem{s, m.q_off, m.q_len, m.prefix, t0, cnt, m.ctx_len, pf_part++, begin * 64, INT32_MAX, 0, 0});
                 ++made;
                 p.pfcmb.push_back(PfCmb{(int32_t)p.pf.size() - made, first, made, 0});
+                // (the lists are exported without this launch detail; the counters hold n_cu words: cut tiles are
+                // fewer than half the CUs)
+                if (opt.for_launch && made <= kPfMergeParts && (int64_t)p.pfcmb.size() * Hkv <= opt.n_cu) {
+                    p.pfcmb.back().in_kernel = 1;
+                    for (int32_t k = 1; k <= made; ++k) p.pf[p.pf.size() - k].merge = (int32_t)p.pfcmb.size();
+                } else {
+                    p.pf_merge_launch = true;
+                }
             }
         } else {
             const int32_t TR = row_tile_tokens(d);

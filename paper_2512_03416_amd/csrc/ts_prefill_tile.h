@@ -212,6 +212,84 @@ __device__ __forceinline__ constexpr int pf_slot_op(bool warm, int j)
     }
 }
 
+// Partial results of the parts of a tile that was cut along the keys.  o: 256 x D fp32 per (part, KV head) as the
+// waves hold them -- register group i (b = i / 4, j = i % 4: dims 32 b + 8 j + 4 h .. + 3 of row 32 wave + n) of lane
+// (n, h) at ((wave * D / 8 + i) * 64 + lane) * 4 -- so that every instruction moves a whole 1 KB run; ml: (reference
+// maximum, weight sum) per row.  The parts pass from one workgroup to another, perhaps on another die, within the
+// launch: stores and loads carry the device-scope bit (sc1), which takes them past the die's L2.
+template <int D>
+struct PfParts {
+    static constexpr int kDevice = 16;                     // cache policy bit sc1
+    static constexpr int kRaw = 0x00027000;                // buffer of untyped 32-bit data, offsets in bytes
+    float* o; float* ml; int64_t step;                     // step: rows between two parts
+    __device__ __forceinline__ PfParts(const AttnArgs& a, int first, int g)
+    {
+        const int64_t row = ((int64_t)first * a.geo.Hkv + g) * kPfPartRows;
+        o = a.pf_part_o + row * D; ml = a.pf_part_ml + row * 2; step = (int64_t)a.geo.Hkv * kPfPartRows;
+    }
+    // (a buffer of no bytes: its loads read nothing and return zeros)
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t o_of(int k, bool in = true) const
+    { return __builtin_amdgcn_make_buffer_rsrc((void*)(o + k * step * D), (short)0, in ? kPfPartRows * D * 4 : 0, kRaw); }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t ml_of(int k, bool in = true) const
+    { return __builtin_amdgcn_make_buffer_rsrc((void*)(ml + k * step * 2), (short)0, in ? kPfPartRows * 8 : 0, kRaw); }
+    static __device__ __forceinline__ int at(int wave, int lane, int i) { return ((wave * (D / 8) + i) * 64 + lane) * 16; }
+    static __device__ __forceinline__ f32x4 load(__amdgpu_buffer_rsrc_t r, int off)
+    { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kDevice)); }
+    static __device__ __forceinline__ f32x2 load_ml(__amdgpu_buffer_rsrc_t r, int row)
+    { return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, row * 8, 0, kDevice)); }
+    __device__ __forceinline__ void store(int k, int wave, int lane, const f32x16 (&acc)[D / 32], float m, float l) const
+    {
+        const __amdgpu_buffer_rsrc_t r = o_of(k);
+#pragma unroll
+        for (int i = 0; i < D / 8; ++i) {
+            const f32x16& x = acc[i / 4];
+            const f32x4 v = {x[4 * (i % 4)], x[4 * (i % 4) + 1], x[4 * (i % 4) + 2], x[4 * (i % 4) + 3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, at(wave, lane, i), 0, kDevice);
+        }
+        if (lane < 32)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{m, l}), ml_of(k), (32 * wave + lane) * 8, 0, kDevice);
+    }
+};
+
+// Merge by the tile's last part, which still holds its own result (part `mine`) in registers, in part order:
+//   M = max m_i,  acc = sum o_i 2^(m_i - M),  l = sum l_i 2^(m_i - M)
+// A register group is read back from the other parts where it is needed and added up in the order of the parts, so
+// the result does not depend on which part came last.
+template <int D>
+__device__ __forceinline__ void pf_merge_parts(const PfParts<D>& parts, int mine, int n_part, int wave, int lane,
+                                               f32x16 (&acc)[D / 32], float m, float& l)
+{
+    f32x2 ml[kPfMergeParts];
+#pragma unroll
+    for (int k = 0; k < kPfMergeParts; ++k) ml[k] = PfParts<D>::load_ml(parts.ml_of(k, k < n_part && k != mine), 32 * wave + (lane & 31));
+    float M = m, w[kPfMergeParts];
+#pragma unroll
+    for (int k = 0; k < kPfMergeParts; ++k) {
+        if (k == mine) ml[k] = f32x2{m, l};
+        if (k < n_part) M = fmaxf(M, ml[k].x);
+    }
+    float L = 0.f;
+#pragma unroll
+    for (int k = 0; k < kPfMergeParts; ++k) {
+        w[k] = k < n_part ? __builtin_amdgcn_exp2f(ml[k].x - M) : 0.f;
+        L += ml[k].y * w[k];
+    }
+    l = L;
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) {
+        f32x16& x = acc[i / 4];
+        const f32x4 own = {x[4 * (i % 4)], x[4 * (i % 4) + 1], x[4 * (i % 4) + 2], x[4 * (i % 4) + 3]};
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kPfMergeParts; ++k) {
+            const f32x4 v = PfParts<D>::load(parts.o_of(k, k < n_part && k != mine), PfParts<D>::at(wave, lane, i));
+            s += (k == mine ? own : v) * w[k];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * (i % 4) + e] = s[e];
+    }
+}
+
 // One causal tile for KV head g, executed by a workgroup of kPfThreads threads.  All threads must call
 // it; it ends with a workgroup barrier, so lds may be reused right after it returns.
 // tid: the thread's index in the workgroup (a caller that runs tiles in a loop passes an opaque copy, so
@@ -637,22 +715,42 @@ __device__ __forceinline__ void prefill_tile(const AttnArgs& a, int item_idx, in
     // store one whole 256-byte row as 16-byte pieces and an instruction covers 4 rows.
     // (Lane indices are derived afresh from an opaque copy of the thread index: nothing of this stage then
     // occupies a register during the loops above.)
+    float l_row = pair32_sum(l_part);
     if (it.part >= 0) {
         // One part of a tile cut along the keys: the unnormalised rows and their (reference maximum, weight sum)
-        // go to the partial-result buffers as they are; prefill_combine_kernel merges the parts.
-        const int tid_o = opaque(tid), wave_o = __builtin_amdgcn_readfirstlane(tid_o >> 6), lane_o = tid_o & 63,
-                  h_o = lane_o >> 5, n_o = lane_o & 31;
-        const int64_t slot = ((int64_t)it.part * a.geo.Hkv + g) * kPfPartRows + 32 * wave_o + n_o;
-        float* po = a.pf_part_o + slot * D + 4 * h_o;
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *(f32x4*)(po + 32 * b + 8 * j) = f32x4{acc[b][4 * j], acc[b][4 * j + 1], acc[b][4 * j + 2], acc[b][4 * j + 3]};
-        const float l_row = pair32_sum(l_part);
-        if (h_o == 0) *(float2*)(a.pf_part_ml + slot * 2) = make_float2(m_ref, l_row);
-        __syncthreads();                                   // LDS may be reused by the caller
-        return;
+        // go to the partial-result buffers as they are.  The part of a tile that gets here last merges them
+        // (pf_merge_parts) and goes on to the output; a tile of many parts is left to prefill_combine_kernel.
+        const int tid_o = opaque(tid), wave_o = __builtin_amdgcn_readfirstlane(tid_o >> 6), lane_o = tid_o & 63;
+        const int merge = as_constant((const int32_t*)(a.pf + opaque_uniform(item_idx)))[10];
+        int first = it.part, n_part = 1;
+        if (merge > 0) {
+            const int32_t TS_CONSTANT* cm = as_constant((const int32_t*)(a.pfcmb + (merge - 1)));
+            first = cm[1]; n_part = cm[2];
+        }
+        const PfParts<D> parts{a, first, g};
+        parts.store(it.part - first, wave_o, lane_o, acc, m_ref, l_row);
+        bool last = false;
+        if (merge > 0) {
+            // (each wave waits for its own stores, the barrier for every wave's: then the part is where the others'
+            // loads find it, and its arrival is counted.  LDS word: behind the rows staged below.)
+            int* const s_last = (int*)(lds.v[kPfRing - 1] + 4 * PB) - 1;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid_o == 0) {
+                int32_t* ctr = a.pf_ctr + (int64_t)(merge - 1) * a.geo.Hkv + g;
+                const int seen = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (seen == n_part - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+                *s_last = seen == n_part - 1;
+            }
+            __syncthreads();
+            last = __builtin_amdgcn_readfirstlane(*s_last) != 0;
+            asm volatile("" ::: "memory");
+            if (last) pf_merge_parts(parts, it.part - first, n_part, wave_o, lane_o, acc, m_ref, l_row);
+        }
+        if (!last) {
+            __syncthreads();                               // LDS may be reused by the caller
+            return;
+        }
     }
     constexpr int kOutStride = 2 * D + 16;                 // bytes of a staged row (16 bytes of padding against bank conflicts)
     constexpr int kLanesPerRow = D / 8, kRowsPerStep = 64 / kLanesPerRow;
@@ -660,7 +758,6 @@ __device__ __forceinline__ void prefill_tile(const AttnArgs& a, int item_idx, in
               h_o = lane_o >> 5, n_o = lane_o & 31;
     unsigned char* ob = (unsigned char*)&lds + wave_o * (32 * kOutStride);
     const float vscale = fp8_cache ? as_constant(a.v_scale)[g] : 1.0f;
-    const float l_row = pair32_sum(l_part);
     const float inv = vscale / l_row;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
