@@ -555,16 +555,15 @@ bool append_seqs_of(const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs
     if ((((uintptr_t)k_new | (uintptr_t)v_new) & 15) != 0) return false;
     s->n = s->n_pages = 0;
     int32_t row = 0;
+    if (num_seqs > kAppendSeqs) return false;
     for (int i = 0; i < num_seqs; ++i) {
-        if (q_lens[i] == 0) continue;
-        if (s->n == kAppendSeqs) return false;
         const int32_t prefix = ctx_lens[i] - q_lens[i];
-        s->seq[s->n++] = AppendSeq{row, i, prefix, s->n_pages};
-        s->n_pages += (ctx_lens[i] - 1) / kPage - prefix / kPage + 1;
+        s->seq[s->n++] = AppendSeq{row, prefix, s->n_pages};
+        if (q_lens[i] > 0) s->n_pages += (ctx_lens[i] - 1) / kPage - prefix / kPage + 1;
         row += q_lens[i];
     }
-    s->seq[s->n] = AppendSeq{row, 0, 0, s->n_pages};
-    return s->n > 0;
+    s->seq[s->n] = AppendSeq{row, 0, s->n_pages};
+    return s->n_pages > 0;
 }
 
 Geometry geometry_of(const ts_attn_desc& d)

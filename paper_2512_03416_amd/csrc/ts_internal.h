@@ -195,11 +195,12 @@ struct AppendArgs {
     const AppRow* apr_host; const AppTile* apt_host;
 };
 
-// Sequences short enough a list to travel as kernel arguments (append of small batches).
-constexpr int kAppendSeqs = 128;
-struct AppendSeq {
+// Sequences short enough a list to travel as kernel arguments (append of small batches): 3 KB of the 4 KB there are.
+// Against lists read from the staging buffer: 200 rows and 4 chunks of 128-512 tokens 170.9 -> 167.1 us a pass, 140 rows
+// of 100-400 tokens 39.9 -> 39.1, 128 rows of 1024-8192 and 4 chunks of 2048 648.8 -> 644.0.
+constexpr int kAppendSeqs = 256;
+struct AppendSeq {             // entry i: sequence i of the batch
     int32_t row0;              // first new token's row; the next entry's row0 (a last one behind the sequences) ends it
-    int32_t seq;
     int32_t prefix;
     int32_t first_page;        // pages that the sequences before it append to
 };
@@ -252,14 +253,18 @@ struct AttnArgs {
     const void* k_new; const void* v_new;
 };
 
-// Work lists short enough to travel as kernel arguments (fused form of small decode-only batches).
-constexpr int kSmallDec = 64, kSmallCmb = 32;
+// Work lists short enough to travel as kernel arguments (fused form of small decode-only batches).  The arguments hold
+// 4 KB: 88 items.  48 rows of 200-6000 tokens dealt out in 79 items (head dim 64): 55.9 us a pass with an append launch
+// and the lists in memory, 54.3 in this form; 80 rows of 500-3000 tokens (e4m3) 58.4 and 56.8.
+constexpr int kSmallDec = 88, kSmallCmb = 32;
 struct SmallLists {
     int32_t n_dec, n_cmb, n_wg, pad;
     DecItem dec[kSmallDec];
     CmbItem cmb[kSmallCmb];
     uint8_t wg[kSmallDec + 4];       // workgroup w works through the items [wg[w], wg[w + 1])
 };
+
+static_assert(sizeof(AttnArgs) + sizeof(SmallLists) <= 4096 && sizeof(AppendArgs) + sizeof(AppendSeqs) <= 4096, "kernel arguments");
 
 // Launchers (defined in the .hip files).  All return a hipError_t cast to int.
 int launch_append(const AppendArgs& a, void* stream);

@@ -258,7 +258,8 @@ __global__ __launch_bounds__(256) void append_run_kernel(AppendArgs a)
 // Batches of few sequences: every new token goes page by page (a decode row is a page with one new token), and the
 // sequences' descriptions arrive as kernel arguments: one launch instead of two for a batch of both kinds, and no
 // list to read over PCIe before the first page id can be asked for.  A workgroup finds its sequence by comparing its
-// page number with the sequences' first page numbers, one per lane.
+// page number with the sequences' first page numbers, one per lane (a sequence without new tokens has none and shares
+// the number of the next one: the last match counts).
 template <typename DST, int D>
 __global__ __launch_bounds__(256) void append_small_kernel(AppendArgs a, AppendSeqs s)
 {
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(256) void append_small_kernel(AppendArgs a, AppendS
     const AppendSeq q = s.seq[i];
     const int q_len = s.seq[i + 1].row0 - q.row0, page_idx = (q.prefix >> 4) + u - q.first_page;
     const int lo = max(q.prefix - page_idx * kPage, 0), hi = min(q.prefix + q_len - page_idx * kPage, kPage);
-    append_any_page<DST, D>(a, AppTile{q.seq, page_idx, lo | hi << 8, q.row0 + page_idx * kPage - q.prefix}, g);
+    append_any_page<DST, D>(a, AppTile{i, page_idx, lo | hi << 8, q.row0 + page_idx * kPage - q.prefix}, g);
 }
 
 template <typename DST, int D>

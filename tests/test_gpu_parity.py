@@ -203,6 +203,22 @@ def test_decode_rows_dealt_out(lengths, kv, head_dim):
         first = out
 
 
+@pytest.mark.parametrize("kv,rows", [("bf16", 70), ("fp8", 88), ("bf16", 89), ("f32", 70), ("bf16", 256), ("fp8", 257), ("f32", 256)])
+def test_sequences_as_kernel_arguments(kv, rows):
+    """Batches around the largest whose decode items (88) and sequences (256) travel as kernel arguments, with
+    sequences that bring nothing in front, between and behind, and chunks next to the rows."""
+    shape = AttnShape(8, 2, 64, "f32" if kv == "f32" else "bf16", kv)
+    rng = np.random.default_rng(rows)
+    ones, ctx = [1] * rows, list(rng.integers(1, 60, rows))
+    mult = 0.7 if kv == "f32" else 0.5 if kv == "bf16" else 1.0
+    check(make_batch(shape, ones, ctx, seed=71, pool_rule=1.1, value_mult=mult), what="rows")
+    for i in (0, 3, 4, rows - 1):
+        ones[i] = 0
+    ones[10], ctx[10] = 37, 37 + 5
+    ones[rows - 2], ctx[rows - 2] = 16, 48
+    check(make_batch(shape, ones, ctx, seed=72, pool_rule=1.1, value_mult=mult), what="rows, chunks and idle sequences")
+
+
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_split_rows_merged_by_their_last_item_or_by_a_launch(kv):
     """Rows cut into 2 ... 60 items: merged by the merge launch (the default for that many) and inside the decode kernel by the last
