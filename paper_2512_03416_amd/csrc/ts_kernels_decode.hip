@@ -42,6 +42,17 @@ __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))
     decode_workgroup<KT, 2, D, false>(a);
 }
 
+// A launch on its own (no resident prefill workgroups next to it): prefetches past the end of an item read nothing.  A
+// wave of decode_kernel_lean repeats its last page up to three times, which matters where rows are short (a wave of a
+// row of 100 tokens has two pages): 200 rows of 16-200 tokens 34.4 -> 31.3 us a pass, 140 of 100-400 39.1 -> 36.3, 256
+// of 512-4096 386.8 -> 384.4, 500 of 100-600 152 -> 142.  (Batches of items cut or dealt out showed no difference.  Within 128 registers the bf16 form spills; at three workgroups per CU it does not.)
+template <typename KT, int D>
+__global__ __launch_bounds__(64 * kDecWaves, 3) void decode_kernel_alone(AttnArgs a)
+{
+    __shared__ DecMerge<kDecWaves, D> mg;
+    decode_item<KT, 2, kDecWaves, D, false, false, true>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+}
+
 // Small decode-only batches are bound by their launches and by the chain of dependent reads at the start of an
 // item.  Their fused form has one launch less and one link less: the items append the rows' new tokens themselves
 // (decode_item<..., FUSED>: no append launch) and arrive as kernel arguments (no upload of the work lists and
@@ -102,6 +113,7 @@ static int launch_decode_t(const AttnArgs& a, hipStream_t st)
     case 4: hipLaunchKernelGGL((decode_kernel<KT, 4, D>), grid, block, 0, st, a); break;
     default:
         if (a.dec_wg || a.cmb_ctr) hipLaunchKernelGGL((decode_kernel_lean_merging<KT, D>), grid, block, 0, st, a);
+        else if (a.n_queue == 0) hipLaunchKernelGGL((decode_kernel_alone<KT, D>), grid, block, 0, st, a);   // (queues: the tiles of a co-resident launch)
         else hipLaunchKernelGGL((decode_kernel_lean<KT, D>), grid, block, 0, st, a);
         break;
     }
