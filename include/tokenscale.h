@@ -187,7 +187,7 @@ const char *ts_last_error(const ts_ctx *ctx);
  *                         which item came last), or by a small launch behind the items.  0 (default) = in the kernel
  *                         while no row of the batch has more than 16 items, 1 = in the kernel always.  (Prefetch
  *                         depths other than the default and mixed_mode 1 always take the launch.)  Same results
- *   "decode_fused_append"  1 (default) / 0.  A pass that appends, holds decode rows only and is small (at most 64
+ *   "decode_fused_append"  1 (default) / 0.  A pass that appends, holds decode rows only and is small (at most 88
  *                         decode items and 32 split rows: its work lists travel as kernel arguments) leaves
  *                         the append to the decode items: the workgroup that reads a row's last page takes the
  *                         new token from k_new / v_new, converts it exactly as the append kernels do, and
