@@ -225,9 +225,11 @@ __device__ __forceinline__ SplitSum merge_chunk(const PARTS& parts, int k0, int 
     for (int j = 0; j < kMergeChunk; ++j) c.m = fmaxf(c.m, ml[j].x);
 #pragma unroll
     for (int j = 0; j < kMergeChunk; ++j) {
-        const float w = k0 + j < n_split ? __builtin_amdgcn_exp2f(ml[j].x - c.m) : 0.0f;
-        c.l += ml[j].y * w;
-        c.o += o[j] * w;
+        if (k0 + j < n_split) {                            // (past the end: no weight of 0, which an infinite sum would turn into NaN)
+            const float w = __builtin_amdgcn_exp2f(ml[j].x - c.m);
+            c.l += ml[j].y * w;
+            c.o += o[j] * w;
+        }
     }
     return c;
 }

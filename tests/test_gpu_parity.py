@@ -250,6 +250,24 @@ def test_split_rows_merged_by_their_last_item_or_by_a_launch(kv):
                 ctx.close()
 
 
+@pytest.mark.parametrize("merge", [0, 1])
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
+def test_split_rows_with_infinite_values_in_their_last_part(kv, merge):
+    """A cut row whose newest token holds an infinite V element: that element of the output is infinite, as the
+    oracle has it, whatever the number of parts (1 ... 20 of them, merged eight at a time), and nothing else is."""
+    shape = AttnShape(8, 2, 64, "f32" if kv == "f32" else "bf16", kv)
+    ctx = [40, 300, 700, 1100, 1300, 1900, 2500]
+    b = make_batch(shape, [1] * len(ctx), ctx, seed=38, pool_rule=1.1, value_mult=0.5)
+    b.v_new[:, :, 3], b.v_new[:, 1, 60] = float("inf"), float("-inf")
+    print(f"[case] {kv} merge={merge}", flush=True)
+    ref, rk, rv = oracle.run_batch(W.to_cpu(b))
+    out, gk, gv = gpu().run_batch(b, options={"decode_split_pages": 8, "decode_merge_in_kernel": merge})
+    assert same_bytes(gk, rk) and same_bytes(gv, rv)
+    ok = np.isfinite(ref)
+    assert np.isinf(ref[~ok]).all() and np.array_equal(out[~ok], ref[~ok])
+    assert np.isfinite(out[ok]).all() and float(np.max(np.abs(out[ok] - ref[ok]))) <= TOL[kv]
+
+
 def test_decode_large_scores_and_shifting_maximum():
     # keys grow along the sequence so the running maximum keeps rising across pages and splits
     shape = AttnShape(8, 2, 128, "bf16", "bf16")
