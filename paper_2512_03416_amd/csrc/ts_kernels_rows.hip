@@ -71,6 +71,41 @@ __device__ __forceinline__ uint32_t word_of(const uint4& v, int i) { return i ==
 __device__ __forceinline__ uint32_t word_of(const uint2& v, int i) { return i == 0 ? v.x : v.y; }
 __device__ __forceinline__ uint32_t word_of(const uint32_t& v, int) { return v; }
 
+// a lane's four tokens of a V row (e: a constant): is element e an infinity or a NaN (e4m3: S.1111.111), and a 0 in its place
+template <typename KT, typename V> __device__ __forceinline__ bool rt_not_finite(const V& v, int e)
+{
+    constexpr int EW = 4 / (int)sizeof(KT);
+    constexpr uint32_t kExp = sizeof(KT) == 4 ? 0x7f800000u : sizeof(KT) == 2 ? 0x7f80u : 0x7fu;
+    const uint32_t m = kExp << (8 * (int)sizeof(KT) * (e % EW));
+    return (word_of(v, e / EW) & m) == m;
+}
+// the same over all elements of all rows
+template <typename KT, typename V, int N> __device__ __forceinline__ bool rt_any_not_finite(const V (&v)[N])
+{
+    if constexpr (sizeof(KT) == 4) {
+        float x = 0.0f, y = 0.0f;                              // (0 as long as every value is finite: one instruction per value)
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+            x = fmaf(__uint_as_float(v[b].x), 0.0f, x); y = fmaf(__uint_as_float(v[b].y), 0.0f, y);
+            x = fmaf(__uint_as_float(v[b].z), 0.0f, x); y = fmaf(__uint_as_float(v[b].w), 0.0f, y);
+        }
+        return x + y != 0.0f;
+    } else {
+        bool x = false;
+#pragma unroll
+        for (int b = 0; b < N; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x |= rt_not_finite<KT>(v[b], e);
+        return x;
+    }
+}
+template <typename KT, typename V> __device__ __forceinline__ void rt_clear_if(V& v, int e, bool clear)
+{
+    if constexpr (sizeof(KT) == 4) (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = clear ? 0u : word_of(v, e);
+    else if constexpr (sizeof(KT) == 2) (e < 2 ? v.x : v.y) &= clear ? ~(0xffffu << (16 * (e & 1))) : ~0u;
+    else v &= clear ? ~(0xffu << (8 * e)) : ~0u;
+}
+
 template <int D> struct RtMerge {                          // LDS image of the non-leading waves' state
     float o[kRtWaves - 1][D / 16][64][4];
     float m[kRtWaves - 1][16];
@@ -134,7 +169,10 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
             next_k += 1;
             next_id = bt[kRtWaves * min(next_k, np - 1)];
         };
-        auto step = [&](T& tile, int page) {
+        // One page.  MASKED: it reaches past the first token's keys: scores of keys that a column does not see, and V of
+        // slots that no column sees, are masked.
+        auto step = [&](T& tile, int page, auto masked) {
+            constexpr bool MASKED = decltype(masked)::value;
             f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;      // (two chains: half the rounding steps in a row)
 #pragma unroll
             for (int b = 0; b < KB; ++b)
@@ -148,7 +186,7 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i) x[i] = (s0[i] + s1[i]) * c;
             const int tok0 = page * kPage + 4 * r;
-            if ((page + 1) * kPage > keys_min) {           // wave-uniform: the page reaches a column's last key
+            if constexpr (MASKED) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) x[i] = tok0 + i < keys ? x[i] : -INFINITY;
             }
@@ -167,22 +205,36 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(x[i] - m_ref);
             l += (p[0] + p[1]) + (p[2] + p[3]);
-            if ((page + 1) * kPage > keys_max) {           // slots that no column sees hold whatever was there before
+            if constexpr (MASKED) {                        // slots that no column sees hold whatever was there before
 #pragma unroll
-                for (int b = 0; b < VB; ++b) {
-                    if constexpr (sizeof(KT) == 4) {
-                        tile.v[b].x = tok0 < keys_max ? tile.v[b].x : 0u;
-                        tile.v[b].y = tok0 + 1 < keys_max ? tile.v[b].y : 0u;
-                        tile.v[b].z = tok0 + 2 < keys_max ? tile.v[b].z : 0u;
-                        tile.v[b].w = tok0 + 3 < keys_max ? tile.v[b].w : 0u;
-                    } else {
-                        constexpr int EB = 8 * (int)sizeof(KT);
-                        const int nv = min(max(keys_max - tok0, 0), 4);
-                        const uint64_t keep = nv * EB >= 64 ? ~0ull : (1ull << (nv * EB)) - 1ull;
-                        if constexpr (sizeof(KT) == 2) {
-                            tile.v[b].x &= (uint32_t)keep;
-                            tile.v[b].y &= (uint32_t)(keep >> 32);
-                        } else tile.v[b] &= (uint32_t)keep;
+                for (int b = 0; b < VB; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) rt_clear_if<KT>(tile.v[b], e, tok0 + e >= keys_max);
+                // A weight of 0 does not undo an infinite or NaN value: the columns of earlier tokens must not meet the V
+                // of later ones at all.  Tokens with such a value (rare, wave-uniform) are added on the vector ALU, to
+                // the columns that see them, and cleared for the product.
+                if (keys_min < keys_max && __any(rt_any_not_finite<KT>(tile.v))) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        bool odd_e = false;
+#pragma unroll
+                        for (int b = 0; b < VB; ++b) odd_e |= rt_not_finite<KT>(tile.v[b], e);
+                        uint64_t odd = __ballot(odd_e);    // lanes 16 g4 .. + 15 hold V and weights of token 4 g4 + e
+                        for (int g4 = 0; odd; ++g4, odd >>= 16) {
+                            if ((odd & 0xffff) == 0) continue;
+                            const bool seen = page * kPage + 4 * g4 + e < keys;
+                            const float w = __shfl(p[e], 16 * g4 + n, 64);
+#pragma unroll
+                            for (int b = 0; b < VB; ++b) {
+                                const float mine = rt_elem<KT>(word_of(tile.v[b], e / EW), e % EW);
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    const float v = __shfl(mine, 16 * g4 + 4 * r + i, 64);
+                                    acc[b][i] = fmaf(w, seen ? v : 0.0f, acc[b][i]);
+                                }
+                                rt_clear_if<KT>(tile.v[b], e, r == g4);
+                            }
+                        }
                     }
                 }
             }
@@ -192,14 +244,25 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
                 for (int b = 0; b < VB; ++b)
                     acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(rt_elem<KT>(word_of(tile.v[b], e / EW), e % EW), p[e], acc[b], 0, 0, 0);
         };
+        // Pages past the first token's keys are the tile's last one or two (it has at most 16 tokens), so a wave has at most
+        // one of them and it comes last: the loop carries no mask arithmetic, and what the masked page needs in registers
+        // it finds in the buffer that is not filled any more.
+        const int first = it.page_begin + wave, page_last = first + kRtWaves * (np - 1);
+        const bool has_tail = (page_last + 1) * kPage > keys_min;   // wave-uniform
+        const int np_main = np - (has_tail ? 1 : 0);
         T buf[2];
         fetch(buf[0]);
         fetch(buf[1]);
-        for (int k = 0; k < np; k += 2) {
-            step(buf[0], it.page_begin + wave + kRtWaves * k);
+        for (int k = 0; k < np_main; k += 2) {
+            step(buf[0], first + kRtWaves * k, std::false_type{});
             fetch(buf[0]);
-            if (k + 1 < np) step(buf[1], it.page_begin + wave + kRtWaves * (k + 1));   // wave-uniform
+            if (k + 1 >= np_main) break;                   // (the second buffer may hold the masked page)
+            step(buf[1], first + kRtWaves * (k + 1), std::false_type{});
             fetch(buf[1]);
+        }
+        if (has_tail) {
+            if ((np - 1) & 1) buf[0] = buf[1];
+            step(buf[0], page_last, std::true_type{});
         }
     }
 

@@ -75,6 +75,36 @@ def test_generic_row_tiles(dtypes, head_dim, heads):
     check(make_batch(shape, [130], [1800], seed=24, value_mult=0.7), options=opts)
 
 
+@pytest.mark.parametrize("bad", ["inf", "nan"])
+@pytest.mark.parametrize("heads", [(4, 1), (5, 1), (2, 2), (16, 1)], ids=lambda h: f"{h[0]}q{h[1]}kv")
+@pytest.mark.parametrize("dtypes,head_dim", [(("f32", "f32"), 64), (("f32", "f32"), 128), (("bf16", "bf16"), 128),
+                                             (("bf16", "bf16"), 64), (("bf16", "fp8"), 64), (("bf16", "fp8"), 128)],
+                         ids=["f32-64", "f32-128", "bf16-128", "bf16-64", "fp8-64", "fp8-128"])
+def test_generic_rows_do_not_see_later_tokens_whatever_their_values(dtypes, head_dim, heads, bad):
+    """Tokens of a chunk whose V (or, one of them, K) is infinite or NaN: the tokens before them, which share their row
+    tile, come out as the oracle has them; tokens that see one have an infinity or NaN exactly where the oracle does.
+    Pages with one and with several such tokens, prefixes inside a page, tiles whose pages are cut."""
+    if dtypes[1] == "fp8" and bad == "inf":
+        pytest.skip("e4m3 saturates infinities")
+    shape = AttnShape(heads[0], heads[1], head_dim, *dtypes)
+    b = make_batch(shape, [8, 37, 1, 5, 33, 40], [8, 58, 30, 19, 2500, 40], seed=37, pool_rule=1.1, value_mult=0.7)
+    val, row0 = float(bad), np.cumsum([0] + list(b.q_lens))
+    for seq, tok, dim, sign in ((0, 3, 5, 1), (1, 20, 0, 1), (1, 24, head_dim - 1, -1), (1, 36, 7, 1), (3, 4, 3, -1),
+                                (4, 1, 9, 1), (4, 2, 9, 1), (4, 32, 1, -1)):
+        b.v_new[row0[seq] + tok, :, dim] = sign * val
+    b.k_new[row0[5] + 11, :, 2] = val
+    opts = {"prefill_path": 1} if dtypes[0] == "bf16" else None
+    print(f"[case] {bad} {shape}", flush=True)
+    ref, rk, rv = oracle.run_batch(W.to_cpu(b))
+    out, gk, gv = gpu().run_batch(b, options=opts)
+    assert same_bytes(gk, rk) and same_bytes(gv, rv)
+    ok = np.isfinite(ref)
+    assert 0.5 < ok.mean() < 1.0
+    assert np.array_equal(ok, np.isfinite(out))
+    assert np.array_equal(np.isposinf(ref), np.isposinf(out)) and np.array_equal(np.isneginf(ref), np.isneginf(out))
+    assert float(np.max(np.abs(out[ok] - ref[ok]))) <= TOL[dtypes[1]]
+
+
 # ---------------------------------------------------------------------------------------------
 # MFMA decode path (bf16 / fp8 cache, head_dim 128 and 64)
 # ---------------------------------------------------------------------------------------------
