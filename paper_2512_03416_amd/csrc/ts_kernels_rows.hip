@@ -24,7 +24,9 @@ namespace ts {
 
 constexpr int kRtWaves = 4;
 constexpr float kRaiseRt = 16.0f;      // log2 units a score may exceed the reference maximum by before it is raised
-constexpr float kNoKey = -3.0e38f;     // reference maximum of a column that has seen no key (finite: differences stay defined)
+// Reference maximum of a column that has seen no key.  Finite, so that differences stay defined, and the lowest value of
+// the type: any higher score raises it (16 is less than a step of the type there), a score equal to it has weight 1.
+constexpr float kNoKey = -3.402823466e38f;
 
 // One (page, KV head) tile in registers: D / 4 elements of K and of V per lane.
 template <typename KT, int D> struct RtTile {

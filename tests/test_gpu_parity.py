@@ -105,6 +105,29 @@ def test_generic_rows_do_not_see_later_tokens_whatever_their_values(dtypes, head
     assert float(np.max(np.abs(out[ok] - ref[ok]))) <= TOL[dtypes[1]]
 
 
+@pytest.mark.parametrize("score", [-2.2e38, -2.355e38])
+@pytest.mark.parametrize("heads,head_dim", [((4, 1), 64), ((2, 2), 128)], ids=["4q1kv-64", "2q2kv-128"])
+def test_generic_rows_normalise_scores_near_the_lowest_fp32_value(heads, head_dim, score):
+    """All scores of a row at -3.17e38 or -3.397e38 (in log2 units; the type ends at -3.403e38): the row is the mean of its
+    values; and where one key in five scores higher by 1 %, the mean of those.  Chunks, decode rows, cut tiles."""
+    shape = AttnShape(heads[0], heads[1], head_dim, "f32", "f32")
+    b = make_batch(shape, [1, 37, 1, 6], [70, 58, 2500, 6], seed=39, pool_rule=1.1, value_mult=0.7)
+    b.sm_scale = 1.0
+    pre0 = 0
+    for name in ("q", "k_new", "k_prefix"):
+        getattr(b, name).zero_()
+    b.q[:, :, 0] = 1.5e19
+    b.k_new[:, :, 0] = b.k_prefix[:, :, 0] = score / 1.5e19
+    for s in range(2):                                      # sequences 0 and 1: some keys of the prefix higher
+        n = int(b.prefix_lens[s])
+        b.k_prefix[pre0:pre0 + n:5, :, 0] *= 0.99
+        pre0 += n
+    ref, _, _ = oracle.run_batch(W.to_cpu(b))
+    out, _, _ = gpu().run_batch(b)
+    assert np.isfinite(ref).all() and np.isfinite(out).all()
+    assert float(np.max(np.abs(out - ref))) <= TOL["f32"]
+
+
 # ---------------------------------------------------------------------------------------------
 # MFMA decode path (bf16 / fp8 cache, head_dim 128 and 64)
 # ---------------------------------------------------------------------------------------------
