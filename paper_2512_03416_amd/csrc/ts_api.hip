@@ -1032,6 +1032,12 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         for (int32_t i = 0; i <= sl.n_wg; ++i) sl.wg[i] = (uint8_t)(p.dec_wg.empty() ? i : p.dec_wg[i]);
         std::copy(p.dec.begin(), p.dec.end(), sl.dec);
         std::copy(p.cmb.begin(), p.cmb.end(), sl.cmb);
+        if (c->static_call && sl.n_cmb > 0) {
+            // (no upload launch here that puts the arrival counters in the shared scratch back to zero)
+            hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(256), 0, st, (const uint4*)nullptr, (uint4*)nullptr, (int64_t)0,
+                               a.cmb_ctr, (int)(sl.n_cmb * c->desc.num_kv_heads));
+            TS_HIP(c, hipGetLastError());
+        }
         e = (hipError_t)timed_launch(c, TS_K_DECODE, true, st, [&] { return launch_decode_fused(a, sl, stream); });
         if (e != hipSuccess) return hip_fail(c, e, "fused decode launch");
     } else {

@@ -1,6 +1,8 @@
 """The allocation-free entry point against the ordinary one (GPU, through the C ABI).
 
 Collected last on purpose: it runs after every other GPU test of the directory."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -84,4 +86,62 @@ def test_noalloc_entry_point_matches_the_ordinary_one(kv, persistent):
     with pytest.raises(ts.TokenScaleError) as e:
         _pass(ctx, b, noalloc=True)
     assert e.value.code == binding.TS_ERR_UNSUPPORTED
+    ctx.close()
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    with open("/proc/self/maps") as f:
+        return ctypes.CDLL(next(l.split()[-1] for l in f if "libamdhip64.so" in l))
+
+
+@pytest.mark.parametrize("kv,head_dim", [("bf16", 128), ("fp8", 128), ("bf16", 64), ("fp8", 64)])
+def test_noalloc_small_decode_passes_with_split_rows(kv, head_dim):
+    """Decode-only passes whose items append the new tokens and merge the split rows through the arrival counters of
+    the shared scratch: three calls in a row and three replays of a captured one, each byte-equal to the ordinary call
+    and within the bar; and the call puts the counters back to zero itself (its graph: that launch and the pass)."""
+    import gpu_harness as g
+    import oracle
+    import paper_2512_03416_amd as ts
+    shape = AttnShape(8, 2, head_dim, "bf16", kv)
+    ctx_lens = [1400, 17, 900, 2500, 512, 2049]
+    b = g.to_dev(make_batch(shape, [1] * 6, ctx_lens, seed=95, pool_rule=1.1, value_mult=0.5 if kv == "bf16" else 1.0))
+    items = ts.plan_export(g.make_desc(b), b.q_lens, b.ctx_lens, "decode")
+    assert len(items) <= 88 and (items[:, 5] >= 0).sum() > 8    # fused, with split rows
+    print(f"[case] noalloc decode kv={kv} D={head_dim} items={len(items)}", flush=True)
+    ref, _, _ = oracle.run_batch(W.to_cpu(make_batch(shape, [1] * 6, ctx_lens, seed=95, pool_rule=1.1,
+                                                     value_mult=0.5 if kv == "bf16" else 1.0)))
+    b = g.to_dev(b)
+    ctx = ts.Context(g.make_desc(b))
+    want = _pass(ctx, b, noalloc=False)
+    got = torch.from_numpy(want[0].copy()).view(torch.bfloat16).double().numpy().reshape(ref.shape)
+    assert float(np.max(np.abs(got - ref))) <= (2e-2 if kv == "bf16" else 6e-2)
+    for _ in range(3):
+        for x, y, what in zip(_pass(ctx, b, noalloc=True), want, ("out", "k cache", "v cache")):
+            assert x.tobytes() == y.tobytes(), what
+    ctx.close()
+
+    hip, stream = _hip(), torch.cuda.Stream()
+    ctx = ts.Context(g.make_desc(b))
+    kc, vc = (torch.from_numpy(a).cuda() for a in want[1:])
+    bt = torch.from_numpy(b.block_table).cuda()
+    out = torch.empty_like(b.q)
+    torch.cuda.synchronize()
+    call = lambda: ctx.mixed_paged_attention(b.q, b.k_new, b.v_new, kc, vc, b.k_scale, b.v_scale, bt, b.q_lens, b.ctx_lens,
+                                             b.sm_scale, out, stream=stream, noalloc=True)
+    call()
+    torch.cuda.synchronize()
+    st, graph, execg, n = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_size_t()
+    assert hip.hipStreamBeginCapture(st, 2) == 0                # relaxed: other threads' calls are not this test's
+    call()
+    assert hip.hipStreamEndCapture(st, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0 and n.value == 2
+    assert hip.hipGraphInstantiate(ctypes.byref(execg), graph, None, None, ctypes.c_size_t(0)) == 0
+    for _ in range(3):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(execg, st) == 0
+        torch.cuda.synchronize()
+        assert out.view(torch.uint8).cpu().numpy().tobytes() == want[0].tobytes()
+    assert hip.hipGraphExecDestroy(execg) == 0 and hip.hipGraphDestroy(graph) == 0
     ctx.close()
