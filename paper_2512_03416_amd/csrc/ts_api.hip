@@ -550,7 +550,7 @@ struct WorkDoneGuard {                                     // records the event 
 
 // The append of a batch of few sequences, described by kernel arguments; false = not such a batch (or source rows that
 // are not 16-byte aligned, which only the token-wise kernel takes).
-bool append_seqs_of(const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs, const void* k_new, const void* v_new, AppendSeqs* s)
+bool append_seqs_of(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs, const void* k_new, const void* v_new, AppendSeqs* s)
 {
     if ((((uintptr_t)k_new | (uintptr_t)v_new) & 15) != 0) return false;
     s->n = s->n_pages = 0;
@@ -563,7 +563,7 @@ bool append_seqs_of(const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs
         row += q_lens[i];
     }
     s->seq[s->n] = AppendSeq{row, 0, s->n_pages};
-    return s->n_pages > 0;
+    return s->n_pages > 0 && (int64_t)s->n_pages * d.num_kv_heads <= kMaxWorkgroups;
 }
 
 Geometry geometry_of(const ts_attn_desc& d)
@@ -850,8 +850,8 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
     c->timing_now = c->timing > 0 && (c->timing_pass++ % (uint64_t)c->timing) == 0;
     AppendSeqs few;
     PlanOptions opt = c->opt;
-    opt.append_only = true;
-    opt.append_lists = !append_seqs_of(q_lens, ctx_lens, num_seqs, k_new, v_new, &few);
+    opt.append_only = opt.for_launch = true;
+    opt.append_lists = !append_seqs_of(c->desc, q_lens, ctx_lens, num_seqs, k_new, v_new, &few);
     build_plan(c->desc, q_lens, ctx_lens, num_seqs, opt, &c->plan);
     if (c->plan.info.total_tokens == 0) return TS_OK;
     if (!k_new || !v_new) return fail(c, TS_ERR_INVALID_ARG, "k_new / v_new is NULL");
@@ -903,7 +903,7 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     c->timing_now = !c->static_call && c->timing > 0 && (c->timing_pass++ % (uint64_t)c->timing) == 0;
     if (c->dec_slots > 0) c->opt.wg_slots = c->dec_slots;
     AppendSeqs few;
-    const bool append_lists = !k_new || !append_seqs_of(q_lens, ctx_lens, num_seqs, k_new, v_new, &few);
+    const bool append_lists = !k_new || !append_seqs_of(c->desc, q_lens, ctx_lens, num_seqs, k_new, v_new, &few);
     {
         PlanOptions opt = c->opt;
         opt.for_launch = true;

@@ -178,6 +178,10 @@ struct Geometry {
     int32_t q_dtype, kv_dtype;
 };
 
+// Workgroups of 256 threads that one launch takes: a grid holds less than 2^32 work items (a list with more of them goes
+// in several launches; some are left for the upload that rides along).
+constexpr int64_t kMaxWorkgroups = ((int64_t)1 << 24) - 1024;
+
 struct AppendArgs {
     Geometry geo;
     const void* k_new; const void* v_new;

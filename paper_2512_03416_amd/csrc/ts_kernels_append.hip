@@ -243,8 +243,7 @@ __global__ __launch_bounds__(256) void append_tile_kernel(AppendArgs a)
     else append_page<DST, D>(a, a.apt[blockIdx.x / a.geo.Hkv], blockIdx.x % a.geo.Hkv);
 }
 
-// fp32 cache, token-wise list: the first record of a page's run of new tokens stands for the run, the workgroups of
-// the others have nothing to do.
+// fp32 cache: one record per run of new tokens of a page.
 template <int D>
 __global__ __launch_bounds__(256) void append_run_kernel(AppendArgs a)
 {
@@ -252,7 +251,7 @@ __global__ __launch_bounds__(256) void append_run_kernel(AppendArgs a)
     if ((int)blockIdx.x >= n) { upload_lists(a, n); return; }
     const AppRow r = a.apr[blockIdx.x / a.geo.Hkv];
     const int lo = r.pos & (kPage - 1);
-    if (r.run > 0) append_page_f32<D>(a, AppTile{r.seq, r.pos >> 4, lo | (lo + r.run) << 8, r.row - lo}, blockIdx.x % a.geo.Hkv);
+    append_page_f32<D>(a, AppTile{r.seq, r.pos >> 4, lo | (lo + r.run) << 8, r.row - lo}, blockIdx.x % a.geo.Hkv);
 }
 
 // Batches of few sequences: every new token goes page by page (a decode row is a page with one new token), and the
@@ -310,19 +309,28 @@ int launch_append(const AppendArgs& args, void* stream)
     if (a.up_blocks > 0) {
         if (a.n_apr > 0) a.apr = a.apr_host; else a.apt = a.apt_host;
     }
-    if (a.n_apr > 0) {
+    if (a.n_apr > 0 && a.geo.q_dtype == TS_F32) {
+        if (a.geo.kv_dtype != TS_F32 || (a.geo.D != 128 && a.geo.D != 64)) return (int)hipErrorInvalidValue;
+        const int64_t most = kMaxWorkgroups > a.geo.Hkv ? kMaxWorkgroups / a.geo.Hkv : 1;
+        for (int64_t first = 0, left = a.n_apr; left > 0; first += most, left -= most) {
+            AppendArgs part = a;
+            part.apr = a.apr + first;
+            part.n_apr = (int32_t)(left < most ? left : most);
+            if (first > 0) part.up_blocks = 0;
+            const dim3 grid((unsigned)part.n_apr * (unsigned)a.geo.Hkv + (unsigned)part.up_blocks);
+            if (a.geo.D == 128) hipLaunchKernelGGL(append_run_kernel<128>, grid, block, 0, st, part);
+            else hipLaunchKernelGGL(append_run_kernel<64>, grid, block, 0, st, part);
+        }
+    } else if (a.n_apr > 0) {
         dim3 grid((unsigned)(a.n_apr + a.up_blocks));
-        const dim3 rgrid((unsigned)a.n_apr * (unsigned)a.geo.Hkv + (unsigned)a.up_blocks);
-        if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32 && a.geo.D == 128)
-            hipLaunchKernelGGL(append_run_kernel<128>, rgrid, block, 0, st, a);
-        else if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32 && a.geo.D == 64)
-            hipLaunchKernelGGL(append_run_kernel<64>, rgrid, block, 0, st, a);
-        else if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16)
+        if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16)
             hipLaunchKernelGGL((append_token_kernel<uint16_t>), grid, block, 0, st, a);
         else if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3)
             hipLaunchKernelGGL((append_token_kernel<uint8_t>), grid, block, 0, st, a);
         else
             return (int)hipErrorInvalidValue;
+    }
+    if (a.n_apr > 0) {
         a.up_blocks = 0;                               // done; the page-wise kernel finds its list on the device
         a.apt = args.apt;
     }

@@ -322,10 +322,15 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
 template <typename QT, typename KT>
 static int launch_rows_d(const AttnArgs& a, hipStream_t st)
 {
-    const dim3 grid((unsigned)a.n_rt * (unsigned)a.geo.Hkv), block(64 * kRtWaves);
-    if (a.geo.D == 64) hipLaunchKernelGGL((row_tile_kernel<QT, KT, 64>), grid, block, 0, st, a);
-    else if (a.geo.D == 128) hipLaunchKernelGGL((row_tile_kernel<QT, KT, 128>), grid, block, 0, st, a);
-    else return (int)hipErrorInvalidValue;
+    if (a.geo.D != 64 && a.geo.D != 128) return (int)hipErrorInvalidValue;
+    const int64_t most = kMaxWorkgroups > a.geo.Hkv ? kMaxWorkgroups / a.geo.Hkv : 1;
+    for (int64_t first = 0, left = a.n_rt; left > 0; first += most, left -= most) {
+        AttnArgs part = a;
+        part.rt = a.rt + first;
+        const dim3 grid((unsigned)(left < most ? left : most) * (unsigned)a.geo.Hkv), block(64 * kRtWaves);
+        if (a.geo.D == 64) hipLaunchKernelGGL((row_tile_kernel<QT, KT, 64>), grid, block, 0, st, part);
+        else hipLaunchKernelGGL((row_tile_kernel<QT, KT, 128>), grid, block, 0, st, part);
+    }
     return (int)hipGetLastError();
 }
 

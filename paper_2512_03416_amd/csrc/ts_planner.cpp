@@ -493,6 +493,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
             for (int32_t i = 0; i < m.q_len; ++i) {
                 const int32_t pos = m.prefix + i;
                 const bool leads = d.kv_dtype == TS_F32 && (i == 0 || pos % kPage == 0);
+                if (opt.for_launch && d.kv_dtype == TS_F32 && !leads) continue;   // (the run's first record stands for it)
                 p.apr.push_back(AppRow{m.q_off + i, s, pos, leads ? std::min(kPage - pos % kPage, m.q_len - i) : 0});
             }
             continue;

@@ -256,7 +256,7 @@ def test_decode_rows_dealt_out(lengths, kv, head_dim):
         first = out
 
 
-@pytest.mark.parametrize("kv,rows", [("bf16", 70), ("fp8", 88), ("bf16", 89), ("f32", 70), ("bf16", 256), ("fp8", 257), ("f32", 256)])
+@pytest.mark.parametrize("kv,rows", [("bf16", 70), ("fp8", 88), ("bf16", 89), ("f32", 70), ("bf16", 256), ("fp8", 257), ("f32", 256), ("f32", 300)])
 def test_sequences_as_kernel_arguments(kv, rows):
     """Batches around the largest whose decode items (88) and sequences (256) travel as kernel arguments, with
     sequences that bring nothing in front, between and behind, and chunks next to the rows."""
@@ -606,6 +606,39 @@ def test_append_only_entry_point_bit_exact():
         assert same_bytes(g.cache_raw(gk, shape.kv_dtype), rk)
         assert same_bytes(g.cache_raw(gv, shape.kv_dtype), rv)
         ctx.close()
+
+
+def test_append_of_more_token_heads_than_a_grid_has_workgroups():
+    """fp32, more than 256 sequences, 2^24 (token, KV head) pairs and more: appended, bit-exact (through the documented
+    layout, on the GPU); pages ragged at both ends."""
+    import paper_2512_03416_amd as ts
+    S, H, D = 300, 64, 64
+    q_lens = np.full(S, 880, np.int32)
+    prefix = (np.arange(S) % 7).astype(np.int32)
+    ctx_lens = q_lens + prefix
+    T, width = int(q_lens.sum()), 56
+    assert T * H >= 1 << 24
+    print(f"[case] append T={T} Hkv={H}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    k = torch.randn((T, H, D), generator=gen, device="cuda")
+    v = -k
+    table = torch.randperm(S * width, generator=gen, device="cuda").to(torch.int32).view(S, width)
+    desc = ts.Desc.make(H, H, D, "f32", "f32", S * width, width)
+    kc, vc = (torch.full((S * width, H, 16 * D), 7.0, device="cuda") for _ in range(2))
+    assert kc.numel() * 4 == ts.cache_bytes(desc)
+    ctx = ts.Context(desc)
+    ctx.kv_append(k, v, kc, vc, None, None, table, q_lens, ctx_lens)
+    torch.cuda.synchronize()
+    for s in range(S):
+        n, p0 = int(ctx_lens[s]), int(prefix[s])
+        ids = table[s, :(n + 15) // 16].long()
+        got_k = kc[ids].view(-1, H, D // 4, 16, 4).permute(0, 3, 1, 2, 4).reshape(-1, H, D)
+        got_v = vc[ids].view(-1, H, D, 16).permute(0, 3, 1, 2).reshape(-1, H, D)
+        rows = slice(int(q_lens[:s].sum()), int(q_lens[:s + 1].sum()))
+        for got, new in ((got_k, k), (got_v, v)):
+            assert torch.equal(got[p0:n], new[rows]) and bool((got[:p0] == 7).all()) and bool((got[n:] == 7).all())
+    ctx.close()
 
 
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
