@@ -71,8 +71,8 @@ struct PfSlot {           // workgroup -> (prefill tile, KV head); item < 0 = no
 };
 
 struct QItem {            // entry of a per-die work queue of the persistent kernels
-    int32_t item;
-    int32_t kind_head;    // KV head (low 16 bits); above it 0 = decode item, 1 = prefill tile
+    int32_t item_kind;    // number of the item << 1 | (0 = decode item, 1 = prefill tile)
+    int32_t head_kv;
 };
 
 struct AppTile {          // one cache page of a chunk's new tokens; launched once per KV head

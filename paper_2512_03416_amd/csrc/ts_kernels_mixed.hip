@@ -48,7 +48,7 @@ __device__ __forceinline__ void drain_queues(const AttnArgs& a, LDS& sh)
             continue;
         }
         const int32_t TS_CONSTANT* q = as_constant((const int32_t*)(a.queue + begin + idx));
-        const int item = q[0], kind = q[1] >> 16, g = q[1] & 0xffff;
+        const int item = q[0] >> 1, kind = q[0] & 1, g = q[1];
         int t = tid;
         asm volatile("" : "+v"(t));                            // (see prefill_tile)
         if constexpr (WITH_DECODE) {

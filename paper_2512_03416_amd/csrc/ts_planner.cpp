@@ -397,7 +397,7 @@ static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool
         // decode items run as a grid of their own next to them.
         p.q_off.assign(xcds + 1, 0);
         for (int x = 0; x < xcds; ++x) {
-            for (const PfSlot& t : tiles_of(x)) p.queue.push_back(QItem{t.item, t.head_kv | 1 << 16});
+            for (const PfSlot& t : tiles_of(x)) p.queue.push_back(QItem{t.item << 1 | 1, t.head_kv});
             p.q_off[x + 1] = (int32_t)p.queue.size();
         }
         return;
@@ -429,11 +429,11 @@ static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool
             if (dkey <= pkey) {                            // decode first on ties (Sec. 4.5.2)
                 const PfSlot& d = dper[x][di++];
                 dacc += p.dec[d.item].page_end - p.dec[d.item].page_begin;
-                p.queue.push_back(QItem{d.item, d.head_kv});
+                p.queue.push_back(QItem{d.item << 1, d.head_kv});
             } else {
                 const PfSlot& t = per[x][ti++];
                 pacc += pf_keys(p.pf[t.item]);
-                p.queue.push_back(QItem{t.item, t.head_kv | 1 << 16});
+                p.queue.push_back(QItem{t.item << 1 | 1, t.head_kv});
             }
         }
         p.q_off[x + 1] = (int32_t)p.queue.size();
@@ -748,7 +748,7 @@ extern "C" int64_t ts_plan_export(const ts_attn_desc* desc, const int32_t* q_len
     case TS_LIST_PFMAP:   src = plan.pfmap.data(); n = (int64_t)plan.pfmap.size(); words = sizeof(ts::PfSlot) / 4; break;
     case TS_LIST_ROWS:    src = rows.data();       n = (int64_t)rows.size();       words = 4; break;
     case TS_LIST_QUEUE:
-        for (const ts::QItem& q : plan.queue) rows.push_back({q.kind_head >> 16, q.item, q.kind_head & 0xffff, 0});
+        for (const ts::QItem& q : plan.queue) rows.push_back({q.item_kind & 1, q.item_kind >> 1, q.head_kv, 0});
         src = rows.data();       n = (int64_t)rows.size();       words = 4; break;
     case TS_LIST_QOFF:    src = plan.q_off.data(); n = (int64_t)plan.q_off.size(); words = 1; break;
     case TS_LIST_APPEND:

@@ -320,6 +320,23 @@ def test_plan_invariants_on_seeded_random_batches(seed):
     assert seen == {(s, p) for s in range(n) for p in range(ctx[s] - ql[s], ctx[s])}
 
 
+@pytest.mark.parametrize("mode,kv_heads", [(1, 8), (2, 8), (1, 70000), (2, 70000)])
+def test_queues_hold_every_item_of_every_kv_head(mode, kv_heads):
+    """The per-die queues name each (decode item, KV head) and (prefill tile, KV head) pair once, whatever the number of
+    KV heads (mode 2: the tiles only)."""
+    desc = ts.Desc.make(kv_heads, kv_heads, 128, "bf16", "bf16", 4096, 512)
+    ql, cl = ([1] * 64 + [2048], [4096] * 65) if kv_heads == 8 else ([1, 300], [4096, 1024])
+    queue = ts.plan_export(desc, ql, cl, "queue", mixed_mode=mode)
+    assert len(queue) > 0
+    want = set()
+    for kind, name in ((0, "decode"), (1, "prefill")):
+        if kind == 1 or mode == 1:
+            n = len(ts.plan_export(desc, ql, cl, name, mixed_mode=mode))
+            want |= {(kind, i, g) for i in range(n) for g in range(kv_heads)}
+    got = [tuple(int(x) for x in r[:3]) for r in queue]
+    assert len(got) == len(want) and set(got) == want
+
+
 @pytest.mark.parametrize("lens,longest_first", [([512, 128, 300, 130, 444, 257, 65, 2], True), ([64] * 16, True),
                                                 ([1024] * 8, False), ([300] * 24, False)])
 def test_launch_order_of_few_prompts(lens, longest_first):
