@@ -211,11 +211,18 @@ int32_t* cmb_ctr_of(const ts_ctx* c, size_t n_rows)
 // Split decode rows are merged by whichever item of a row finishes last when the rows have few items (at most
 // kMergeInKernelMax, or by option), else by a launch behind them (NULL).  The last item of a row adds up its partials
 // on one CU; the launch spreads a row over one workgroup per head.
-constexpr int kMergeInKernelMax = 16;
-int32_t* merge_counters(const ts_ctx* c, const Plan& p)
+// A small decode-only pass (`small`: its lists fit the kernel arguments) would lose its append to a launch of its own
+// as well, so it merges in the kernel up to kMergeChunksSmall rounds of loads (a workgroup takes 256 groups of four dims
+// and eight splits a round): one row of 9000 tokens (32/8 heads of 128, 18 items) 21.5 -> 14.2 us a pass, of 20 000
+// 25.9 -> 20.5, of 131 000 with 12/3 heads (85 items, 11 rounds) 42.3 -> 40.7; of 100 000 with 64/4 heads (64 items,
+// 16 rounds) the launches are the better: 30.2 against 34.2.
+constexpr int kMergeInKernelMax = 16, kMergeChunksSmall = 12;
+int32_t* merge_counters(const ts_ctx* c, const Plan& p, bool small)
 {
     if (p.cmb.empty() || !p.rt.empty() || p.info.mixed_mode == TS_MIXED_ONE_KERNEL) return nullptr;
-    if (!c->merge_in_kernel && p.max_split > kMergeInKernelMax) return nullptr;
+    const int32_t groups = (c->desc.num_q_heads / c->desc.num_kv_heads) * (c->desc.head_dim / 4);
+    const int32_t rounds = (groups + 255) / 256 * ((p.max_split + 7) / 8);
+    if (!c->merge_in_kernel && p.max_split > kMergeInKernelMax && !(small && rounds <= kMergeChunksSmall)) return nullptr;
     if ((int64_t)p.max_split * c->desc.num_q_heads * c->desc.head_dim * 4 >= (int64_t)1 << 31) return nullptr;
     return cmb_ctr_of(c, p.cmb.size());
 }
@@ -934,11 +941,12 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     // new tokens to append and no page check: the upload rides along in the first append launch (not in the
     // allocation-free call, whose upload launch also puts the shared queue heads back to zero)
     const bool ride = k_new && !c->validate_pages && !c->static_call;
-    int32_t* const ctr = merge_counters(c, p);
     // decode-only batch of matrix-core items whose lists fit into the kernel arguments: the items append the new tokens
-    const bool fuse = k_new && !c->validate_pages && c->fused_append && desc_uses_mfma_decode(c->desc) && !p.dec.empty() && p.pf.empty() &&
-                p.rt.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 && (p.cmb.empty() || ctr) &&
+    const bool small = k_new && !c->validate_pages && c->fused_append && desc_uses_mfma_decode(c->desc) && !p.dec.empty() && p.pf.empty() &&
+                p.rt.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 &&
                 p.dec.size() <= (size_t)kSmallDec && p.cmb.size() <= (size_t)kSmallCmb;
+    int32_t* const ctr = merge_counters(c, p, small);
+    const bool fuse = small && (p.cmb.empty() || ctr);
     UploadJob job;
     rc = upload_plan(c, st, w, ride || fuse ? &job : nullptr);   // (fused form: nothing to upload)
     if (rc != TS_OK) return rc;
