@@ -108,6 +108,12 @@ struct RowCut {           // a range of a row tile's pages
     int32_t n_split;      // ranges the tile's pages are cut into
 };
 
+struct RowPacking {       // whole decode rows packed over the CUs (working memory of the planner)
+    std::vector<int32_t> pages, by_len, tmp;
+    std::vector<int32_t> row, count;     // row[round * CUs + CU], rows per CU
+    std::vector<int64_t> load, open;
+};
+
 struct Plan {
     std::vector<SeqMeta> seqs;       // S + 1
     std::vector<DecItem> dec;
@@ -125,6 +131,7 @@ struct Plan {
     std::vector<RowTile> rt;         // generic kernel: row tiles, longest first
     std::vector<RowCut> rtcut;       // ... and the page ranges of the cut ones
     std::vector<WideItem> wide;      // fp8 caches: pages to widen, in the order of their widened copies
+    RowPacking packing;
     int32_t max_split = 1;           // most items that a decode row is cut into
     std::vector<int32_t> wide_base;  // per sequence: number of its first widened page, -1 = not widened
     ts_plan_info info{};

@@ -13,7 +13,6 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
-#include <queue>
 #include <utility>
 
 #include "ts_internal.h"
@@ -267,31 +266,71 @@ static bool deal_decode_evenly(Plan& p, int num_seqs, int64_t pages, const ts_at
 }
 
 // Whole rows over the CUs when all their workgroups are resident at once: the memory system serves the CUs alike, so
-// what matters is the pages per CU.  Rows go, longest first, to the CU with the least; returns the most loaded CU's
-// pages.  order: rows in the order of launch (workgroups are placed round-robin: the first rows of all CUs, then the
-// second rows, ...).
-static int64_t pack_rows(const std::vector<int32_t>& pages, int64_t cus, std::vector<int32_t>* order)
+// what matters is the pages per CU.  Rows go, longest first, to the CU with the least that has room (no CU gets more
+// rows than it must); returns the most loaded CU's pages.  order: rows in the order of launch (workgroups are placed
+// round-robin: the first rows of all CUs, then the second rows, ...).
+// Flat arrays that the plan keeps, and no queue of CUs while they get their first two rows: in the order of the rows'
+// lengths the loads are sorted as they are.  (With a queue of (load, CU) pairs and a list per CU, packed once to decide
+// and once more for the order, planning a pass took 12.6 us for 88 rows, 16.0 for 128 and 182 for 700 rows of one KV
+// head; it takes 2.6, 3.8 and 24.)
+static int64_t pack_rows(RowPacking& k, int64_t cus)
 {
-    std::vector<int32_t> by_len(pages.size());
-    for (size_t i = 0; i < by_len.size(); ++i) by_len[i] = (int32_t)i;
-    std::stable_sort(by_len.begin(), by_len.end(), [&](int32_t a, int32_t b) { return pages[a] > pages[b]; });
-    const size_t most = (pages.size() + cus - 1) / cus;
-    std::vector<std::vector<int32_t>> bin(cus);
-    std::priority_queue<std::pair<int64_t, int64_t>, std::vector<std::pair<int64_t, int64_t>>, std::greater<>> open;   // (load, CU)
-    for (int64_t b = 0; b < cus; ++b) open.push({0, b});
-    int64_t longest = 0;
-    for (int32_t i : by_len) {
-        const auto [load, b] = open.top();
-        open.pop();
-        bin[b].push_back(i);
-        longest = std::max(longest, load + pages[i] + kItemPages);
-        if (bin[b].size() < most) open.push({load + pages[i] + kItemPages, b});
+    const int32_t n = (int32_t)k.pages.size(), n_cu = (int32_t)cus;
+    int32_t top = 0;
+    for (int32_t x : k.pages) top = std::max(top, x);
+    // longest first, equal lengths in batch order (one byte of the length at a time)
+    k.by_len.resize(n);
+    for (int32_t i = 0; i < n; ++i) k.by_len[i] = i;
+    for (int shift = 0; shift < 32 && (top >> shift) > 0; shift += 8) {
+        int32_t at[257] = {};
+        for (int32_t i : k.by_len) ++at[256 - (k.pages[i] >> shift & 255)];
+        for (int v = 1; v <= 256; ++v) at[v] += at[v - 1];
+        k.tmp.resize(n);
+        for (int32_t i : k.by_len) k.tmp[at[255 - (k.pages[i] >> shift & 255)]++] = i;
+        k.by_len.swap(k.tmp);
     }
-    if (order) {
-        std::stable_sort(bin.begin(), bin.end(), [](const std::vector<int32_t>& a, const std::vector<int32_t>& b) { return a.size() > b.size(); });
-        for (size_t r = 0; r < most; ++r)
-            for (const auto& v : bin)
-                if (r < v.size()) order->push_back(v[r]);
+    const int32_t most = (n + n_cu - 1) / n_cu;            // rows per CU
+    k.row.assign((size_t)most * n_cu, -1);                 // [round][CU]
+    k.count.assign(n_cu, 0);
+    k.load.assign(n_cu, 0);
+    int64_t longest = 0;
+    auto put = [&](int32_t i, int32_t b) {
+        k.row[(size_t)k.count[b]++ * n_cu + b] = i;
+        k.load[b] += k.pages[i] + kItemPages;
+        longest = std::max(longest, k.load[b]);
+    };
+    const int32_t n1 = std::min(n, n_cu);
+    for (int32_t j = 0; j < n1; ++j) put(k.by_len[j], j);
+    if (most == 2) {
+        // the CUs by load: from the last one up, equal loads in order of the CUs
+        int32_t hi = n_cu, lo = n_cu;
+        for (int32_t j = n1, b = n_cu; j < n; ++j, ++b) {
+            if (b >= hi) {
+                hi = lo;
+                for (lo = hi - 1; lo > 0 && k.load[lo - 1] == k.load[hi - 1]; --lo) {}
+                b = lo;
+            }
+            put(k.by_len[j], b);
+        }
+    } else if (most > 2) {
+        // a heap of the CUs with room, least load first (then the CU's number)
+        k.open.resize(n_cu);
+        for (int32_t b = 0; b < n_cu; ++b) k.open[b] = k.load[b] << 24 | b;
+        std::make_heap(k.open.begin(), k.open.end(), std::greater<>());
+        int64_t* const h = k.open.data();
+        for (int32_t j = n1, left = n_cu; j < n; ++j) {
+            const int32_t b = (int32_t)(h[0] & 0xffffff);
+            put(k.by_len[j], b);
+            const int64_t x = k.count[b] < most ? k.load[b] << 24 | b : h[--left];   // takes the top's place
+            int32_t at = 0;
+            for (int32_t c = 1; c < left; c = 2 * at + 1) {
+                c += c + 1 < left && h[c + 1] < h[c];
+                if (h[c] >= x) break;
+                h[at] = h[c];
+                at = c;
+            }
+            h[at] = x;
+        }
     }
     return longest;
 }
@@ -300,24 +339,32 @@ static int64_t pack_rows(const std::vector<int32_t>& pages, int64_t cus, std::ve
 // the average: dealing out costs about as much (60 rows of 300-1000 tokens: 36.6 us whole, 41.5 us dealt out; 40 rows
 // of 500-1220 tokens, 20 pages over the average: 34.5 against 39.1; 100 rows of 1600-5700 tokens, e4m3, 36 over:
 // 155 against 142; 48 rows, head dim 64, 44 over: 62.3 against 57.6).
-static bool rows_stay_whole(const Plan& p, int num_seqs, int64_t pages, const ts_attn_desc& d, const PlanOptions& opt)
+static bool rows_stay_whole(Plan& p, int num_seqs, int64_t pages, const ts_attn_desc& d, const PlanOptions& opt)
 {
     const int64_t cus = std::max<int64_t>(1, opt.n_cu / d.num_kv_heads), rows = p.info.decode_tokens;
     if (rows < cus || rows * d.num_kv_heads > opt.wg_slots) return false;
-    std::vector<int32_t> n;
-    for (int s = 0; s < num_seqs; ++s)
-        if (p.seqs[s].q_len == 1) n.push_back((p.seqs[s].ctx_len + kPage - 1) / kPage);
     const int64_t page_bytes = 2 * kPage * d.head_dim * (d.kv_dtype == TS_FP8_E4M3 ? 1 : 2);
-    return pack_rows(n, cus, nullptr) <= (pages + rows * kItemPages) / cus + 24 * 8192 / page_bytes;
+    const int64_t most = (pages + rows * kItemPages) / cus + 24 * 8192 / page_bytes;
+    p.packing.pages.clear();
+    for (int s = 0; s < num_seqs; ++s)
+        if (p.seqs[s].q_len == 1) {
+            p.packing.pages.push_back((p.seqs[s].ctx_len + kPage - 1) / kPage);
+            if (p.packing.pages.back() + kItemPages > most) return false;
+        }
+    return pack_rows(p.packing, cus) <= most;
 }
 
-static void balance_over_cus(Plan& p, int64_t cus)
+// The items of rows that stay whole (one per row, in batch order) in the order of launch: CUs with more rows first.
+static void order_whole_rows(Plan& p)
 {
-    std::vector<int32_t> pages, order;
-    for (const DecItem& it : p.dec) pages.push_back(it.page_end - it.page_begin);
-    pack_rows(pages, cus, &order);
+    const RowPacking& k = p.packing;
+    const size_t cus = k.count.size(), most = k.row.size() / cus;
     std::vector<DecItem> packed;
-    for (int32_t i : order) packed.push_back(p.dec[i]);
+    packed.reserve(p.dec.size());
+    for (size_t r = 0; r < most; ++r)
+        for (int32_t c = (int32_t)most; c > (int32_t)r; --c)
+            for (size_t b = 0; b < cus; ++b)
+                if (k.count[b] == c) packed.push_back(p.dec[k.row[r * cus + b]]);
     p.dec.swap(packed);
 }
 
@@ -646,10 +693,8 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     }
     p.info.widened_pages = (int64_t)p.wide.size();
     // longest first (stable, so equal lengths keep batch order and runs stay reproducible)
-    if (!even) {
-        sort_decode_items(p.dec);
-        if (whole) balance_over_cus(p, std::max<int64_t>(1, opt.n_cu / Hkv));
-    }
+    if (whole) order_whole_rows(p);
+    else if (!even) sort_decode_items(p.dec);
     {
         // (the merge list refers to the tiles by position: sort a permutation and carry the references along)
         auto keys_of = [](const PfItem& t) {

@@ -320,6 +320,45 @@ def test_plan_invariants_on_seeded_random_batches(seed):
     assert seen == {(s, p) for s in range(n) for p in range(ctx[s] - ql[s], ctx[s])}
 
 
+def test_whole_decode_rows_are_packed_in_little_host_time():
+    """Rows that come out even over the CUs stay whole (a plain longest-first packing says when), and deciding so costs a
+    batch of 700 rows on 256 CUs no more host time than planning 800 rows that are not packed (with room for noise)."""
+    import heapq
+    import time
+    rng = np.random.default_rng(11)
+    whole = 0
+    for kv_heads, lo, hi in [(8, 100, 400), (8, 300, 900), (4, 16, 700), (2, 16, 300), (1, 16, 200), (3, 50, 600)] * 6:
+        desc = ts.Desc.make(4 * kv_heads, kv_heads, 128, "bf16", "bf16", 1 << 20, 256)
+        cus = 256 // kv_heads
+        n = int(rng.integers(cus, 768 // kv_heads + 1))
+        ctx = rng.integers(lo, hi + 1, n)
+        pages = sorted(((int(c) + 15) // 16 + 4 for c in ctx), reverse=True)         # 4: what an item costs
+        room, heap = -(-n // cus), [(0, b, 0) for b in range(cus)]
+        longest = 0
+        for p in pages:
+            load, b, k = heapq.heappop(heap)
+            longest = max(longest, load + p)
+            if k + 1 < room:
+                heapq.heappush(heap, (load + p, b, k + 1))
+        if longest <= sum(pages) // cus + 24:
+            whole += 1
+            info = ts.plan_describe(desc, np.ones(n, np.int32), ctx)
+            assert info.n_decode_items == n and info.n_combine_rows == 0
+    assert whole > 12
+
+    desc = ts.Desc.make(4, 1, 128, "bf16", "bf16", 1 << 20, 256)
+
+    def host_time(n):
+        q, ctx = np.ones(n, np.int32), rng.integers(16, 201, n).astype(np.int32)
+        best = 1.0
+        for _ in range(300):
+            t = time.perf_counter()
+            ts.plan_describe(desc, q, ctx)
+            best = min(best, time.perf_counter() - t)
+        return best
+    assert host_time(700) <= 2.0 * host_time(800)
+
+
 @pytest.mark.parametrize("mode,kv_heads", [(1, 8), (2, 8), (1, 70000), (2, 70000)])
 def test_queues_hold_every_item_of_every_kv_head(mode, kv_heads):
     """The per-die queues name each (decode item, KV head) and (prefill tile, KV head) pair once, whatever the number of
