@@ -320,6 +320,33 @@ def test_plan_invariants_on_seeded_random_batches(seed):
     assert seen == {(s, p) for s in range(n) for p in range(ctx[s] - ql[s], ctx[s])}
 
 
+@pytest.mark.parametrize("q_lens,ctx_lens", [(5, 9), (np.int64(5), np.array(9)), ([5], (9,)), ([5, 0, 1], np.array([9, 3, 4])),
+                                             (np.array([5, 1, 7, 1])[::2], np.array([9, 8], np.uint8)), ([], []),
+                                             (np.array([5.0, 1.0]), [9, 4])])
+def test_binding_takes_lengths_in_every_form(q_lens, ctx_lens):
+    """Lengths reach the library as int32 arrays of as many sequences: a single number, lists, arrays of any integer type
+    and stride, none at all."""
+    calls = []
+
+    class Library:
+        def __getattr__(self, name):
+            return lambda *args: calls.append((name, args)) or 0
+    ctx = binding.Context.__new__(binding.Context)
+    ctx._lib, ctx._h = Library(), ctypes.c_void_p(1)
+    ctx.kv_append(None, None, None, None, None, None, None, q_lens, ctx_lens, stream=0)
+    for noalloc in (False, True):
+        ctx.mixed_paged_attention(None, None, None, None, None, None, None, None, q_lens, ctx_lens, 0.0, None, stream=0,
+                                  noalloc=noalloc)
+    ctx._h = None
+    want_q, want_c = (np.atleast_1d(np.asarray(x)).astype(np.int32) for x in (q_lens, ctx_lens))
+    assert [c[0] for c in calls[:3]] == ["ts_kv_append", "ts_mixed_paged_attention", "ts_mixed_paged_attention_noalloc"]
+    for _, args in calls[:3]:
+        at = next(i for i, x in enumerate(args) if isinstance(x, bytes))
+        assert np.array_equal(np.frombuffer(args[at], np.int32), want_q)
+        assert np.array_equal(np.frombuffer(args[at + 1], np.int32), want_c)
+        assert args[at + 2] == len(want_q)
+
+
 def test_whole_decode_rows_are_packed_in_little_host_time():
     """Rows that come out even over the CUs stay whole (a plain longest-first packing says when), and deciding so costs a
     batch of 700 rows on 256 CUs no more host time than planning 800 rows that are not packed (with room for noise)."""
