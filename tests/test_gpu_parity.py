@@ -173,23 +173,25 @@ def test_decode_items_append_their_rows_tokens_or_the_append_kernel_does(kv, hea
 
 
 def test_fused_append_converts_every_bf16_pattern_like_the_append_kernel():
-    """All 65 536 bf16 bit patterns as the new K and V of 128 decode rows (4 kv heads = 4 scales) through the fused
-    form: the e4m3 cache bytes equal the oracle's (NaNs, infinities, values beyond the range, -0, denormals)."""
+    """All 65 536 bf16 bit patterns as the new K and V of two batches of 64 decode rows (4 kv heads = 4 scales), few
+    enough for the fused form: the e4m3 cache bytes equal the oracle's (NaNs, infinities, values beyond the range, -0,
+    denormals)."""
     import paper_2512_03416_amd as ts
     shape = AttnShape(4, 4, 128, "bf16", "fp8")
-    n = 65536 // (4 * 128)
+    n = 65536 // (4 * 128) // 2
     rng = np.random.default_rng(34)
     ctxs = [int(x) for x in rng.integers(1, 70, size=n)]
     b = make_batch(shape, [1] * n, ctxs, seed=52)
     bits = torch.arange(65536, dtype=torch.int32).to(torch.int16)
-    allv = bits.view(torch.bfloat16).view(n, 4, 128)
+    allv = bits.view(torch.bfloat16).view(2, n, 4, 128)
     g = gpu()
-    for rot in range(2):
-        b.k_new = torch.roll(allv, rot, dims=1).contiguous()
-        b.v_new = torch.roll(allv, rot + 1, dims=1).contiguous()
+    assert len(ts.plan_export(g.make_desc(b), b.q_lens, b.ctx_lens, "decode")) <= 88
+    for half, rot in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        b.k_new = torch.roll(allv[half], rot, dims=1).contiguous()
+        b.v_new = torch.roll(allv[half], rot + 1, dims=1).contiguous()
         b.k_scale = torch.tensor([1.0, 0.0078125, 0.0123, 3.7])
         b.v_scale = torch.tensor([1.0 / 448.0, 2.5, 0.3, 1e-3])
-        print(f"[case] fused append, every bf16 pattern, rotation {rot}", flush=True)
+        print(f"[case] fused append, every bf16 pattern, half {half}, rotation {rot}", flush=True)
         _, rk, rv = oracle.run_batch(W.to_cpu(b))
         _, gk, gv = g.run_batch(b, options={"decode_fused_append": 1})
         assert same_bytes(gk, rk) and same_bytes(gv, rv)
@@ -235,8 +237,9 @@ def test_head_dim_64_mixed_batch_and_every_fp8_code():
 @pytest.mark.parametrize("lengths", ["whole", "even", "even_short_rows", "even_long", "fit", "many"])
 def test_decode_rows_dealt_out(lengths, kv, head_dim):
     """The ways decode rows are cut (whole rows packed over the CUs; dealt out evenly, one or more items per workgroup,
-    rows of one page between long ones, a row cut into more items than are merged in the kernel; pieces that fit
-    the CUs; more rows than workgroups), each against the oracle on every row, and run-to-run identical."""
+    rows of one page between long ones, rows cut into many items; pieces that fit the CUs; more rows than workgroups),
+    each against the oracle on every row; three passes on one context (arrival counters back at zero behind each), with
+    and without the append in the items, bit-identical."""
     import paper_2512_03416_amd as ts
     rng = np.random.default_rng(5)
     ctx = {"whole": rng.integers(300, 700, 64), "even": rng.integers(500, 9000, 36), "fit": rng.integers(20, 900, 16),
@@ -247,13 +250,49 @@ def test_decode_rows_dealt_out(lengths, kv, head_dim):
     b = make_batch(shape, ones, ctx, seed=36, pool_rule=1.1, value_mult=0.5 if kv == "bf16" else 1.0)
     print(f"[case] {lengths} kv={kv} D={head_dim} rows={len(ctx)}", flush=True)
     ref, rk, rv = oracle.run_batch(W.to_cpu(b))
-    first = None
-    for rep in range(3):
-        out, gk, gv = gpu().run_batch(b, fused_append=rep > 0)
-        assert same_bytes(gk, rk) and same_bytes(gv, rv)
-        assert float(np.max(np.abs(out - ref))) <= TOL[kv]
-        assert first is None or rep == 1 or np.array_equal(out, first)
-        first = out
+    gpu().to_dev(b)
+    for fused in (False, True):
+        c, first = ts.Context(gpu().make_desc(b)), None
+        for rep in range(3):
+            out, gk, gv = gpu().run_batch(b, ctx=c, fused_append=fused)
+            assert same_bytes(gk, rk) and same_bytes(gv, rv)
+            assert float(np.max(np.abs(out - ref))) <= TOL[kv]
+            assert first is None or np.array_equal(out, first)
+            first = out
+        c.close()
+
+
+@pytest.mark.parametrize("kv,head_dim", [("bf16", 128), ("fp8", 128), ("bf16", 64), ("fp8", 64)])
+def test_small_decode_passes_dealt_out(kv, head_dim):
+    """Rows dealt out in few enough items to travel as kernel arguments, several items to a workgroup (rows of one page
+    between rows of up to eight workgroups): the items append, scan and merge in one launch.  Against the oracle, four
+    passes on one context bit-identical, and the form with an append launch and the lists in memory alike."""
+    import paper_2512_03416_amd as ts
+    shape = AttnShape(16, 8, head_dim, "bf16", kv)
+    rng = np.random.default_rng(6)
+    ctx = np.where(np.arange(22) % 2 == 0, rng.integers(7000, 11000, 22), rng.integers(1, 17, 22))
+    b = make_batch(shape, [1] * 22, ctx, seed=41, pool_rule=1.1, value_mult=0.5 if kv == "bf16" else 1.0)
+    desc = gpu().make_desc(b)
+    items = ts.plan_export(desc, b.q_lens, b.ctx_lens, "decode")
+    combine = ts.plan_export(desc, b.q_lens, b.ctx_lens, "combine")
+    wgs = 64 if (kv, head_dim) == ("fp8", 64) else 32         # workgroups per KV head
+    print(f"[case] kv={kv} D={head_dim} items={len(items)} split rows={len(combine)}", flush=True)
+    assert wgs < len(items) <= 88 and 8 < len(combine) <= 32 and max(r[2] for r in combine) <= 16
+    ref, rk, rv = oracle.run_batch(W.to_cpu(b))
+    gpu().to_dev(b)
+    for fused in (1, 0):
+        c, first = ts.Context(desc), None
+        c.set_option("decode_fused_append", fused)
+        c.set_option("kernel_timing", 1)
+        for rep in range(4):
+            out, gk, gv = gpu().run_batch(b, ctx=c)
+            assert same_bytes(gk, rk) and same_bytes(gv, rv)
+            assert float(np.max(np.abs(out - ref))) <= TOL[kv]
+            assert first is None or np.array_equal(out, first)
+            first = out
+        times = c.kernel_times()
+        assert times["append"][0] == (4 if fused else 8) and times["combine"][0] == 0   # (the prefix: one append a pass)
+        c.close()
 
 
 @pytest.mark.parametrize("kv,rows", [("bf16", 70), ("fp8", 88), ("bf16", 89), ("f32", 70), ("bf16", 256), ("fp8", 257), ("f32", 256), ("f32", 300)])
@@ -513,7 +552,8 @@ def test_fp8_prefill_widened_pages_and_in_tile_widening_agree(mode):
 def test_prefill_tiles_cut_along_the_keys(kv, heads, head_dim):
     """A short chunk over a long prefix cannot give every CU a tile: the tiles are cut along the keys and the
     parts merged.  Chunks whose prefix ends inside a page, a stage and a part; parts of 64 keys (the finest cut)
-    and the default; next to decode rows (one persistent kernel) and alone; same results with cutting off."""
+    and the default; next to decode rows (one persistent kernel) and alone; same results with cutting off; three
+    passes on one context (arrival counters of the cut tiles back at zero behind each) bit-identical."""
     import paper_2512_03416_amd as ts
     shape = AttnShape(heads[0], heads[1], head_dim, "bf16", kv)
     g = gpu()
@@ -528,7 +568,11 @@ def test_prefill_tiles_cut_along_the_keys(kv, heads, head_dim):
             last["prefill_widen_pages"] = 0                  # (head dim 64 reads an e4m3 cache through widened pages only)
         for opts in ({}, {"prefill_split_min_keys": 64}, {"prefill_split_min_keys": 0}, last):
             print(f"[case] cut tiles kv={kv} heads={heads} q={q} ctx={c} opts={opts}", flush=True)
-            out, gk, gv = g.run_batch(mk(), options=opts)
+            ctx = ts.Context(g.make_desc(b))
+            out, gk, gv = g.run_batch(b, ctx=ctx, options=opts)
+            for _ in range(2):
+                assert np.array_equal(g.run_batch(b, ctx=ctx)[0], out)
+            ctx.close()
             assert same_bytes(gk, rk) and same_bytes(gv, rv)
             assert np.all(np.isfinite(out))
             err = float(np.max(np.abs(out - ref)))

@@ -434,9 +434,10 @@ def test_kernels_fit_their_register_budget_without_spilling():
     import subprocess
     from paper_2512_03416_amd import build as B
     budgets = {"prefill_resident_kernel": 192, "prefill_kernel": 192, "decode_kernel_lean": 128, "mixed_kernel": 256,
-               "decode_kernel": 256}
+               "decode_kernel": 256, "row_tile_kernel": 256}
     seen = set()
-    for src in ("ts_kernels_mixed.hip", "ts_kernels_prefill.hip", "ts_kernels_decode.hip"):
+    for src in ("ts_kernels_mixed.hip", "ts_kernels_prefill.hip", "ts_kernels_decode.hip", "ts_kernels_rows.hip",
+                "ts_kernels_append.hip"):
         r = subprocess.run([B.HIPCC] + B.FLAGS + ["-Rpass-analysis=kernel-resource-usage", "-x", "hip", "-c",
                                                  os.path.join(B.CSRC, src), "-o", os.devnull],
                            capture_output=True, text=True)
