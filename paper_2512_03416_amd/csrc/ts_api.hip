@@ -555,8 +555,9 @@ struct WorkDoneGuard {                                     // records the event 
     ~WorkDoneGuard() { if (c->cur_slot) (void)mark_work_done(c, st); }
 };
 
-// The append of a batch of few sequences, described by kernel arguments; false = not such a batch (or source rows that
-// are not 16-byte aligned, which only the token-wise kernel takes).
+// The append of a batch of few sequences, described by kernel arguments; false = not such a batch, or source rows that
+// are not 16-byte aligned: decode rows and chunks of less than eight tokens then go through the token-wise kernel,
+// which reads element by element (longer bf16 chunks are read in 16-byte pieces in either form).
 bool append_seqs_of(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs, const void* k_new, const void* v_new, AppendSeqs* s)
 {
     if ((((uintptr_t)k_new | (uintptr_t)v_new) & 15) != 0) return false;

@@ -141,7 +141,7 @@ struct Plan {
 
 struct PlanOptions {
     int32_t split_pages = 0;    // 0 = auto
-    int32_t wg_slots = 768;     // decode workgroups resident at once (256 CUs x 3)
+    int32_t wg_slots = 768;     // decode workgroups resident at once (a context asks for those of decode_kernel_lean)
     int32_t n_cu = 256;         // compute units of the GPU
     int32_t xcds = 8;           // accelerator dies; workgroup i is dispatched to die i % xcds
     int32_t mixed_mode = TS_MIXED_CORESIDENT;   // how a batch with decode rows and prefill chunks is launched
@@ -208,7 +208,7 @@ struct AppendArgs {
 
 // Sequences short enough a list to travel as kernel arguments (append of small batches): 3 KB of the 4 KB there are.
 // Against lists read from the staging buffer: 200 rows and 4 chunks of 128-512 tokens 170.9 -> 167.1 us a pass, 140 rows
-// of 100-400 tokens 39.9 -> 39.1, 128 rows of 1024-8192 and 4 chunks of 2048 648.8 -> 644.0.
+// of 100-400 tokens 39.9 -> 39.1; no difference beyond noise in batches of several hundred microseconds.
 constexpr int kAppendSeqs = 256;
 struct AppendSeq {             // entry i: sequence i of the batch
     int32_t row0;              // first new token's row; the next entry's row0 (a last one behind the sequences) ends it
@@ -253,8 +253,8 @@ struct AttnArgs {
     float* pf_part_o; float* pf_part_ml;
     // Arrival counters of the split decode rows, one per (combine row, KV head), zero between launches: the
     // workgroup that finds n_split - 1 in it is the last of the row and merges the partials itself.  NULL = the
-    // items only write their partials and combine_kernel merges them (always so for the prefetch depths other than
-    // the default and in the one-kernel launch, whose kernels do not hold the merge).
+    // items only write their partials and combine_kernel merges them (rows of many items, batches with generic rows,
+    // the one-kernel launch, whose kernel does not hold the merge, and too few counters in the static scratch).
     int32_t* cmb_ctr;
     // split-K partials: o [slot][Hq][D] fp32 (unnormalised), ml [slot][Hq][2] = (max, sum) in log2 units
     float* part_o; float* part_ml;

@@ -44,8 +44,9 @@ __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))
 
 // A launch on its own (no resident prefill workgroups next to it): prefetches past the end of an item read nothing.  A
 // wave of decode_kernel_lean repeats its last page up to three times, which matters where rows are short (a wave of a
-// row of 100 tokens has two pages): 200 rows of 16-200 tokens 34.4 -> 31.3 us a pass, 140 of 100-400 39.1 -> 36.3, 256
-// of 512-4096 386.8 -> 384.4, 500 of 100-600 152 -> 142.  (Batches of items cut or dealt out showed no difference.  Within 128 registers the bf16 form spills; at three workgroups per CU it does not.)
+// row of 100 tokens has two pages): 200 rows of 16-200 tokens 34.4 -> 31.3 us a pass, 140 of 100-400 39.1 -> 36.3, 500
+// of 100-600 152 -> 142.  (Rows of thousands of tokens, and batches of items cut or dealt out, showed no difference beyond
+// noise.  Within 128 registers the bf16 form spills; at three workgroups per CU it does not.)
 template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves, 3) void decode_kernel_alone(AttnArgs a)
 {

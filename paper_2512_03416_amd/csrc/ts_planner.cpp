@@ -113,7 +113,7 @@ int validate_batch(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* 
 //      outnumber the CUs, and at least 32 pages (auto_split_pages).  8 rows of 1500 tokens in pieces of 32 pages
 //      take 17.3 us a pass, in pieces of 28 (a few items more than CUs) 20.5; 16 rows of 500-3000 tokens 28.1 us
 //      in 28 items per KV head, 36.2 us in pieces of 32 pages (64 items);
-//   4. batches whose rows outnumber the resident workgroups: a row is cut when it exceeds 5/4 of a workgroup slot's
+//   4. batches whose rows outnumber the workgroup slots (those of decode_kernel_lean, see rows_stay_whole): a row is cut when it exceeds 5/4 of a workgroup slot's
 //      fair share, and the dispatcher balances the items, longest first (180 rows of 600-5700 tokens: 382 us
 //      against 390 cut at the fair share itself; with a heavy tail, 600-25 700 tokens and e4m3: 290, at 3/2: 298,
 //      uncut: 382).
@@ -215,8 +215,9 @@ static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t p
 }
 
 // Decode items dealt out evenly: every workgroup gets the same number of pages, whatever rows they belong to; one
-// workgroup per CU with three KV tiles in flight per wave (two per CU with two tiles where a tile is only 2 KB, head
-// dim 64 and e4m3; twice as many where the rows are many, so that a workgroup has not more than two or three).
+// workgroup per CU (two where a tile is only 2 KB, head dim 64 and e4m3; twice as many where the rows are many, so that
+// a workgroup has not more than two or three).  Its waves have three KV tiles in flight (two where a tile is 2 KB), except
+// in passes whose lists are kernel arguments -- of the batches below the first three --: decode_kernel_fused has two.
 // Measured against pieces of one length: 3 rows of 30-131 Ki tokens (64/8 heads, e4m3) 95 us for 119-123, 48 rows of
 // 200-6000 tokens (head dim 64) 57.6 for 61.9, 20 rows of 500-8000 tokens 62 for 74, 100 rows of 1600-5700 tokens
 // (e4m3) 142 for 150; shares below about 80 pages lose to rule 3 (16 rows of 500-4000 tokens, e4m3, 68 pages each:
@@ -265,7 +266,7 @@ static bool deal_decode_evenly(Plan& p, int num_seqs, int64_t pages, const ts_at
     return true;
 }
 
-// Whole rows over the CUs when all their workgroups are resident at once: the memory system serves the CUs alike, so
+// Whole rows over the CUs, for launches that are resident at once or nearly so: the memory system serves the CUs alike, so
 // what matters is the pages per CU.  Rows go, longest first, to the CU with the least that has room (no CU gets more
 // rows than it must); returns the most loaded CU's pages.  order: rows in the order of launch (workgroups are placed
 // round-robin: the first rows of all CUs, then the second rows, ...).
@@ -339,6 +340,12 @@ static int64_t pack_rows(RowPacking& k, int64_t cus)
 // the average: dealing out costs about as much (60 rows of 300-1000 tokens: 36.6 us whole, 41.5 us dealt out; 40 rows
 // of 500-1220 tokens, 20 pages over the average: 34.5 against 39.1; 100 rows of 1600-5700 tokens, e4m3, 36 over:
 // 155 against 142; 48 rows, head dim 64, 44 over: 62.3 against 57.6).
+// They may be as many as decode_kernel_lean has workgroups resident at once (opt.wg_slots; bf16: 1024 with head dim 128,
+// 1792 with 64).  The kernel that runs them, decode_kernel_alone, has fewer (768 and 1536): beyond those up to a quarter
+// start when the first ones end, and the packing no longer describes where.  The line lies where it does because the
+// rules behind it are slower there all the same: whole rows against cut ones, 8 KV heads, bf16: 120 rows of 200-800
+// tokens 49.6 us for 56.8, 104 of 400-1600 77.9 for 87.2, 110 of 300-3000 127.2 for 135.0, head dim 64, 216 of 100-900
+// 45.9 for 53.3 and 224 of 1000-4000 186.1 for 193.7; 128 of 1000-8000 is the exception, 384.9 for 380.9.
 static bool rows_stay_whole(Plan& p, int num_seqs, int64_t pages, const ts_attn_desc& d, const PlanOptions& opt)
 {
     const int64_t cus = std::max<int64_t>(1, opt.n_cu / d.num_kv_heads), rows = p.info.decode_tokens;
