@@ -185,10 +185,9 @@ const char *ts_last_error(const ts_ctx *ctx);
  *   "decode_merge_in_kernel"  decode rows cut into several items are merged by whichever item of a row finishes last
  *                         (arrival counters; the partials are read in item order, so the result does not depend on
  *                         which item came last), or by a small launch behind the items.  0 (default) = in the kernel
- *                         while no row of the batch has more than 16 items, and in the passes of "decode_fused_append"
- *                         with longer rows as well where the merge takes its last item no more than 12 rounds of
- *                         loads; 1 = in the kernel always.  Always the launch: mixed_mode 1, batches with rows of the
- *                         generic kernel, and more split rows than the allocation-free call has counters for
+ *                         while no row of the batch has more than 16 items, 1 = in the kernel always.  Always the
+ *                         launch: mixed_mode 1, batches with rows of the generic kernel, and in the allocation-free
+ *                         call the passes of "decode_fused_append" and more split rows than it has counters for
  *                         (768 / KV heads).  Same results
  *   "decode_fused_append"  1 (default) / 0.  A pass that appends, holds decode rows only and is small (at most 88
  *                         decode items and 32 split rows: its work lists travel as kernel arguments) leaves

@@ -211,18 +211,15 @@ int32_t* cmb_ctr_of(const ts_ctx* c, size_t n_rows)
 // Split decode rows are merged by whichever item of a row finishes last when the rows have few items (at most
 // kMergeInKernelMax, or by option), else by a launch behind them (NULL).  The last item of a row adds up its partials
 // on one CU; the launch spreads a row over one workgroup per head.
-// A small decode-only pass (`small`: its lists fit the kernel arguments) would lose its append to a launch of its own
-// as well, so it merges in the kernel up to kMergeChunksSmall rounds of loads (a workgroup takes 256 groups of four dims
-// and eight splits a round): one row of 9000 tokens (32/8 heads of 128, 18 items) 21.5 -> 14.2 us a pass, of 20 000
-// 25.9 -> 20.5, of 131 000 with 12/3 heads (85 items, 11 rounds) 42.3 -> 40.7; of 100 000 with 64/4 heads (64 items,
-// 16 rounds) the launches are the better: 30.2 against 34.2.
-constexpr int kMergeInKernelMax = 16, kMergeChunksSmall = 12;
-int32_t* merge_counters(const ts_ctx* c, const Plan& p, bool small)
+// In a small decode-only pass, whose lists are kernel arguments, either way: one row of 9000 tokens (32/8 heads of 128, 18
+// items) takes 14.2 us a pass with the launch and 14.4 without, of 100 000 with 64/4 heads (64 items) 25.4 and 35.3, of
+// 40 000 with 16/1 heads (79 items) 16.4 and 25.7; 8 rows of 1500 (3 items each) 16.4 and 15.1, one of 3000 (6) 14.5
+// and 13.4.
+constexpr int kMergeInKernelMax = 16;
+int32_t* merge_counters(const ts_ctx* c, const Plan& p)
 {
     if (p.cmb.empty() || !p.rt.empty() || p.info.mixed_mode == TS_MIXED_ONE_KERNEL) return nullptr;
-    const int32_t groups = (c->desc.num_q_heads / c->desc.num_kv_heads) * (c->desc.head_dim / 4);
-    const int32_t rounds = (groups + 255) / 256 * ((p.max_split + 7) / 8);
-    if (!c->merge_in_kernel && p.max_split > kMergeInKernelMax && !(small && rounds <= kMergeChunksSmall)) return nullptr;
+    if (!c->merge_in_kernel && p.max_split > kMergeInKernelMax) return nullptr;
     if ((int64_t)p.max_split * c->desc.num_q_heads * c->desc.head_dim * 4 >= (int64_t)1 << 31) return nullptr;
     return cmb_ctr_of(c, p.cmb.size());
 }
@@ -943,11 +940,11 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     // allocation-free call, whose upload launch also puts the shared queue heads back to zero)
     const bool ride = k_new && !c->validate_pages && !c->static_call;
     // decode-only batch of matrix-core items whose lists fit into the kernel arguments: the items append the new tokens
-    const bool small = k_new && !c->validate_pages && c->fused_append && desc_uses_mfma_decode(c->desc) && !p.dec.empty() && p.pf.empty() &&
+    const bool fuse = k_new && !c->validate_pages && c->fused_append && desc_uses_mfma_decode(c->desc) && !p.dec.empty() && p.pf.empty() &&
                 p.rt.empty() && p.apt.empty() && p.info.prefill_tokens == 0 && c->dec_nbuf == 2 &&
                 p.dec.size() <= (size_t)kSmallDec && p.cmb.size() <= (size_t)kSmallCmb;
-    int32_t* const ctr = merge_counters(c, p, small);
-    const bool fuse = small && (p.cmb.empty() || ctr);
+    // (the fused form has no upload launch, which puts the counters in the shared scratch back to zero: they are not used)
+    int32_t* const ctr = fuse && c->static_call ? nullptr : merge_counters(c, p);
     UploadJob job;
     rc = upload_plan(c, st, w, ride || fuse ? &job : nullptr);   // (fused form: nothing to upload)
     if (rc != TS_OK) return rc;
@@ -1041,12 +1038,6 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         for (int32_t i = 0; i <= sl.n_wg; ++i) sl.wg[i] = (uint8_t)(p.dec_wg.empty() ? i : p.dec_wg[i]);
         std::copy(p.dec.begin(), p.dec.end(), sl.dec);
         std::copy(p.cmb.begin(), p.cmb.end(), sl.cmb);
-        if (c->static_call && sl.n_cmb > 0) {
-            // (no upload launch here that puts the arrival counters in the shared scratch back to zero)
-            hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(256), 0, st, (const uint4*)nullptr, (uint4*)nullptr, (int64_t)0,
-                               a.cmb_ctr, (int)(sl.n_cmb * c->desc.num_kv_heads));
-            TS_HIP(c, hipGetLastError());
-        }
         e = (hipError_t)timed_launch(c, TS_K_DECODE, true, st, [&] { return launch_decode_fused(a, sl, stream); });
         if (e != hipSuccess) return hip_fail(c, e, "fused decode launch");
     } else {

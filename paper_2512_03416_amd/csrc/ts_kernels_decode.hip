@@ -69,18 +69,18 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel_fused(AttnArgs a
         split |= s.dec[i].part >= 0;
         decode_item<KT, 2, kDecWaves, D, true, true, true>(a, s.dec[i], g, mg, i > first);
     }
-    if (split) arrive_and_merge<D, 64 * kDecWaves>(a, s.dec + first, end - first, s.cmb, g);
+    if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves>(a, s.dec + first, end - first, s.cmb, g);
 }
 
-// Merge of split rows as a launch: one workgroup per (row, head); its groups of D / 4 lanes take a chunk of eight
+// Merge of split rows as a launch (the rows from the device work list, or as kernel arguments behind the fused form): one
+// workgroup per (row, head); its groups of D / 4 lanes take a chunk of eight
 // splits each, the first group adds the chunks up in order.  (A row of 100 splits waits for two loads; one group
 // walking all its splits took 10.6 us for three rows of 32 splits.)
-__global__ __launch_bounds__(256) void combine_kernel(AttnArgs a)
+__device__ __forceinline__ void combine_row(const AttnArgs& a, const CmbItem it)
 {
     constexpr int kMaxGroups = 16;                         // 256 threads / (64 dims / 4)
     __shared__ f32x4 s_o[kMaxGroups][32];
     __shared__ float s_m[kMaxGroups], s_l[kMaxGroups];
-    const CmbItem it = a.cmb[blockIdx.x];
     const int h = blockIdx.y, DQ = a.geo.D / 4, groups = 256 / DQ;
     const int grp = threadIdx.x / DQ, lane = threadIdx.x % DQ;
     const SplitParts parts(a, it.part_begin, it.n_split);
@@ -104,6 +104,8 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnArgs a)
     }
     if (grp == 0) store_merged(a, sum, it.row, h, 4 * lane);
 }
+__global__ __launch_bounds__(256) void combine_kernel(AttnArgs a) { combine_row(a, a.cmb[blockIdx.x]); }
+__global__ __launch_bounds__(256) void combine_kernel_fused(AttnArgs a, SmallLists s) { combine_row(a, s.cmb[blockIdx.x]); }
 
 template <typename KT, int D>
 static int launch_decode_t(const AttnArgs& a, hipStream_t st)
@@ -161,13 +163,15 @@ static int launch_fused_t(const AttnArgs& a, const SmallLists& s, hipStream_t st
 {
     dim3 grid((unsigned)s.n_wg * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
     hipLaunchKernelGGL((decode_kernel_fused<KT, D>), grid, block, 0, st, a, s);
+    if (s.n_cmb > 0 && !a.cmb_ctr)
+        hipLaunchKernelGGL(combine_kernel_fused, dim3((unsigned)s.n_cmb, (unsigned)a.geo.Hq), dim3(256), 0, st, a, s);
     return (int)hipGetLastError();
 }
 
 int launch_decode_fused(const AttnArgs& a, const SmallLists& s, void* stream)
 {
     if (s.n_dec <= 0) return (int)hipSuccess;
-    if (s.n_dec > kSmallDec || s.n_cmb > kSmallCmb || !a.k_new || !a.v_new || (s.n_cmb > 0 && !a.cmb_ctr)) return (int)hipErrorInvalidValue;
+    if (s.n_dec > kSmallDec || s.n_cmb > kSmallCmb || !a.k_new || !a.v_new) return (int)hipErrorInvalidValue;
     if ((a.geo.D != 128 && a.geo.D != 64) || a.geo.q_dtype != TS_BF16) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
     if (a.geo.kv_dtype == TS_BF16) return a.geo.D == 64 ? launch_fused_t<uint16_t, 64>(a, s, st) : launch_fused_t<uint16_t, 128>(a, s, st);

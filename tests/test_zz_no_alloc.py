@@ -97,9 +97,9 @@ def _hip():
 
 @pytest.mark.parametrize("kv,head_dim", [("bf16", 128), ("fp8", 128), ("bf16", 64), ("fp8", 64)])
 def test_noalloc_small_decode_passes_with_split_rows(kv, head_dim):
-    """Decode-only passes whose items append the new tokens and merge the split rows through the arrival counters of
-    the shared scratch: three calls in a row and three replays of a captured one, each byte-equal to the ordinary call
-    and within the bar; and the call puts the counters back to zero itself (its graph: that launch and the pass)."""
+    """Decode-only passes whose items append the new tokens: three calls in a row and three replays of a captured one, each
+    byte-equal to the ordinary call and within the bar.  Nothing in them zeroes the arrival counters of the shared
+    scratch, which another call may have left in any state, so the split rows are merged by a second launch."""
     import gpu_harness as g
     import oracle
     import paper_2512_03416_amd as ts
