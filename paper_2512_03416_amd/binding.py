@@ -142,11 +142,17 @@ def _dev_ptr(t) -> int:
     return t.data_ptr()
 
 
-def _i32_bytes(a):
-    """(int32 values as bytes, their number): a void* argument takes bytes as they are (host arrays are consumed by the
-    call).  A quarter of the time of going through numpy's ctypes interface, twice per pass."""
-    a = np.asarray(a, dtype=np.int32)
-    return a.tobytes(), len(a) if a.ndim else 1
+def _i32_bytes(a) -> bytes:
+    """int32 values as bytes, which a void* argument takes as they are (host arrays are consumed by the call).
+    A quarter of the time of going through numpy's ctypes interface, twice per pass."""
+    return np.asarray(a, dtype=np.int32).tobytes()
+
+
+def _count(lens) -> int:
+    try:
+        return len(lens)
+    except TypeError:                                      # a single number
+        return 1
 
 
 def check_desc(desc: Desc) -> int:
@@ -262,19 +268,18 @@ class Context:
 
     def kv_append(self, k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_table, q_lens,
                   ctx_lens, stream=None):
-        ql, n = _i32_bytes(q_lens)
         self._check(self._lib.ts_kv_append(self._h, self._stream(stream), _dev_ptr(k_new), _dev_ptr(v_new),
                                            _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(k_scale),
-                                           _dev_ptr(v_scale), _dev_ptr(block_table), ql, _i32_bytes(ctx_lens)[0], n))
+                                           _dev_ptr(v_scale), _dev_ptr(block_table), _i32_bytes(q_lens),
+                                           _i32_bytes(ctx_lens), _count(q_lens)))
 
     def mixed_paged_attention(self, q, k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_table,
                               q_lens, ctx_lens, sm_scale: float, out, stream=None, noalloc: bool = False):
         """noalloc=True calls ts_mixed_paged_attention_noalloc (same arguments)."""
         fn = self._lib.ts_mixed_paged_attention_noalloc if noalloc else self._lib.ts_mixed_paged_attention
-        ql, n = _i32_bytes(q_lens)
         rc = fn(self._h, self._stream(stream), _dev_ptr(q), _dev_ptr(k_new), _dev_ptr(v_new),
                 _dev_ptr(k_cache), _dev_ptr(v_cache), _dev_ptr(k_scale), _dev_ptr(v_scale),
-                _dev_ptr(block_table), ql, _i32_bytes(ctx_lens)[0], n, sm_scale, _dev_ptr(out))
+                _dev_ptr(block_table), _i32_bytes(q_lens), _i32_bytes(ctx_lens), _count(q_lens), sm_scale, _dev_ptr(out))
         if rc != TS_OK:
             self._check(rc)
 
