@@ -1,4 +1,6 @@
 // Step a2 (+a4): launchers of the decode kernel and of the merge of split rows.
+#include <algorithm>
+
 #include "ts_decode_item.h"
 
 namespace ts {
@@ -105,7 +107,8 @@ __device__ __forceinline__ void combine_row(const AttnArgs& a, const CmbItem it)
     if (grp == 0) store_merged(a, sum, it.row, h, 4 * lane);
 }
 __global__ __launch_bounds__(256) void combine_kernel(AttnArgs a) { combine_row(a, a.cmb[blockIdx.x]); }
-__global__ __launch_bounds__(256) void combine_kernel_fused(AttnArgs a, SmallLists s) { combine_row(a, s.cmb[blockIdx.x]); }
+struct SmallRows { CmbItem row[kSmallCmb]; };
+__global__ __launch_bounds__(256) void combine_kernel_fused(AttnArgs a, SmallRows s) { combine_row(a, s.row[blockIdx.x]); }
 
 template <typename KT, int D>
 static int launch_decode_t(const AttnArgs& a, hipStream_t st)
@@ -163,8 +166,11 @@ static int launch_fused_t(const AttnArgs& a, const SmallLists& s, hipStream_t st
 {
     dim3 grid((unsigned)s.n_wg * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
     hipLaunchKernelGGL((decode_kernel_fused<KT, D>), grid, block, 0, st, a, s);
-    if (s.n_cmb > 0 && !a.cmb_ctr)
-        hipLaunchKernelGGL(combine_kernel_fused, dim3((unsigned)s.n_cmb, (unsigned)a.geo.Hq), dim3(256), 0, st, a, s);
+    if (s.n_cmb > 0 && !a.cmb_ctr) {
+        SmallRows rows;
+        std::copy(s.cmb, s.cmb + kSmallCmb, rows.row);
+        hipLaunchKernelGGL(combine_kernel_fused, dim3((unsigned)s.n_cmb, (unsigned)a.geo.Hq), dim3(256), 0, st, a, rows);
+    }
     return (int)hipGetLastError();
 }
 
