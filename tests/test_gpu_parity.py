@@ -75,17 +75,16 @@ def test_generic_row_tiles(dtypes, head_dim, heads):
     check(make_batch(shape, [130], [1800], seed=24, value_mult=0.7), options=opts)
 
 
-@pytest.mark.parametrize("bad", ["inf", "nan"])
 @pytest.mark.parametrize("heads", [(4, 1), (5, 1), (2, 2), (16, 1)], ids=lambda h: f"{h[0]}q{h[1]}kv")
-@pytest.mark.parametrize("dtypes,head_dim", [(("f32", "f32"), 64), (("f32", "f32"), 128), (("bf16", "bf16"), 128),
-                                             (("bf16", "bf16"), 64), (("bf16", "fp8"), 64), (("bf16", "fp8"), 128)],
-                         ids=["f32-64", "f32-128", "bf16-128", "bf16-64", "fp8-64", "fp8-128"])
+@pytest.mark.parametrize("dtypes,head_dim,bad", [
+    (d, n, bad) for d, n in [(("f32", "f32"), 64), (("f32", "f32"), 128), (("bf16", "bf16"), 128), (("bf16", "bf16"), 64),
+                             (("bf16", "fp8"), 64), (("bf16", "fp8"), 128)]
+    for bad in ("inf", "nan") if (d[1], bad) != ("fp8", "inf")],                 # (e4m3 saturates infinities)
+    ids=lambda x: x[1] if isinstance(x, tuple) else str(x))
 def test_generic_rows_do_not_see_later_tokens_whatever_their_values(dtypes, head_dim, heads, bad):
     """Tokens of a chunk whose V (or, one of them, K) is infinite or NaN: the tokens before them, which share their row
     tile, come out as the oracle has them; tokens that see one have an infinity or NaN exactly where the oracle does.
     Pages with one and with several such tokens, prefixes inside a page, tiles whose pages are cut."""
-    if dtypes[1] == "fp8" and bad == "inf":
-        pytest.skip("e4m3 saturates infinities")
     shape = AttnShape(heads[0], heads[1], head_dim, *dtypes)
     b = make_batch(shape, [8, 37, 1, 5, 33, 40], [8, 58, 30, 19, 2500, 40], seed=37, pool_rule=1.1, value_mult=0.7)
     val, row0 = float(bad), np.cumsum([0] + list(b.q_lens))
