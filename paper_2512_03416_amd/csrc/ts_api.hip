@@ -95,12 +95,17 @@ struct ts_ctx {
     uint64_t prefill_tokens = 0, decode_tokens = 0, passes = 0;
     bool window_open = false;
     std::chrono::steady_clock::time_point t0;
-    // One event per call, recorded behind its last kernel (the staging slot's): it frees the slot, it is
-    // what a call on another stream waits for (the work-list buffer, the partials and the queue heads
-    // are reused by every call), and it ends the last pass for the velocity counters.  (Every event
-    // record keeps the GPU idle for about 5 us, so a call records exactly one.)
+    // One event per call, on its last kernel (the staging slot's): it frees the slot, it is what a call on another
+    // stream waits for (the work-list buffer, the partials and the queue heads are reused by every call), and it ends
+    // the last pass for the velocity counters.  It rides on the kernel's own packet (launch_kernel); only under stream
+    // capture, and where a call ends early, it is recorded behind the kernels.  A co-resident call ends with two kernels
+    // on two streams: their ends are two events (the second is ev_join), without a third one behind the join (a 2024-token chunk
+    // next to 24 decode rows, events recorded behind the kernels and now: 113.3 -> 110.5 us a pass; 8 decode rows, one
+    // launch: 15.4 -> 14.2).
     HostSlot* cur_slot = nullptr;      // slot of the call in progress
+    bool end_marked = false;           // ... whose event is on a kernel already
     hipEvent_t last_event = nullptr;   // event of the most recent call
+    hipEvent_t last_side_event = nullptr;   // ... and that of its side stream, or NULL
     hipStream_t last_stream = nullptr;
     bool have_work = false;
     // Co-resident launch of a mixed batch: the decode grid runs on this internal stream (default priority),
@@ -388,7 +393,10 @@ int upload_plan(ts_ctx* c, hipStream_t st, const WorkLayout& w, UploadJob* defer
 {
     int rc = ensure_work(c, w.total);
     if (rc != TS_OK) return rc;
-    if (c->have_work && st != c->last_stream) TS_HIP(c, hipStreamWaitEvent(st, c->last_event, 0));
+    if (c->have_work && st != c->last_stream) {
+        TS_HIP(c, hipStreamWaitEvent(st, c->last_event, 0));
+        if (c->last_side_event) TS_HIP(c, hipStreamWaitEvent(st, c->last_side_event, 0));
+    }
     HostSlot* slot = nullptr;
     rc = acquire_slot(c, w.total, &slot);
     if (rc != TS_OK) return rc;
@@ -411,7 +419,8 @@ int upload_plan(ts_ctx* c, hipStream_t st, const WorkLayout& w, UploadJob* defer
     if (!p.wide_base.empty()) memcpy(h + w.wide_base, p.wide_base.data(), p.wide_base.size() * sizeof(int32_t));
     const int64_t n16 = (int64_t)(w.total / 16);           // (every list starts at a multiple of 16)
     const int blocks = (int)std::min<int64_t>(256, (n16 + 255) / 256);
-    c->cur_slot = slot;                                    // its event is recorded by mark_work_done
+    c->cur_slot = slot;                                    // its event marks the end of the call
+    c->end_marked = false;
     if (defer) {
         *defer = UploadJob{(const uint4*)slot->dev_ptr, (uint4*)work_base(c), n16, blocks, (const char*)slot->dev_ptr};
         return TS_OK;
@@ -532,9 +541,19 @@ void probe_side_stream(ts_ctx* c, hipStream_t st)
     c->side_state = 1;
 }
 
-// Marks the end of a call's device work on its stream: the call's one event.  Runs on every path that
-// follows a successful upload_plan, error paths included (the upload kernel may still be reading the slot).
-int mark_work_done(ts_ctx* c, hipStream_t st)
+// Can events ride on the kernels of this stream?  (A captured kernel would leave them out of the graph.)
+bool events_on_kernels(hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Marks the end of a call's device work on its stream: the call's one event, unless it is on the last kernel already.
+// side: the event on the last kernel of the side stream, if that is not ordered before the call's own.  Runs on every
+// path that follows a successful upload_plan, error paths included (the upload kernel may still be reading the slot).
+int mark_work_done(ts_ctx* c, hipStream_t st, hipEvent_t side = nullptr)
 {
     HostSlot* slot = c->cur_slot;
     c->cur_slot = nullptr;
@@ -543,13 +562,14 @@ int mark_work_done(ts_ctx* c, hipStream_t st)
     c->last_stream = st;
     c->have_work = true;
     c->last_event = slot->ev;
-    TS_HIP(c, hipEventRecord(slot->ev, st));
+    c->last_side_event = side;
+    if (!c->end_marked) TS_HIP(c, hipEventRecord(slot->ev, st));
     return TS_OK;
 }
 
 struct WorkDoneGuard {                                     // records the event when a call leaves early
     ts_ctx* c; hipStream_t st;
-    ~WorkDoneGuard() { if (c->cur_slot) (void)mark_work_done(c, st); }
+    ~WorkDoneGuard() { if (c->cur_slot) { c->end_marked = false; (void)mark_work_done(c, st); } }
 };
 
 // The append of a batch of few sequences, described by kernel arguments; false = not such a batch, or source rows that
@@ -882,8 +902,10 @@ extern "C" int ts_kv_append(ts_ctx* c, void* stream, const void* k_new, const vo
         a.apt_host = (const AppTile*)(job.host_lists + w.apt);
         a.up_src = job.src; a.up_dst = job.dst; a.up_n16 = job.n16; a.up_blocks = job.blocks;
     }
-    hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return opt.append_lists ? launch_append(a, stream) : launch_append_few(a, few, stream); });
+    const hipEvent_t done = events_on_kernels(st) ? c->cur_slot->ev : nullptr;
+    hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return opt.append_lists ? launch_append(a, stream, done) : launch_append_few(a, few, stream, done); });
     if (e != hipSuccess) return hip_fail(c, e, "append launch");
+    c->end_marked = done != nullptr;
     return mark_work_done(c, st);
 }
 
@@ -954,6 +976,14 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
 
     const Geometry geo = geometry_of(c->desc);
     const char* wb = work_base(c);
+    // Events on the kernels: the call's end on its last one, the fork of a co-resident launch on the last one before it
+    // (recorded as before while the side stream is being probed: the probe's kernel comes in between).
+    const bool coresident = !p.queue.empty() && p.info.mixed_mode == TS_MIXED_CORESIDENT;
+    const bool on_kernels = events_on_kernels(st);
+    const hipEvent_t done = on_kernels ? c->cur_slot->ev : nullptr;
+    const hipEvent_t fork = on_kernels && coresident && (c->side_state == 2 || !c->h_probe) ? c->ev_fork : nullptr;
+    bool forked = false;
+    hipEvent_t side_end = nullptr;
     if (k_new && !fuse) {
         AppendArgs ap{};
         ap.geo = geo;
@@ -967,8 +997,10 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
             ap.apt_host = (const AppTile*)(job.host_lists + w.apt);
             ap.up_src = job.src; ap.up_dst = job.dst; ap.up_n16 = job.n16; ap.up_blocks = job.blocks;
         }
-        hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return append_lists ? launch_append(ap, stream) : launch_append_few(ap, few, stream); });
+        const hipEvent_t ev = p.wide.empty() ? fork : nullptr;
+        hipError_t e = (hipError_t)timed_launch(c, TS_K_APPEND, true, st, [&] { return append_lists ? launch_append(ap, stream, ev) : launch_append_few(ap, few, stream, ev); });
         if (e != hipSuccess) return hip_fail(c, e, "append launch");
+        forked = ev != nullptr;
     }
     AttnArgs a{};
     a.geo = geo;
@@ -1001,34 +1033,42 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
 
     hipError_t e;
     // fp8 cache: bf16 copies of the pages the prefill tiles read (behind the append: the chunk's own tokens are among them)
-    e = (hipError_t)timed_launch(c, TS_K_PREFILL, false, st, [&] { return launch_widen(a, c->d_wide_k, c->d_wide_v, stream); });
+    e = (hipError_t)timed_launch(c, TS_K_PREFILL, false, st, [&] { return launch_widen(a, c->d_wide_k, c->d_wide_v, stream, fork); });
     if (e != hipSuccess) return hip_fail(c, e, "widen launch");
+    forked = forked || (fork && a.n_wide > 0);
     // decode first: the serving loop's TPOT depends on these rows (Sec. 4.5.2)
-    if (a.n_queue > 0 && p.info.mixed_mode == TS_MIXED_CORESIDENT) {
+    const bool merge_launch = a.n_cmb > 0 && !a.cmb_ctr, pf_merge = p.pf_merge_launch;
+    if (coresident) {
         // mixed batch, co-resident: the prefill tiles go to resident workgroups on this stream, the decode items
         // (and the merge of split rows) to a grid of their own on the side stream, which starts behind everything
         // this stream holds so far (the append) and which this stream waits for again before the call's end
         // is marked.  The prefill launch comes first so that its workgroups take their places on the CUs.
         // Timed as one unit (TS_K_MIXED): events between the two launches would serialise them.
         probe_side_stream(c, st);
+        const hipEvent_t pf_end = pf_merge ? nullptr : done;
+        const hipEvent_t join = on_kernels ? c->ev_join : nullptr;
         e = (hipError_t)timed_launch(c, TS_K_MIXED, true, st, [&] {
-            hipError_t r = hipEventRecord(c->ev_fork, st);
-            if (r == hipSuccess) r = (hipError_t)launch_prefill_resident(a, stream);
+            hipError_t r = forked ? hipSuccess : hipEventRecord(c->ev_fork, st);
+            if (r == hipSuccess) r = (hipError_t)launch_prefill_resident(a, stream, pf_end);
             if (r == hipSuccess) r = hipStreamWaitEvent(c->side, c->ev_fork, 0);
-            if (r == hipSuccess) r = (hipError_t)launch_decode(a, (void*)c->side);
-            if (r == hipSuccess && !a.cmb_ctr) r = (hipError_t)launch_combine(a, (void*)c->side);
+            if (r == hipSuccess) r = (hipError_t)launch_decode(a, (void*)c->side, merge_launch ? nullptr : join);
+            if (r == hipSuccess && merge_launch) r = (hipError_t)launch_combine(a, (void*)c->side, join);
             // (the join is made even after a failed launch: the side stream must not run on unordered)
-            const hipError_t j1 = hipEventRecord(c->ev_join, c->side);
+            const hipError_t j1 = join && r == hipSuccess ? hipSuccess : hipEventRecord(c->ev_join, c->side);
             const hipError_t j2 = j1 == hipSuccess ? hipStreamWaitEvent(st, c->ev_join, 0) : j1;
             return (int)(r != hipSuccess ? r : j2);
         });
         if (e != hipSuccess) return hip_fail(c, e, "co-resident launch");
+        c->end_marked = pf_end != nullptr;
+        side_end = pf_end ? c->ev_join : nullptr;
     } else if (a.n_queue > 0) {
         // mixed batch, by option: decode items and prefill tiles share the workgroups of one persistent launch
-        e = (hipError_t)timed_launch(c, TS_K_MIXED, true, st, [&] { return launch_mixed(a, stream); });
+        const hipEvent_t mixed_end = merge_launch || pf_merge ? nullptr : done, merge_end = pf_merge ? nullptr : done;
+        e = (hipError_t)timed_launch(c, TS_K_MIXED, true, st, [&] { return launch_mixed(a, stream, mixed_end); });
         if (e != hipSuccess) return hip_fail(c, e, "mixed launch");
-        e = (hipError_t)timed_launch(c, TS_K_COMBINE, a.n_cmb > 0 && !a.cmb_ctr, st, [&] { return a.cmb_ctr ? 0 : launch_combine(a, stream); });
+        e = (hipError_t)timed_launch(c, TS_K_COMBINE, merge_launch, st, [&] { return merge_launch ? launch_combine(a, stream, merge_end) : 0; });
         if (e != hipSuccess) return hip_fail(c, e, "combine launch");
+        c->end_marked = merge_end != nullptr;
     } else if (fuse) {
         // small decode-only batch: the lists travel as kernel arguments, the items append the new tokens
         // (nothing was uploaded: the staging slot only lends the call its event)
@@ -1038,21 +1078,29 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
         for (int32_t i = 0; i <= sl.n_wg; ++i) sl.wg[i] = (uint8_t)(p.dec_wg.empty() ? i : p.dec_wg[i]);
         std::copy(p.dec.begin(), p.dec.end(), sl.dec);
         std::copy(p.cmb.begin(), p.cmb.end(), sl.cmb);
-        e = (hipError_t)timed_launch(c, TS_K_DECODE, true, st, [&] { return launch_decode_fused(a, sl, stream); });
+        e = (hipError_t)timed_launch(c, TS_K_DECODE, true, st, [&] { return launch_decode_fused(a, sl, stream, done); });
         if (e != hipSuccess) return hip_fail(c, e, "fused decode launch");
+        c->end_marked = done != nullptr;
     } else {
-        e = (hipError_t)timed_launch(c, TS_K_DECODE, a.n_dec > 0, st, [&] { return launch_decode(a, stream); });
+        // (the last of these that has work carries the call's event)
+        const bool has_pf = a.n_pf > 0, has_rows = a.n_rt > 0;
+        auto end_if_last = [&](bool more) { return more || pf_merge ? nullptr : done; };
+        e = (hipError_t)timed_launch(c, TS_K_DECODE, a.n_dec > 0, st, [&] { return launch_decode(a, stream, end_if_last(has_rows || merge_launch || has_pf)); });
         if (e != hipSuccess) return hip_fail(c, e, "decode launch");
-        e = (hipError_t)timed_launch(c, TS_K_ROWS, a.n_rt > 0, st, [&] { return launch_rows(a, stream); });
+        e = (hipError_t)timed_launch(c, TS_K_ROWS, has_rows, st, [&] { return launch_rows(a, stream, end_if_last(merge_launch || has_pf)); });
         if (e != hipSuccess) return hip_fail(c, e, "rows launch");
-        e = (hipError_t)timed_launch(c, TS_K_COMBINE, a.n_cmb > 0 && !a.cmb_ctr, st, [&] { return a.cmb_ctr ? 0 : launch_combine(a, stream); });
+        e = (hipError_t)timed_launch(c, TS_K_COMBINE, merge_launch, st, [&] { return merge_launch ? launch_combine(a, stream, end_if_last(has_pf)) : 0; });
         if (e != hipSuccess) return hip_fail(c, e, "combine launch");
-        e = (hipError_t)timed_launch(c, TS_K_PREFILL, a.n_pf > 0, st, [&] { return launch_prefill(a, stream); });
+        e = (hipError_t)timed_launch(c, TS_K_PREFILL, has_pf, st, [&] { return launch_prefill(a, stream, end_if_last(false)); });
         if (e != hipSuccess) return hip_fail(c, e, "prefill launch");
+        c->end_marked = !pf_merge && done != nullptr && (a.n_dec > 0 || has_rows || merge_launch || has_pf);
     }
-    e = (hipError_t)timed_launch(c, TS_K_COMBINE, p.pf_merge_launch, st, [&] { return p.pf_merge_launch ? launch_prefill_combine(a, stream) : 0; });
-    if (e != hipSuccess) return hip_fail(c, e, "prefill combine launch");
-    rc = mark_work_done(c, st);
+    if (pf_merge) {
+        e = (hipError_t)timed_launch(c, TS_K_COMBINE, true, st, [&] { return launch_prefill_combine(a, stream, done); });
+        if (e != hipSuccess) return hip_fail(c, e, "prefill combine launch");
+        c->end_marked = done != nullptr && a.n_pfcmb > 0;
+    }
+    rc = mark_work_done(c, st, side_end);
     if (rc != TS_OK) return rc;
     {
         std::lock_guard<std::mutex> lk(c->mu);
@@ -1099,6 +1147,7 @@ extern "C" int ts_token_velocity(ts_ctx* c, ts_velocity* out, int flags)
     if ((flags & TS_VELOCITY_SYNC) && c->have_work) {
         DeviceGuard guard(c->device);
         TS_HIP(c, hipEventSynchronize(c->last_event));     // the most recent call's end (a pass or an append)
+        if (c->last_side_event) TS_HIP(c, hipEventSynchronize(c->last_side_event));
     }
     std::lock_guard<std::mutex> lk(c->mu);
     ts_velocity v{};

@@ -277,21 +277,22 @@ struct SmallLists {
 
 static_assert(sizeof(AttnArgs) + sizeof(SmallLists) <= 4096 && sizeof(AppendArgs) + sizeof(AppendSeqs) <= 4096, "kernel arguments");
 
-// Launchers (defined in the .hip files).  All return a hipError_t cast to int.
-int launch_append(const AppendArgs& a, void* stream);
-int launch_append_few(const AppendArgs& a, const AppendSeqs& s, void* stream);
-int launch_rows(const AttnArgs& a, void* stream);
-int launch_decode(const AttnArgs& a, void* stream);
-int launch_combine(const AttnArgs& a, void* stream);
-int launch_decode_fused(const AttnArgs& a, const SmallLists& lists, void* stream);   // decode items + merge of split rows
+// Launchers (defined in the .hip files).  All return a hipError_t cast to int.  done: a hipEvent_t recorded at the end of
+// the (last) kernel that is launched, or NULL; a launcher without work does not record it.
+int launch_append(const AppendArgs& a, void* stream, void* done);
+int launch_append_few(const AppendArgs& a, const AppendSeqs& s, void* stream, void* done);
+int launch_rows(const AttnArgs& a, void* stream, void* done);
+int launch_decode(const AttnArgs& a, void* stream, void* done);
+int launch_combine(const AttnArgs& a, void* stream, void* done);
+int launch_decode_fused(const AttnArgs& a, const SmallLists& lists, void* stream, void* done);   // decode items + merge of split rows
 // Resident workgroups of the decode / persistent kernel on the current device (0 if unknown).  The
 // caller keeps the answers per context: two contexts may sit on different GPUs.
 int decode_resident_workgroups(int kv_dtype, int nbuf, int head_dim);
 int mixed_resident_workgroups(int kv_dtype);
-int launch_widen(const AttnArgs& a, void* wide_k, void* wide_v, void* stream);
-int launch_prefill(const AttnArgs& a, void* stream);
-int launch_mixed(const AttnArgs& a, void* stream);
-int launch_prefill_resident(const AttnArgs& a, void* stream);
-int launch_prefill_combine(const AttnArgs& a, void* stream);
+int launch_widen(const AttnArgs& a, void* wide_k, void* wide_v, void* stream, void* done);
+int launch_prefill(const AttnArgs& a, void* stream, void* done);
+int launch_mixed(const AttnArgs& a, void* stream, void* done);
+int launch_prefill_resident(const AttnArgs& a, void* stream, void* done);
+int launch_prefill_combine(const AttnArgs& a, void* stream, void* done);
 
 }  // namespace ts

@@ -16,6 +16,7 @@
 //     by token wrote 5.5x the new bytes: every 2-byte V element dirtied its own cache sector.)
 // All convert to the cache element type with the same functions, so the bytes are identical.
 #include "ts_device.h"
+#include "ts_launch.h"
 
 namespace ts {
 
@@ -277,34 +278,36 @@ __global__ __launch_bounds__(256) void append_small_kernel(AppendArgs a, AppendS
 }
 
 template <typename DST, int D>
-static int launch_append_small(const AppendArgs& a, const AppendSeqs& s, hipStream_t st)
+static int launch_append_small(const AppendArgs& a, const AppendSeqs& s, hipStream_t st, hipEvent_t done)
 {
     const dim3 grid((unsigned)s.n_pages * (unsigned)a.geo.Hkv + (unsigned)a.up_blocks);
-    hipLaunchKernelGGL((append_small_kernel<DST, D>), grid, dim3(256), 0, st, a, s);
-    return (int)hipGetLastError();
+    return launch_kernel(append_small_kernel<DST, D>, grid, dim3(256), st, done, a, s);
 }
 
-int launch_append_few(const AppendArgs& a, const AppendSeqs& s, void* stream)
+int launch_append_few(const AppendArgs& a, const AppendSeqs& s, void* stream, void* done)
 {
     if (s.n <= 0) return (int)hipSuccess;
     if (s.n > kAppendSeqs || s.n_pages <= 0 || (a.geo.D != 128 && a.geo.D != 64)) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
+    hipEvent_t ev = (hipEvent_t)done;
     const bool d128 = a.geo.D == 128;
     if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32)
-        return d128 ? launch_append_small<float, 128>(a, s, st) : launch_append_small<float, 64>(a, s, st);
+        return d128 ? launch_append_small<float, 128>(a, s, st, ev) : launch_append_small<float, 64>(a, s, st, ev);
     if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16)
-        return d128 ? launch_append_small<uint16_t, 128>(a, s, st) : launch_append_small<uint16_t, 64>(a, s, st);
+        return d128 ? launch_append_small<uint16_t, 128>(a, s, st, ev) : launch_append_small<uint16_t, 64>(a, s, st, ev);
     if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3)
-        return d128 ? launch_append_small<uint8_t, 128>(a, s, st) : launch_append_small<uint8_t, 64>(a, s, st);
+        return d128 ? launch_append_small<uint8_t, 128>(a, s, st, ev) : launch_append_small<uint8_t, 64>(a, s, st, ev);
     return (int)hipErrorInvalidValue;
 }
 
-int launch_append(const AppendArgs& args, void* stream)
+int launch_append(const AppendArgs& args, void* stream, void* done)
 {
     if (args.total_tokens <= 0) return (int)hipSuccess;
     hipStream_t st = (hipStream_t)stream;
+    hipEvent_t ev = args.n_apt > 0 ? nullptr : (hipEvent_t)done;     // (of the token-wise launch)
     dim3 block(256);
     AppendArgs a = args;
+    int e = (int)hipSuccess;
     // the upload (if any) rides in the first launch, which then reads its own list from the staging buffer
     if (a.up_blocks > 0) {
         if (a.n_apr > 0) a.apr = a.apr_host; else a.apt = a.apt_host;
@@ -312,21 +315,22 @@ int launch_append(const AppendArgs& args, void* stream)
     if (a.n_apr > 0 && a.geo.q_dtype == TS_F32) {
         if (a.geo.kv_dtype != TS_F32 || (a.geo.D != 128 && a.geo.D != 64)) return (int)hipErrorInvalidValue;
         const int64_t most = kMaxWorkgroups > a.geo.Hkv ? kMaxWorkgroups / a.geo.Hkv : 1;
-        for (int64_t first = 0, left = a.n_apr; left > 0; first += most, left -= most) {
+        for (int64_t first = 0, left = a.n_apr; left > 0 && e == (int)hipSuccess; first += most, left -= most) {
             AppendArgs part = a;
             part.apr = a.apr + first;
             part.n_apr = (int32_t)(left < most ? left : most);
             if (first > 0) part.up_blocks = 0;
             const dim3 grid((unsigned)part.n_apr * (unsigned)a.geo.Hkv + (unsigned)part.up_blocks);
-            if (a.geo.D == 128) hipLaunchKernelGGL(append_run_kernel<128>, grid, block, 0, st, part);
-            else hipLaunchKernelGGL(append_run_kernel<64>, grid, block, 0, st, part);
+            const hipEvent_t pe = left <= most ? ev : nullptr;
+            if (a.geo.D == 128) e = launch_kernel(append_run_kernel<128>, grid, block, st, pe, part);
+            else e = launch_kernel(append_run_kernel<64>, grid, block, st, pe, part);
         }
     } else if (a.n_apr > 0) {
         dim3 grid((unsigned)(a.n_apr + a.up_blocks));
         if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16)
-            hipLaunchKernelGGL((append_token_kernel<uint16_t>), grid, block, 0, st, a);
+            e = launch_kernel(append_token_kernel<uint16_t>, grid, block, st, ev, a);
         else if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3)
-            hipLaunchKernelGGL((append_token_kernel<uint8_t>), grid, block, 0, st, a);
+            e = launch_kernel(append_token_kernel<uint8_t>, grid, block, st, ev, a);
         else
             return (int)hipErrorInvalidValue;
     }
@@ -334,20 +338,18 @@ int launch_append(const AppendArgs& args, void* stream)
         a.up_blocks = 0;                               // done; the page-wise kernel finds its list on the device
         a.apt = args.apt;
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || a.n_apt == 0) return (int)e;
+    if (e != (int)hipSuccess || a.n_apt == 0) return e;
     if (a.geo.q_dtype != TS_BF16 || (a.geo.D != 128 && a.geo.D != 64)) return (int)hipErrorInvalidValue;
     if (a.geo.kv_dtype != TS_BF16 && a.geo.kv_dtype != TS_FP8_E4M3) return (int)hipErrorInvalidValue;
     dim3 tgrid((unsigned)a.n_apt * (unsigned)a.geo.Hkv + (unsigned)a.up_blocks);
     const bool bf = a.geo.kv_dtype == TS_BF16;
+    const hipEvent_t te = (hipEvent_t)done;
     if (a.geo.D == 128) {
-        if (bf) hipLaunchKernelGGL((append_tile_kernel<uint16_t, 128>), tgrid, block, 0, st, a);
-        else hipLaunchKernelGGL((append_tile_kernel<uint8_t, 128>), tgrid, block, 0, st, a);
-    } else {
-        if (bf) hipLaunchKernelGGL((append_tile_kernel<uint16_t, 64>), tgrid, block, 0, st, a);
-        else hipLaunchKernelGGL((append_tile_kernel<uint8_t, 64>), tgrid, block, 0, st, a);
+        if (bf) return launch_kernel(append_tile_kernel<uint16_t, 128>, tgrid, block, st, te, a);
+        return launch_kernel(append_tile_kernel<uint8_t, 128>, tgrid, block, st, te, a);
     }
-    return (int)hipGetLastError();
+    if (bf) return launch_kernel(append_tile_kernel<uint16_t, 64>, tgrid, block, st, te, a);
+    return launch_kernel(append_tile_kernel<uint8_t, 64>, tgrid, block, st, te, a);
 }
 
 }  // namespace ts

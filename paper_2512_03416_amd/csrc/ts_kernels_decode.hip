@@ -2,6 +2,7 @@
 #include <algorithm>
 
 #include "ts_decode_item.h"
+#include "ts_launch.h"
 
 namespace ts {
 
@@ -111,19 +112,17 @@ struct SmallRows { CmbItem row[kSmallCmb]; };
 __global__ __launch_bounds__(256) void combine_kernel_fused(AttnArgs a, SmallRows s) { combine_row(a, s.row[blockIdx.x]); }
 
 template <typename KT, int D>
-static int launch_decode_t(const AttnArgs& a, hipStream_t st)
+static int launch_decode_t(const AttnArgs& a, hipStream_t st, hipEvent_t done)
 {
     dim3 grid((unsigned)(a.dec_wg ? a.n_dec_wg : a.n_dec) * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
     switch (a.dec_nbuf) {
-    case 3: hipLaunchKernelGGL((decode_kernel<KT, 3, D>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((decode_kernel<KT, 4, D>), grid, block, 0, st, a); break;
+    case 3: return launch_kernel(decode_kernel<KT, 3, D>, grid, block, st, done, a);
+    case 4: return launch_kernel(decode_kernel<KT, 4, D>, grid, block, st, done, a);
     default:
-        if (a.dec_wg || a.cmb_ctr) hipLaunchKernelGGL((decode_kernel_lean_merging<KT, D>), grid, block, 0, st, a);
-        else if (a.n_queue == 0) hipLaunchKernelGGL((decode_kernel_alone<KT, D>), grid, block, 0, st, a);   // (queues: the tiles of a co-resident launch)
-        else hipLaunchKernelGGL((decode_kernel_lean<KT, D>), grid, block, 0, st, a);
-        break;
+        if (a.dec_wg || a.cmb_ctr) return launch_kernel(decode_kernel_lean_merging<KT, D>, grid, block, st, done, a);
+        if (a.n_queue == 0) return launch_kernel(decode_kernel_alone<KT, D>, grid, block, st, done, a);   // (queues: the tiles of a co-resident launch)
+        return launch_kernel(decode_kernel_lean<KT, D>, grid, block, st, done, a);
     }
-    return (int)hipGetLastError();
 }
 
 template <typename KT, int D>
@@ -151,45 +150,45 @@ int decode_resident_workgroups(int kv_dtype, int nbuf, int head_dim)
     return cus * per_cu;
 }
 
-int launch_decode(const AttnArgs& a, void* stream)
+int launch_decode(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_dec <= 0) return (int)hipSuccess;
     if ((a.geo.D != 128 && a.geo.D != 64) || a.geo.q_dtype != TS_BF16) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
-    if (a.geo.kv_dtype == TS_BF16) return a.geo.D == 64 ? launch_decode_t<uint16_t, 64>(a, st) : launch_decode_t<uint16_t, 128>(a, st);
-    if (a.geo.kv_dtype == TS_FP8_E4M3) return a.geo.D == 64 ? launch_decode_t<uint8_t, 64>(a, st) : launch_decode_t<uint8_t, 128>(a, st);
+    hipEvent_t ev = (hipEvent_t)done;
+    if (a.geo.kv_dtype == TS_BF16) return a.geo.D == 64 ? launch_decode_t<uint16_t, 64>(a, st, ev) : launch_decode_t<uint16_t, 128>(a, st, ev);
+    if (a.geo.kv_dtype == TS_FP8_E4M3) return a.geo.D == 64 ? launch_decode_t<uint8_t, 64>(a, st, ev) : launch_decode_t<uint8_t, 128>(a, st, ev);
     return (int)hipErrorInvalidValue;
 }
 
 template <typename KT, int D>
-static int launch_fused_t(const AttnArgs& a, const SmallLists& s, hipStream_t st)
+static int launch_fused_t(const AttnArgs& a, const SmallLists& s, hipStream_t st, hipEvent_t done)
 {
     dim3 grid((unsigned)s.n_wg * (unsigned)a.geo.Hkv), block(64 * kDecWaves);
-    hipLaunchKernelGGL((decode_kernel_fused<KT, D>), grid, block, 0, st, a, s);
-    if (s.n_cmb > 0 && !a.cmb_ctr) {
-        SmallRows rows;
-        std::copy(s.cmb, s.cmb + kSmallCmb, rows.row);
-        hipLaunchKernelGGL(combine_kernel_fused, dim3((unsigned)s.n_cmb, (unsigned)a.geo.Hq), dim3(256), 0, st, a, rows);
-    }
-    return (int)hipGetLastError();
+    const bool merge = s.n_cmb > 0 && !a.cmb_ctr;
+    const int e = launch_kernel(decode_kernel_fused<KT, D>, grid, block, st, merge ? nullptr : done, a, s);
+    if (e != (int)hipSuccess || !merge) return e;
+    SmallRows rows;
+    std::copy(s.cmb, s.cmb + kSmallCmb, rows.row);
+    return launch_kernel(combine_kernel_fused, dim3((unsigned)s.n_cmb, (unsigned)a.geo.Hq), dim3(256), st, done, a, rows);
 }
 
-int launch_decode_fused(const AttnArgs& a, const SmallLists& s, void* stream)
+int launch_decode_fused(const AttnArgs& a, const SmallLists& s, void* stream, void* done)
 {
     if (s.n_dec <= 0) return (int)hipSuccess;
     if (s.n_dec > kSmallDec || s.n_cmb > kSmallCmb || !a.k_new || !a.v_new) return (int)hipErrorInvalidValue;
     if ((a.geo.D != 128 && a.geo.D != 64) || a.geo.q_dtype != TS_BF16) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
-    if (a.geo.kv_dtype == TS_BF16) return a.geo.D == 64 ? launch_fused_t<uint16_t, 64>(a, s, st) : launch_fused_t<uint16_t, 128>(a, s, st);
-    if (a.geo.kv_dtype == TS_FP8_E4M3) return a.geo.D == 64 ? launch_fused_t<uint8_t, 64>(a, s, st) : launch_fused_t<uint8_t, 128>(a, s, st);
+    hipEvent_t ev = (hipEvent_t)done;
+    if (a.geo.kv_dtype == TS_BF16) return a.geo.D == 64 ? launch_fused_t<uint16_t, 64>(a, s, st, ev) : launch_fused_t<uint16_t, 128>(a, s, st, ev);
+    if (a.geo.kv_dtype == TS_FP8_E4M3) return a.geo.D == 64 ? launch_fused_t<uint8_t, 64>(a, s, st, ev) : launch_fused_t<uint8_t, 128>(a, s, st, ev);
     return (int)hipErrorInvalidValue;
 }
 
-int launch_combine(const AttnArgs& a, void* stream)
+int launch_combine(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_cmb <= 0) return (int)hipSuccess;
-    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)a.n_cmb, (unsigned)a.geo.Hq), dim3(256), 0, (hipStream_t)stream, a);
-    return (int)hipGetLastError();
+    return launch_kernel(combine_kernel, dim3((unsigned)a.n_cmb, (unsigned)a.geo.Hq), dim3(256), (hipStream_t)stream, (hipEvent_t)done, a);
 }
 
 }  // namespace ts

@@ -15,6 +15,7 @@
 //   - the last workgroup to leave puts the queue heads back to zero for the next launch.
 // The work itself is the same code as the stand-alone kernels (decode_item, prefill_tile).
 #include "ts_decode_item.h"
+#include "ts_launch.h"
 #include "ts_prefill_tile.h"
 
 namespace ts {
@@ -107,16 +108,15 @@ int mixed_resident_workgroups(int kv_dtype)
 }
 
 template <typename KT, typename PKT, bool WIDE>
-static int launch_mixed_t(const AttnArgs& a, hipStream_t st)
+static int launch_mixed_t(const AttnArgs& a, hipStream_t st, hipEvent_t done)
 {
     const int n = a.mixed_wgs;                                 // resident workgroups on the context's GPU
     if (n <= 0) return (int)hipErrorInvalidValue;
     const int grid = n < a.n_queue ? n : a.n_queue;
-    hipLaunchKernelGGL((mixed_kernel<KT, PKT, WIDE, 2>), dim3((unsigned)grid), dim3(kPfThreads), 0, st, a);
-    return (int)hipGetLastError();
+    return launch_kernel(mixed_kernel<KT, PKT, WIDE, 2>, dim3((unsigned)grid), dim3(kPfThreads), st, done, a);
 }
 
-int launch_prefill_resident(const AttnArgs& a, void* stream)
+int launch_prefill_resident(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_queue <= 0) return (int)hipSuccess;
     if (a.geo.D != 128 || a.geo.q_dtype != TS_BF16 || a.n_xcd <= 0 || a.n_xcd > 64 || a.n_cu <= 0) return (int)hipErrorInvalidValue;
@@ -124,21 +124,22 @@ int launch_prefill_resident(const AttnArgs& a, void* stream)
     const int grid = want < a.n_queue ? want : a.n_queue;
     hipStream_t st = (hipStream_t)stream;
     const dim3 g3((unsigned)grid), b3(kPfThreads);
-    if (a.geo.kv_dtype == TS_BF16) hipLaunchKernelGGL((prefill_resident_kernel<uint16_t, false>), g3, b3, 0, st, a);
-    else if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) hipLaunchKernelGGL((prefill_resident_kernel<uint16_t, true>), g3, b3, 0, st, a);
-    else if (a.geo.kv_dtype == TS_FP8_E4M3) hipLaunchKernelGGL((prefill_resident_kernel<uint8_t, false>), g3, b3, 0, st, a);
-    else return (int)hipErrorInvalidValue;
-    return (int)hipGetLastError();
+    const hipEvent_t ev = (hipEvent_t)done;
+    if (a.geo.kv_dtype == TS_BF16) return launch_kernel(prefill_resident_kernel<uint16_t, false>, g3, b3, st, ev, a);
+    if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) return launch_kernel(prefill_resident_kernel<uint16_t, true>, g3, b3, st, ev, a);
+    if (a.geo.kv_dtype == TS_FP8_E4M3) return launch_kernel(prefill_resident_kernel<uint8_t, false>, g3, b3, st, ev, a);
+    return (int)hipErrorInvalidValue;
 }
 
-int launch_mixed(const AttnArgs& a, void* stream)
+int launch_mixed(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_queue <= 0) return (int)hipSuccess;
     if (a.geo.D != 128 || a.geo.q_dtype != TS_BF16 || a.n_xcd <= 0 || a.n_xcd > 64) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
-    if (a.geo.kv_dtype == TS_BF16) return launch_mixed_t<uint16_t, uint16_t, false>(a, st);
-    if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) return launch_mixed_t<uint8_t, uint16_t, true>(a, st);
-    if (a.geo.kv_dtype == TS_FP8_E4M3) return launch_mixed_t<uint8_t, uint8_t, false>(a, st);
+    hipEvent_t ev = (hipEvent_t)done;
+    if (a.geo.kv_dtype == TS_BF16) return launch_mixed_t<uint16_t, uint16_t, false>(a, st, ev);
+    if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) return launch_mixed_t<uint8_t, uint16_t, true>(a, st, ev);
+    if (a.geo.kv_dtype == TS_FP8_E4M3) return launch_mixed_t<uint8_t, uint8_t, false>(a, st, ev);
     return (int)hipErrorInvalidValue;
 }
 

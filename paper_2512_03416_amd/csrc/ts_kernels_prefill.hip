@@ -1,4 +1,5 @@
 // Step a3: launcher of the prefill-tile kernel.
+#include "ts_launch.h"
 #include "ts_prefill_tile.h"
 
 namespace ts {
@@ -116,43 +117,43 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(AttnArgs a)
     }
 }
 
-int launch_prefill_combine(const AttnArgs& a, void* stream)
+int launch_prefill_combine(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_pfcmb <= 0) return (int)hipSuccess;
     if ((a.geo.D != 128 && a.geo.D != 64) || !a.pf_part_o || !a.pf_part_ml) return (int)hipErrorInvalidValue;
     const unsigned grid = (unsigned)a.n_pfcmb * (unsigned)a.geo.Hkv * (unsigned)(kPfPartRows / kPfCmbRows);
-    if (a.geo.D == 64) hipLaunchKernelGGL(prefill_combine_kernel<64>, dim3(grid), dim3(256), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL(prefill_combine_kernel<128>, dim3(grid), dim3(256), 0, (hipStream_t)stream, a);
-    return (int)hipGetLastError();
+    if (a.geo.D == 64) return launch_kernel(prefill_combine_kernel<64>, dim3(grid), dim3(256), (hipStream_t)stream, (hipEvent_t)done, a);
+    return launch_kernel(prefill_combine_kernel<128>, dim3(grid), dim3(256), (hipStream_t)stream, (hipEvent_t)done, a);
 }
 
-int launch_widen(const AttnArgs& a, void* wide_k, void* wide_v, void* stream)
+int launch_widen(const AttnArgs& a, void* wide_k, void* wide_v, void* stream, void* done)
 {
     if (a.n_wide <= 0) return (int)hipSuccess;
     if ((a.geo.D != 128 && a.geo.D != 64) || a.geo.kv_dtype != TS_FP8_E4M3 || !wide_k || !wide_v) return (int)hipErrorInvalidValue;
-    const dim3 grid((unsigned)a.n_wide * (unsigned)a.geo.Hkv);
-    if (a.geo.D == 64) hipLaunchKernelGGL(widen_kernel<64>, grid, dim3(256), 0, (hipStream_t)stream, a, (uint16_t*)wide_k, (uint16_t*)wide_v);
-    else hipLaunchKernelGGL(widen_kernel<128>, grid, dim3(256), 0, (hipStream_t)stream, a, (uint16_t*)wide_k, (uint16_t*)wide_v);
-    return (int)hipGetLastError();
+    const dim3 grid((unsigned)a.n_wide * (unsigned)a.geo.Hkv), block(256);
+    hipStream_t st = (hipStream_t)stream;
+    hipEvent_t ev = (hipEvent_t)done;
+    if (a.geo.D == 64) return launch_kernel(widen_kernel<64>, grid, block, st, ev, a, (uint16_t*)wide_k, (uint16_t*)wide_v);
+    return launch_kernel(widen_kernel<128>, grid, block, st, ev, a, (uint16_t*)wide_k, (uint16_t*)wide_v);
 }
 
-int launch_prefill(const AttnArgs& a, void* stream)
+int launch_prefill(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_pf <= 0) return (int)hipSuccess;
     if ((a.geo.D != 128 && a.geo.D != 64) || a.geo.q_dtype != TS_BF16) return (int)hipErrorInvalidValue;
     dim3 grid((unsigned)a.n_pfmap), block(kPfThreads);
     hipStream_t st = (hipStream_t)stream;
+    hipEvent_t ev = (hipEvent_t)done;
     // (an fp8 cache whose pages were widened beforehand is read through the bf16 form; head dim 64 has no other)
     if (a.geo.D == 64) {
-        if (a.geo.kv_dtype == TS_BF16) hipLaunchKernelGGL((prefill_kernel<uint16_t, false, 64>), grid, block, 0, st, a);
-        else if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) hipLaunchKernelGGL((prefill_kernel<uint16_t, true, 64>), grid, block, 0, st, a);
-        else return (int)hipErrorInvalidValue;
+        if (a.geo.kv_dtype == TS_BF16) return launch_kernel(prefill_kernel<uint16_t, false, 64>, grid, block, st, ev, a);
+        if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) return launch_kernel(prefill_kernel<uint16_t, true, 64>, grid, block, st, ev, a);
+        return (int)hipErrorInvalidValue;
     }
-    else if (a.geo.kv_dtype == TS_BF16) hipLaunchKernelGGL((prefill_kernel<uint16_t, false, 128>), grid, block, 0, st, a);
-    else if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) hipLaunchKernelGGL((prefill_kernel<uint16_t, true, 128>), grid, block, 0, st, a);
-    else if (a.geo.kv_dtype == TS_FP8_E4M3) hipLaunchKernelGGL((prefill_kernel<uint8_t, false, 128>), grid, block, 0, st, a);
-    else return (int)hipErrorInvalidValue;
-    return (int)hipGetLastError();
+    if (a.geo.kv_dtype == TS_BF16) return launch_kernel(prefill_kernel<uint16_t, false, 128>, grid, block, st, ev, a);
+    if (a.geo.kv_dtype == TS_FP8_E4M3 && a.wide_base) return launch_kernel(prefill_kernel<uint16_t, true, 128>, grid, block, st, ev, a);
+    if (a.geo.kv_dtype == TS_FP8_E4M3) return launch_kernel(prefill_kernel<uint8_t, false, 128>, grid, block, st, ev, a);
+    return (int)hipErrorInvalidValue;
 }
 
 }  // namespace ts

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "ts_device.h"
+#include "ts_launch.h"
 
 namespace ts {
 
@@ -320,27 +321,30 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
 }
 
 template <typename QT, typename KT>
-static int launch_rows_d(const AttnArgs& a, hipStream_t st)
+static int launch_rows_d(const AttnArgs& a, hipStream_t st, hipEvent_t done)
 {
     if (a.geo.D != 64 && a.geo.D != 128) return (int)hipErrorInvalidValue;
     const int64_t most = kMaxWorkgroups > a.geo.Hkv ? kMaxWorkgroups / a.geo.Hkv : 1;
-    for (int64_t first = 0, left = a.n_rt; left > 0; first += most, left -= most) {
+    int e = (int)hipSuccess;
+    for (int64_t first = 0, left = a.n_rt; left > 0 && e == (int)hipSuccess; first += most, left -= most) {
         AttnArgs part = a;
         part.rt = a.rt + first;
         const dim3 grid((unsigned)(left < most ? left : most) * (unsigned)a.geo.Hkv), block(64 * kRtWaves);
-        if (a.geo.D == 64) hipLaunchKernelGGL((row_tile_kernel<QT, KT, 64>), grid, block, 0, st, part);
-        else hipLaunchKernelGGL((row_tile_kernel<QT, KT, 128>), grid, block, 0, st, part);
+        const hipEvent_t ev = left <= most ? done : nullptr;
+        if (a.geo.D == 64) e = launch_kernel(row_tile_kernel<QT, KT, 64>, grid, block, st, ev, part);
+        else e = launch_kernel(row_tile_kernel<QT, KT, 128>, grid, block, st, ev, part);
     }
-    return (int)hipGetLastError();
+    return e;
 }
 
-int launch_rows(const AttnArgs& a, void* stream)
+int launch_rows(const AttnArgs& a, void* stream, void* done)
 {
     if (a.n_rt <= 0) return (int)hipSuccess;
     hipStream_t st = (hipStream_t)stream;
-    if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32) return launch_rows_d<float, float>(a, st);
-    if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16) return launch_rows_d<uint16_t, uint16_t>(a, st);
-    if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3) return launch_rows_d<uint16_t, uint8_t>(a, st);
+    hipEvent_t ev = (hipEvent_t)done;
+    if (a.geo.q_dtype == TS_F32 && a.geo.kv_dtype == TS_F32) return launch_rows_d<float, float>(a, st, ev);
+    if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_BF16) return launch_rows_d<uint16_t, uint16_t>(a, st, ev);
+    if (a.geo.q_dtype == TS_BF16 && a.geo.kv_dtype == TS_FP8_E4M3) return launch_rows_d<uint16_t, uint8_t>(a, st, ev);
     return (int)hipErrorInvalidValue;
 }
 
