@@ -253,13 +253,173 @@ __device__ __forceinline__ DecItem load_dec_item(const DecItem* p)
     return DecItem{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
 }
 
+// Two pages of a KV head in registers, taken through the softmax together (decode_pairs): K of each page, V with the two
+// pages' pieces side by side, as the 16x16x32 MFMA takes its 32 tokens.
+template <typename KT, int D> struct KVPair;
+template <int D> struct KVPair<uint16_t, D> { uint4 k[2][D / 32]; uint4 v[D / 16]; };
+template <int D> struct KVPair<uint8_t, D>  { uint4 k[2][D / 64]; uint2 v[D / 16]; };
+
+__device__ __forceinline__ uint4 flip_signs(uint4 v)
+{
+    return make_uint4(v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u);
+}
+
+// (through buffer descriptors of the tile: the base is in scalar registers, and one offset register serves all loads)
+template <int H, typename KT, int D>
+__device__ __forceinline__ void load_pair_k(KVPair<KT, D>& t, const char* kc, int64_t tile, int ko)
+{
+    constexpr int kBytes = 16 * D * (int)sizeof(KT);
+    const auto kr = tile_buffer(kc + tile * kBytes, kBytes);
+#pragma unroll
+    for (int b = 0; b < kBytes / 1024; ++b)
+        t.k[H][b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kr, ko, b * 1024, kNonTemporal));
+}
+template <int H, typename KT, int D>
+__device__ __forceinline__ void load_pair_v(KVPair<KT, D>& t, const char* vc, int64_t tile, int vo)
+{
+    constexpr int kBytes = 16 * D * (int)sizeof(KT);
+    const auto vr = tile_buffer(vc + tile * kBytes, kBytes);
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b) {
+        if constexpr (sizeof(KT) == 2) {
+            const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(vr, vo, b * 512, kNonTemporal);
+            if constexpr (H == 0) { t.v[b].x = x.x; t.v[b].y = x.y; } else { t.v[b].z = x.x; t.v[b].w = x.y; }
+        } else {
+            const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(vr, vo, b * 256, kNonTemporal);
+            if constexpr (H == 0) t.v[b].x = x; else t.v[b].y = x;
+        }
+    }
+}
+__device__ __forceinline__ uint32_t swap_halves16(uint32_t x)  // lanes n and n ^ 8 of every sixteen trade places
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);   // row rotated by 8
+}
+
+// The scan of a wave's np pages (ids at bt[step * k], k = 0 .. np - 1, the first of them page `first` of the sequence),
+// two pages at a time, for groups of at most eight query heads.  Columns n and n + 8 of the score products are the same
+// head (column n is head n % 8), so of the two pages' scores the lanes of columns 0-7 take the first page's and those of
+// columns 8-15 the second's: one round of softmax arithmetic serves both pages.  The packed weights then trade places
+// between the two halves, every column has both pages', and one 16x16x32 MFMA per 16 dims takes the 32 tokens.  Against
+// a page at a time this is about 14 vector instructions per page for 26 and 8 MFMAs for 12 (bf16).  The scan alone
+// does not notice (it waits for memory); next to prefill tiles, which leave it little of the SIMDs, it counts.
+// A wave's last page (the only one that can be partly filled) goes through the masked single step.
+template <typename KT, int D>
+__device__ __forceinline__ void decode_pairs(const AttnArgs& a, const bf16x8 (&qb)[D / 32], float c, int n_keys, int first, int step, int np,
+                                             const int32_t TS_CONSTANT* bt, int g, int lane, f32x4 (&acc)[D / 16], float& m_ref, float& l)
+{
+    constexpr int DB = D / 16;
+    const int Hkv = a.geo.Hkv, r = lane >> 4, n = lane & 15;
+    const bool second = n >= 8;
+    const char* kc = (const char*)a.k_cache;
+    const char* vc = (const char*)a.v_cache;
+    KVPair<KT, D> t;
+    const int ko = lane * 16, vo = ((lane & 15) * (16 * (int)sizeof(KT)) + (lane >> 4) * (4 * (int)sizeof(KT)));
+    auto page_at = [&](int k) { return bt[step * min(k, np - 1)]; };   // (past the end: the last page again)
+    auto k_of = [&](int h) {
+        KVTile<KT, D> x;
+#pragma unroll
+        for (int b = 0; b < (int)(sizeof(x.k) / sizeof(uint4)); ++b) x.k[b] = t.k[h][b];
+        return x;
+    };
+    auto raise_if = [&](float lmax, bool both) {               // lmax: highest score of the lane's four tokens
+        if (__any(lmax > m_ref + kRaise)) {                    // rare
+            float full = pair32_max(pair16_max(lmax));
+            if (both) full = fmaxf(full, __uint_as_float(swap_halves16(__float_as_uint(full))));
+            const float m_new = fmaxf(m_ref, full);
+            const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+#pragma unroll
+            for (int b = 0; b < DB; ++b) acc[b] *= alpha;
+            l *= alpha;
+            m_ref = m_new;
+        }
+    };
+    auto pack = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2)); };
+    int32_t id0 = page_at(0), id1 = page_at(1);
+    int32_t next0 = page_at(2), next1 = page_at(3);
+    load_pair_k<0>(t, kc, (int64_t)id0 * Hkv + g, ko);
+    load_pair_k<1>(t, kc, (int64_t)id1 * Hkv + g, ko);
+    load_pair_v<0>(t, vc, (int64_t)id0 * Hkv + g, vo);
+    load_pair_v<1>(t, vc, (int64_t)id1 * Hkv + g, vo);
+    // (an opaque copy: the ids of the next pair are then read a round ahead, not where they are used)
+    id0 = opaque_uniform(next0); id1 = opaque_uniform(next1);
+    const bool has_tail = (first + step * (np - 1) + 1) * kPage > n_keys;   // wave-uniform
+    const int n_pair = (np - (has_tail ? 1 : 0)) / 2;
+    for (int p = 0; p < n_pair; ++p) {
+        const f32x4 s0 = qk_tile(k_of(0), qb), s1 = qk_tile(k_of(1), qb);
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = second ? s1[i] : s0[i];
+        __builtin_amdgcn_sched_barrier(0);                     // (the next pages' pieces land in the registers just read)
+        load_pair_k<0>(t, kc, (int64_t)id0 * Hkv + g, ko);
+        load_pair_k<1>(t, kc, (int64_t)id1 * Hkv + g, ko);
+        next0 = page_at(2 * p + 4); next1 = page_at(2 * p + 5);
+        raise_if(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) * c, true);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[i], c, -m_ref));
+        l += (x[0] + x[1]) + (x[2] + x[3]);
+        const uint32_t w0 = pack(x[0], x[1]), w1 = pack(x[2], x[3]);
+        const uint32_t o0 = swap_halves16(w0), o1 = swap_halves16(w1);
+        const bf16x8 pv = as_bf16x8(make_uint4(second ? o0 : w0, second ? o1 : w1, second ? w0 : o0, second ? w1 : o1));
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            uint4 vv;
+            if constexpr (sizeof(KT) == 2) vv = t.v[b];
+            else {
+                const uint2 v0 = fp8x4_to_bf16x4(t.v[b].x), v1 = fp8x4_to_bf16x4(t.v[b].y);
+                vv = make_uint4(v0.x, v0.y, v1.x, v1.y);
+            }
+            acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vv), pv, acc[b], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_pair_v<0>(t, vc, (int64_t)id0 * Hkv + g, vo);
+        load_pair_v<1>(t, vc, (int64_t)id1 * Hkv + g, vo);
+        id0 = next0; id1 = next1;
+    }
+    // the one or two pages that are left sit in t: singly, the last one with its mask
+    auto single = [&](int page, auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+        const f32x4 s = qk_tile(k_of(0), qb);
+        const int nvalid = n_keys - (page * kPage + 4 * r);    // tokens 4 r .. 4 r + 3 valid if < nvalid
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = MASKED && nvalid <= i ? -INFINITY : s[i] * c;
+        raise_if(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), false);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = __builtin_amdgcn_exp2f(x[i] - m_ref);
+        l += second ? 0.0f : (x[0] + x[1]) + (x[2] + x[3]);    // (the two halves' sums are added at the end)
+        const s16x4 pv = as_s16x4(make_uint2(pack(x[0], x[1]), pack(x[2], x[3])));
+        const uint64_t keep = !MASKED || nvalid >= 4 ? ~0ull : (nvalid <= 0 ? 0ull : ((1ull << (16 * nvalid)) - 1ull));
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            uint2 vv;
+            if constexpr (sizeof(KT) == 2) vv = make_uint2(t.v[b].x, t.v[b].y); else vv = fp8x4_to_bf16x4(t.v[b].x);
+            vv.x &= (uint32_t)keep; vv.y &= (uint32_t)(keep >> 32);
+            acc[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_s16x4(vv), pv, acc[b], 0, 0, 0);
+        }
+    };
+    int k = 2 * n_pair;
+    if (np - k == 2) {                                         // wave-uniform, as the next
+        single(first + step * k, std::false_type{});
+#pragma unroll
+        for (int b = 0; b < (int)(sizeof(t.k[0]) / sizeof(uint4)); ++b) t.k[0][b] = t.k[1][b];
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            if constexpr (sizeof(KT) == 2) { t.v[b].x = t.v[b].z; t.v[b].y = t.v[b].w; } else t.v[b].x = t.v[b].y;
+        }
+        ++k;
+    }
+    if (k < np) single(first + step * k, std::true_type{});
+    l += __uint_as_float(swap_halves16(__float_as_uint(l)));
+}
+
 // One decode item for KV head g, executed by a workgroup of WAVES waves.  All waves must call
 // it; it contains one workgroup barrier, and another one must come before mg is reused: the caller's, or (mg_busy)
 // one in here just before mg is written, so that the waves that have nothing to merge start on the next item.
 // EXACT: prefetches past the end read nothing (load_tile_if).
 // THROUGH: partial results of split rows are stored for arrive_and_merge.
 // FUSED: the row's new token comes from a.k_new / a.v_new and is written into the cache here (see AttnArgs).
-template <typename KT, int NBUF, int WAVES, int D = 128, bool THROUGH = false, bool FUSED = false, bool EXACT = false>
+// PAIRS: at most eight query heads per KV head, two pages at a time (decode_pairs).
+template <typename KT, int NBUF, int WAVES, int D = 128, bool THROUGH = false, bool FUSED = false, bool EXACT = false, bool PAIRS = false>
 __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it, int g, DecMerge<WAVES, D>& mg, bool mg_busy = false)
 {
     constexpr int KB = D / 32, DB = D / 16;    // 32-dim steps of K Q^T, 16-dim blocks of O^T
@@ -268,7 +428,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
     // from it -- the page-id loads above all -- on the scalar unit)
     // (an opaque copy where the caller loops over items: the lane offsets are worked out per item instead of being
     // kept across the loop)
-    const int tid = THROUGH ? opaque((int)threadIdx.x) : (int)threadIdx.x;
+    const int tid = THROUGH || PAIRS ? opaque((int)threadIdx.x) : (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, r = lane >> 4, n = lane & 15;
     const int Hq = a.geo.Hq, Hkv = a.geo.Hkv, G = a.geo.G;
@@ -315,12 +475,21 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
         // (their results are finite and never stored)
         bf16x8 qb[KB];
         {
-            const uint16_t* qrow = (const uint16_t*)a.q + ((int64_t)it_row * Hq + g * G + min(n, G - 1)) * D;
+            const uint16_t* qrow = (const uint16_t*)a.q + ((int64_t)it_row * Hq + g * G + min(PAIRS ? n & 7 : n, G - 1)) * D;
 #pragma unroll
             for (int b = 0; b < KB; ++b) qb[b] = as_bf16x8(*(const uint4*)(qrow + q_dim0<KT>(b, r)));
         }
         const float kscale = (sizeof(KT) == 1) ? a.k_scale[g] : 1.0f;
         const float c = a.sm_scale * kscale * kLog2e;
+        if constexpr (PAIRS) {
+            static_assert(!FUSED && !EXACT, "");
+            if (c < 0.0f) {                                       // (a negative K scale: the maximum is taken before the scale)
+#pragma unroll
+                for (int b = 0; b < KB; ++b) qb[b] = as_bf16x8(flip_signs(__builtin_bit_cast(uint4, qb[b])));
+            }
+            const float cu = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(fabsf(c))));   // (in a scalar register)
+            decode_pairs<KT, D>(a, qb, cu, it_keys, it_pb + wave, WAVES, np, bt, g, lane, acc, m_ref, l);
+        } else {
         const char* kc = (const char*)a.k_cache;
         const char* vc = (const char*)a.v_cache;
 
@@ -457,12 +626,13 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
             for (int j = 0; j < NBUF; ++j)
                 if (j == jt) page_step(buf[j], page_last, std::true_type{});
         }
+        }
     }
 
     float l_tot = l + __shfl_xor(l, 16, 64);
     l_tot += __shfl_xor(l_tot, 32, 64);
 
-    const int lane_o = THROUGH ? opaque((int)threadIdx.x) & 63 : lane, r_o = lane_o >> 4, n_o = lane_o & 15;   // (derived afresh: see above)
+    const int lane_o = THROUGH || PAIRS ? opaque((int)threadIdx.x) & 63 : lane, r_o = lane_o >> 4, n_o = lane_o & 15;   // (derived afresh: see above)
     // ---- merge the waves' states (wave order, so the result is reproducible) ----------------------
     if (mg_busy) __syncthreads();
     if (wave > 0) {

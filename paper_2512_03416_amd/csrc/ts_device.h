@@ -63,6 +63,13 @@ __device__ __forceinline__ float pair32_sum(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The same for lanes l and l ^ 16 (a swap of neighbouring rows of sixteen).
+__device__ __forceinline__ float pair16_max(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // bf16 bits <-> float
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t h) { return __uint_as_float(h << 16); }
 

@@ -32,12 +32,16 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { de
 // (see prefill_resident_kernel), and four fit on a CU of their own.  A single workgroup of four waves per CU
 // already keeps enough loads in flight for the bf16 scan to run at its full rate.
 // decode_kernel_lean: one item per workgroup, no merge in the kernel -- next to resident prefill workgroups the
-// shorter code is worth 1.5 % of the pair (the burst configuration: 633 us a pass against 643).
-template <typename KT, int D>
+// shorter code is worth 1.5 % of the pair (the burst configuration: 633 us a pass against 643).  PAIRS (up to eight heads per
+// KV head): two pages at a time, half the vector instructions.  What bounds it there is not memory but what the tiles leave it
+// of the SIMDs: a 4096-token chunk over 4096 next to 128 rows, a prefill workgroup on every CU, 570 -> 500 us a pass (and
+// with that more of the CUs can hold one); 256 rows of 256-1500 tokens next to 2048 tokens 218 -> 210; where the tiles
+// outlast the scan it changes nothing (the burst configuration, 64 Ki prompt tokens next to 512 rows).
+template <typename KT, int D, bool PAIRS>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean(AttnArgs a)
 {
     __shared__ DecMerge<kDecWaves, D> mg;
-    decode_item<KT, 2, kDecWaves, D>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+    decode_item<KT, 2, kDecWaves, D, false, false, false, PAIRS>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
 }
 template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean_merging(AttnArgs a)
@@ -121,7 +125,10 @@ static int launch_decode_t(const AttnArgs& a, hipStream_t st, hipEvent_t done)
     default:
         if (a.dec_wg || a.cmb_ctr) return launch_kernel(decode_kernel_lean_merging<KT, D>, grid, block, st, done, a);
         if (a.n_queue == 0) return launch_kernel(decode_kernel_alone<KT, D>, grid, block, st, done, a);   // (queues: the tiles of a co-resident launch)
-        return launch_kernel(decode_kernel_lean<KT, D>, grid, block, st, done, a);
+        if constexpr (D == 128) {
+            if (a.geo.G <= 8) return launch_kernel(decode_kernel_lean<KT, D, true>, grid, block, st, done, a);
+        }
+        return launch_kernel(decode_kernel_lean<KT, D, false>, grid, block, st, done, a);
     }
 }
 
@@ -133,7 +140,7 @@ static int resident_t(int nbuf)
     switch (nbuf) {
     case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<KT, 3, D>, 64 * kDecWaves, 0); break;
     case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<KT, 4, D>, 64 * kDecWaves, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel_lean<KT, D>, 64 * kDecWaves, 0); break;
+    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel_lean<KT, D, false>, 64 * kDecWaves, 0); break;
     }
     return e == hipSuccess ? per_cu : 0;
 }
