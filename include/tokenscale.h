@@ -186,7 +186,8 @@ const char *ts_last_error(const ts_ctx *ctx);
  *                         (arrival counters; the partials are read in item order, so the result does not depend on
  *                         which item came last), or by a small launch behind the items.  0 (default) = in the kernel
  *                         while no row of the batch has more than 16 items, 1 = in the kernel always.  Always the
- *                         launch: mixed_mode 1, batches with rows of the generic kernel, and in the allocation-free
+ *                         launch: mixed batches launched with resident workgroups, batches with rows of the generic
+ *                         kernel, and in the allocation-free
  *                         call the passes of "decode_fused_append" and more split rows than it has counters for
  *                         (768 / KV heads).  Same results
  *   "decode_fused_append"  1 (default) / 0.  A pass that appends, holds decode rows only and is small (at most 88

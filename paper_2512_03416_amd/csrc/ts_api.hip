@@ -216,6 +216,8 @@ int32_t* cmb_ctr_of(const ts_ctx* c, size_t n_rows)
 // Split decode rows are merged by whichever item of a row finishes last when the rows have few items (at most
 // kMergeInKernelMax, or by option), else by a launch behind them (NULL).  The last item of a row adds up its partials
 // on one CU; the launch spreads a row over one workgroup per head.
+// Next to resident prefill workgroups always the launch: the items' kernel is then the shorter one (64 rows of 2000-16 000
+// tokens cut at 192 pages next to 16 chunks of 300-1024 tokens 482 -> 469 us a pass, 128 rows cut at 256 566 -> 531).
 // In a small decode-only pass, whose lists are kernel arguments, either way: one row of 9000 tokens (32/8 heads of 128, 18
 // items) takes 14.2 us a pass with the launch and 14.4 without, of 100 000 with 64/4 heads (64 items) 25.4 and 35.3, of
 // 40 000 with 16/1 heads (79 items) 16.4 and 25.7; 8 rows of 1500 (3 items each) 16.4 and 15.1, one of 3000 (6) 14.5
@@ -223,7 +225,7 @@ int32_t* cmb_ctr_of(const ts_ctx* c, size_t n_rows)
 constexpr int kMergeInKernelMax = 16;
 int32_t* merge_counters(const ts_ctx* c, const Plan& p)
 {
-    if (p.cmb.empty() || !p.rt.empty() || p.info.mixed_mode == TS_MIXED_ONE_KERNEL) return nullptr;
+    if (p.cmb.empty() || !p.rt.empty() || p.info.mixed_mode != TS_MIXED_SEPARATE) return nullptr;
     if (!c->merge_in_kernel && p.max_split > kMergeInKernelMax) return nullptr;
     if ((int64_t)p.max_split * c->desc.num_q_heads * c->desc.head_dim * 4 >= (int64_t)1 << 31) return nullptr;
     return cmb_ctr_of(c, p.cmb.size());

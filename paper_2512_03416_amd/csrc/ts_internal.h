@@ -254,7 +254,7 @@ struct AttnArgs {
     // Arrival counters of the split decode rows, one per (combine row, KV head), zero between launches: the
     // workgroup that finds n_split - 1 in it is the last of the row and merges the partials itself.  NULL = the
     // items only write their partials and combine_kernel merges them (rows of many items, batches with generic rows,
-    // the one-kernel launch, whose kernel does not hold the merge, and too few counters in the static scratch).
+    // launches with resident workgroups, and too few counters in the static scratch).
     int32_t* cmb_ctr;
     // split-K partials: o [slot][Hq][D] fp32 (unnormalised), ml [slot][Hq][2] = (max, sum) in log2 units
     float* part_o; float* part_ml;

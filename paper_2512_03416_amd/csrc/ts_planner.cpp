@@ -125,13 +125,20 @@ int validate_batch(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* 
 // microsecond, all CUs).
 constexpr double kDecBytePerUs = 6.2e6;
 constexpr double kPfFlopPerUs = 1.25e9;
-// Co-resident launch: share of the CUs that get a resident prefill workgroup, from the ratio r of the two times:
-// kPfShare0 + kPfShare1 * r, at most all of them.  Measured on one chunk of 128 ... 16 256 tokens over a prefix of 0
-// or 4096 next to 128 decode rows of 1024-8192 tokens, and on the two burst configurations: too few workgroups
-// make the tiles the critical path (the time rises steeply), a few too many cost 3-8 %; r = 0.3: best at 80-128 of
-// 256, r = 0.8: 160-192, r = 1.0: 224, r >= 1.3: all.
-constexpr double kPfShare0 = 0.25;
-constexpr double kPfShare1 = 0.6;
+// Co-resident launch: the CUs that get a resident prefill workgroup, from the ratio r of the two times (prefill to decode).
+// All of them where the tiles would take about as long as the scan or longer (r >= kPfAllRatio; passes with a scan of less
+// than kPfAllUs: r >= kPfAllRatioShort): a CU without one takes four decode workgroups, each of them then four times as slow as
+// the ones that share a CU with tiles, and the longest rows end late there (248 workgroups instead of 256: 568 us for 510
+// in the first example below).  Else the share kPfShare0 + kPfShare1 * r.  Measured over 33 mixed batches, every
+// multiple of 16 workgroups: with too few the tiles end late (the time rises steeply), with a few too many the scan does.
+// A 4096-token chunk over 4096 next to 128 rows of 1024-8192 (r = 0.83): 508 us with 256, 576 with 192; 4 chunks of 2048 next
+// to 128 (r = 0.97): 585 and 640; r > 1.7 always 256.  Over 21 batches with r = 0.07 ... 0.95 the share is within 1.7 % of
+// the best number on average (5.6 % at most; 64 rows of 500-4000 tokens next to 8 chunks of 300-512, r = 0.52: 151 us with
+// 128, 156 with 136, 200 with 256; 2048 tokens next to 32 rows, r = 0.73: 130 with 144, 184 with 256; 3500 over 3000 next to
+// 128, r = 0.55: 526 with 128, 485 with 160, 545 with 256).
+constexpr double kPfShare0 = 0.46, kPfShare1 = 0.16;
+constexpr double kStageUs = 1.5;                           // a tile's 64 keys
+constexpr double kPfAllRatio = 0.8, kPfAllUs = 150.0, kPfAllRatioShort = 1.4;
 // A mixed batch is launched class by class when either class is estimated below this many microseconds: running
 // side by side hides about 40 % of the shorter class, and the fork and join of the co-resident launch cost
 // 10-15 us.  Measured: 128 decode rows (395 us) next to a chunk of 128 / 896 tokens without prefix (estimates
@@ -141,6 +148,14 @@ constexpr double kPfShare1 = 0.6;
 constexpr double kCoresidentMinUs = 20.0;
 
 constexpr int64_t kMinSplitPages = 32;
+// Co-resident launch.  A CU with a resident prefill workgroup serves its one decode workgroup faster than a CU without
+// one serves each of its four, so items of a workgroup's fair share do not end together.  Where the rows are few (less
+// than one and a half times the slots of the whole GPU), items of at most kCoItemPages pages let the dispatch even it out: 64
+// rows of 2000-16 000 tokens next to 16 chunks of 300-1024 499 -> 470 us, 16 rows of 8000-64 000 (e4m3) next to 8 chunks
+// of 100-300 386 -> 331, 3072 tokens over 2048 next to 128 rows of 1024-8192 514 -> 468; with more rows the partial results
+// cost more than it gains (256 rows of 1024-8192 tokens, e4m3, 474 -> 517; 512 of 512-4096 786 -> 818).  With a prefill
+// workgroup on every CU rows of up to kWholePages pages stay whole (24 rows of 300-3000 tokens 111.5 -> 110.3).
+constexpr int64_t kCoItemPages = 160, kWholePages = 192;
 
 static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tiles, int64_t decode_pages, int Hkv,
                                 int32_t wg_slots, int32_t n_cu, bool filled_by_prefill, int32_t pf_wgs)
@@ -151,6 +166,8 @@ static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tile
     if (filled_by_prefill && pf_wgs > 0 && pf_wgs < n_cu)
         slots = pf_wgs + (int64_t)(n_cu - pf_wgs) * std::max(1, wg_slots / n_cu);
     int64_t L = std::max<int64_t>(kMinSplitPages, (decode_tiles + slots - 1) / slots);
+    if (pf_wgs >= n_cu) L = std::max(L, kWholePages);
+    else if (pf_wgs > 0 && 2 * p.info.decode_tokens * Hkv < 3 * wg_slots) L = std::min(L, kCoItemPages);
     if (!filled_by_prefill && p.info.decode_tokens * Hkv <= n_cu && decode_pages > 0) {
         const int64_t want_items = std::max<int64_t>(1, n_cu / Hkv);   // per KV head
         int64_t fit = std::max<int64_t>(kMinSplitPages, (decode_pages + want_items - 1) / want_items);
@@ -568,6 +585,9 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     // How a batch with both kinds of rows is launched.  Co-resident by default; class by class when either class
     // is too short for the overlap to pay for the fork and join (kCoresidentMinUs).
     int mixed_mode = opt.mixed_mode;
+    int32_t longest = 0;                                   // keys of the longest tile
+    for (int s = 0; s < num_seqs; ++s)
+        if (p.seqs[s].q_len > 1) longest = std::max(longest, p.seqs[s].ctx_len);
     double t_pf = 0, t_dec = 0;                            // microseconds each kind would take alone
     if (mixed_mode == TS_MIXED_CORESIDENT) {
         double flop = 0;
@@ -595,8 +615,13 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         if (opt.pf_resident_wgs > 0) {
             pf_wgs = std::min(all, opt.pf_resident_wgs);
         } else {
-            const double share = t_dec > 0 ? kPfShare0 + kPfShare1 * t_pf / t_dec : 1.0;
-            pf_wgs = share >= 1.0 ? all : (int32_t)std::ceil(share * all);
+            const double r = t_dec > 0 ? t_pf / t_dec : 1e9;
+            // (plans that are only described keep the share until kPfAllRatioShort)
+            const bool every = r >= (opt.for_launch && t_dec >= kPfAllUs ? kPfAllRatio : kPfAllRatioShort);
+            pf_wgs = every ? all : (int32_t)std::ceil((kPfShare0 + kPfShare1 * r) * all);
+            // (not a few tiles more than whole rounds: 55 tiles per die on 19 workgroups 485 us, on 18 509)
+            const int64_t per_die = (tile_heads + x - 1) / x, n = (pf_wgs + x - 1) / x, rounds = per_die / n;
+            if (rounds > 0 && per_die % n > 0 && per_die % n <= n / 8) pf_wgs = (int32_t)((per_die + rounds - 1) / rounds * x);
         }
         pf_wgs = std::min(all, std::max(x, (pf_wgs + x - 1) / x * x));
     }
@@ -617,7 +642,10 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     const bool even = mfma_dec && !whole && opt.split_pages == 0 && mixed_mode == TS_MIXED_SEPARATE &&
                       deal_decode_evenly(p, num_seqs, decode_pages, d, opt, &part);
     // parts per prefill tile that would give every CU a workgroup (1 = the tiles fill the GPU as they are)
-    const int64_t pf_parts_wanted = tile_heads > 0 ? std::min<int64_t>(16, (pf_wgs > 0 ? pf_wgs : opt.n_cu) / tile_heads) : 1;
+    // (next to a scan that outlasts the longest tile there is nothing to gain: 512 tokens over 4096 next to 128 rows 416 us
+    // whole, 428 in two parts)
+    const bool parts_pay = mixed_mode != TS_MIXED_CORESIDENT || kStageUs * longest / 64 > t_dec;
+    const int64_t pf_parts_wanted = tile_heads > 0 && parts_pay ? std::min<int64_t>(16, (pf_wgs > 0 ? pf_wgs : opt.n_cu) / tile_heads) : 1;
     for (int s = 0; s < num_seqs; ++s) {
         const SeqMeta& m = p.seqs[s];
         if (m.q_len == 0) continue;
