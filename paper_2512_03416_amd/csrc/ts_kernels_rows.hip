@@ -16,6 +16,10 @@
 //
 // What bounds it: chunk rows, the matrix instruction (64 flop per clock and SIMD: 2048 clocks per page and KV head
 // with head dim 128); decode rows, HBM.
+//
+// Decode rows of groups of at most four heads (fp32) would fill four of the sixteen columns and take the matrix
+// instructions' time four times over -- next to chunk tiles on the same SIMD that is what bounds the pass.  They take the
+// form with sixteen blocks of 4x4x1 instead, 512 clocks per page and KV head: ROWS4 below.
 #include <type_traits>
 
 #include "ts_device.h"
@@ -40,23 +44,29 @@ template <typename KT, int D> struct RtTile {
 // in: else nothing is read (a buffer of no bytes, whose loads return zeros).  The prefetch needs no branch that way; it
 // used to repeat a wave's last page up to three times: 4 rows and 2 chunks of 200-300 tokens (32/8 heads of 128, fp32)
 // 59.0 -> 53.5 us a pass, 24 rows and 2 chunks with head dim 64 48.1 -> 46.1.
-template <typename KT, int D>
-__device__ __forceinline__ void rt_load(RtTile<KT, D>& t, const char* kc, const char* vc, int64_t tile, int lane, bool in)
+constexpr int kRtRaw = 0x00027000;                         // buffer of untyped 32-bit data, offsets in bytes
+template <int POLICY, typename KT, int D>
+__device__ __forceinline__ void rt_load_k(RtTile<KT, D>& t, const char* kc, int64_t tile, int lane, bool in)
+{
+    constexpr int kBytes = 16 * D * (int)sizeof(KT);
+    const auto kr = __builtin_amdgcn_make_buffer_rsrc((void*)(kc + tile * kBytes), (short)0, in ? kBytes : 0, kRtRaw);
+    const int ko = lane * 16;
+#pragma unroll
+    for (int b = 0; b < RtTile<KT, D>::KB; ++b) t.k[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kr, ko + b * 1024, 0, POLICY));
+}
+template <int POLICY, typename KT, int D>
+__device__ __forceinline__ void rt_load_v(RtTile<KT, D>& t, const char* vc, int64_t tile, int lane, bool in)
 {
     using T = RtTile<KT, D>;
-    constexpr int ES = (int)sizeof(KT), kRaw = 0x00027000; // untyped 32-bit data, offsets in bytes
-    const int bytes = in ? 16 * D * ES : 0;
-    const auto kr = __builtin_amdgcn_make_buffer_rsrc((void*)(kc + tile * (16 * D * ES)), (short)0, bytes, kRaw);
-    const auto vr = __builtin_amdgcn_make_buffer_rsrc((void*)(vc + tile * (16 * D * ES)), (short)0, bytes, kRaw);
-    const int ko = lane * 16, vo = (lane & 15) * (16 * ES) + (lane >> 4) * (4 * ES);
-#pragma unroll
-    for (int b = 0; b < T::KB; ++b) t.k[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(kr, ko + b * 1024, 0, 0));
+    constexpr int ES = (int)sizeof(KT), kBytes = 16 * D * ES;
+    const auto vr = __builtin_amdgcn_make_buffer_rsrc((void*)(vc + tile * kBytes), (short)0, in ? kBytes : 0, kRtRaw);
+    const int vo = (lane & 15) * (16 * ES) + (lane >> 4) * (4 * ES);
 #pragma unroll
     for (int b = 0; b < T::VB; ++b) {
         const int at = vo + b * (256 * ES);
-        if constexpr (ES == 4) t.v[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vr, at, 0, 0));
-        else if constexpr (ES == 2) t.v[b] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, at, 0, 0));
-        else t.v[b] = __builtin_amdgcn_raw_buffer_load_b32(vr, at, 0, 0);
+        if constexpr (ES == 4) t.v[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vr, at, 0, POLICY));
+        else if constexpr (ES == 2) t.v[b] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(vr, at, 0, POLICY));
+        else t.v[b] = __builtin_amdgcn_raw_buffer_load_b32(vr, at, 0, POLICY);
     }
 }
 
@@ -118,7 +128,7 @@ template <int D> struct RtMerge {                          // LDS image of the n
 // KV heads vary fastest over the grid (as in the decode kernel: the Hkv tiles of a page are neighbours in memory,
 // and with eight heads every tile of a (sequence, head) stream runs on one die, whose L2 then holds its pages).
 template <typename QT, typename KT, int D>
-__global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
+__global__ __launch_bounds__(64 * kRtWaves, D == 64 ? 4 : 2) void row_tile_kernel(AttnArgs a)
 {
     using T = RtTile<KT, D>;
     constexpr int X = T::X, KB = T::KB, VB = T::VB, EW = 4 / (int)sizeof(KT);   // EW: elements per register
@@ -150,10 +160,19 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
     for (int b = 0; b < VB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_ref = kNoKey, l = 0.0f;
 
-    if (np > 0) {                                          // wave-uniform
+    // ROWS4: one token, at most four heads.  Lane (r, n) is row n % 4 or column n % 4 of block (r, n / 4):
+    //   - S^T: block (r, n / 4) multiplies tokens 4 (n / 4) .. + 3 with heads 0 .. 3 over the dims of lane group r (the K
+    //     pieces as they are); the lane groups' sums are added, and every lane of column j has the scores of the four
+    //     tokens of its block for head j;
+    //   - O^T: block (r, n / 4) multiplies dims 16 b + 4 (n / 4) .. + 3 with the weights of tokens 4 r .. + 3 (the V pieces as
+    //     they are), which lane (r, n) fetches from the block that holds them; the lane groups' sums are added at the end.
+    auto scan = [&](auto rows4) {
+        constexpr bool ROWS4 = decltype(rows4)::value;
+        constexpr int kPolicy = ROWS4 ? 2 : 0;             // non-temporal: nobody else reads a decode row's pages
+        const int from = 4 * (20 * r + (n & 3));           // lane (r, 4 r + n % 4), as a byte index
         float q[D / 4];                                    // B operands of K Q^T: dims (4 b + r) X + e of the column
         {
-            const QT* qrow = (const QT*)a.q + ((int64_t)(it.row0 + t) * Hq + g * G + hd) * D;
+            const QT* qrow = (const QT*)a.q + ((int64_t)(it.row0 + t) * Hq + g * G + (ROWS4 ? min(n & 3, G - 1) : hd)) * D;
 #pragma unroll
             for (int b = 0; b < KB; ++b)
 #pragma unroll
@@ -168,13 +187,15 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
         const char* vc = (const char*)a.v_cache;
         int next_k = 0, next_id = bt[0];
         auto fetch = [&](T& tile) {
-            rt_load<KT, D>(tile, kc, vc, (int64_t)next_id * Hkv + g, lane, next_k < np);
+            rt_load_k<kPolicy, KT, D>(tile, kc, (int64_t)next_id * Hkv + g, lane, next_k < np);
+            rt_load_v<kPolicy, KT, D>(tile, vc, (int64_t)next_id * Hkv + g, lane, next_k < np);
             next_k += 1;
             next_id = bt[kRtWaves * min(next_k, np - 1)];
         };
         // One page.  MASKED: it reaches past the first token's keys: scores of keys that a column does not see, and V of
         // slots that no column sees, are masked.
-        auto step = [&](T& tile, int page, auto masked) {
+        // behind_k: called when K has been used.
+        auto step = [&](T& tile, int page, auto masked, auto&& behind_k) {
             constexpr bool MASKED = decltype(masked)::value;
             f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;      // (two chains: half the rounding steps in a row)
 #pragma unroll
@@ -183,20 +204,29 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
                 for (int e = 0; e < X; ++e) {
                     const float kv = rt_elem<KT>(word_of(tile.k[b], e / EW), e % EW);
                     f32x4& s = (e & 1) ? s1 : s0;
-                    s = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, q[b * X + e], s, 0, 0, 0);
+                    if constexpr (ROWS4) s = __builtin_amdgcn_mfma_f32_4x4x1f32(kv, q[b * X + e], s, 0, 0, 0);
+                    else s = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, q[b * X + e], s, 0, 0, 0);
                 }
             float x[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = (s0[i] + s1[i]) * c;
-            const int tok0 = page * kPage + 4 * r;
+            for (int i = 0; i < 4; ++i) x[i] = (ROWS4 ? pair32_sum(pair16_sum(s0[i] + s1[i])) : s0[i] + s1[i]) * c;
+            behind_k();
+            const int tok0 = page * kPage + 4 * r;         // first of the lane's tokens in V ...
+            const int score0 = ROWS4 ? page * kPage + (n & 12) : tok0;   // ... and of its scores
             if constexpr (MASKED) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = tok0 + i < keys ? x[i] : -INFINITY;
+                for (int i = 0; i < 4; ++i) x[i] = score0 + i < keys ? x[i] : -INFINITY;
             }
             const float lmax = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
             if (__any(lmax > m_ref + kRaiseRt)) {          // raise the reference (rare)
-                float full = fmaxf(lmax, __shfl_xor(lmax, 16, 64));
-                full = fmaxf(full, __shfl_xor(full, 32, 64));
+                float full;
+                if constexpr (ROWS4) {
+                    full = fmaxf(lmax, rotate16<4>(lmax));
+                    full = fmaxf(full, rotate16<8>(full));
+                } else {
+                    full = fmaxf(lmax, __shfl_xor(lmax, 16, 64));
+                    full = fmaxf(full, __shfl_xor(full, 32, 64));
+                }
                 const float m_new = fmaxf(m_ref, full);
                 const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
 #pragma unroll
@@ -216,7 +246,7 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
                 // A weight of 0 does not undo an infinite or NaN value: the columns of earlier tokens must not meet the V
                 // of later ones at all.  Tokens with such a value (rare, wave-uniform) are added on the vector ALU, to
                 // the columns that see them, and cleared for the product.
-                if (keys_min < keys_max && __any(rt_any_not_finite<KT>(tile.v))) {
+                if (!ROWS4 && keys_min < keys_max && __any(rt_any_not_finite<KT>(tile.v))) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         bool odd_e = false;
@@ -241,11 +271,18 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
                     }
                 }
             }
+            if constexpr (ROWS4) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[i] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(p[i])));
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int b = 0; b < VB; ++b)
-                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(rt_elem<KT>(word_of(tile.v[b], e / EW), e % EW), p[e], acc[b], 0, 0, 0);
+                for (int b = 0; b < VB; ++b) {
+                    const float v = rt_elem<KT>(word_of(tile.v[b], e / EW), e % EW);
+                    if constexpr (ROWS4) acc[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(v, p[e], acc[b], 0, 0, 0);
+                    else acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, p[e], acc[b], 0, 0, 0);
+                }
         };
         // Pages past the first token's keys are the tile's last one or two (it has at most 16 tokens), so a wave has at most
         // one of them and it comes last: the loop carries no mask arithmetic, and what the masked page needs in registers
@@ -253,24 +290,64 @@ __global__ __launch_bounds__(64 * kRtWaves) void row_tile_kernel(AttnArgs a)
         const int first = it.page_begin + wave, page_last = first + kRtWaves * (np - 1);
         const bool has_tail = (page_last + 1) * kPage > keys_min;   // wave-uniform
         const int np_main = np - (has_tail ? 1 : 0);
-        T buf[2];
-        fetch(buf[0]);
-        fetch(buf[1]);
-        for (int k = 0; k < np_main; k += 2) {
-            step(buf[0], first + kRtWaves * k, std::false_type{});
+        if constexpr (ROWS4) {
+            // One page in flight per wave, K and V of the next one asked for as soon as this one's are used, with the
+            // non-temporal hint: with two pages 264 workgroups had 34 MB on the way, five microseconds of memory traffic, which
+            // is slower by itself and stands in front of every load of the chunk tiles, and what they read pushed the
+            // chunks' pages out of the L2.  16 rows of 64-2048 tokens next to a 231-token chunk over 300 (32/8 heads of
+            // 128) 57.0 -> 51.5 us a pass, without the chunk 42.4 -> 36.5, 32 rows of 500-2048 76.3 -> 67.1.
+            T t;
+            fetch(t);
+            for (int k = 0; k < np_main; ++k) {
+                const int64_t tile = (int64_t)next_id * Hkv + g;
+                const bool in = next_k < np;
+                step(t, first + kRtWaves * k, std::false_type{}, [&] {
+                    __builtin_amdgcn_sched_barrier(0);
+                    rt_load_k<kPolicy, KT, D>(t, kc, tile, lane, in);
+                    next_k += 1;
+                    next_id = bt[kRtWaves * min(next_k, np - 1)];
+                });
+                __builtin_amdgcn_sched_barrier(0);
+                rt_load_v<kPolicy, KT, D>(t, vc, tile, lane, in);
+            }
+            if (has_tail) step(t, page_last, std::true_type{}, [] {});
+        } else {
+            T buf[2];
             fetch(buf[0]);
-            if (k + 1 >= np_main) break;                   // (the second buffer may hold the masked page)
-            step(buf[1], first + kRtWaves * (k + 1), std::false_type{});
             fetch(buf[1]);
+            for (int k = 0; k < np_main; k += 2) {
+                step(buf[0], first + kRtWaves * k, std::false_type{}, [] {});
+                fetch(buf[0]);
+                if (k + 1 >= np_main) break;               // (the second buffer may hold the masked page)
+                step(buf[1], first + kRtWaves * (k + 1), std::false_type{}, [] {});
+                fetch(buf[1]);
+            }
+            if (has_tail) {
+                if ((np - 1) & 1) buf[0] = buf[1];
+                step(buf[0], page_last, std::true_type{}, [] {});
+            }
         }
-        if (has_tail) {
-            if ((np - 1) & 1) buf[0] = buf[1];
-            step(buf[0], page_last, std::true_type{});
+        if constexpr (ROWS4) {                             // to the order of the other form: dims 16 b + 4 r .. + 3 of column n
+#pragma unroll
+            for (int b = 0; b < VB; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc[b][i] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(pair32_sum(pair16_sum(acc[b][i])))));
+            l += rotate16<4>(l);
+            l += rotate16<8>(l);
+        } else {
+            l += __shfl_xor(l, 16, 64);
+            l += __shfl_xor(l, 32, 64);
+        }
+    };
+    if (np > 0) {                                          // wave-uniform
+        if constexpr (sizeof(KT) == 4) {
+            if (G <= 4 && it.n_tok == 1) scan(std::true_type{}); else scan(std::false_type{});
+        } else {
+            scan(std::false_type{});
         }
     }
-
-    float l_tot = l + __shfl_xor(l, 16, 64);
-    l_tot += __shfl_xor(l_tot, 32, 64);
+    float l_tot = l;
 
     // merge the waves' states in wave order (results are run-to-run identical)
     if (wave > 0) {

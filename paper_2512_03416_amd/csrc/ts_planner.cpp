@@ -186,7 +186,11 @@ static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tile
 // Generic row tiles longer than a fair share of the workgroups that the GPU holds at once (two of four waves per
 // CU) are cut along the pages into ranges of at most that share; a range has at least 16 pages (four per wave:
 // shorter ones spend longer starting up and merging than multiplying).
-constexpr int kRowTileMinPages = 16, kRowTileWgsPerCu = 2;
+// Next to chunk tiles, which the matrix instruction bounds, ranges of decode rows are twice as long from kRowTileLongPages
+// on: half the workgroups keep enough of the scan on the way, and the chunk tiles find more places from the start (30 rows of
+// 500-2000 tokens and 3 chunks of 100-300, 32/8 heads of 128, 93.0 -> 89.5 us a pass; without chunks they are slower,
+// 67.5 -> 74.0, and so are short ones next to chunks, 4 rows and 2 chunks 33.8 -> 35.2).
+constexpr int kRowTileMinPages = 16, kRowTileWgsPerCu = 2, kRowTileLongPages = 32;
 
 static int32_t row_tile_tokens(const ts_attn_desc& d) { return 16 / (d.num_q_heads / d.num_kv_heads); }
 
@@ -210,7 +214,9 @@ static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t p
     if (opt.row_cut_few_only && (int64_t)p.rt.size() * Hkv >= slots) return part;
     int64_t pages = 0;
     for (const RowTile& t : p.rt) pages += row_tile_pages(p, t);
-    const int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
+    int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
+    const bool chunks = std::any_of(p.rt.begin(), p.rt.end(), [](const RowTile& t) { return t.n_tok_cut > 1; });
+    if (chunks && L >= kRowTileLongPages) L *= 2;
     auto cuts = [&](const RowTile& t) { return (row_tile_pages(p, t) + L - 1) / L; };
     int64_t need = part;
     for (const RowTile& t : p.rt)
