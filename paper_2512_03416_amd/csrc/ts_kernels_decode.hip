@@ -8,10 +8,10 @@ namespace ts {
 
 // KV heads vary fastest over the grid: the Hkv workgroups of one item start together and read the
 // Hkv adjacent tiles of each page (one contiguous run of the cache) at about the same time.
-template <typename KT, int NBUF, int D, bool EXACT>
+template <typename KT, int NBUF, int D, bool EXACT, int HEADS = 16>
 __device__ __forceinline__ void decode_workgroup(const AttnArgs& a)
 {
-    __shared__ DecMerge<kDecWaves, D> mg;
+    __shared__ DecMerge<kDecWaves, D, HEADS> mg;
     const int w = blockIdx.x / a.geo.Hkv, g = blockIdx.x % a.geo.Hkv;
     int first = w, end = w + 1;
     if (a.dec_wg) { first = as_constant(a.dec_wg)[w]; end = as_constant(a.dec_wg)[w + 1]; }
@@ -21,7 +21,7 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a)
         split |= it.part >= 0;
         decode_item<KT, NBUF, kDecWaves, D, true, false, EXACT>(a, it, g, mg, i > first);
     }
-    if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves>(a, a.dec + first, end - first, a.cmb, g);
+    if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves, false>(a, a.dec + first, end - first, a.cmb, g);
 }
 
 template <typename KT, int NBUF, int D>
@@ -36,17 +36,19 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { de
 // KV head): two pages at a time, half the vector instructions.  What bounds it there is not memory but what the tiles leave it
 // of the SIMDs: a 4096-token chunk over 4096 next to 128 rows, a prefill workgroup on every CU, 570 -> 500 us a pass (and
 // with that more of the CUs can hold one); 256 rows of 256-1500 tokens next to 2048 tokens 218 -> 210; where the tiles
-// outlast the scan it changes nothing (the burst configuration, 64 Ki prompt tokens next to 512 rows).
-template <typename KT, int D, bool PAIRS>
+// outlast the scan it changes nothing (the burst configuration, 64 Ki prompt tokens next to 512 rows).  Groups of more heads run
+// decode_kernel_lean_merging there (the page-by-page scan in the short form no longer fits 128 registers since all of a
+// workgroup's threads merge).
+template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean(AttnArgs a)
 {
-    __shared__ DecMerge<kDecWaves, D> mg;
-    decode_item<KT, 2, kDecWaves, D, false, false, false, PAIRS>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+    __shared__ DecMerge<kDecWaves, D, 8> mg;               // (what resident prefill workgroups leave of a CU's LDS: 32 KB)
+    decode_item<KT, 2, kDecWaves, D, false, false, false, D == 128>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
 }
 template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean_merging(AttnArgs a)
 {
-    decode_workgroup<KT, 2, D, false>(a);
+    decode_workgroup<KT, 2, D, false, 8>(a);
 }
 
 // A launch on its own (no resident prefill workgroups next to it): prefetches past the end of an item read nothing.  A
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel_fused(AttnArgs a
         split |= s.dec[i].part >= 0;
         decode_item<KT, 2, kDecWaves, D, true, true, true>(a, s.dec[i], g, mg, i > first);
     }
-    if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves>(a, s.dec + first, end - first, s.cmb, g);
+    if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves, true>(a, s.dec + first, end - first, s.cmb, g);
 }
 
 // Merge of split rows as a launch (the rows from the device work list, or as kernel arguments behind the fused form): one
@@ -95,7 +97,7 @@ __device__ __forceinline__ void combine_row(const AttnArgs& a, const CmbItem it)
     for (int k0 = 0; k0 < it.n_split; k0 += groups * kMergeChunk) {
         const int mine = k0 + grp * kMergeChunk;
         if (mine < it.n_split) {
-            const SplitSum c = merge_chunk(parts, mine, it.n_split, h, 4 * lane);
+            const SplitSum c = sum_chunk(load_chunk(parts, mine, it.n_split, h, 4 * lane), mine, it.n_split);
             s_o[grp][lane] = c.o;
             if (lane == 0) { s_m[grp] = c.m; s_l[grp] = c.l; }
         }
@@ -123,12 +125,9 @@ static int launch_decode_t(const AttnArgs& a, hipStream_t st, hipEvent_t done)
     case 3: return launch_kernel(decode_kernel<KT, 3, D>, grid, block, st, done, a);
     case 4: return launch_kernel(decode_kernel<KT, 4, D>, grid, block, st, done, a);
     default:
-        if (a.dec_wg || a.cmb_ctr) return launch_kernel(decode_kernel_lean_merging<KT, D>, grid, block, st, done, a);
+        if (a.dec_wg || a.cmb_ctr || (a.n_queue > 0 && D == 128 && a.geo.G > 8)) return launch_kernel(decode_kernel_lean_merging<KT, D>, grid, block, st, done, a);
         if (a.n_queue == 0) return launch_kernel(decode_kernel_alone<KT, D>, grid, block, st, done, a);   // (queues: the tiles of a co-resident launch)
-        if constexpr (D == 128) {
-            if (a.geo.G <= 8) return launch_kernel(decode_kernel_lean<KT, D, true>, grid, block, st, done, a);
-        }
-        return launch_kernel(decode_kernel_lean<KT, D, false>, grid, block, st, done, a);
+        return launch_kernel(decode_kernel_lean<KT, D>, grid, block, st, done, a);
     }
 }
 
@@ -140,7 +139,7 @@ static int resident_t(int nbuf)
     switch (nbuf) {
     case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<KT, 3, D>, 64 * kDecWaves, 0); break;
     case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<KT, 4, D>, 64 * kDecWaves, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel_lean<KT, D, false>, 64 * kDecWaves, 0); break;
+    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel_lean<KT, D>, 64 * kDecWaves, 0); break;
     }
     return e == hipSuccess ? per_cu : 0;
 }
