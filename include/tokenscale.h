@@ -232,7 +232,8 @@ const char *ts_last_error(const ts_ctx *ctx);
  *                         of the chunks' sequences are widened from e4m3 to bf16 once per pass, into scratch of
  *                         8 KiB * num_kv_heads per page, and the tiles read that copy; a batch whose chunk
  *                         sequences hold more pages than this value (default 16384; 0 = never widen) has its
- *                         tiles widen the cache themselves.  Results are identical either way
+ *                         tiles widen the cache themselves, and so has one with head dim 128 whose tiles read a page
+ *                         too few times for the copy to pay.  Results are identical either way
  *   "xcd_count"           accelerator dies the prefill launch order is laid out for (default 8)
  *   "kernel_timing"       N > 0 = record HIP events around the launches of every N-th call
  *                         (see ts_kernel_times), 0 = off
@@ -277,7 +278,8 @@ typedef struct {
     int64_t ctx_pages;          /* sum over sequences of ceil(ctx_len/16)                      */
     int32_t mixed_mode;         /* TS_MIXED_* the batch is launched with (SEPARATE if one kind only) */
     int32_t prefill_workgroups; /* co-resident launch: resident workgroups that work through the prefill tiles (else 0) */
-    int64_t widened_pages;      /* fp8 caches: pages widened to bf16 before the prefill tiles run   */
+    int64_t widened_pages;      /* fp8 caches: pages widened to bf16 before the prefill tiles run (a
+                                   launch leaves them out where its tiles read a page few times)    */
     int64_t prefill_parts;      /* partial results of prefill tiles cut along the keys (0 = none cut) */
 } ts_plan_info;
 

@@ -423,6 +423,25 @@ static int64_t pf_keys(const PfItem& t)
     return std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
 }
 
+// Do the tiles over an e4m3 cache gain by bf16 copies of their pages, or do they convert while they stage?  The copies cost a
+// launch and three bytes of traffic per element in front of everything else, decode rows included; converting costs a tile
+// 4-8 % of every stage.  So it depends on how often a page is read.  Whole passes, converting against copies, 8 KV heads:
+// 4 chunks of 64 over 8200 (1-2 reads a page) 51.5 us against 82.3; 8 of 256 over 8200 (4) 250 against 301; 512 over 8200 (16)
+// 136.1 against 140.3; 512 over 8200 next to 128 rows of 1-8 Ki tokens 310 against 335; 1024 over 4000 (29) next to 400 rows
+// 267 against 262; 4 of 1024 over 8200 (30) 996 against 974; 2048 over 8200 (57) 530 against 511.  Few pages: the copies are a
+// few microseconds and the tile's first stages arrive later where they are converted: one chunk of 512 alone (32 pages) 23.4
+// against 22.8, of 32 16.0 against 13.2; 32 over 1000 (65 pages) 31.7 against 31.6; 8 of 256 (128 pages) 33.8 against 36.2.
+constexpr int64_t kWidenReads = 26;
+constexpr int64_t kWidenFewPages = 512;                    // (pages times KV heads)
+static bool widening_pays(const Plan& p, int64_t pages, int Hkv)
+{
+    if (pages * Hkv < kWidenFewPages) return true;
+    int64_t keys = 0;                                      // that tiles read, per KV head
+    for (const PfItem& t : p.pf) keys += std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
+    return keys > kWidenReads * kPage * pages;
+}
+
+
 static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool for_launch, int64_t kv_row_bytes,
                                 int32_t n_cu)
 {
@@ -720,10 +739,9 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
         }
     }
     if (!p.rt.empty()) part = cut_row_tiles(p, Hkv, opt, part);
-    // fp8 caches: the pages of the chunks' sequences are widened to bf16 once per pass (every tile of a chunk
-    // reads the whole prefix: widening inside the tiles repeats the conversion once per tile and costs the tile
-    // kernel 8 % of its time), provided they fit the scratch the option allows
-    if (widen && !p.pf.empty()) {
+    // fp8 caches: the pages of the chunks' sequences are widened to bf16 once per pass, provided they fit the scratch the
+    // option allows and a launch gains by it (see widening_pays)
+    if (widen && !p.pf.empty() && (!opt.for_launch || d.head_dim != 128 || widening_pays(p, chunk_pages, Hkv))) {
         p.wide_base.assign((size_t)num_seqs, -1);
         for (int s = 0; s < num_seqs; ++s) {
             if (p.seqs[s].q_len <= 1) continue;
