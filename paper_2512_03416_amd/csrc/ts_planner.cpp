@@ -423,6 +423,22 @@ static int64_t pf_keys(const PfItem& t)
     return std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
 }
 
+// Parts of a tile that is cut along the keys (`below`: keys at or below its first query position that may be cut off).
+// Up to four are merged by the last of them, about 5 us on top of a tile whose 64 keys take 1-1.5 us; more by a launch, as
+// much again.  So four parts of half the shortest range come before five or more of it, and a tile with less than one and a
+// half ranges stays whole.  One part per range only, before: 32 tokens over 1000 29.1 -> 24.8 us a pass, 128 over 1500 31.2 ->
+// 27.0, 400 over 1000 (head dim 64) 24.5 -> 21.0, 128 over 2700 (five parts then) 36.2 -> 31.1; from six ranges on the launch:
+// 32 over 4200 32.7 against 35.6 in four parts.  Whole below 768 keys: 32 over 500 in two parts 22.7 against 20.6.
+constexpr int32_t kPfLaunchParts = 6;
+static int32_t parts_of_tile(int32_t below, int32_t min_keys, int32_t wanted)
+{
+    if (min_keys <= 0) return 1;
+    const int32_t longer = below / min_keys;
+    if (longer >= kPfLaunchParts) return std::min(wanted, longer);
+    if (2 * (int64_t)below < 3 * (int64_t)min_keys) return 1;
+    return std::max(1, std::min({wanted, kPfMergeParts, (int32_t)(2 * (int64_t)below / min_keys)}));
+}
+
 // Do the tiles over an e4m3 cache gain by bf16 copies of their pages, or do they convert while they stage?  The copies cost a
 // launch and three bytes of traffic per element in front of everything else, decode rows included; converting costs a tile
 // 4-8 % of every stage.  So it depends on how often a page is read.  Whole passes, converting against copies, 8 KV heads:
@@ -698,9 +714,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
                 // workgroups otherwise).  Cuts lie at multiples of 64 keys at or below the tile's first query
                 // position, so that every row sees the first key of every part; parts are of equal length.
                 const int32_t below = (m.prefix + t0) / 64;                       // whole stages every row sees fully
-                int32_t n_part = 1;
-                if (pf_parts_wanted > 1 && opt.pf_split_min_keys > 0)
-                    n_part = (int32_t)std::max<int64_t>(1, std::min<int64_t>(pf_parts_wanted, (int64_t)below * 64 / opt.pf_split_min_keys));
+                const int32_t n_part = pf_parts_wanted > 1 ? parts_of_tile(below * 64, opt.pf_split_min_keys, (int32_t)pf_parts_wanted) : 1;
                 if (n_part == 1) {
                     p.pf.push_back(PfItem{s, m.q_off, m.q_len, m.prefix, t0, cnt, m.ctx_len, -1, 0, INT32_MAX, 0, 0});
                     continue;

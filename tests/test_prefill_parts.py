@@ -1,0 +1,41 @@
+"""How prefill tiles are cut along the keys: every key once, cuts on stages that all rows see, four parts before more."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from workloads import AttnShape, make_batch
+
+
+@pytest.mark.parametrize("heads", [(32, 8), (64, 8), (4, 1)], ids=lambda h: f"{h[0]}q{h[1]}kv")
+def test_cut_tiles_cover_their_keys_once(heads):
+    import paper_2512_03416_amd as ts
+    from paper_2512_03416_amd import binding
+    d = ts.Desc.make(heads[0], heads[1], 128, "bf16", "bf16", 1 << 14, 1 << 10)
+    for prefix in [0, 63, 64, 448, 511, 512, 767, 768, 831, 1000, 1024, 1500, 2047, 2048, 2560, 3071, 3072, 3500, 4096, 9000]:
+        tiles = binding.plan_export(d, [40], [prefix + 40], "prefill")
+        by_tile = {}
+        for t in tiles:
+            by_tile.setdefault(int(t[4]), []).append((int(t[8]), int(t[9])))
+        for tok, ranges in by_tile.items():
+            ranges.sort()
+            assert ranges[0][0] == 0 and ranges[-1][1] == 2**31 - 1
+            for (_, end), (begin, _) in zip(ranges, ranges[1:]):
+                assert end == begin and begin % 64 == 0 and 0 < begin <= prefix + tok
+            below = (prefix + tok) // 64 * 64
+            most = 16 if below >= 6 * 512 else 4 if below >= 768 else 1
+            assert len(ranges) <= most and (len(ranges) > 1) == (below >= 768), (prefix, tok, ranges)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv,heads,head_dim", [("bf16", (8, 2), 128), ("fp8", (16, 2), 128), ("bf16", (8, 2), 64)])
+@pytest.mark.parametrize("prefix", [767, 768, 1100, 2047, 3071, 3072])
+def test_short_chunks_over_prefixes_of_a_few_parts(kv, heads, head_dim, prefix):
+    import gpu_harness as g
+    mk = lambda: make_batch(AttnShape(heads[0], heads[1], head_dim, "bf16", kv), [70], [prefix + 70], seed=97, pool_rule=1.25, value_mult=0.5)
+    ref, rk, rv = oracle.run_batch(W.to_cpu(mk()))
+    print(f"[case] kv={kv} heads={heads} D={head_dim} prefix={prefix}", flush=True)
+    out, gk, gv = g.run_batch(mk())
+    assert gk.tobytes() == rk.tobytes() and gv.tobytes() == rv.tobytes()
+    # (the bars of the tiles elsewhere)
+    assert np.all(np.isfinite(out)) and float(np.max(np.abs(out - ref))) <= {"bf16": 2e-2, "fp8": 6e-2}[kv]
