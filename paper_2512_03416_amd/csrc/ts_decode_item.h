@@ -157,7 +157,8 @@ constexpr int kDecWaves = 4;               // stand-alone decode kernel; the mix
 // LDS image of the waves' states: the group's heads (at most HEADS) only, four dims of a head per entry, a row of which is
 // one entry longer than the head so that the heads lie in different banks.  All threads of the workgroup add up an
 // entry each.  (One wave adding up whole accumulators, unused columns included, while the others had nothing to do, was a
-// serial end to every item: four rows of 17-900 tokens 15.3 -> 14.8 us a pass, one e4m3 row of 128 Ki 92.0 -> 90.8.)
+// serial end to every item: eight rows of 500-2500 tokens 15.3 -> 14.8 us a
+// pass, three e4m3 rows of 30-131 Ki 92.0 -> 90.8.)
 template <int WAVES, int D = 128, int HEADS = 16>
 struct DecMerge {
     static constexpr int kHeads = HEADS;

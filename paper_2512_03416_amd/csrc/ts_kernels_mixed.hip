@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kPfThreads) void mixed_kernel(AttnArgs a)
 // Co-resident form: one of these workgroups per CU stays for the whole launch and works through the prefill
 // tiles; it is held to 192 vector registers per lane (two waves per SIMD: 384 of 512) and uses 128 of the
 // 160 KB of LDS, so that every CU keeps room for one 4-wave decode workgroup of 128 registers per lane and
-// 25 KB -- the decode grid that the host launches next to it on a second stream.  The HBM-bound scan then
+// 17 KB -- the decode grid that the host launches next to it on a second stream.  The HBM-bound scan then
 // runs in the shadow of the MFMA-bound tiles on the same CU instead of taking turns with them.
 // (The register attribute counts in units of two on this architecture: 96 means 192.)
 template <typename KT, bool WIDE>
