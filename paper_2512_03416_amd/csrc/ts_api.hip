@@ -979,11 +979,13 @@ int mixed_pass(ts_ctx* c, void* stream, const void* q, const void* k_new, const 
     const Geometry geo = geometry_of(c->desc);
     const char* wb = work_base(c);
     // Events on the kernels: the call's end on its last one, the fork of a co-resident launch on the last one before it
-    // (recorded as before while the side stream is being probed: the probe's kernel comes in between).
+    // (recorded as before while the side stream is being probed: the probe's kernel comes in between; and in a timed pass,
+    // where the time stamp in front of the prefill launch would let the decode grid take the CUs first: the pair of the burst
+    // configuration 745 us timed so, 575 with the fork recorded behind the time stamp).
     const bool coresident = !p.queue.empty() && p.info.mixed_mode == TS_MIXED_CORESIDENT;
     const bool on_kernels = events_on_kernels(st);
     const hipEvent_t done = on_kernels ? c->cur_slot->ev : nullptr;
-    const hipEvent_t fork = on_kernels && coresident && (c->side_state == 2 || !c->h_probe) ? c->ev_fork : nullptr;
+    const hipEvent_t fork = on_kernels && coresident && !c->timing_now && (c->side_state == 2 || !c->h_probe) ? c->ev_fork : nullptr;
     bool forked = false;
     hipEvent_t side_end = nullptr;
     if (k_new && !fuse) {
