@@ -186,10 +186,15 @@ static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tile
 // Generic row tiles longer than a fair share of the workgroups that the GPU holds at once (two of four waves per
 // CU) are cut along the pages into ranges of at most that share; a range has at least 16 pages (four per wave:
 // shorter ones spend longer starting up and merging than multiplying).
-// Next to chunk tiles, which the matrix instruction bounds, ranges of decode rows are twice as long from kRowTileLongPages
-// on: half the workgroups keep enough of the scan on the way, and the chunk tiles find more places from the start (30 rows of
-// 500-2000 tokens and 3 chunks of 100-300, 32/8 heads of 128, 93.0 -> 89.5 us a pass; without chunks they are slower,
-// 67.5 -> 74.0, and so are short ones next to chunks, 4 rows and 2 chunks 33.8 -> 35.2).
+// From shares of kRowTileLongPages pages on (fewer: 4 rows and 2 chunks 33.8 -> 35.2 with longer ones):
+//   - ranges of decode rows next to chunk tiles, which the matrix instruction bounds, are twice as long: half the workgroups
+//     keep enough of the scan on the way, and the chunk tiles, cut as ever, find more places from the start (32/8 heads of 128, 30
+//     rows of 500-2000 tokens and 3 chunks of 100-300 91.5 -> 85.9 us a pass, 16 rows of 1000-2048 and a chunk of 231 over 1000
+//     79.0 -> 72.2; rows without chunks are slower, 67.5 -> 74.0);
+//   - chunks without decode rows stay whole where no tile is longer than twice the share (they give every CU a workgroup then): cut,
+//     their ranges would be more than the places, one short round behind the other, and a merge (one chunk of 240 tokens over
+//     500 46.2 -> 32.5, of 150 over 1000 47.6 -> 44.1, over 1500 58.0 -> 58.9).  Longer tiles are cut at the share (64 tokens
+//     over 16384: 143 us; at twice the share 153).
 constexpr int kRowTileMinPages = 16, kRowTileWgsPerCu = 2, kRowTileLongPages = 32;
 
 static int32_t row_tile_tokens(const ts_attn_desc& d) { return 16 / (d.num_q_heads / d.num_kv_heads); }
@@ -214,10 +219,16 @@ static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t p
     if (opt.row_cut_few_only && (int64_t)p.rt.size() * Hkv >= slots) return part;
     int64_t pages = 0;
     for (const RowTile& t : p.rt) pages += row_tile_pages(p, t);
-    int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
-    const bool chunks = std::any_of(p.rt.begin(), p.rt.end(), [](const RowTile& t) { return t.n_tok_cut > 1; });
-    if (chunks && L >= kRowTileLongPages) L *= 2;
-    auto cuts = [&](const RowTile& t) { return (row_tile_pages(p, t) + L - 1) / L; };
+    const int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
+    auto decode_row = [&](const RowTile& t) { return p.seqs[t.seq].q_len == 1; };
+    const auto n_dec = std::count_if(p.rt.begin(), p.rt.end(), decode_row);
+    const bool longer = L >= kRowTileLongPages;
+    if (longer && n_dec == 0 && std::all_of(p.rt.begin(), p.rt.end(), [&](const RowTile& t) { return row_tile_pages(p, t) <= 2 * L; })) return part;
+    const int32_t L_dec = longer && n_dec < (int64_t)p.rt.size() ? 2 * L : L;
+    auto cuts = [&](const RowTile& t) {
+        const int32_t most = decode_row(t) ? L_dec : L;
+        return (row_tile_pages(p, t) + most - 1) / most;
+    };
     int64_t need = part;
     for (const RowTile& t : p.rt)
         if (cuts(t) > 1) need += (int64_t)cuts(t) * t.n_tok_cut;
