@@ -154,11 +154,16 @@ constexpr int64_t kMinSplitPages = 32;
 // rows of 2000-16 000 tokens next to 16 chunks of 300-1024 499 -> 470 us, 16 rows of 8000-64 000 (e4m3) next to 8 chunks
 // of 100-300 386 -> 331, 3072 tokens over 2048 next to 128 rows of 1024-8192 514 -> 468; with more rows the partial results
 // cost more than it gains (256 rows of 1024-8192 tokens, e4m3, 474 -> 517; 512 of 512-4096 786 -> 818).  With a prefill
-// workgroup on every CU rows of up to kWholePages pages stay whole (24 rows of 300-3000 tokens 111.5 -> 110.3).
+// workgroup on every CU rows of up to kWholePages pages stay whole if their scan, kCoPageUs a page next to tiles, ends within the
+// tiles' time: 20 rows of 3000 tokens (188 pages, 53 us) next to 2000 over 1500 (tiles 82 us) 131.0 us a pass, in pieces of 72-160 pages
+// 138; 24 e4m3 rows of 3000 next to 1024 over 1500 (54 us) 98 and 101; 24 rows of 300-3000 next to 2024 over 1000 (67 us) 109.6 and 111;
+// but 12 of 3000 next to 1024 over 2300 (38 us) 100.8 whole and 86.3 in two, 16 of 1500-3000 next to 1500 over 1000 (40/8 heads, 43
+// us) 94.4 and 86.5, 12 of 3000 next to 1500 over 1500 (44 us) 94.2 and 90.0.
 constexpr int64_t kCoItemPages = 160, kWholePages = 192;
+constexpr double kCoPageUs = 0.28;
 
 static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tiles, int64_t decode_pages, int Hkv,
-                                int32_t wg_slots, int32_t n_cu, bool filled_by_prefill, int32_t pf_wgs)
+                                int32_t wg_slots, int32_t n_cu, bool filled_by_prefill, int32_t pf_wgs, double t_pf)
 {
     // (next to a resident prefill workgroup a CU has room for one decode workgroup; the CUs without one hold
     // their usual share of the stand-alone slots)
@@ -166,7 +171,7 @@ static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tile
     if (filled_by_prefill && pf_wgs > 0 && pf_wgs < n_cu)
         slots = pf_wgs + (int64_t)(n_cu - pf_wgs) * std::max(1, wg_slots / n_cu);
     int64_t L = std::max<int64_t>(kMinSplitPages, (decode_tiles + slots - 1) / slots);
-    if (pf_wgs >= n_cu) L = std::max(L, kWholePages);
+    if (pf_wgs >= n_cu) L = std::max(L, std::min(kWholePages, (int64_t)(t_pf / kCoPageUs)));
     else if (pf_wgs > 0 && 2 * p.info.decode_tokens * Hkv < 3 * wg_slots) L = std::min(L, kCoItemPages);
     if (!filled_by_prefill && p.info.decode_tokens * Hkv <= n_cu && decode_pages > 0) {
         const int64_t want_items = std::max<int64_t>(1, n_cu / Hkv);   // per KV head
@@ -681,7 +686,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     const int32_t L = opt.split_pages > 0
                           ? opt.split_pages
                           : auto_split_pages(p, num_seqs, decode_tiles, decode_pages, Hkv, opt.wg_slots,
-                                             std::max(1, opt.n_cu), filled_by_prefill, pf_wgs);
+                                             std::max(1, opt.n_cu), filled_by_prefill, pf_wgs, t_pf);
     // (rows up to this many pages stay whole: see 4. above)
     const bool many = mixed_mode == TS_MIXED_SEPARATE && p.info.decode_tokens * Hkv > opt.wg_slots;
     const int32_t keep_whole = opt.split_pages > 0 || !many ? L : L + L / 4;
