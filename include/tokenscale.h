@@ -264,7 +264,8 @@ typedef struct {
 int ts_kernel_times(ts_ctx *ctx, ts_kernel_stats *out, int reset);
 
 /* Host only -- step a0.  Describes the work the planner makes of a batch, without touching a
- * GPU: how many decode split items, combine rows, prefill tiles and generic rows.
+ * GPU: how many decode split items, combine rows, prefill tiles and generic rows a pass with default
+ * options launches.
  * split_pages = 0 lets the planner choose. */
 typedef struct {
     int64_t total_tokens, decode_tokens, prefill_tokens;
@@ -278,8 +279,7 @@ typedef struct {
     int64_t ctx_pages;          /* sum over sequences of ceil(ctx_len/16)                      */
     int32_t mixed_mode;         /* TS_MIXED_* the batch is launched with (SEPARATE if one kind only) */
     int32_t prefill_workgroups; /* co-resident launch: resident workgroups that work through the prefill tiles (else 0) */
-    int64_t widened_pages;      /* fp8 caches: pages widened to bf16 before the prefill tiles run (a
-                                   launch leaves them out where its tiles read a page few times)    */
+    int64_t widened_pages;      /* fp8 caches: pages widened to bf16 before the prefill tiles run      */
     int64_t prefill_parts;      /* partial results of prefill tiles cut along the keys (0 = none cut) */
 } ts_plan_info;
 

@@ -147,7 +147,9 @@ struct PlanOptions {
     int32_t mixed_mode = TS_MIXED_CORESIDENT;   // how a batch with decode rows and prefill chunks is launched
     bool append_only = false;   // nothing but the append lists is wanted
     bool append_lists = true;   // the append lists are wanted
-    bool for_launch = false;    // leave out the one of pfmap / queue that the launch form does not read
+    bool for_launch = false;    // launch details: the one of pfmap / queue that the launch form does not read and the fp32 records that a
+                                // run's first stands for are left out, cut tiles are marked for the merge in the kernel (no rule
+                                // of what is launched looks at it)
     bool generic_only = false;  // every row through the generic kernel
     bool prefill_generic = false;
     int32_t tile_tokens = 0;    // query tokens per prefill tile

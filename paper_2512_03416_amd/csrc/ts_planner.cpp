@@ -673,8 +673,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
             pf_wgs = std::min(all, opt.pf_resident_wgs);
         } else {
             const double r = t_dec > 0 ? t_pf / t_dec : 1e9;
-            // (plans that are only described keep the share until kPfAllRatioShort)
-            const bool every = r >= (opt.for_launch && t_dec >= kPfAllUs ? kPfAllRatio : kPfAllRatioShort);
+            const bool every = r >= (t_dec >= kPfAllUs ? kPfAllRatio : kPfAllRatioShort);
             pf_wgs = every ? all : (int32_t)std::ceil((kPfShare0 + kPfShare1 * r) * all);
             // (not a few tiles more than whole rounds: 55 tiles per die on 19 workgroups 485 us, on 18 509)
             const int64_t per_die = (tile_heads + x - 1) / x, n = (pf_wgs + x - 1) / x, rounds = per_die / n;
@@ -770,8 +769,8 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     }
     if (!p.rt.empty()) part = cut_row_tiles(p, Hkv, opt, part);
     // fp8 caches: the pages of the chunks' sequences are widened to bf16 once per pass, provided they fit the scratch the
-    // option allows and a launch gains by it (see widening_pays)
-    if (widen && !p.pf.empty() && (!opt.for_launch || d.head_dim != 128 || widening_pays(p, chunk_pages, Hkv))) {
+    // option allows and the pass gains by it (see widening_pays)
+    if (widen && !p.pf.empty() && (d.head_dim != 128 || widening_pays(p, chunk_pages, Hkv))) {
         p.wide_base.assign((size_t)num_seqs, -1);
         for (int s = 0; s < num_seqs; ++s) {
             if (p.seqs[s].q_len <= 1) continue;

@@ -20,3 +20,67 @@ def test_rows_stay_whole_only_if_their_scan_ends_with_the_tiles(batch, tiles_us,
     assert info.mixed_mode == 2 and info.n_decode_items == pieces * rows
     items = binding.plan_export(d, q, ctx, "decode")
     assert max(int(i[4] - i[3]) for i in items) * 0.28 <= tiles_us
+
+
+HARNESS = r"""
+#include <cstdio>
+#include <cstring>
+#include <random>
+#include "ts_internal.h"
+using namespace ts;
+template <typename T> static bool same(const std::vector<T>& a, const std::vector<T>& b)
+{
+    return a.size() == b.size() && (a.empty() || !memcmp(a.data(), b.data(), a.size() * sizeof(T)));
+}
+int main()
+{
+    std::mt19937 rng(11);
+    auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+    int mixed = 0, widened = 0;
+    for (int it = 0; it < 1500; ++it) {
+        ts_attn_desc d{};
+        const int hkv[] = {1, 2, 4, 8};
+        d.num_kv_heads = hkv[rng() % 4]; d.num_q_heads = d.num_kv_heads * pick(1, 16); d.head_dim = it % 4 ? 128 : 64;
+        d.page_size = 16; d.num_pages = 1 << 20; d.max_pages_per_seq = 1 << 16;
+        d.q_dtype = it % 7 ? TS_BF16 : TS_F32;
+        d.kv_dtype = d.q_dtype == TS_F32 ? TS_F32 : it % 2 ? TS_BF16 : TS_FP8_E4M3;
+        const int rows = pick(0, 200), chunks = pick(0, 6), most = 1 << pick(6, 13), len = 1 << pick(4, 12), before = 1 << pick(0, 13);
+        std::vector<int32_t> q, c;
+        for (int i = 0; i < rows; ++i) { q.push_back(1); c.push_back(pick(1, most)); }
+        for (int i = 0; i < chunks; ++i) { q.push_back(pick(2, len)); c.push_back(q.back() + pick(0, before)); }
+        if (q.empty()) continue;
+        PlanOptions o, l;
+        l.for_launch = true;
+        Plan a, b;
+        build_plan(d, q.data(), c.data(), (int)q.size(), o, &a);
+        build_plan(d, q.data(), c.data(), (int)q.size(), l, &b);
+        for (PfItem& t : b.pf) t.merge = 0;
+        if (memcmp(&a.info, &b.info, sizeof a.info) || !same(a.dec, b.dec) || !same(a.dec_wg, b.dec_wg) || !same(a.cmb, b.cmb) || !same(a.pf, b.pf) ||
+            !same(a.rt, b.rt) || !same(a.queue, b.queue) || !same(a.q_off, b.q_off) || !same(a.wide, b.wide)) {
+            printf("batch %d: described %d workgroups, %d items, %lld partials, %lld widened; launched %d, %d, %lld, %lld\n", it, a.info.prefill_workgroups,
+                   a.info.n_decode_items, (long long)a.info.partial_slots, (long long)a.info.widened_pages, b.info.prefill_workgroups,
+                   b.info.n_decode_items, (long long)b.info.partial_slots, (long long)b.info.widened_pages);
+            return 1;
+        }
+        mixed += b.info.mixed_mode == TS_MIXED_CORESIDENT;
+        widened += b.info.widened_pages > 0;
+    }
+    printf("%d co-resident, %d widened\n", mixed, widened);
+    return mixed > 50 && widened > 50 ? 0 : 2;
+}
+"""
+
+
+def test_the_described_plan_is_the_launched_one(tmp_path):
+    """Over random batches: the plan of a launch has the described counts and lists (but for the details that a launch
+    adds: marks of tiles merged in the kernel, one record per run of fp32 tokens)."""
+    import os
+    import subprocess
+    from paper_2512_03416_amd import build as B
+    src = tmp_path / "plans.cpp"
+    src.write_text(HARNESS)
+    exe = str(tmp_path / "plans")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", B.CSRC, "-I", os.path.join(os.path.dirname(B.CSRC), "..", "include"), str(src),
+                    os.path.join(B.CSRC, "ts_planner.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout

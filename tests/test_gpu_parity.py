@@ -520,12 +520,13 @@ def test_co_resident_launch_with_any_number_of_resident_prefill_workgroups(kv):
 def test_fp8_prefill_widened_pages_and_in_tile_widening_agree(mode):
     """fp8 cache: the prefill tiles read bf16 copies of the chunk sequences' pages made once per pass (default)
     or widen the cache themselves (option 0, or more pages than the option allows); both must match the oracle
-    and each other bit for bit (the conversion is exact), in every launch mode, with ragged page tails."""
+    and each other bit for bit (the conversion is exact), in every launch mode, with ragged page tails.  (The tiles
+    read a page 30 times on average: with 26 or fewer the default makes no copies.)"""
     import paper_2512_03416_amd as ts
-    shape = AttnShape(32, 8, 128, "bf16", "fp8")
-    q = [1] * 60 + [333, 1800, 64, 2] + [1] * 9
+    shape = AttnShape(32, 4, 128, "bf16", "fp8")
+    q = [1] * 60 + [333, 2300, 64, 2] + [1] * 9
     rng = np.random.default_rng(6)
-    c = list(rng.integers(1, 4000, size=60)) + [333 + 1111, 1800, 64 + 15, 2 + 640] + list(rng.integers(1, 900, size=9))
+    c = list(rng.integers(1, 4000, size=60)) + [333 + 111, 2300, 64 + 15, 2 + 40] + list(rng.integers(1, 900, size=9))
     mk = lambda: make_batch(shape, q, c, seed=45, pool_rule=1.25, value_mult=1.0)
     g = gpu()
     b = mk()

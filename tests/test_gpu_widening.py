@@ -9,13 +9,13 @@ from workloads import AttnShape, make_batch
 
 pytestmark = pytest.mark.gpu
 
-# (query lengths, context lengths), 32 query heads over 2 KV heads: tiles of 16 tokens
+# (query lengths, context lengths, pages copied with head dim 128), 32 query heads over 2 KV heads: tiles of 16 tokens
 BATCHES = {
-    "few pages": ([333], [600]),                                        # 38 pages: copies
-    "pages read 20 times": ([320], [4096 + 320]),                       # converted in the tiles
-    "pages read 27 times": ([450], [4096 + 450]),                       # copies
-    "next to rows, few reads": ([1] * 9 + [2, 40, 17], [1, 16, 17, 300, 900, 64, 65, 2000, 31, 3000, 1500 + 40, 17]),
-    "next to rows, many reads": ([1, 1, 450, 1], [700, 33, 4096 + 450, 1025]),
+    "few pages": ([333], [600], 38),
+    "pages read 20 times": ([320], [4096 + 320], 0),                    # converted in the tiles
+    "pages read 27 times": ([450], [4096 + 450], 285),
+    "next to rows, few reads": ([1] * 9 + [2, 40, 17], [1, 16, 17, 300, 900, 64, 65, 2000, 31, 3000, 1500 + 40, 17], 0),
+    "next to rows, many reads": ([1, 1, 450, 1], [700, 33, 4096 + 450, 1025], 285),
 }
 
 
@@ -23,8 +23,11 @@ BATCHES = {
 @pytest.mark.parametrize("batch", list(BATCHES))
 def test_both_sides_of_the_line(batch, head_dim):
     import gpu_harness as g
-    q, ctx = BATCHES[batch]
+    import paper_2512_03416_amd as ts
+    q, ctx, copied = BATCHES[batch]
     mk = lambda: make_batch(AttnShape(32, 2, head_dim, "bf16", "fp8"), q, ctx, seed=95, pool_rule=1.25, value_mult=1.0)
+    every = sum(-(-c // 16) for n, c in zip(q, ctx) if n > 1)
+    assert ts.plan_describe(g.make_desc(mk()), q, ctx).widened_pages == (copied if head_dim == 128 else every) and copied in (0, every)
     ref, rk, rv = oracle.run_batch(W.to_cpu(mk()))
     q_off = np.concatenate([[0], np.cumsum(q)])
     chunk = np.concatenate([np.arange(q_off[i], q_off[i + 1]) for i in range(len(q)) if q[i] > 1])
@@ -32,7 +35,8 @@ def test_both_sides_of_the_line(batch, head_dim):
         outs = []
         for options in ({}, {"prefill_widen_pages": 0})[:2 if head_dim == 128 else 1]:
             print(f"[case] {batch} D={head_dim} mode={mode} {options}", flush=True)
-            out, gk, gv = g.run_batch(mk(), options={"mixed_mode": mode, **options})
+            # (a stated number of resident workgroups keeps so small a batch co-resident)
+            out, gk, gv = g.run_batch(mk(), options={"mixed_mode": mode, "prefill_resident_workgroups": 8, **options})
             assert gk.tobytes() == rk.tobytes() and gv.tobytes() == rv.tobytes()
             # (the bar of the e4m3 caches elsewhere)
             assert np.all(np.isfinite(out)) and float(np.max(np.abs(out - ref))) <= 6e-2
