@@ -141,7 +141,7 @@ struct Plan {
 
 struct PlanOptions {
     int32_t split_pages = 0;    // 0 = auto
-    int32_t wg_slots = 768;     // decode workgroups resident at once (a context asks for those of decode_kernel_lean)
+    int32_t wg_slots = 0;       // decode workgroups resident at once (0 = decode_places_per_cu on every CU; a context asks its GPU)
     int32_t n_cu = 256;         // compute units of the GPU
     int32_t xcds = 8;           // accelerator dies; workgroup i is dispatched to die i % xcds
     int32_t mixed_mode = TS_MIXED_CORESIDENT;   // how a batch with decode rows and prefill chunks is launched
@@ -166,6 +166,10 @@ struct PlanOptions {
 bool desc_uses_mfma(const ts_attn_desc& d);
 bool desc_uses_mfma_decode(const ts_attn_desc& d);
 bool desc_uses_mfma_tiles(const ts_attn_desc& d);      // (head dim 64: bf16 pages only, one launch per class)
+// Workgroups of the decode kernels with two tiles in flight that a CU holds: those of decode_kernel_lean (128 registers), of
+// forms with at most 73 registers with head dim 64 (decode_kernel_alone of a bf16 cache has 75 and one workgroup less; the line
+// up to which rows stay whole lies at seven all the same, see rows_stay_whole).
+constexpr int32_t decode_places_per_cu(int head_dim) { return head_dim == 64 ? 7 : 4; }
 int32_t prefill_tile_tokens(const ts_attn_desc& d);
 
 // Upper bound of the partial results that the cut generic row tiles of such a batch take.

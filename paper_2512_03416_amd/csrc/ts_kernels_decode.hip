@@ -43,7 +43,8 @@ template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean(AttnArgs a)
 {
     __shared__ DecMerge<kDecWaves, D, 8> mg;               // (what resident prefill workgroups leave of a CU's LDS: 32 KB)
-    decode_item<KT, 2, kDecWaves, D, false, false, false, D == 128>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
+    static_assert(D == 128, "");
+    decode_item<KT, 2, kDecWaves, D, false, false, false, true>(a, load_dec_item(a.dec + blockIdx.x / a.geo.Hkv), blockIdx.x % a.geo.Hkv, mg);
 }
 template <typename KT, int D>
 __global__ __launch_bounds__(64 * kDecWaves) __attribute__((amdgpu_num_vgpr(64))) void decode_kernel_lean_merging(AttnArgs a)
@@ -125,9 +126,11 @@ static int launch_decode_t(const AttnArgs& a, hipStream_t st, hipEvent_t done)
     case 3: return launch_kernel(decode_kernel<KT, 3, D>, grid, block, st, done, a);
     case 4: return launch_kernel(decode_kernel<KT, 4, D>, grid, block, st, done, a);
     default:
-        if (a.dec_wg || a.cmb_ctr || (a.n_queue > 0 && D == 128 && a.geo.G > 8)) return launch_kernel(decode_kernel_lean_merging<KT, D>, grid, block, st, done, a);
-        if (a.n_queue == 0) return launch_kernel(decode_kernel_alone<KT, D>, grid, block, st, done, a);   // (queues: the tiles of a co-resident launch)
-        return launch_kernel(decode_kernel_lean<KT, D>, grid, block, st, done, a);
+        if (a.dec_wg || a.cmb_ctr || (a.n_queue > 0 && a.geo.G > 8)) return launch_kernel(decode_kernel_lean_merging<KT, D>, grid, block, st, done, a);
+        if constexpr (D == 128) {
+            if (a.n_queue > 0) return launch_kernel(decode_kernel_lean<KT, D>, grid, block, st, done, a);   // (queues: the tiles of a co-resident launch)
+        }
+        return launch_kernel(decode_kernel_alone<KT, D>, grid, block, st, done, a);
     }
 }
 
@@ -139,7 +142,10 @@ static int resident_t(int nbuf)
     switch (nbuf) {
     case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<KT, 3, D>, 64 * kDecWaves, 0); break;
     case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel<KT, 4, D>, 64 * kDecWaves, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel_lean<KT, D>, 64 * kDecWaves, 0); break;
+    default:
+        if constexpr (D == 64) return decode_places_per_cu(D);     // (no resident prefill workgroups, so no decode_kernel_lean)
+        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_kernel_lean<KT, D>, 64 * kDecWaves, 0);
+        break;
     }
     return e == hipSuccess ? per_cu : 0;
 }

@@ -578,8 +578,10 @@ void Plan::clear()
 }
 
 void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx_lens, int num_seqs,
-                const PlanOptions& opt, Plan* plan)
+                const PlanOptions& options, Plan* plan)
 {
+    PlanOptions opt = options;
+    if (opt.wg_slots <= 0) opt.wg_slots = decode_places_per_cu(d.head_dim) * std::max(1, opt.n_cu);
     Plan& p = *plan;
     p.clear();
     const bool mfma = desc_uses_mfma(d) && !opt.generic_only;

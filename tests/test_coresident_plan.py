@@ -84,3 +84,16 @@ def test_the_described_plan_is_the_launched_one(tmp_path):
                     os.path.join(B.CSRC, "ts_planner.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("head_dim,rows", [(128, 128), (64, 224)])
+def test_the_default_places_are_those_of_the_kernels(head_dim, rows):
+    """Rows stay whole up to as many workgroups as the GPU holds at once: four on a CU, seven with head dim 64."""
+    d = ts.Desc.make(32, 8, head_dim, "bf16", "bf16", 1 << 16, 1 << 10)
+    places = (4 if head_dim == 128 else 7) * 256
+    for n in (rows - 1, rows, rows + 1):
+        for ctx in ([1600] * n, [1600] * (n - 1) + [16000]):
+            info = ts.plan_describe(d, [1] * n, ctx)
+            stated = binding.plan_export(d, [1] * n, ctx, "decode", 0, places)
+            assert (binding.plan_export(d, [1] * n, ctx, "decode") == stated).all() and info.n_decode_items == len(stated)
+            assert n > rows or ctx[-1] > 1600 or len(stated) == n
