@@ -139,6 +139,12 @@ constexpr double kPfFlopPerUs = 1.25e9;
 constexpr double kPfShare0 = 0.46, kPfShare1 = 0.16;
 constexpr double kStageUs = 1.5;                           // a tile's 64 keys
 constexpr double kPfAllRatio = 0.8, kPfAllUs = 150.0, kPfAllRatioShort = 1.4;
+// With more than eight query heads per KV head the scan takes its pages one by one (decode_kernel_lean_merging) and costs the tiles
+// more where they share a CU: all CUs from kPfAllRatioWide on; below, over bf16 caches, the share grows faster with r.  Scans of kPfAllUs
+// and more next to one chunk, 128 rows of 1024-8192 tokens, us a pass: 128/8 heads, 2048 over 2048 (r = 0.83) 602-610 with 256 workgroups,
+// 597 with 192 and 633 with 160, 3072 over 1000 (1.02) 645, 688 and 737; 96/8 heads, 2500 over 2000 (0.80) 619, 581 and 620; e4m3, 128/8
+// heads, 1500 over 1500 (0.89) 443, 399 and 404, 390 with 128; e4m3, 256 rows next to 2500 over 1500 (0.91) 734, 723 and 723.
+constexpr double kPfAllRatioWide = 1.0, kPfShare0Wide = 0.25, kPfShare1Wide = 0.6;
 // A mixed batch is launched class by class when either class is estimated below this many microseconds: running
 // side by side hides about 40 % of the shorter class, and the fork and join of the co-resident launch cost
 // 10-15 us.  Measured: 128 decode rows (395 us) next to a chunk of 128 / 896 tokens without prefix (estimates
@@ -153,7 +159,9 @@ constexpr int64_t kMinSplitPages = 32;
 // than one and a half times the slots of the whole GPU), items of at most kCoItemPages pages let the dispatch even it out: 64
 // rows of 2000-16 000 tokens next to 16 chunks of 300-1024 499 -> 470 us, 16 rows of 8000-64 000 (e4m3) next to 8 chunks
 // of 100-300 386 -> 331, 3072 tokens over 2048 next to 128 rows of 1024-8192 514 -> 468; with more rows the partial results
-// cost more than it gains (256 rows of 1024-8192 tokens, e4m3, 474 -> 517; 512 of 512-4096 786 -> 818).  With a prefill
+// cost more than it gains (256 rows of 1024-8192 tokens, e4m3, 474 -> 517; 512 of 512-4096 786 -> 818), and so they do for groups of
+// more than eight heads over a bf16 cache (128 rows of 1024-8192, 128/8 heads, next to 1024 over 2048 471 -> 494, next to 512 over
+// 4096 452 -> 478; 96/8 heads, 1500 over 2000, 478 -> 503; e4m3, 1500 over 1500, 442 -> 407).  With a prefill
 // workgroup on every CU rows of up to kWholePages pages stay whole if their scan, kCoPageUs a page next to tiles, ends within the
 // tiles' time: 20 rows of 3000 tokens (188 pages, 53 us) next to 2000 over 1500 (tiles 82 us) 131.0 us a pass, in pieces of 72-160 pages
 // 138; 24 e4m3 rows of 3000 next to 1024 over 1500 (54 us) 98 and 101; 24 rows of 300-3000 next to 2024 over 1000 (67 us) 109.6 and 111;
@@ -163,7 +171,8 @@ constexpr int64_t kCoItemPages = 160, kWholePages = 192;
 constexpr double kCoPageUs = 0.28;
 
 static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tiles, int64_t decode_pages, int Hkv,
-                                int32_t wg_slots, int32_t n_cu, bool filled_by_prefill, int32_t pf_wgs, double t_pf)
+                                int32_t wg_slots, int32_t n_cu, bool filled_by_prefill, int32_t pf_wgs, double t_pf,
+                                bool wide_bf16)
 {
     // (next to a resident prefill workgroup a CU has room for one decode workgroup; the CUs without one hold
     // their usual share of the stand-alone slots)
@@ -172,7 +181,7 @@ static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tile
         slots = pf_wgs + (int64_t)(n_cu - pf_wgs) * std::max(1, wg_slots / n_cu);
     int64_t L = std::max<int64_t>(kMinSplitPages, (decode_tiles + slots - 1) / slots);
     if (pf_wgs >= n_cu) L = std::max(L, std::min(kWholePages, (int64_t)(t_pf / kCoPageUs)));
-    else if (pf_wgs > 0 && 2 * p.info.decode_tokens * Hkv < 3 * wg_slots) L = std::min(L, kCoItemPages);
+    else if (pf_wgs > 0 && !wide_bf16 && 2 * p.info.decode_tokens * Hkv < 3 * wg_slots) L = std::min(L, kCoItemPages);
     if (!filled_by_prefill && p.info.decode_tokens * Hkv <= n_cu && decode_pages > 0) {
         const int64_t want_items = std::max<int64_t>(1, n_cu / Hkv);   // per KV head
         int64_t fit = std::max<int64_t>(kMinSplitPages, (decode_pages + want_items - 1) / want_items);
@@ -675,8 +684,10 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
             pf_wgs = std::min(all, opt.pf_resident_wgs);
         } else {
             const double r = t_dec > 0 ? t_pf / t_dec : 1e9;
-            const bool every = r >= (t_dec >= kPfAllUs ? kPfAllRatio : kPfAllRatioShort);
-            pf_wgs = every ? all : (int32_t)std::ceil((kPfShare0 + kPfShare1 * r) * all);
+            const bool wide = d.num_q_heads > 8 * d.num_kv_heads;
+            const bool every = r >= (t_dec < kPfAllUs ? kPfAllRatioShort : wide ? kPfAllRatioWide : kPfAllRatio);
+            const bool steep = wide && t_dec >= kPfAllUs && d.kv_dtype == TS_BF16;
+            pf_wgs = every ? all : (int32_t)std::ceil((steep ? kPfShare0Wide + kPfShare1Wide * r : kPfShare0 + kPfShare1 * r) * all);
             // (not a few tiles more than whole rounds: 55 tiles per die on 19 workgroups 485 us, on 18 509)
             const int64_t per_die = (tile_heads + x - 1) / x, n = (pf_wgs + x - 1) / x, rounds = per_die / n;
             if (rounds > 0 && per_die % n > 0 && per_die % n <= n / 8) pf_wgs = (int32_t)((per_die + rounds - 1) / rounds * x);
@@ -687,7 +698,8 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     const int32_t L = opt.split_pages > 0
                           ? opt.split_pages
                           : auto_split_pages(p, num_seqs, decode_tiles, decode_pages, Hkv, opt.wg_slots,
-                                             std::max(1, opt.n_cu), filled_by_prefill, pf_wgs, t_pf);
+                                             std::max(1, opt.n_cu), filled_by_prefill, pf_wgs, t_pf,
+                                             d.num_q_heads > 8 * d.num_kv_heads && d.kv_dtype == TS_BF16);
     // (rows up to this many pages stay whole: see 4. above)
     const bool many = mixed_mode == TS_MIXED_SEPARATE && p.info.decode_tokens * Hkv > opt.wg_slots;
     const int32_t keep_whole = opt.split_pages > 0 || !many ? L : L + L / 4;

@@ -22,6 +22,25 @@ def test_rows_stay_whole_only_if_their_scan_ends_with_the_tiles(batch, tiles_us,
     assert max(int(i[4] - i[3]) for i in items) * 0.28 <= tiles_us
 
 
+# 128 rows of 1024-8192 tokens next to a chunk: (query heads of 8 KV heads, cache, chunk, prefix), resident workgroups (with the plan of
+# groups of up to eight heads: 256 for all but the second), items of at most 160 pages
+WIDE_GROUPS = [((128, "bf16", 2048, 2048), range(176, 209), False), ((128, "bf16", 1024, 2048), range(96, 161), False),
+               ((96, "bf16", 2500, 2000), range(176, 209), False), ((128, "fp8", 1500, 1500), range(120, 201), True),
+               ((128, "bf16", 3072, 1000), range(256, 257), False)]
+
+
+@pytest.mark.parametrize("batch,workgroups,cut", WIDE_GROUPS, ids=lambda x: str(x))
+def test_groups_of_more_than_eight_heads_are_sized_by_their_own_measurements(batch, workgroups, cut):
+    """Such a scan runs page by page and takes more from the tiles: not all CUs from 0.8 of its time on, and over a bf16 cache
+    no cuts at 160 pages."""
+    import numpy as np
+    heads, kv, chunk, prefix = batch
+    rows = np.random.default_rng(1).integers(1024, 8193, 128).tolist()
+    d = ts.Desc.make(heads, 8, 128, "bf16", kv, 1 << 17, 1 << 10)
+    info = ts.plan_describe(d, [1] * 128 + [chunk], rows + [prefix + chunk])
+    assert info.mixed_mode == 2 and info.prefill_workgroups in workgroups and (info.split_pages <= 160) == cut
+
+
 HARNESS = r"""
 #include <cstdio>
 #include <cstring>
