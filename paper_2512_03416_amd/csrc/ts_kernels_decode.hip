@@ -24,8 +24,12 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a)
     if (split && a.cmb_ctr) arrive_and_merge<D, 64 * kDecWaves, false>(a, a.dec + first, end - first, a.cmb, g);
 }
 
+// (the image of eight heads, 17 KB, as in the forms below: by option this kernel runs next to resident prefill workgroups too,
+// and with an e4m3 cache and three tiles it fits there, where the image of sixteen, 34 KB, made the scan wait for the tiles:
+// 128 rows of 1024-8192 tokens next to 4 chunks of 2048, 64/8 heads, 1095 -> 902 us a pass.  Alone the second turn of groups of more than eight
+// heads costs nothing: 20 rows of 500-8000 tokens with 128/8 heads 60.6 us either way)
 template <typename KT, int NBUF, int D>
-__global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { decode_workgroup<KT, NBUF, D, true>(a); }
+__global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { decode_workgroup<KT, NBUF, D, true, 8>(a); }
 
 // The default forms, two KV tiles in flight per wave, held to 128 vector registers per lane (the attribute
 // counts in units of two here): one such workgroup then fits on a CU next to a resident prefill workgroup
