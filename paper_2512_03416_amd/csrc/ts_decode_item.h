@@ -148,7 +148,7 @@ template <typename KT> __device__ __forceinline__ int q_dim0(int b, int r)
 
 // One workgroup of kDecWaves waves per item = (decode row, KV head, page range).  Wave w streams the
 // pages begin+w, begin+w+kDecWaves, ... so the waves read neighbouring tiles at the same time; at
-// the end their (max, sum, O) states meet in LDS and wave 0 merges them in wave order.  A row that
+// the end their (max, sum, O) states meet in LDS and all threads add them up, in wave order.  A row that
 // fits one item is finished here (no partial ever goes to HBM: stores into the middle of a saturated
 // read stream were measured to cost ~10x their byte share); only rows longer than one workgroup's
 // fair share are cut into several items whose partials go through combine_kernel.
@@ -157,8 +157,7 @@ constexpr int kDecWaves = 4;               // stand-alone decode kernel; the mix
 // LDS image of the waves' states: the group's heads (at most HEADS) only, four dims of a head per entry, a row of which is
 // one entry longer than the head so that the heads lie in different banks.  All threads of the workgroup add up an
 // entry each.  (One wave adding up whole accumulators, unused columns included, while the others had nothing to do, was a
-// serial end to every item: eight rows of 500-2500 tokens 15.3 -> 14.8 us a
-// pass, three e4m3 rows of 30-131 Ki 92.0 -> 90.8.)
+// serial end to every item: eight rows of 500-2500 tokens 15.3 -> 14.8 us a pass, three e4m3 rows of 30-131 Ki 92.0 -> 90.8.)
 template <int WAVES, int D = 128, int HEADS = 16>
 struct DecMerge {
     static constexpr int kHeads = HEADS;
@@ -310,7 +309,8 @@ __device__ __forceinline__ uint32_t swap_halves16(uint32_t x)  // lanes n and n 
 // head (column n is head n % 8), so of the two pages' scores the lanes of columns 0-7 take the first page's and those of
 // columns 8-15 the second's: one round of softmax arithmetic serves both pages.  The packed weights then trade places
 // between the two halves, every column has both pages', and one 16x16x32 MFMA per 16 dims takes the 32 tokens.  Against
-// a page at a time this is about 14 vector instructions per page for 26 and 8 MFMAs for 12 (bf16).  The scan alone
+// a page at a time the compiled loop has 17.5 vector instructions per page for 26 and 8 MFMAs for 12 (bf16; e4m3, where 32 of them
+// are conversions, 49.5 for 56).  The scan alone
 // does not notice (it waits for memory); next to prefill tiles, which leave it little of the SIMDs, it counts.
 // A wave's last page (the only one that can be partly filled) goes through the masked single step.
 template <typename KT, int D>
@@ -422,9 +422,11 @@ __device__ __forceinline__ void decode_pairs(const AttnArgs& a, const bf16x8 (&q
     l += __uint_as_float(swap_halves16(__float_as_uint(l)));
 }
 
-// One decode item for KV head g, executed by a workgroup of WAVES waves.  All waves must call
-// it; it contains one workgroup barrier, and another one must come before mg is reused: the caller's, or (mg_busy)
-// one in here just before mg is written, so that the waves that have nothing to merge start on the next item.
+// One decode item for KV head g, executed by a workgroup of WAVES waves.  All waves must call it and all merge.  It contains
+// one workgroup barrier per turn of HEADS heads, between the waves' writes of mg and everybody's reads, and one between two turns
+// (HEADS < 16 and G > HEADS: two turns, three barriers; G is the same for all).  Nothing follows the last reads, so a barrier must come before
+// mg is written again: the caller's, or (mg_busy) one in here just before the first write, so that a wave that has merged its
+// share starts on the next item's pages.
 // EXACT: prefetches past the end read nothing (load_tile_if).
 // THROUGH: partial results of split rows are stored for arrive_and_merge.
 // FUSED: the row's new token comes from a.k_new / a.v_new and is written into the cache here (see AttnArgs).
@@ -436,7 +438,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const DecItem it,
     const int it_row = it.row, it_seq = it.seq, it_keys = it.n_keys, it_pb = it.page_begin, it_pe = it.page_end, it_part = it.part;
     // (readfirstlane tells the compiler the wave index is uniform, which keeps everything derived
     // from it -- the page-id loads above all -- on the scalar unit)
-    // (an opaque copy where the caller loops over items: the lane offsets are worked out per item instead of being
+    // (an opaque copy: where the caller loops over items the lane offsets are worked out per item instead of being
     // kept across the loop)
     const int tid = opaque((int)threadIdx.x);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

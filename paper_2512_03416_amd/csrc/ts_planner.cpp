@@ -118,7 +118,7 @@ int validate_batch(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* 
 //      against 390 cut at the fair share itself; with a heavy tail, 600-25 700 tokens and e4m3: 290, at 3/2: 298,
 //      uncut: 382).
 // In a mixed batch launched with resident workgroups (co-resident launch or one persistent kernel: a CU that
-// holds a resident workgroup has room for one decode workgroup, a third of the stand-alone slots), 3 does not
+// holds a resident workgroup has room for one decode workgroup, a quarter of the stand-alone slots), 3 does not
 // apply and the fair share is that of the slots actually there: measured on the burst configuration,
 // 706 -> 692 us and no combine launch.
 // Rates the two kinds of work reach on their own (decode scan: bytes per microsecond; prefill tiles: flop per
@@ -478,10 +478,9 @@ static bool widening_pays(const Plan& p, int64_t pages, int Hkv)
 {
     if (pages * Hkv < kWidenFewPages) return true;
     int64_t keys = 0;                                      // that tiles read, per KV head
-    for (const PfItem& t : p.pf) keys += std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
+    for (const PfItem& t : p.pf) keys += pf_keys(t);
     return keys > kWidenReads * kPage * pages;
 }
-
 
 static void map_prefill_to_xcds(Plan& p, int Hkv, int xcds, int mixed_mode, bool for_launch, int64_t kv_row_bytes,
                                 int32_t n_cu)
@@ -672,7 +671,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     if (!mfma_dec) { decode_tiles = 0; decode_pages = 0; }
     p.info.mixed_mode = mixed_mode;
     // Co-resident launch: how many CUs get a resident prefill workgroup.  Such a CU has room for one decode
-    // workgroup instead of three, so a batch whose decode scan outlasts its tiles (one restricted chunk next to a
+    // workgroup instead of four, so a batch whose decode scan outlasts its tiles (one restricted chunk next to a
     // large decode batch, Sec. 4.4) keeps part of the CUs for decode rows alone: the tiles get a share of the CUs
     // that grows with the ratio of the two times (estimated from the batch's flops and bytes at the rates the
     // kernels reach alone), in multiples of the number of dies.
@@ -799,12 +798,9 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     else if (!even) sort_decode_items(p.dec);
     {
         // (the merge list refers to the tiles by position: sort a permutation and carry the references along)
-        auto keys_of = [](const PfItem& t) {
-            return std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
-        };
         std::vector<int32_t> order(p.pf.size()), where(p.pf.size());
         for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
-        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return keys_of(p.pf[a]) > keys_of(p.pf[b]); });
+        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return pf_keys(p.pf[a]) > pf_keys(p.pf[b]); });
         std::vector<PfItem> sorted(p.pf.size());
         for (size_t i = 0; i < order.size(); ++i) { sorted[i] = p.pf[order[i]]; where[order[i]] = (int32_t)i; }
         p.pf.swap(sorted);
