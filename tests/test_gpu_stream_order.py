@@ -89,3 +89,50 @@ def test_a_pass_on_another_stream_follows_both_ends_of_a_co_resident_one(kv):
         torch.cuda.synchronize()
         assert torch.equal(seen, alone[0].cpu())
     ctx.close()
+
+
+@pytest.mark.parametrize("other", [False, True], ids=["same stream", "other stream"])
+@pytest.mark.parametrize("form", ["fused", "one launch per class", "co-resident", "co-resident, copied pages", "fp32"])
+def test_captured_passes_between_eager_ones(form, other):
+    """Events ride on the kernels of eager passes and are recorded in captured ones: a pass captured behind eager ones of the
+    same context, on their stream or another, and replayed with eager passes in between, gives the same bytes each time."""
+    import gpu_harness as g
+    import paper_2512_03416_amd as ts
+    q, c, kv, dtype, options = {"fused": ([1, 1], [500, 900], "bf16", "bf16", {}),
+                                "one launch per class": ([1, 1, 40], [500, 900, 70], "bf16", "bf16", {}),
+                                "co-resident": ([1] * 40 + [40], [2000] * 40 + [70], "bf16", "bf16", {"prefill_resident_workgroups": 8}),
+                                "co-resident, copied pages": ([1] * 40 + [40], [2000] * 40 + [70], "fp8", "bf16", {"prefill_resident_workgroups": 8}),
+                                "fp32": ([1] * 4 + [40], [200] * 4 + [70], "f32", "f32", {})}[form]
+    b = make_batch(AttnShape(16, 4, 128, dtype, kv), q, c, seed=3, pool_rule=1.2, value_mult=0.5)
+    ref = oracle.run_batch(W.to_cpu(b))[0]
+    b = g.to_dev(b)
+    print(f"[case] captured: {form}, other stream {other}", flush=True)
+    ctx = ts.Context(g.make_desc(b))
+    for name, value in options.items():
+        ctx.set_option(name, value)
+    ctx.reserve(b.total_q, b.num_seqs, sum(-(-n // 16) for n in c))
+    kc, vc = g.new_caches(b)
+    bt = torch.from_numpy(b.block_table).cuda()
+    ctx.kv_append(b.k_prefix, b.v_prefix, kc, vc, b.k_scale, b.v_scale, bt, b.prefix_lens, b.prefix_lens)
+    out = torch.zeros_like(b.q)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def call(stream):
+        ctx.mixed_paged_attention(b.q, b.k_new, b.v_new, kc, vc, b.k_scale, b.v_scale, bt, b.q_lens, b.ctx_lens, b.sm_scale, out, stream=stream)
+    for _ in range(2):
+        call(s1)
+        torch.cuda.synchronize()
+    want = out.clone()
+    assert worst_of_rms(want.double().cpu().numpy(), ref) <= OF_RMS
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s2 if other else s1, capture_error_mode="relaxed"):
+        call(s2 if other else s1)
+    for _ in range(3):
+        for again in (graph.replay, lambda: call(s1)):
+            out.zero_()
+            torch.cuda.synchronize()
+            again()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+    ctx.close()
