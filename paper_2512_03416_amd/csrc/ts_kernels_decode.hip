@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(AttnArgs a) { de
 // already keeps enough loads in flight for the bf16 scan to run at its full rate.
 // decode_kernel_lean: one item per workgroup, no merge in the kernel -- next to resident prefill workgroups the
 // shorter code is worth 1.5 % of the pair (the burst configuration: 633 us a pass against 643).  Head dim 128 (up to eight heads
-// per KV head): two pages at a time, a third less vector instructions (bf16; see decode_pairs).  What bounds it there is not memory but what the tiles leave it
+// per KV head): two pages at a time, fewer vector and matrix instructions (see decode_pairs).  What bounds it there is not memory but what the tiles leave it
 // of the SIMDs: a 4096-token chunk over 4096 next to 128 rows, a prefill workgroup on every CU, 570 -> 500 us a pass (and
 // with that more of the CUs can hold one); 256 rows of 256-1500 tokens next to 2048 tokens 218 -> 210; where the tiles
 // outlast the scan it changes nothing (the burst configuration, 64 Ki prompt tokens next to 512 rows).  Groups of more heads run
