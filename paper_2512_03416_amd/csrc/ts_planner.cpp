@@ -129,16 +129,18 @@ constexpr double kPfFlopPerUs = 1.25e9;
 // All of them where the tiles would take about as long as the scan or longer (r >= kPfAllRatio; passes with a scan of less
 // than kPfAllUs: r >= kPfAllRatioShort): a CU without one takes four decode workgroups, each of them then four times as slow as
 // the ones that share a CU with tiles, and the longest rows end late there (248 workgroups instead of 256: 568 us for 510
-// in the first example below).  Else the share kPfShare0 + kPfShare1 * r.  Measured over 33 mixed batches, every
-// multiple of 16 workgroups: with too few the tiles end late (the time rises steeply), with a few too many the scan does.
-// A 4096-token chunk over 4096 next to 128 rows of 1024-8192 (r = 0.83): 508 us with 256, 576 with 192; 4 chunks of 2048 next
-// to 128 (r = 0.97): 585 and 640; r > 1.7 always 256.  Over 21 batches with r = 0.07 ... 0.95 the share is within 1.7 % of
-// the best number on average (5.6 % at most; 64 rows of 500-4000 tokens next to 8 chunks of 300-512, r = 0.52: 151 us with
-// 128, 156 with 136, 200 with 256; 2048 tokens next to 32 rows, r = 0.73: 130 with 144, 184 with 256; 3500 over 3000 next to
-// 128, r = 0.55: 526 with 128, 485 with 160, 545 with 256).
-constexpr double kPfShare0 = 0.46, kPfShare1 = 0.16;
+// in the first example below).  Else the share kPfShare0 + kPfShare1 * r; beside a bf16 scan of kPfAllUs or more
+// at least kPfSteep0 + kPfSteep1 * r, which is the larger from r = 0.45 on.  Measured over 60 mixed batches, every multiple of 16
+// workgroups: with too few the tiles end late (the time rises steeply), with a few too many the scan does.
+// 128 rows of 1024-8192 tokens next to 4096 over 4096 (r = 0.83): 508 us with 256, 576 with 192; 4 chunks of 2048 (r = 0.97): 585 and
+// 640; r > 1.7 always 256.  Over 49 of them with r = 0.07 ... 0.96 this is within 1.4 % of the best number on average (6.7 % at
+// most).  With the flat share alone bf16 batches between r = 0.5 and 0.8 get too few: next to 3968 over 4096 (r = 0.79) 629 us a
+// pass with 152 workgroups, 533 with 256; 3968 over 3000 (0.65) 557 with 144, 522 with 192; 4600 over 2000 (0.65) 549 and 513; 8 chunks of
+// 700-1100 (0.59) 560 with 144, 533 with 176.  Next to an e4m3 scan, which takes more of the SIMDs per byte, it is enough: 256 rows, 3600 over
+// 3600 (0.65) 621 with 144, 630 with 192.
+constexpr double kPfShare0 = 0.46, kPfShare1 = 0.16, kPfSteep0 = 0.1, kPfSteep1 = 0.96;
 constexpr double kStageUs = 1.5;                           // a tile's 64 keys
-constexpr double kPfAllRatio = 0.8, kPfAllUs = 150.0, kPfAllRatioShort = 1.4;
+constexpr double kPfAllRatio = 0.75, kPfAllUs = 150.0, kPfAllRatioShort = 1.4;
 // With more than eight query heads per KV head the scan takes its pages one by one (decode_kernel_lean_merging) and costs the tiles
 // more where they share a CU: all CUs from kPfAllRatioWide on; below, over bf16 caches, the share grows faster with r.  Scans of kPfAllUs
 // and more next to one chunk, 128 rows of 1024-8192 tokens, us a pass: 128/8 heads, 2048 over 2048 (r = 0.83) 602-610 with 256 workgroups,
@@ -685,8 +687,10 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
             const double r = t_dec > 0 ? t_pf / t_dec : 1e9;
             const bool wide = d.num_q_heads > 8 * d.num_kv_heads;
             const bool every = r >= (t_dec < kPfAllUs ? kPfAllRatioShort : wide ? kPfAllRatioWide : kPfAllRatio);
-            const bool steep = wide && t_dec >= kPfAllUs && d.kv_dtype == TS_BF16;
-            pf_wgs = every ? all : (int32_t)std::ceil((steep ? kPfShare0Wide + kPfShare1Wide * r : kPfShare0 + kPfShare1 * r) * all);
+            double share = kPfShare0 + kPfShare1 * r;
+            if (t_dec >= kPfAllUs && d.kv_dtype == TS_BF16)
+                share = wide ? kPfShare0Wide + kPfShare1Wide * r : std::max(share, kPfSteep0 + kPfSteep1 * r);
+            pf_wgs = every ? all : (int32_t)std::ceil(share * all);
             // (not a few tiles more than whole rounds: 55 tiles per die on 19 workgroups 485 us, on 18 509)
             const int64_t per_die = (tile_heads + x - 1) / x, n = (pf_wgs + x - 1) / x, rounds = per_die / n;
             if (rounds > 0 && per_die % n > 0 && per_die % n <= n / 8) pf_wgs = (int32_t)((per_die + rounds - 1) / rounds * x);

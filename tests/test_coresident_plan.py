@@ -22,6 +22,22 @@ def test_rows_stay_whole_only_if_their_scan_ends_with_the_tiles(batch, tiles_us,
     assert max(int(i[4] - i[3]) for i in items) * 0.28 <= tiles_us
 
 
+# (cache, decode rows of 1024-8192 tokens, chunk, prefix) with 32/8 heads, resident workgroups: tiles of 0.5-0.8 of the scan's time
+BETWEEN = [(("bf16", 128, 3968, 4096), range(256, 257)), (("bf16", 128, 3968, 3000), range(176, 209)), (("bf16", 128, 4600, 2000), range(176, 217)),
+           (("bf16", 128, 3200, 4096), range(160, 217)), (("bf16", 128, 2400, 4096), range(120, 161)), (("fp8", 256, 3600, 3600), range(128, 169))]
+
+
+@pytest.mark.parametrize("batch,workgroups", BETWEEN, ids=lambda x: str(x))
+def test_tiles_of_more_than_half_the_scan_get_a_share_that_grows_with_them(batch, workgroups):
+    """With the flat share they end late: 3968 tokens over 4096 615-629 us a pass with 152 workgroups, 533-548 with 224 or 256."""
+    import numpy as np
+    kv, rows, chunk, prefix = batch
+    d = ts.Desc.make(32, 8, 128, "bf16", kv, 1 << 17, 1 << 10)
+    ctx = np.random.default_rng(1).integers(1024, 8193, rows).tolist()
+    info = ts.plan_describe(d, [1] * rows + [chunk], ctx + [prefix + chunk])
+    assert info.mixed_mode == 2 and info.prefill_workgroups in workgroups, info.prefill_workgroups
+
+
 # 128 rows of 1024-8192 tokens next to a chunk: (query heads of 8 KV heads, cache, chunk, prefix), resident workgroups (with the plan of
 # groups of up to eight heads: 256 for all but the second), items of at most 160 pages
 WIDE_GROUPS = [((128, "bf16", 2048, 2048), range(176, 209), False), ((128, "bf16", 1024, 2048), range(96, 161), False),
