@@ -127,7 +127,7 @@ constexpr double kDecBytePerUs = 6.2e6;
 constexpr double kPfFlopPerUs = 1.25e9;
 // Co-resident launch: the CUs that get a resident prefill workgroup, from the ratio r of the two times (prefill to decode).
 // All of them where the tiles would take about as long as the scan or longer (r >= kPfAllRatio; passes with a scan of less
-// than kPfAllUs: r >= kPfAllRatioShort): a CU without one takes four decode workgroups, each of them then four times as slow as
+// than kPfAllUs: r >= kPfAllRatioShort, over an e4m3 cache kPfAllRatioShort8): a CU without one takes four decode workgroups, each of them then four times as slow as
 // the ones that share a CU with tiles, and the longest rows end late there (248 workgroups instead of 256: 568 us for 510
 // in the first example below).  Else the share kPfShare0 + kPfShare1 * r; beside a bf16 scan of kPfAllUs or more
 // at least kPfSteep0 + kPfSteep1 * r, which is the larger from r = 0.45 on.  Measured over 60 mixed batches, every multiple of 16
@@ -138,9 +138,14 @@ constexpr double kPfFlopPerUs = 1.25e9;
 // pass with 152 workgroups, 533 with 256; 3968 over 3000 (0.65) 557 with 144, 522 with 192; 4600 over 2000 (0.65) 549 and 513; 8 chunks of
 // 700-1100 (0.59) 560 with 144, 533 with 176.  Next to an e4m3 scan, which takes more of the SIMDs per byte, it is enough: 256 rows, 3600 over
 // 3600 (0.65) 621 with 144, 630 with 192.
-constexpr double kPfShare0 = 0.46, kPfShare1 = 0.16, kPfSteep0 = 0.1, kPfSteep1 = 0.96;
+// Short scans over bf16: at least kPfShort0 + kPfShort1 * r (the larger from r = 0.71 on), 16 batches with r = 0.51 ... 1.7, within 0.9 % of
+// the best on average.  The line of the e4m3 ones, 1.4, held for both before: 50 rows of 1500-4800 next to 3300 over 1500 (r = 1.32) 240 us with
+// 176 workgroups, 212 with 256; 40/8 heads, 40 rows next to 2600 over 1000 (1.18) 184 and 166; 24 rows next to 2 chunks of 1100 (64/8 heads,
+// 0.96) 123 with 160, 116 with 192.  e4m3: 60 rows next to 2400 over 1500 (1.32) 171 with 176, 189 with 256; 64/8 heads, 1700 over 1000
+// (1.33) 172 and 182.
+constexpr double kPfShare0 = 0.46, kPfShare1 = 0.16, kPfSteep0 = 0.1, kPfSteep1 = 0.96, kPfShort0 = 0.12, kPfShort1 = 0.64;
 constexpr double kStageUs = 1.5;                           // a tile's 64 keys
-constexpr double kPfAllRatio = 0.75, kPfAllUs = 150.0, kPfAllRatioShort = 1.4;
+constexpr double kPfAllRatio = 0.75, kPfAllUs = 150.0, kPfAllRatioShort = 1.1, kPfAllRatioShort8 = 1.4;
 // With more than eight query heads per KV head the scan takes its pages one by one (decode_kernel_lean_merging) and costs the tiles
 // more where they share a CU: all CUs from kPfAllRatioWide on; below, over bf16 caches, the share grows faster with r.  Scans of kPfAllUs
 // and more next to one chunk, 128 rows of 1024-8192 tokens, us a pass: 128/8 heads, 2048 over 2048 (r = 0.83) 602-610 with 256 workgroups,
@@ -685,11 +690,11 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
             pf_wgs = std::min(all, opt.pf_resident_wgs);
         } else {
             const double r = t_dec > 0 ? t_pf / t_dec : 1e9;
-            const bool wide = d.num_q_heads > 8 * d.num_kv_heads;
-            const bool every = r >= (t_dec < kPfAllUs ? kPfAllRatioShort : wide ? kPfAllRatioWide : kPfAllRatio);
+            const bool wide = d.num_q_heads > 8 * d.num_kv_heads, bf16 = d.kv_dtype == TS_BF16, short_scan = t_dec < kPfAllUs;
+            const bool every = r >= (short_scan ? (bf16 ? kPfAllRatioShort : kPfAllRatioShort8) : wide ? kPfAllRatioWide : kPfAllRatio);
             double share = kPfShare0 + kPfShare1 * r;
-            if (t_dec >= kPfAllUs && d.kv_dtype == TS_BF16)
-                share = wide ? kPfShare0Wide + kPfShare1Wide * r : std::max(share, kPfSteep0 + kPfSteep1 * r);
+            if (bf16 && short_scan) share = std::max(share, kPfShort0 + kPfShort1 * r);
+            else if (bf16) share = wide ? kPfShare0Wide + kPfShare1Wide * r : std::max(share, kPfSteep0 + kPfSteep1 * r);
             pf_wgs = every ? all : (int32_t)std::ceil(share * all);
             // (not a few tiles more than whole rounds: 55 tiles per die on 19 workgroups 485 us, on 18 509)
             const int64_t per_die = (tile_heads + x - 1) / x, n = (pf_wgs + x - 1) / x, rounds = per_die / n;

@@ -38,6 +38,24 @@ def test_tiles_of_more_than_half_the_scan_get_a_share_that_grows_with_them(batch
     assert info.mixed_mode == 2 and info.prefill_workgroups in workgroups, info.prefill_workgroups
 
 
+# (query heads of 8 KV heads, cache, rows, shortest and longest, chunks, chunk, prefix): scans of less than 150 us
+SHORT = [((32, "bf16", 50, 1500, 4800, 1, 3300, 1500), range(256, 257)), ((40, "bf16", 40, 1500, 4800, 1, 2600, 1000), range(256, 257)),
+         ((64, "bf16", 24, 1500, 4800, 2, 1100, 300), range(176, 209)), ((128, "bf16", 30, 2000, 5000, 1, 1200, 800), range(256, 257)),
+         ((32, "fp8", 60, 1500, 5000, 1, 2400, 1500), range(152, 193))]
+
+
+@pytest.mark.parametrize("batch,workgroups", SHORT, ids=lambda x: str(x))
+def test_short_scans_over_bf16_leave_the_tiles_more(batch, workgroups):
+    """50 rows next to 3300 over 1500: 240 us a pass with 176 workgroups, 212 with 256; e4m3, 60 rows next to 2400 over 1500: 171
+    with 176, 189 with 256."""
+    import numpy as np
+    heads, kv, rows, lo, hi, chunks, chunk, prefix = batch
+    d = ts.Desc.make(heads, 8, 128, "bf16", kv, 1 << 17, 1 << 10)
+    ctx = np.random.default_rng(2).integers(lo, hi + 1, rows).tolist()
+    info = ts.plan_describe(d, [1] * rows + [chunk] * chunks, ctx + [prefix + chunk] * chunks)
+    assert info.mixed_mode == 2 and info.prefill_workgroups in workgroups, info.prefill_workgroups
+
+
 # 128 rows of 1024-8192 tokens next to a chunk: (query heads of 8 KV heads, cache, chunk, prefix), resident workgroups (with the plan of
 # groups of up to eight heads: 256 for all but the second), items of at most 160 pages
 WIDE_GROUPS = [((128, "bf16", 2048, 2048), range(176, 209), False), ((128, "bf16", 1024, 2048), range(96, 161), False),
