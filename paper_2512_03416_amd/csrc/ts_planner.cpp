@@ -455,20 +455,55 @@ static int64_t pf_keys(const PfItem& t)
     return std::min(t.prefix + t.tok_begin + t.tok_count, t.kv_end) - t.kv_begin;
 }
 
-// Parts of a tile that is cut along the keys (`below`: keys at or below its first query position that may be cut off).
+// Parts of a tile that is cut along the keys (`below`: keys at or below its first query position that may be cut off): one per
+// shortest range ...
+static int32_t parts_in_ranges(int32_t below, int32_t min_keys, int32_t wanted)
+{
+    return min_keys > 0 ? std::max(1, std::min(wanted, below / min_keys)) : 1;
+}
+// ... or, where half_ranges_pay, four parts of half the shortest range before five or more of it, and nothing below one and a half.
 // Up to four are merged by the last of them, about 5 us on top of a tile whose 64 keys take 1-1.5 us; more by a launch, as
-// much again.  So four parts of half the shortest range come before five or more of it, and a tile with less than one and a
-// half ranges stays whole.  One part per range only, before: 32 tokens over 1000 29.1 -> 24.8 us a pass, 128 over 1500 31.2 ->
-// 27.0, 400 over 1000 (head dim 64) 24.5 -> 21.0, 128 over 2700 (five parts then) 36.2 -> 31.1; from six ranges on the launch:
+// much again.  One part per range and four halves: 32 tokens over 1000 29.1 and 24.8 us a pass, 128 over 1500 31.2 and
+// 27.0, 400 over 1000 (head dim 64) 24.5 and 21.0, 128 over 2700 (five parts) 36.2 and 31.1; from six ranges on the launch:
 // 32 over 4200 32.7 against 35.6 in four parts.  Whole below 768 keys: 32 over 500 in two parts 22.7 against 20.6.
 constexpr int32_t kPfLaunchParts = 6;
 static int32_t parts_of_tile(int32_t below, int32_t min_keys, int32_t wanted)
 {
-    if (min_keys <= 0) return 1;
-    const int32_t longer = below / min_keys;
-    if (longer >= kPfLaunchParts) return std::min(wanted, longer);
+    if (below / min_keys >= kPfLaunchParts) return std::min(wanted, below / min_keys);
     if (2 * (int64_t)below < 3 * (int64_t)min_keys) return 1;
     return std::max(1, std::min({wanted, kPfMergeParts, (int32_t)(2 * (int64_t)below / min_keys)}));
+}
+// Halves do not pay
+//   - where some tile goes into more than four parts: a merge is launched anyway (32/8 heads, e4m3, 3 chunks of 7-30 over 2645-5403
+//     42.0 us with halves, 34.2 in ranges);
+//   - where a die has not a CU for each: in a launch of its own the tiles of a (sequence, head) stream stay on one die, so
+//     with few KV heads some dies fill while others are idle (64/4 heads, chunks of 106 and 339 over 993, 44 pieces on a die, 46.6
+//     and 33.7; 16/2, 900 over 800, 95 pieces, 65.5 and 52.1; 28/4, 3 chunks of 172-300 over 828-2418 39.4 and 34.1; but 8/4,
+//     1164-1645 alone, 30 pieces, 27.8 and 32.9) -- unless ranges would come to a launch (4/2, 1306-2152 over 715-1446, 48.5 and 57.1);
+//   - in two parts over a bf16 cache, where nearly every CU has a tile as it is (3 chunks of 294-327 over 885-1026 34.0 and 32.0,
+//     430-856 over 705-823 33.3 and 32.2; e4m3 gains: 3 of 767-1187, 8/8 heads, 31.3 and 35.4).
+// (parts_of_tile grows with the keys: a sequence's last tile has the most parts)
+static bool half_ranges_pay(const Plan& p, int num_seqs, int32_t TT, int Hkv, int32_t kv_dtype, const PlanOptions& opt, int32_t min_keys,
+                            int32_t wanted, bool pinned)
+{
+    if (wanted < 3 && kv_dtype != TS_FP8_E4M3) return false;
+    const int64_t xcds = std::max(1, opt.xcds);
+    int64_t chunks = 0, pieces = 0;                        // pieces of the stream that has most
+    int32_t most = 1, ranges = 1;
+    for (int s = 0; s < num_seqs; ++s) {
+        const SeqMeta& m = p.seqs[s];
+        if (m.q_len <= 1) continue;
+        const int32_t last = (m.prefix + (m.q_len - 1) / TT * TT) / 64 * 64;
+        chunks += 1;
+        most = std::max(most, parts_of_tile(last, min_keys, wanted));
+        ranges = std::max(ranges, parts_in_ranges(last, min_keys, wanted));
+        if (!pinned || Hkv % xcds == 0) continue;          // (as many KV heads as dies: `wanted` parts a tile have a CU each)
+        int64_t n = 0;
+        for (int32_t t0 = 0; t0 < m.q_len; t0 += TT) n += parts_of_tile((m.prefix + t0) / 64 * 64, min_keys, wanted);
+        pieces = std::max(pieces, n);
+    }
+    if (most > kPfMergeParts) return false;
+    return ranges > kPfMergeParts || (chunks * Hkv + xcds - 1) / xcds * pieces <= opt.n_cu / xcds;
 }
 
 // Do the tiles over an e4m3 cache gain by bf16 copies of their pages, or do they convert while they stage?  The copies cost a
@@ -724,6 +759,8 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     // whole, 428 in two parts)
     const bool parts_pay = mixed_mode != TS_MIXED_CORESIDENT || kStageUs * longest / 64 > t_dec;
     const int64_t pf_parts_wanted = tile_heads > 0 && parts_pay ? std::min<int64_t>(16, (pf_wgs > 0 ? pf_wgs : opt.n_cu) / tile_heads) : 1;
+    const int32_t min_keys = pf_parts_wanted > 1 ? opt.pf_split_min_keys : 0, most_parts = (int32_t)pf_parts_wanted;
+    const bool halves = min_keys > 0 && half_ranges_pay(p, num_seqs, TT, Hkv, d.kv_dtype, opt, min_keys, most_parts, mixed_mode == TS_MIXED_SEPARATE);
     for (int s = 0; s < num_seqs; ++s) {
         const SeqMeta& m = p.seqs[s];
         if (m.q_len == 0) continue;
@@ -751,7 +788,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
                 // workgroups otherwise).  Cuts lie at multiples of 64 keys at or below the tile's first query
                 // position, so that every row sees the first key of every part; parts are of equal length.
                 const int32_t below = (m.prefix + t0) / 64;                       // whole stages every row sees fully
-                const int32_t n_part = pf_parts_wanted > 1 ? parts_of_tile(below * 64, opt.pf_split_min_keys, (int32_t)pf_parts_wanted) : 1;
+                const int32_t n_part = halves ? parts_of_tile(below * 64, min_keys, most_parts) : parts_in_ranges(below * 64, min_keys, most_parts);
                 if (n_part == 1) {
                     p.pf.push_back(PfItem{s, m.q_off, m.q_len, m.prefix, t0, cnt, m.ctx_len, -1, 0, INT32_MAX, 0, 0});
                     continue;

@@ -24,8 +24,35 @@ def test_cut_tiles_cover_their_keys_once(heads):
             for (_, end), (begin, _) in zip(ranges, ranges[1:]):
                 assert end == begin and begin % 64 == 0 and 0 < begin <= prefix + tok
             below = (prefix + tok) // 64 * 64
-            most = 16 if below >= 6 * 512 else 4 if below >= 768 else 1
-            assert len(ranges) <= most and (len(ranges) > 1) == (below >= 768), (prefix, tok, ranges)
+            launch = (prefix + max(by_tile)) // 64 * 64 >= 6 * 512              # (a merge is launched: all tiles in whole ranges)
+            least = 1024 if launch else 768
+            most = 16 if launch else 4 if below >= 768 else 1
+            assert len(ranges) <= most and (len(ranges) > 1) == (below >= least), (prefix, tok, ranges)
+
+
+# (query heads, KV heads, cache, chunks, prefixes), parts of the tiles in query order, sequence by sequence
+HALVES = {
+    "a merge is launched for another tile": ((32, 8, "fp8", [7, 30, 20], [2645, 5403, 4000]), [[5], [10], [7]]),
+    "more pieces than a die has CUs, few KV heads": ((64, 4, "bf16", [106, 339], [993, 993]), [[1] * 2 + [2] * 5, [1] * 2 + [2] * 20]),
+    "the same, one chunk": ((16, 2, "bf16", [160, 160], [800, 800]), [[3, 3, 3, 3, 3]] * 2),
+    "the same, one longer chunk": ((16, 2, "bf16", [900], [800]), [[1] * 7 + [2] * 16 + [3] * 6]),
+    "nearly a tile per CU, bf16": ((32, 8, "bf16", [300, 294, 327], [900, 885, 1026]), [[1, 1, 2, 2, 2], [1, 1, 1, 2, 2], [2] * 6]),
+    "nearly a tile per CU, e4m3": ((32, 8, "fp8", [300, 294, 327], [900, 885, 1026]), [[2] * 5, [2] * 5, [2] * 6]),
+    "a prompt of varied tiles, few KV heads": ((8, 4, "bf16", [1400], [0]), [[1] * 6 + [3, 3, 4, 4, 4]]),
+    "ranges would come to a launch": ((4, 2, "bf16", [1700], [1400]), [[4] * 14]),
+}
+
+
+@pytest.mark.parametrize("case", list(HALVES))
+def test_halves_of_the_shortest_range_only_where_they_pay(case):
+    from paper_2512_03416_amd import binding
+    import paper_2512_03416_amd as ts
+    (hq, hkv, kv, q, prefix), want = HALVES[case]
+    d = ts.Desc.make(hq, hkv, 128, "bf16", kv, 1 << 14, 1 << 10)
+    got = [{} for _ in q]
+    for t in binding.plan_export(d, q, [a + b for a, b in zip(q, prefix)], "prefill"):
+        got[int(t[0])][int(t[4])] = got[int(t[0])].get(int(t[4]), 0) + 1
+    assert [[g[t] for t in sorted(g)] for g in got] == want
 
 
 @pytest.mark.gpu
