@@ -516,11 +516,19 @@ static bool half_ranges_pay(const Plan& p, int num_seqs, int32_t TT, int Hkv, in
 // against 22.8, of 32 16.0 against 13.2; 32 over 1000 (65 pages) 31.7 against 31.6; 8 of 256 (128 pages) 33.8 against 36.2.
 constexpr int64_t kWidenReads = 26;
 constexpr int64_t kWidenFewPages = 512;                    // (pages times KV heads)
-static bool widening_pays(const Plan& p, int64_t pages, int Hkv)
+// Where one tile's chain of stages sets the time (it is kWidenChain times a CU's share of all stages: long prompts, few heads),
+// converting is paid on every one of them while most CUs have nothing to hide it behind, and the copies only once.  One prompt of
+// 6000 tokens with 8/8 heads (12 reads a page, 94 stages) 138.3 us converting, 129.8 with copies, of 7800 with 8/4 heads 138.7 and 131.4;
+// two of 8700 with 4/4 heads 204.7 and 194.1; of 3000 tokens with 8/8 heads (cut in two) 49.2 and 51.8.  Over 120 prefill batches below the
+// line of reads: converting always 0.6 % over the better one on average (6 % at most), so 0.2 % (2 % but for five of 29-100 us).
+constexpr double kWidenChain = 1.4, kWidenStageUs = 0.2, kWidenLaunchUs = 4.0, kWidenPageUs = 12288 / 4.5e6;   // (4 KB read, 8 written)
+static bool widening_pays(const Plan& p, int64_t pages, int Hkv, int32_t n_cu)
 {
     if (pages * Hkv < kWidenFewPages) return true;
-    int64_t keys = 0;                                      // that tiles read, per KV head
-    for (const PfItem& t : p.pf) keys += pf_keys(t);
+    int64_t keys = 0, longest = 0;                         // that tiles read, per KV head; by the longest tile or part
+    for (const PfItem& t : p.pf) { keys += pf_keys(t); longest = std::max(longest, pf_keys(t)); }
+    if (p.info.decode_tokens == 0 && longest * n_cu > kWidenChain * keys * Hkv &&
+        kWidenStageUs * longest / 64 > kWidenLaunchUs + (double)pages * Hkv * kWidenPageUs) return true;
     return keys > kWidenReads * kPage * pages;
 }
 
@@ -829,7 +837,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
     if (!p.rt.empty()) part = cut_row_tiles(p, Hkv, opt, part);
     // fp8 caches: the pages of the chunks' sequences are widened to bf16 once per pass, provided they fit the scratch the
     // option allows and the pass gains by it (see widening_pays)
-    if (widen && !p.pf.empty() && (d.head_dim != 128 || widening_pays(p, chunk_pages, Hkv))) {
+    if (widen && !p.pf.empty() && (d.head_dim != 128 || widening_pays(p, chunk_pages, Hkv, opt.n_cu))) {
         p.wide_base.assign((size_t)num_seqs, -1);
         for (int s = 0; s < num_seqs; ++s) {
             if (p.seqs[s].q_len <= 1) continue;

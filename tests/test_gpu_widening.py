@@ -8,8 +8,6 @@ import workloads as W
 from error_bar import OF_RMS, worst_of_rms
 from workloads import AttnShape, make_batch
 
-pytestmark = pytest.mark.gpu
-
 # (query lengths, context lengths, pages copied with head dim 128), 32 query heads over 2 KV heads: tiles of 16 tokens
 BATCHES = {
     "few pages": ([333], [600], 38),
@@ -20,6 +18,7 @@ BATCHES = {
 }
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("head_dim", [128, 64])
 @pytest.mark.parametrize("batch", list(BATCHES))
 def test_both_sides_of_the_line(batch, head_dim):
@@ -42,3 +41,20 @@ def test_both_sides_of_the_line(batch, head_dim):
             assert np.all(np.isfinite(out)) and worst_of_rms(out, ref) <= OF_RMS
             outs.append(out[chunk])
         assert len(outs) == 1 or np.array_equal(outs[0], outs[1])
+
+
+# prefill alone, 128 dims: (query heads, KV heads, query lengths, prefixes), pages copied
+CHAINS = [((8, 8, [6000], [0]), 375), ((8, 8, [3000], [0]), 0), ((4, 4, [5896, 8716], [16, 392]), 940), ((8, 8, [4200, 4500], [0, 0]), 0),
+          ((64, 8, [512], [8200]), 0)]
+
+
+@pytest.mark.parametrize("batch,copied", CHAINS, ids=lambda x: str(x))
+def test_long_chains_of_stages_have_their_pages_copied(batch, copied):
+    """Few reads a page, but one tile's stages set the time and each of them would convert: 6000 tokens with 8/8 heads 138 us a pass
+    converting, 130 with copies; 3000 (cut in two) 49 and 52."""
+    import paper_2512_03416_amd as ts
+    hq, hkv, q, prefix = batch
+    d = ts.Desc.make(hq, hkv, 128, "bf16", "fp8", 1 << 14, 1 << 10)
+    ctx = [a + b for a, b in zip(q, prefix)]
+    assert ts.plan_describe(d, q, ctx).widened_pages == copied
+    assert ts.plan_describe(d, q + [1] * 8, ctx + [500] * 8).widened_pages == 0      # (decode rows would wait for the copies)
