@@ -211,12 +211,17 @@ static int32_t auto_split_pages(const Plan& p, int num_seqs, int64_t decode_tile
 //   - ranges of decode rows next to chunk tiles, which the matrix instruction bounds, are twice as long: half the workgroups
 //     keep enough of the scan on the way, and the chunk tiles, cut as ever, find more places from the start (32/8 heads of 128, 30
 //     rows of 500-2000 tokens and 3 chunks of 100-300 91.5 -> 85.9 us a pass, 16 rows of 1000-2048 and a chunk of 231 over 1000
-//     79.0 -> 72.2; rows without chunks are slower, 67.5 -> 74.0);
-//   - chunks without decode rows stay whole where no tile is longer than twice the share (they give every CU a workgroup then): cut,
+//     79.0 -> 72.2; rows without chunks are slower, 67.5 -> 74.0).  Where the chunk tiles have kRowChunkShare of all pages or more, over
+//     150 random mixes: ranges twice as long take 0.92 of the time there on average, 1.01 at shares of 0.1-0.4 and 1.05 below
+//     (43 rows of 220-1900 next to 37 tokens over 200 75.7 and 69.4 us).  Groups of more than four heads, whose rows the matrix
+//     instruction bounds too, from kRowChunkShareWide on: 0.97 of the time between the two lines (64/8 heads, 24 rows of 1106-1501 next
+//     to 80 over 400 52.1 and 61.6);
+//   - from the same lines on all tiles stay whole where none is longer than twice the share (they give every CU a workgroup then): cut,
 //     their ranges would be more than the places, one short round behind the other, and a merge (one chunk of 240 tokens over
-//     500 46.2 -> 32.5, of 150 over 1000 47.6 -> 44.1, over 1500 58.0 -> 58.9).  Longer tiles are cut at the share (64 tokens
-//     over 16384: 143 us; at twice the share 153).
+//     500 46.2 -> 32.5, of 150 over 1000 47.6 -> 44.1, over 1500 58.0 -> 58.9; 64/8 heads, 9 rows of 458-618 next to 2 chunks of 29-53
+//     over 615-653 46.4 -> 33.0).  Longer chunk tiles are cut at the share (64 tokens over 16384: 143 us; at twice the share 153).
 constexpr int kRowTileMinPages = 16, kRowTileWgsPerCu = 2, kRowTileLongPages = 32;
+constexpr double kRowChunkShare = 0.4, kRowChunkShareWide = 0.15;
 
 static int32_t row_tile_tokens(const ts_attn_desc& d) { return 16 / (d.num_q_heads / d.num_kv_heads); }
 
@@ -234,18 +239,20 @@ static int32_t row_tile_pages(const Plan& p, const RowTile& t)
     return cut ? p.rtcut[cut - 1].page_end - p.rtcut[cut - 1].page_begin : (t.pos0 + t.n_tok_cut - 1) / kPage + 1;
 }
 
-static int32_t cut_row_tiles(Plan& p, int Hkv, const PlanOptions& opt, int32_t part)
+static int32_t cut_row_tiles(Plan& p, int G, int Hkv, const PlanOptions& opt, int32_t part)
 {
     const int64_t slots = kRowTileWgsPerCu * (int64_t)std::max(1, opt.n_cu);
     if (opt.row_cut_few_only && (int64_t)p.rt.size() * Hkv >= slots) return part;
-    int64_t pages = 0;
-    for (const RowTile& t : p.rt) pages += row_tile_pages(p, t);
-    const int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
     auto decode_row = [&](const RowTile& t) { return p.seqs[t.seq].q_len == 1; };
-    const auto n_dec = std::count_if(p.rt.begin(), p.rt.end(), decode_row);
-    const bool longer = L >= kRowTileLongPages;
-    if (longer && n_dec == 0 && std::all_of(p.rt.begin(), p.rt.end(), [&](const RowTile& t) { return row_tile_pages(p, t) <= 2 * L; })) return part;
-    const int32_t L_dec = longer && n_dec < (int64_t)p.rt.size() ? 2 * L : L;
+    int64_t pages = 0, chunk_pages = 0;
+    for (const RowTile& t : p.rt) {
+        pages += row_tile_pages(p, t);
+        if (!decode_row(t)) chunk_pages += row_tile_pages(p, t);
+    }
+    const int32_t L = (int32_t)std::max<int64_t>(kRowTileMinPages, (pages * Hkv + slots - 1) / slots);
+    const bool longer = L >= kRowTileLongPages && chunk_pages >= (G <= 4 ? kRowChunkShare : kRowChunkShareWide) * pages;
+    if (longer && std::all_of(p.rt.begin(), p.rt.end(), [&](const RowTile& t) { return row_tile_pages(p, t) <= 2 * L; })) return part;
+    const int32_t L_dec = longer ? 2 * L : L;
     auto cuts = [&](const RowTile& t) {
         const int32_t most = decode_row(t) ? L_dec : L;
         return (row_tile_pages(p, t) + most - 1) / most;
@@ -834,7 +841,7 @@ void build_plan(const ts_attn_desc& d, const int32_t* q_lens, const int32_t* ctx
             rt_tokens += m.q_len;
         }
     }
-    if (!p.rt.empty()) part = cut_row_tiles(p, Hkv, opt, part);
+    if (!p.rt.empty()) part = cut_row_tiles(p, d.num_q_heads / Hkv, Hkv, opt, part);
     // fp8 caches: the pages of the chunks' sequences are widened to bf16 once per pass, provided they fit the scratch the
     // option allows and the pass gains by it (see widening_pays)
     if (widen && !p.pf.empty() && (d.head_dim != 128 || widening_pays(p, chunk_pages, Hkv, opt.n_cu))) {

@@ -1,7 +1,6 @@
 """How the tiles of the generic kernel are cut along the pages: ranges of a fair share of the GPU's places (two
-workgroups on each of 256 CUs); twice that for decode rows next to chunks only; chunks alone whole while no tile is longer than
-twice the share."""
-import numpy as np
+workgroups on each of 256 CUs); where chunks have two fifths of all pages or more, twice that for decode rows, and none at all while
+no tile is longer than twice the share."""
 import pytest
 
 import paper_2512_03416_amd as ts
@@ -16,6 +15,8 @@ BATCHES = {                                                # (query lengths, pre
     "a ragged last tile": ([150, 5], [1000, 9000]),
     "decode rows alone": ([1] * 32, [500 + 50 * i for i in range(32)]),
     "both": ([1] * 30 + [300, 100, 257], [500 + 150 * i for i in range(30)] + [0, 500, 300]),
+    "both, hardly any chunk": ([1] * 43 + [37], [220 + 40 * i for i in range(43)] + [200]),
+    "both, none longer than twice a share": ([1] * 20 + [100, 150], [360 + 4 * i for i in range(20)] + [400, 700]),
     "both, few pages": ([1] * 4 + [200, 300], [100, 40, 600, 333, 0, 100]),
     "both, a long prefix": ([1] * 8 + [100], [1000 + 125 * i for i in range(8)] + [4000]),
 }
@@ -32,11 +33,11 @@ def test_ranges_of_generic_row_tiles(batch):
             tiles.append((row + i, cnt, (p + i + cnt - 1) // 16 + 1, n == 1))
         row += n
     share = max(16, -(-sum(t[2] for t in tiles) * HEADS[1] // 512))
-    kinds = {t[3] for t in tiles}
+    chunk_share = sum(t[2] for t in tiles if not t[3]) / sum(t[2] for t in tiles)
     want = {}
     for first, cnt, pages, dec in tiles:
-        most = 2 * share if share >= 32 and dec and len(kinds) == 2 else share
-        if share >= 32 and kinds == {False} and max(t[2] for t in tiles) <= 2 * share:
+        most = 2 * share if share >= 32 and dec and chunk_share >= 0.4 else share
+        if share >= 32 and chunk_share >= 0.4 and max(t[2] for t in tiles) <= 2 * share:
             most = pages
         n = -(-pages // most)
         n = -(-pages // (-(-pages // n)))
@@ -48,4 +49,4 @@ def test_ranges_of_generic_row_tiles(batch):
     assert ts.plan_describe(d, q, ctx).partial_slots == sum(want.values())
     if batch == "a short chunk over a long prefix":        # every place of the GPU gets a workgroup
         assert sum(want.values()) // 4 * HEADS[1] >= 512
-    assert bool(want) == (batch not in ("chunk tiles of nearly a share", "chunk tiles of twice a share"))
+    assert bool(want) == (batch not in ("chunk tiles of nearly a share", "chunk tiles of twice a share", "both, none longer than twice a share"))
