@@ -310,7 +310,7 @@ __device__ __forceinline__ uint32_t swap_halves16(uint32_t x)  // lanes n and n 
 // columns 8-15 the second's: one round of softmax arithmetic serves both pages.  The packed weights then trade places
 // between the two halves, every column has both pages', and one 16x16x32 MFMA per 16 dims takes the 32 tokens.  Against
 // a page at a time a launch has 20.6 vector instructions per page, start and merge included, for 24.4 (17.5 in the loop; e4m3, where 32
-// are conversions, 52.2 for 58.5), 8 MFMAs for 12 and two thirds of the scalar instructions; its loads take more
+// are conversions, 52.2 for 58.5) and 8 MFMAs for 12; its loads take more
 // issue cycles (V in 8-byte pieces of two tiles).  The scan alone does not notice (it waits for memory); next to prefill tiles,
 // which leave it little of the vector ALU and of the matrix pipe, it counts.
 // A wave's last page (the only one that can be partly filled) goes through the masked single step.
